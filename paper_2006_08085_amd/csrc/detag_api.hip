@@ -21,10 +21,9 @@ struct detag_ctx {
   int device = -1;
   int32_t *d_rowptr = nullptr, *d_colidx = nullptr;
   float *d_vals = nullptr;
-  uint32_t *d_ell_table = nullptr;  // neighbour table of the on-chip kernel for arbitrary W
-  int ell_deg = 0;
-  bool ell_uniform = false;
-  bool fused_generic = false;             // build_ell succeeded for this W
+  LdsTable lds;                           // neighbour table of the LDS-resident kernels; its arrays in one allocation
+  void *d_lds = nullptr;
+  bool fused_generic = false;             // the LDS-resident family serves this W: n <= 256, at most 8 neighbours
   // per-round path: n x ld fp32 matrices; [0],[1] hold z_r between rounds, [2],[3] the widened copies of bf16 X and Y
   void *scratch[4] = {nullptr, nullptr, nullptr, nullptr};
   double *d_partials = nullptr;           // consensus-error partial sums
@@ -137,8 +136,37 @@ detag_status resolve_eta(const detag_ctx *ctx, double eta_in, float *eta_out) {
 DevCsr dev_csr(const detag_ctx *ctx) {
   DevCsr w;
   w.rowptr = ctx->d_rowptr, w.colidx = ctx->d_colidx, w.vals = ctx->d_vals;
-  w.ell_table = ctx->d_ell_table, w.ell_deg = ctx->ell_deg, w.ell_uniform = ctx->ell_uniform;
   return w;
+}
+
+// The workers and degrees the LDS-resident family is offered for (detag_get_kernel).
+bool lds_family_serves(const HostW &W) {
+  if (W.n > 256) return false;
+  for (int i = 0; i < W.n; ++i) {
+    int neighbours = 0;
+    for (int k = W.rowptr[i]; k < W.rowptr[i + 1]; ++k) neighbours += W.colidx[k] != i;
+    if (neighbours > 8) return false;
+  }
+  return true;
+}
+
+hipError_t upload_lds_table(detag_ctx *ctx, const LdsTableHost &t) {
+  // 16-byte pairs first, then whatever needs 4-byte alignment
+  const size_t words[4] = {t.pairs.size(), t.byte_table.size(), t.rows.size(), t.groups.size()};
+  const void *src[4] = {t.pairs.data(), t.byte_table.data(), t.rows.data(), t.groups.data()};
+  const uint32_t *at[4];
+  hipError_t e = hipMalloc(&ctx->d_lds, (words[0] + words[1] + words[2] + words[3]) * 4);
+  uint32_t *next = static_cast<uint32_t *>(ctx->d_lds);
+  for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+    at[k] = words[k] ? next : nullptr;
+    if (words[k]) e = hipMemcpy(next, src[k], words[k] * 4, hipMemcpyHostToDevice);
+    next += words[k];
+  }
+  if (e != hipSuccess) return e;
+  ctx->lds.bytes_deg = t.bytes_deg, ctx->lds.weight = t.weight, ctx->lds.byte_table = at[1];
+  ctx->lds.pairs = at[0], ctx->lds.rows = reinterpret_cast<const int32_t *>(at[2]), ctx->lds.groups = at[3];
+  ctx->lds.pair_count = int(t.pairs.size() / 4), ctx->lds.max_pairs = t.max_pairs;
+  return hipSuccess;
 }
 
 enum Chosen { kPerRound, kFusedStructured, kFusedGeneric, kDense };
@@ -286,8 +314,10 @@ detag_status detag_create(const detag_topology *topo, int32_t n, int64_t d, int6
   if (!ctx) return set_err(nullptr, DETAG_ENOMEM, "out of host memory");
   std::string err;
   detag_status st;
+  LdsTableHost table;
   try {
     st = build_gossip_matrix(topo, n, ctx->W, err);
+    if (st == DETAG_OK) ctx->fused_generic = lds_family_serves(ctx->W) && build_lds_table(ctx->W, d, table);
   } catch (const std::bad_alloc &) {
     st = DETAG_ENOMEM, err = "out of host memory";
   }
@@ -296,9 +326,6 @@ detag_status detag_create(const detag_topology *topo, int32_t n, int64_t d, int6
     return set_err(nullptr, st, err);
   }
   ctx->shape.n = n, ctx->shape.d = d, ctx->shape.ld = ld, ctx->shape.bf16 = state == DETAG_BF16;
-
-  EllHost ell;
-  ctx->fused_generic = build_ell(ctx->W, ell);
 
   int count = 0;
   if (hipGetDeviceCount(&count) != hipSuccess || count < 1) {
@@ -324,12 +351,7 @@ detag_status detag_create(const detag_topology *topo, int32_t n, int64_t d, int6
     e = hipMemcpy(ctx->d_rowptr, ctx->W.rowptr.data(), (size_t(n) + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ctx->d_colidx, ctx->W.colidx.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ctx->d_vals, vals32.data(), nnz * sizeof(float), hipMemcpyHostToDevice);
-  if (ctx->fused_generic) {
-    ctx->ell_deg = ell.deg, ctx->ell_uniform = ell.uniform;
-    const size_t bytes = ell.table.size() * sizeof(uint32_t);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&ctx->d_ell_table), bytes);
-    if (e == hipSuccess) e = hipMemcpy(ctx->d_ell_table, ell.table.data(), bytes, hipMemcpyHostToDevice);
-  }
+  if (e == hipSuccess && ctx->fused_generic) e = upload_lds_table(ctx, table);
   if (e != hipSuccess) {
     const int rc = int(e);
     detag_destroy(ctx);
@@ -346,7 +368,7 @@ void detag_destroy(detag_ctx *ctx) {
     (void)hipFree(ctx->d_rowptr);
     (void)hipFree(ctx->d_colidx);
     (void)hipFree(ctx->d_vals);
-    (void)hipFree(ctx->d_ell_table);
+    (void)hipFree(ctx->d_lds);
     (void)hipFree(ctx->d_partials);
     (void)hipFree(ctx->d_resid);
     for (void *p : ctx->scratch) (void)hipFree(p);
@@ -472,7 +494,7 @@ detag_status detag_gossip_accel(detag_ctx *ctx, void *Z_dev, int32_t K, double e
       rc = launch_fused_structured(ctx->shape, ctx->W, 0, Z_dev, nullptr, nullptr, nullptr, 0.f, K, e, stream);
       break;
     case kFusedGeneric:
-      rc = launch_fused_generic(ctx->shape, ctx->W, dev_csr(ctx), 0, Z_dev, nullptr, nullptr, nullptr, 0.f, K, e, stream);
+      rc = launch_fused_generic(ctx->shape, ctx->lds, 0, Z_dev, nullptr, nullptr, nullptr, 0.f, K, e, stream);
       break;
     case kDense: {
       const uint16_t *frag = nullptr;
@@ -529,7 +551,7 @@ detag_status detag_step(detag_ctx *ctx, void *X_dev, void *Y_dev, const float *G
     return rc ? hip_fail(ctx, "fused phase", rc) : DETAG_OK;
   }
   if (path == kFusedGeneric) {
-    const int rc = launch_fused_generic(s, ctx->W, dev_csr(ctx), mode, X_dev, Y_dev, Gnew_dev, Gold_dev, a, K, e, stream);
+    const int rc = launch_fused_generic(s, ctx->lds, mode, X_dev, Y_dev, Gnew_dev, Gold_dev, a, K, e, stream);
     return rc ? hip_fail(ctx, "fused phase", rc) : DETAG_OK;
   }
   if (path == kDense) {
@@ -847,7 +869,7 @@ detag_status detag_step_quadratic(detag_ctx *ctx, void *X_dev, void *Y_dev, floa
       return set_err(ctx, DETAG_EUNSUPPORTED,
                      "Algorithm 2 as printed in one kernel needs the register-resident family (ring or torus on its "
                      "list); use detag_grad_quadratic_diag + detag_step");
-    rc = launch_fused_generic_quadratic(ctx->shape, dev_csr(ctx), X_dev, Y_dev, G_dev, h_dev, h_per_worker != 0, b_dev,
+    rc = launch_fused_generic_quadratic(ctx->shape, ctx->lds, X_dev, Y_dev, G_dev, h_dev, h_per_worker != 0, b_dev,
                                         float(alpha), K, e, sigma, seed, step, stream);
   }
   return rc ? hip_fail(ctx, "fused gradient + phase", rc) : DETAG_OK;

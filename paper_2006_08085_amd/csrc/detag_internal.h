@@ -56,24 +56,31 @@ struct DevCsr {
   const int32_t *rowptr = nullptr;  // n+1
   const int32_t *colidx = nullptr;  // nnz
   const float *vals = nullptr;      // nnz, fp32 copies of W_ji
-  // the same matrix for the on-chip kernel for arbitrary W: one packed record per row (see EllHost)
-  const uint32_t *ell_table = nullptr;
-  int ell_deg = 0;
-  bool ell_uniform = false;
 };
 
-// Neighbour table of the on-chip kernel for arbitrary W (256 row slots, wavefront-major: row i sits at slot
-// (i % 16) * 16 + i / 16).  Per slot: deg/2 words of packed 16-bit LDS byte offsets of the neighbours' rows, then
-// the off-diagonal weights as fp32 bit patterns (one word if every row has equal off-diagonal weights, else deg
-// words).  Missing neighbours point at the row itself: the kernel works with differences z_j - z_i, so they
-// contribute nothing.
-struct EllHost {
-  int deg = 0;            // table width: 2, 4 or 8
-  bool uniform = false;   // each row's off-diagonal weights are all equal
-  std::vector<uint32_t> table;
+// Neighbour table of the LDS-resident kernels for arbitrary W, in one of two forms (fused_generic_common.hpp).
+struct LdsTableHost {
+  // one byte per neighbour, 256 rows of bytes_deg (2, 4 or 8) entries padded with the row itself; 0: the lists below
+  int bytes_deg = 0;
+  float weight = 0.f;  // the one off-diagonal weight
+  std::vector<uint32_t> byte_table;
+  // lists of (LDS row offset, weight) pairs for the geometry of (n, d), and the row at every position
+  std::vector<int32_t> rows;
+  std::vector<uint32_t> groups, pairs;
+  int max_pairs = 0;  // longest list, in pairs
 };
-// false if W has more than 256 rows or a row with more than 8 off-diagonal terms.
-bool build_ell(const HostW &W, EllHost &out);
+// The device copy.
+struct LdsTable {
+  int bytes_deg = 0;
+  float weight = 0.f;
+  const uint32_t *byte_table = nullptr;
+  const int32_t *rows = nullptr;
+  const uint32_t *groups = nullptr, *pairs = nullptr;
+  int pair_count = 0;  // 16-byte words in `pairs`
+  int max_pairs = 0;
+};
+// false if a tile of n rows and the lists do not fit the LDS of a compute unit.
+bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out);
 
 struct Shape {
   int n;
@@ -131,12 +138,11 @@ int launch_fused_structured(const Shape &s, const HostW &W, int mode, void *X, v
 int launch_fused_quadratic(const Shape &s, const HostW &W, bool alg2, void *X, void *Y, float *G, const float *h,
                            bool h_per_worker, const float *b, float alpha, int K, float eta, float sigma, uint64_t seed,
                            uint32_t step, void *stream);
-bool fused_generic_available(const HostW &W, const Shape &s);
-int launch_fused_generic_quadratic(const Shape &s, const DevCsr &w, void *X, void *Y, float *G, const float *h,
+int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, void *Y, float *G, const float *h,
                                    bool h_per_worker, const float *b, float alpha, int K, float eta, float sigma,
                                    uint64_t seed, uint32_t step, void *stream);
-int launch_fused_generic(const Shape &s, const HostW &W, const DevCsr &w, int mode, void *X, void *Y,
-                         const float *Gn, const float *Go, float alpha, int K, float eta, void *stream);
+int launch_fused_generic(const Shape &s, const LdsTable &t, int mode, void *X, void *Y, const float *Gn, const float *Go,
+                         float alpha, int K, float eta, void *stream);
 
 // Diagnostics
 int launch_mean(const Shape &s, const void *X, float *xbar, void *stream);

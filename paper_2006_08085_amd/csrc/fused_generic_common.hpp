@@ -1,136 +1,505 @@
-// Shared by the LDS-resident kernels: K-round fused DeTAG phase for an arbitrary sparse gossip matrix with up to
-// 256 workers and at most 8 neighbours per worker (e.g. a random regular graph
-// with Metropolis weights).
+// Shared by the LDS-resident kernels: the K-round fused DeTAG phase for a sparse gossip matrix without compile-time
+// structure (a random regular graph, a user's own network, rings and tori off the register family's list).
 //
-// A block of 16 wavefronts owns 64 columns and all n rows of them.  Wavefront w
-// owns the rows w, w+16, w+32, ... (RPT of them, RPT = 1, 2, 4, 8 or 16 by the
-// number of workers); lane l owns column l.  Each lane
-// keeps z_r and the velocity z_r - z_{r-1} of its own rows in registers; z_r
-// of ALL rows also sits in LDS (16*RPT x 64 fp32), where the neighbours of a row
-// are read.  Row indices are wavefront-uniform:
-// the neighbour list of a row is a handful of scalars (16-bit LDS offsets packed
-// in pairs, the weights), read once per kernel, and every LDS access is 64
-// consecutive words, free of bank conflicts.  One round = read the neighbours
-// from LDS, barrier, write the new values back, barrier.  HBM sees the state
-// once per phase (16 B per element with bf16 state, 24 B with fp32); the rounds
-// run at the LDS bandwidth, (deg+1) LDS words per
-// output per round.  The kernel is kept within 64 VGPRs so that two blocks
-// share a compute unit (2 x 64 KiB of LDS): one block's loads and stores then
-// run under the other's rounds.
+// A block owns `cols` (16 ... 256) adjacent columns and all n rows of them.  A lane owns FOUR ADJACENT columns of S rows:
+// cols/4 lanes side by side cover a row, a wavefront 256/cols rows, and lane t of a block of T threads owns the rows at
+// LDS offsets 16 t + 16 T s, s < S.  z_r and the velocity of its rows stay in registers; z_r of all rows also sits in
+// LDS, where the neighbours of a row are read: one round = read the neighbours, barrier, write the new values back,
+// barrier.  HBM sees the state once per phase (24 B per element with fp32 state, 16 B with bf16, whatever K is).
+//
+// Why four columns per lane: the rounds are bound by LDS traffic, (deg + 1) words per output, and gfx950's LDS
+// delivers 240 B per clock and compute unit to 16-byte reads but 116 to 4-byte reads (measured; with the one write
+// per four reads of a 4-regular graph 174 against 98).  A read also needs one address per four outputs instead of
+// one per output.  With one column per lane (and one row per wavefront, so that row offsets were scalars) the step of
+// the 256-worker workload took 3.14 ms; now 2.12 ms, of which the rounds (26.5 us for 64 Mi elements of X and Y) run
+// at the rate the LDS and the vector ALUs, about equally busy, allow.
+//
+// S = 4 is the form for matrices that fill the chip.  S = 1 and 2 spread a small matrix over more wavefronts: its time
+// is the length of the chain load - K rounds - store, so a lane does less, keeps its neighbour list in registers, and
+// the rounds alternate between two tiles in LDS, which saves one of the two barriers.
+//
+// Forms of the neighbour table:
+//   ByteRounds<DEG, S>  n <= 256, at most 8 neighbours, one weight for the whole matrix (any regular graph with uniform
+//                    or Metropolis weights): a neighbour is one byte, the high byte of its row's LDS offset, so the table
+//                    of a row is DEG/4 registers and an address is one byte permute.
+//   ListRounds<S>    any weights, at most 8 neighbours, S < 4: the row's (offset, weight) pairs in registers.
+//   CsrRounds<S>     any weights and degrees, n <= 1024: the rows' lists sit in LDS next to the tile as pairs of (offset,
+//                    weight), two per 16-byte read, which all lanes of a row read together.  The host orders the
+//                    rows by degree, so that the rows a wavefront walks together have lists of about one length.
+// All evaluate a round in velocity form, v = z_r - z_{r-1},
+//   v_i <- (1+eta) * sum_j W_ji (z_j - z_i) + eta * v_i,   z_i <- z_i + v_i,
+// in which equal values across the workers are a fixed point exactly whatever the rounding of the weights (the worker
+// mean does not drift with K) and the only rounding at the magnitude of z is the last add.
+//
+// The ByteRounds kernels with S = 4 are kept within 64 VGPRs (three arrays of 16 values per lane in a phase), so that 32
+// wavefronts share a compute unit: one block's loads and stores run under the other blocks' rounds.
 //
 // Paper: Algorithm 3 (accelerated gossip) and Algorithm 2 / the matrix form in
 // the proof of Theorem 3 (phase update).
 #pragma once
 
+#include <type_traits>
+
 #include "detag_internal.h"
 #include "dev_common.hpp"
+#include "fused_common.hpp"
 
 namespace detag {
 namespace lds_tile {
 
-constexpr int kWaves = 16, kThreads = 64 * kWaves, kCols = 64, kRptMax = 16, kRowsMax = kWaves * kRptMax;  // 256 rows
+constexpr int kSlotsMax = 4;         // rows per lane (S above)
+constexpr int kThreadsMax = 1024;
 
-// Rows per wavefront (RPT below): the smallest of 1, 2, 4, 8, 16 that gives all n workers a slot (16 * RPT >= n).
-// A block's arithmetic, LDS footprint and table are proportional to its slots, not to n, so a small graph on
-// the 256-slot layout would pay for 256 workers (measured on a 7-worker ring: 18 times the time per byte of the
-// 256-worker case).
-inline int rows_per_wave(int n) {
-  int r = 1;
-  while (r < kRptMax && kWaves * r < n) r *= 2;
+typedef float f4 __attribute__((ext_vector_type(4)));
+// the same for rows that start anywhere (an odd pitch): one access all the same, memory needs no 16-byte alignment
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned short u4_any __attribute__((ext_vector_type(4), aligned(2)));
+
+// Four adjacent columns of a row from column c on.  FULL: the block's columns all exist.  Otherwise columns past the
+// last one repeat it: they are computed and never stored.
+template <bool FULL>
+__device__ __forceinline__ f4 load4(const float *base, int64_t row_off, int64_t c, int64_t d) {
+  if constexpr (FULL) return __builtin_nontemporal_load(reinterpret_cast<const f4_any *>(base + (row_off + c)));
+  f4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = base[row_off + (c + e < d ? c + e : d - 1)];
+  return v;
+}
+template <bool FULL>
+__device__ __forceinline__ f4 load4(const bf16_t *base, int64_t row_off, int64_t c, int64_t d) {
+  f4 v;
+  if constexpr (FULL) {
+    const u4_any t = __builtin_nontemporal_load(reinterpret_cast<const u4_any *>(base + (row_off + c)));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = to_f32(base[row_off + (c + e < d ? c + e : d - 1)]);
+  }
+  return v;
+}
+template <bool FULL>
+__device__ __forceinline__ void store4(float *base, int64_t row_off, int64_t c, int64_t d, f4 v) {
+  if constexpr (FULL) {
+    __builtin_nontemporal_store(f4_any(v), reinterpret_cast<f4_any *>(base + (row_off + c)));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c + e < d) base[row_off + c + e] = v[e];
+  }
+}
+template <bool FULL>
+__device__ __forceinline__ void store4(bf16_t *base, int64_t row_off, int64_t c, int64_t d, f4 v) {
+  if constexpr (FULL) {
+    u4_any t;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = bf16_bits_rne(v[e]);
+    __builtin_nontemporal_store(t, reinterpret_cast<u4_any *>(base + (row_off + c)));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c + e < d) base[row_off + c + e].bits = bf16_bits_rne(v[e]);
+  }
+}
+
+__device__ __forceinline__ f4 fma4(float a, f4 b, f4 c) {
+  f4 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = fmaf(a, b[e], c[e]);
   return r;
 }
 
-// Table words per row: DEG/2 words of packed 16-bit LDS byte offsets, then the
-// neighbour weights (one word if they are all equal, else DEG).  W_ii is not
-// stored: a round is evaluated in velocity form, v = z_r - z_{r-1},
-//   v_i <- (1+eta) * sum_j W_ji (z_j - z_i) + eta * v_i,   z_i <- z_i + v_i,
-// in which equal values across the workers are a fixed point exactly whatever
-// the rounding of the weights (the worker mean does not drift with K) and the
-// only rounding at the magnitude of z is the last add.
-// Padding entries point at the row itself (difference zero).
-constexpr int table_stride(int deg, bool uniform) { return deg / 2 + (uniform ? 1 : deg); }
+__device__ __forceinline__ void pin4(f4 &v) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    float t = v[e];
+    pin_vgpr(t);
+    v[e] = t;
+  }
+}
 
-template <int DEG, bool UNI>
-struct RowTab {
-  uint32_t w[table_stride(DEG, UNI)];
-  __device__ __forceinline__ uint32_t off(int k) const { return (k & 1) ? w[k >> 1] >> 16 : w[k >> 1] & 0xffffu; }
-  __device__ __forceinline__ float val(int k) const { return __uint_as_float(w[DEG / 2 + (UNI ? 0 : k)]); }
+// The tile starts at LDS offset 0: the kernels have no other LDS.  Addressed as numbers, an access costs no addition of
+// a base that is zero.
+typedef __attribute__((address_space(3))) f4 lds_f4;
+__device__ __forceinline__ f4 lds_read(uint32_t off) { return *reinterpret_cast<const lds_f4 *>(off); }
+__device__ __forceinline__ void lds_write(uint32_t off, f4 v) { *reinterpret_cast<lds_f4 *>(off) = v; }
+
+// Where a lane sits: its column (in the block's tile) and its position among the rows of a slot.
+struct Place {
+  uint32_t tid, threads;
+  int lpr_log2;  // lanes per row = cols / 4
+  __device__ __forceinline__ uint32_t col() const { return (tid & ((1u << lpr_log2) - 1u)) * 4u; }
+  __device__ __forceinline__ uint32_t pos(int s) const { return (tid + s * threads) >> lpr_log2; }
+  __device__ __forceinline__ uint32_t own(int s) const { return (tid + s * threads) * 16u; }
+  // What was derived from tid so far (row addresses, LDS offsets) is derived anew from here on instead of being kept.
+  __device__ __forceinline__ void forget() { asm volatile("" : "+v"(tid)); }
 };
 
-// One round for this lane's rows, with the velocity kept divided by (1+eta) (and, for rows whose neighbour
-// weights are all equal, also by that weight; the table then holds (1+eta)*weight, see scale_uniform_weights):
-//   u <- sum_k W_ji (lds[j] - z) + eta * u;   z <- z + (1+eta) * u;   then publish z.
-// Two multiplications fewer per output and round than with the velocity itself; the kernel issues about as many
-// vector-ALU cycles as LDS cycles per round, so they count.
-template <int DEG, bool UNI, bool FIRST, int RPT>
-__device__ __forceinline__ void round_step(float (&z)[RPT], float (&u)[RPT], const char *lds_b, float *lds, int w,
-                                           int lane, RowTab<DEG, UNI> (&tab)[RPT], float cm, float eta) {
-  // The packed offset words are made opaque once per round: otherwise their 16-bit halves are unpacked ahead
-  // of the round loop into 4*DEG*... scalar registers of their own, which do not fit beside the table at two
-  // blocks per compute unit and end up spilled.
+// Blocks of S < 4 hold two tiles; the second one starts here (a compile-time distance, so that it costs no address).
+constexpr uint32_t second_tile(int S) { return uint32_t(S) * kThreadsMax * 16u; }
+
+template <int DEG, int S>
+struct ByteRounds {
+  static constexpr int kSlots = S, kWords = DEG <= 4 ? 1 : DEG / 4;
+  static constexpr int kWaves = S == 4 ? 8 : 4;  // wavefronts per SIMD asked of the register allocator
+  static constexpr int kParked = S == 4 ? 1 : 0;
+  struct Args {
+    const uint32_t *table;  // kWords words per row, 256 rows: one byte per neighbour, its row number
+    float weight;
+  };
+  uint32_t w[S][kWords];
+  uint32_t low;  // low byte of the lane's column offset
+  float b;
+
+  __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
+    // row r starts at r * cols * 4 bytes and the columns add up to cols * 4 - 1: the neighbour's byte becomes bits 8..15
+    // of the address of the lane's columns in that row (cols is 64, 128 or 256; n * cols <= 16384)
+    const uint32_t byte_col = p.col() * 4u, scale = 1u << (p.lpr_log2 - 4);
+    low = byte_col & 0xffu;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r)
+    for (int s = 0; s < S; ++s)
 #pragma unroll
-    for (int q = 0; q < DEG / 2; ++q) asm volatile("" : "+s"(tab[r].w[q]));
-  const uint32_t lane4 = uint32_t(lane) * 4u;
-  auto nb = [&](int r, int k) { return *reinterpret_cast<const float *>(lds_b + (tab[r].off(k) + lane4)); };
+      for (int q = 0; q < kWords; ++q)
+        w[s][q] = a.table[p.pos(s) * kWords + q] * scale + (byte_col >> 8) * 0x01010101u;
+    b = (1.f + eta) * a.weight;
+  }
+  __device__ __forceinline__ static int row(const Args &, const Place &p, int s) { return int(p.pos(s)); }
+
+  // sum_j (z_j - z_i) on the tile at offset IN: the neighbours pairwise, so that DEG equal values sum exactly and
+  // cancel DEG * z exactly
+  template <uint32_t IN>
+  __device__ __forceinline__ f4 diff_sum(int s, f4 z) const {
+    auto nb = [&](int k) {
+      return lds_read(__builtin_amdgcn_perm(w[s][k / 4], low, 0x0c0c0000u | (4u + (k & 3)) << 8) + IN);
+    };
+    f4 sum;
+    if constexpr (DEG == 2) sum = nb(0) + nb(1);
+    else if constexpr (DEG == 4) sum = (nb(0) + nb(2)) + (nb(1) + nb(3));
+    else sum = ((nb(0) + nb(4)) + (nb(2) + nb(6))) + ((nb(1) + nb(5)) + (nb(3) + nb(7)));
+    return fma4(-float(DEG), z, sum);
+  }
+  __device__ __forceinline__ float scale() const { return b; }
+  // The table's registers are made opaque once per round: otherwise the addresses, 4 DEG of them, are computed ahead
+  // of the round loop and kept, in four times the registers.
+  __device__ __forceinline__ void keep_packed() {
+    if constexpr (S == kSlotsMax) {
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    float acc;
-    if constexpr (UNI) {
-      // pairwise tree: DEG equal values sum exactly, so s - DEG*z is exactly zero for them
-      float s[DEG];
+      for (int s = 0; s < S; ++s)
 #pragma unroll
-      for (int k = 0; k < DEG; ++k) s[k] = nb(r, k);
-#pragma unroll
-      for (int len = DEG / 2; len >= 1; len /= 2)
-#pragma unroll
-        for (int k = 0; k < len; ++k) s[k] += s[k + len];
-      acc = fmaf(-float(DEG), z[r], s[0]);
-    } else {
-      acc = 0.f;
-#pragma unroll
-      for (int k = 0; k < DEG; ++k) acc = fmaf(tab[r].val(k), nb(r, k) - z[r], acc);
+        for (int q = 0; q < kWords; ++q) asm volatile("" : "+v"(w[s][q]));
     }
-    u[r] = FIRST ? acc : fmaf(eta, u[r], acc);
   }
-  __syncthreads();  // every read of z_r is done
+};
+
+// The lists of a context, laid out for its geometry.
+struct ListArgs {
+  // 4 * threads / lanes-per-row positions: row number of each (-1: none)
+  const int32_t *rows;
+  // per (wavefront, slot): first pair of its lists (pairs of all its rows are interleaved), pairs per row
+  const uint32_t *groups;
+  // the lists: {offset 0, weight 0, offset 1, weight 1}; offsets are LDS byte offsets of rows
+  const f4 *pairs;
+  int pair_count;       // 16-byte words in `pairs`
+  uint32_t tile_bytes;  // where CsrRounds keeps the lists in LDS
+};
+
+template <int S>
+struct CsrRounds {
+  static constexpr int kSlots = S, kWaves = S == 4 ? 6 : 4, kParked = 0;
+  using Args = ListArgs;
+  uint32_t first[S], count[S];  // uniform in a wavefront
+  uint32_t list;                // LDS offset of the lane's row in a group's first pair
+  uint32_t col_bytes, step;
+  float cm;
+
+  __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
+    for (int k = int(p.tid); k < a.pair_count; k += int(p.threads)) lds_write(a.tile_bytes + 16u * k, a.pairs[k]);
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(p.tid >> 6), rows_per_wave = 64u >> p.lpr_log2;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    z[r] = fmaf(UNI ? tab[r].val(0) : cm, u[r], z[r]);
-    lds[(w + kWaves * r) * kCols + lane] = z[r];
+    for (int s = 0; s < S; ++s) first[s] = a.groups[2 * (wave * S + s)], count[s] = a.groups[2 * (wave * S + s) + 1];
+    step = 16u * rows_per_wave;
+    list = a.tile_bytes + 16u * ((p.tid & 63u) >> p.lpr_log2);
+    col_bytes = p.col() * 4u;
+    cm = 1.f + eta;
   }
-  __syncthreads();  // z_{r+1} is visible
+  __device__ __forceinline__ static int row(const Args &a, const Place &p, int s) { return a.rows[p.pos(s)]; }
+
+  // sum_j W_ji (z_j - z_i); lists are padded to an even length with the row itself, weight 0
+  template <uint32_t IN>
+  __device__ __forceinline__ f4 diff_sum(int s, f4 z) const {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    uint32_t at = list + first[s] * 16u;
+    for (uint32_t k = 0; k < count[s]; ++k, at += step) {
+      const f4 e = lds_read(at);
+      const f4 n0 = lds_read(__float_as_uint(e[0]) + col_bytes + IN), n1 = lds_read(__float_as_uint(e[2]) + col_bytes + IN);
+      acc = fma4(e[1], n0 - z, acc);
+      acc = fma4(e[3], n1 - z, acc);
+    }
+    return acc;
+  }
+  __device__ __forceinline__ float scale() const { return cm; }
+  __device__ __forceinline__ void keep_packed() { asm volatile("" : "+v"(list), "+v"(col_bytes)); }
+};
+
+// The same lists held in registers: at most kListPairs pairs per row.
+constexpr int kListPairs = 4;
+template <int S>
+struct ListRounds {
+  static constexpr int kSlots = S, kWaves = 4, kParked = 0;
+  using Args = ListArgs;
+  uint32_t at[S][2 * kListPairs];
+  float weight[S][2 * kListPairs];
+  int pairs[S];  // uniform in a wavefront
+  float cm;
+
+  __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(p.tid >> 6), rows_per_wave = 64u >> p.lpr_log2;
+    const uint32_t in_wave = (p.tid & 63u) >> p.lpr_log2, col_bytes = p.col() * 4u;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const uint32_t first = a.groups[2 * (wave * S + s)];
+      pairs[s] = int(a.groups[2 * (wave * S + s) + 1]);
+#pragma unroll
+      for (int q = 0; q < kListPairs; ++q) {
+        f4 e = {__uint_as_float(0u), 0.f, __uint_as_float(0u), 0.f};
+        if (q < pairs[s]) e = a.pairs[first + q * rows_per_wave + in_wave];
+        at[s][2 * q] = __float_as_uint(e[0]) + col_bytes, weight[s][2 * q] = e[1];
+        at[s][2 * q + 1] = __float_as_uint(e[2]) + col_bytes, weight[s][2 * q + 1] = e[3];
+      }
+    }
+    cm = 1.f + eta;
+  }
+  __device__ __forceinline__ static int row(const Args &a, const Place &p, int s) { return a.rows[p.pos(s)]; }
+
+  template <uint32_t IN>
+  __device__ __forceinline__ f4 diff_sum(int s, f4 z) const {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto pair = [&](int q) {
+      const f4 n0 = lds_read(at[s][2 * q] + IN), n1 = lds_read(at[s][2 * q + 1] + IN);
+      acc = fma4(weight[s][2 * q], n0 - z, acc);
+      acc = fma4(weight[s][2 * q + 1], n1 - z, acc);
+    };
+    // all reads of a list are in flight together; the lists of a wavefront's rows are about as long as each other
+    if (pairs[s] <= 2) {
+      pair(0), pair(1);
+    } else {
+      pair(0), pair(1), pair(2), pair(3);
+    }
+    return acc;
+  }
+  __device__ __forceinline__ float scale() const { return cm; }
+  __device__ __forceinline__ void keep_packed() {}
+};
+
+// The second array of a phase, which waits while the first runs its rounds.  The last kParked of the lane's rows
+// wait in LDS behind the tile (16 bytes per lane and row; a lane reads back what it wrote, so there is no barrier).
+template <class R>
+struct Waiting {
+  static constexpr int kHeld = R::kSlots - R::kParked;
+  f4 v[kHeld];
+  __device__ __forceinline__ void put(const Place &p, int s, f4 x) {
+    if (s < kHeld) v[s] = x;
+    else lds_write(p.own(s + R::kParked), x);
+  }
+  __device__ __forceinline__ f4 get(const Place &p, int s) const {
+    return s < kHeld ? v[s] : lds_read(p.own(s + R::kParked));
+  }
+};
+
+// One round: z_r of all rows is in the tile at IN, z_{r+1} goes to the one at OUT.
+template <uint32_t IN, uint32_t OUT, class R>
+__device__ __forceinline__ void round_step(f4 (&z)[R::kSlots], f4 (&u)[R::kSlots], R &rounds, Place &p, float c, float eta) {
+  constexpr int S = R::kSlots;
+  rounds.keep_packed();
+  if constexpr (S == kSlotsMax) p.forget();
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    const f4 t = rounds.template diff_sum<IN>(s, z[s]);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float ue = u[s][e];
+      fused::momentum(ue, eta, t[e]);
+      u[s][e] = ue;
+    }
+    if constexpr (S == kSlotsMax) __builtin_amdgcn_sched_barrier(0);
+  }
+  if constexpr (IN == OUT) __syncthreads();  // every read of z_r is done
+#pragma unroll
+  for (int s = 0; s < S; ++s) {
+    z[s] = fma4(c, u[s], z[s]);
+    lds_write(p.own(s) + OUT, z[s]);
+  }
+  __syncthreads();  // z_{r+1} is visible (and with two tiles, every read of z_r is done)
 }
 
-// For rows with one weight, the table's weight word becomes (1+eta)*weight, a wavefront-uniform value kept in a
-// scalar register like the weight it replaces.
-template <int DEG, bool UNI, int RPT>
-__device__ __forceinline__ void scale_uniform_weights(RowTab<DEG, UNI> (&tab)[RPT], float cm) {
-  if constexpr (UNI) {
+// K >= 1 rounds from z_{-1} = z_0 = z.  Result in z; u is scratch: the velocity divided by scale(), which takes one
+// multiplication per output and round out.
+template <class R>
+__device__ __forceinline__ void gossip(f4 (&z)[R::kSlots], R &rounds, Place &p, float eta, int K) {
+  constexpr int S = R::kSlots;
+  f4 u[S];
+  p.forget();
 #pragma unroll
-    for (int r = 0; r < RPT; ++r)
-      tab[r].w[DEG / 2] = __builtin_amdgcn_readfirstlane(__float_as_uint(cm * tab[r].val(0)));
-  }
-}
-
-// K >= 1 rounds from z_{-1} = z_0 = z.  Result in z; v is scratch.  The table's weights are already scaled.
-template <int DEG, bool UNI, int RPT>
-__device__ __forceinline__ void gossip(float (&z)[RPT], float (&v)[RPT], float *lds, int w, int lane,
-                                       RowTab<DEG, UNI> (&tab)[RPT], float eta, int K) {
-  const float cm = 1.f + eta;
-  const char *lds_b = reinterpret_cast<const char *>(lds);
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) lds[(w + kWaves * r) * kCols + lane] = z[r];
+  for (int s = 0; s < S; ++s) lds_write(p.own(s), z[s]), u[s] = f4{0.f, 0.f, 0.f, 0.f};
   __syncthreads();
-  round_step<DEG, UNI, true, RPT>(z, v, lds_b, lds, w, lane, tab, cm, eta);
-  for (int r = 1; r < K; ++r) round_step<DEG, UNI, false, RPT>(z, v, lds_b, lds, w, lane, tab, cm, eta);
+  const float c = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(rounds.scale())));
+  if constexpr (S == kSlotsMax) {
+    for (int r = 0; r < K; ++r) round_step<0u, 0u>(z, u, rounds, p, c, eta);
+  } else {
+    constexpr uint32_t kSecond = second_tile(S);
+    int r = 0;
+    for (; r + 2 <= K; r += 2) {
+      round_step<0u, kSecond>(z, u, rounds, p, c, eta);
+      round_step<kSecond, 0u>(z, u, rounds, p, c, eta);
+    }
+    if (r < K) {
+      round_step<0u, kSecond>(z, u, rounds, p, c, eta);
+      // the next use of the first tile starts with writes to it; its last readers passed the barrier above
+    }
+  }
+  p.forget();
 }
 
-// Window of row i of the tile; rows >= n get an empty window (loads give 0, stores are dropped).
-template <typename E>
-__device__ __forceinline__ rsrc_t win(const E *base, int64_t tile, int64_t ld, int i, int n, uint32_t valid) {
-  return row_of(base, tile, ld, i < n ? i : 0, i < n ? valid : 0u);
+// Calls f(full, s, row offset, column, mine) for the lane's rows in turn, with the scheduler fenced in between: left
+// alone, the compiler issues every row's loads at once and spills.  `full` is a compile-time truth value.  A position
+// past the last row reads row 0 and must not store (mine = false); no list names it.
+template <class R, class F>
+__device__ __forceinline__ void each_row(const typename R::Args &ra, Place &p, bool full, int n, int64_t ld,
+                                         int64_t first, F &&f) {
+  auto go = [&](auto is_full) {
+#pragma unroll
+    for (int s = 0; s < R::kSlots; ++s) {
+      p.forget();
+      const int64_t c = first + p.col();
+      const int row = R::row(ra, p, s);
+      const bool mine = row >= 0 && row < n;
+      f(is_full, s, int64_t(mine ? row : 0) * ld, c, mine);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (full) go(std::true_type{});
+  else go(std::false_type{});
+}
+
+// Columns, rows per lane and threads of a block.  A tile takes 16 bytes per lane and row: 64 KiB at most.
+struct Geometry {
+  int cols = 0, slots = 0, threads = 0;
+  int lpr_log2() const { return __builtin_ctz(unsigned(cols)) - 2; }
+  int positions() const { return slots * threads / (cols / 4); }
+  // LDS without lists: the tile and the parked rows, or two tiles
+  size_t tile_bytes(int parked) const {
+    return slots < kSlotsMax ? second_tile(slots) + size_t(slots) * threads * 16 : size_t(slots + parked) * threads * 16;
+  }
+};
+
+inline Geometry geometry_for(int n, int cols, int slots) {
+  Geometry g;
+  const int lanes = (n + slots - 1) / slots * (cols / 4), threads = (lanes + 63) / 64 * 64;
+  if (threads <= kThreadsMax) g.cols = cols, g.slots = slots, g.threads = threads;
+  return g;
+}
+
+constexpr int kByteRows = 256;                 // rows a one-byte table can name
+constexpr size_t kLdsMax = size_t(160) << 10;  // LDS of a compute unit
+
+// A matrix is small while one row per lane leaves it no more wavefronts than the chip runs at a time (256 compute units
+// x 32 wavefronts of 64 lanes x 4 columns: 2 Mi elements).  Measured per step, K = 12, fp32, one row or two per lane
+// against four: n = 64, d = 16,000 10.6 against 21.8 us (10.6 is what a call takes the host), n = 12 irregular,
+// d = 64,000 12.8 against 39 us; from 3 Mi elements on four rows are as fast or faster (n = 48, d = 64,000, K = 2: 19
+// against 22 us).
+inline bool small_matrix(int n, int64_t d) { return int64_t(n) * ((d + 3) / 4) <= int64_t(8192) * 64; }
+
+// A small matrix: the fewest rows per lane with which a tile of at most 64 columns fits a block.  cols = 0: none does.
+inline Geometry small_geometry(int n, int cols_min) {
+  Geometry g;
+  for (int slots = 1; slots < kSlotsMax; slots *= 2)
+    for (int cols = 64; cols >= cols_min; cols /= 2) {
+      g = geometry_for(n, cols, slots);
+      if (g.cols) return g;
+    }
+  return g;
+}
+
+// Four rows per lane: as wide a tile as a block of about 256 threads holds, between 64 and 256 columns: several small
+// blocks on a compute unit drift apart and keep memory and LDS busy at once, where two blocks of 1024 threads tend to
+// load and to compute in turn (64 Mi elements, fp32, 4-regular, K = 8, tile of 64 / 128 / 256 columns: n = 64 331 /
+// 333 / 380 us, n = 128 385 / 458 us, n = 24 374 / 329 / 354 us).  Tiles of 32 columns for n > 128 (an instruction more
+// per address, row pieces of 64 to 128 bytes) measured slower (n = 256, bf16 state, K = 8: 457 against 417 us).  Up to 8
+// workers take 128 columns, which makes a block one wavefront (n = 7, bf16: 277 us against 333 us with two).
+inline Geometry byte_geometry(int n, int64_t d) {
+  Geometry g;
+  if (small_matrix(n, d)) {
+    g = small_geometry(n, 64);
+    if (g.cols) return g;
+  }
+  for (int cols = n > 4 && n <= 8 ? 128 : 256; cols >= 64; cols /= 2) {
+    g = geometry_for(n, cols, kSlotsMax);
+    if (g.cols && g.threads <= 320) break;
+  }
+  return g;
+}
+
+// The same for the lists, which go down to 32 columns (n = 100 610 against 681 us with 64, n = 256 647 against 793 us)
+// and to 16 where a tile of 32 does not fit a block.  cols = 0: n does not fit.
+inline Geometry csr_geometry(int n, int64_t d) {
+  Geometry g;
+  if (small_matrix(n, d)) {
+    g = small_geometry(n, 16);
+    if (g.cols) return g;
+  }
+  for (int cols = 256; cols >= 16; cols /= 2) {
+    g = geometry_for(n, cols, kSlotsMax);
+    if (g.cols && (g.threads <= 256 || cols == 32)) break;
+  }
+  return g;
+}
+
+// A launch that asks for more LDS than the default limit has to raise it for its kernel first.
+inline int allow_lds(const void *kernel, size_t bytes) {
+  if (bytes <= 65536) return 0;
+  return hip_rc(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
+}
+
+template <class R>
+struct RoundsTag {
+  using type = R;
+};
+
+// Calls f(RoundsTag<R>, geometry, LDS bytes, R::Args) for the table's form and the shape's geometry.
+template <class F>
+int with_rounds(const Shape &s, const LdsTable &t, F &&f) {
+  if (t.bytes_deg) {
+    const Geometry g = byte_geometry(s.n, s.d);
+    auto go = [&](auto r) {
+      using R = typename decltype(r)::type;
+      return f(r, g, g.tile_bytes(R::kParked), typename R::Args{t.byte_table, t.weight});
+    };
+    auto with_degree = [&](auto slots) {
+      constexpr int S = decltype(slots)::value;
+      switch (t.bytes_deg) {
+        case 2: return go(RoundsTag<ByteRounds<2, S>>{});
+        case 4: return go(RoundsTag<ByteRounds<4, S>>{});
+        default: return go(RoundsTag<ByteRounds<8, S>>{});
+      }
+    };
+    return g.slots == 1   ? with_degree(std::integral_constant<int, 1>{})
+           : g.slots == 2 ? with_degree(std::integral_constant<int, 2>{})
+                          : with_degree(std::integral_constant<int, 4>{});
+  }
+  if (!t.pairs) return -1;
+  const Geometry g = csr_geometry(s.n, s.d);
+  auto go = [&](auto r) {
+    using R = typename decltype(r)::type;
+    const size_t tile = g.tile_bytes(R::kParked), lists = t.max_pairs <= kListPairs && R::kSlots < kSlotsMax ? 0 : t.pair_count;
+    return f(r, g, tile + lists * 16,
+             ListArgs{t.rows, t.groups, reinterpret_cast<const f4 *>(t.pairs), t.pair_count, uint32_t(tile)});
+  };
+  const bool in_registers = t.max_pairs <= kListPairs;
+  switch (g.slots) {
+    case 1: return in_registers ? go(RoundsTag<ListRounds<1>>{}) : go(RoundsTag<CsrRounds<1>>{});
+    case 2: return in_registers ? go(RoundsTag<ListRounds<2>>{}) : go(RoundsTag<CsrRounds<2>>{});
+    default: return go(RoundsTag<CsrRounds<4>>{});
+  }
 }
 
 }  // namespace lds_tile

@@ -1,9 +1,12 @@
 // The LDS-resident kernels for an arbitrary sparse gossip matrix (layout and round arithmetic in
 // fused_generic_common.hpp): plain K-round gossip and the two forms of the DeTAG phase, and the host side that
-// packs the neighbour table.
+// packs the neighbour tables.
 //
 // Paper: Algorithm 3 (accelerated gossip) and Algorithm 2 / the matrix form in
 // the proof of Theorem 3 (phase update).
+#include <algorithm>
+#include <numeric>
+
 #include "fused_generic_common.hpp"
 
 namespace detag {
@@ -13,224 +16,179 @@ using namespace lds_tile;
 
 // mode 0: Z <- M(Z) on X.  mode 1 (ATC): X <- M(X - alpha*Y), Y <- M(Y + Gn - Go).
 // mode 2 (ALG2): X <- M(X) - alpha*M(Y), Y <- M(Y) + Gn - Go.
-template <typename ST, int DEG, bool UNI, int MODE, int RPT>
-__global__ __launch_bounds__(kThreads, 8) void fused_generic_kernel(ST *X, ST *Y, const float *__restrict__ Gn,
-                                                                    const float *__restrict__ Go, int n, int64_t d,
-                                                                    int64_t ld, const uint32_t *__restrict__ table,
-                                                                    float eta, float alpha, int K) {
-  extern __shared__ float lds[];  // 16*RPT x 64
-  // the wavefront index is uniform: say so, or the row indices and with them every
-  // table access are treated as per-lane values
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int64_t tile = int64_t(blockIdx.x) * kCols;
-  const uint32_t valid = uint32_t(d - tile < kCols ? d - tile : kCols);
-  const uint32_t so = lane * uint32_t(sizeof(ST)), fo = lane * 4u;
-  constexpr int TS = table_stride(DEG, UNI);
-  RowTab<DEG, UNI> tab[RPT];
-#pragma unroll
-  for (int r = 0; r < RPT; ++r)
-#pragma unroll
-    for (int q = 0; q < TS; ++q) tab[r].w[q] = table[(w * RPT + r) * TS + q];
-  scale_uniform_weights<DEG, UNI, RPT>(tab, 1.f + eta);
-  float cur[RPT], prev[RPT];
-  auto row = [&](int r) { return w + kWaves * r; };
-  // Loads and stores go four rows at a time with the scheduler fenced in between: left alone, the compiler
-  // issues all 16 rows' loads of every array at once, and the registers they hold decide how many blocks
-  // fit on a compute unit.  Two blocks per unit is what lets one block's memory phases run under the
-  // other's rounds.
-  constexpr int kBatch = RPT < 4 ? RPT : 4;
+template <typename ST, int MODE, class R>
+__global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(ST *X, ST *Y, const float *__restrict__ Gn,
+                                                                       const float *__restrict__ Go, int n, int64_t d,
+                                                                       int64_t ld, int lpr_log2, typename R::Args ra,
+                                                                       float eta, float alpha, int K) {
+  Place p{threadIdx.x, blockDim.x, lpr_log2};
+  const int64_t first = fused::xcd_tile(blockIdx.x, gridDim.x) << (lpr_log2 + 2);
+  const bool full = first + (int64_t(4) << lpr_log2) <= d;
+  f4 z[R::kSlots];
+  Waiting<R> v;
+  auto rows = [&](auto f) { each_row<R>(ra, p, full, n, ld, first, f); };
+  R rounds;  // set up after the first loads: until then its registers are free for them
   if constexpr (MODE == 0) {
-#pragma unroll
-    for (int r0 = 0; r0 < RPT; r0 += kBatch) {
-#pragma unroll
-      for (int r = r0; r < r0 + kBatch; ++r) cur[r] = buf_load<ST>(win(X, tile, ld, row(r), n, valid), so);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) buf_store<ST>(win(X, tile, ld, row(r), n, valid), so, cur[r]);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool) { z[s] = load4<F>(X, off, c, d); });
+    rounds.init(ra, p, eta);
+    gossip(z, rounds, p, eta, K);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(X, off, c, d, z[s]); });
   } else if constexpr (MODE == 1) {
     // every input is read once: the second gossip's input Y + Gn - Go waits in registers under the first
-    float v0[RPT];
-#pragma unroll
-    for (int r0 = 0; r0 < RPT; r0 += kBatch) {
-      float x[kBatch], y[kBatch], gn[kBatch], go[kBatch];
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q) {
-        x[q] = buf_load<ST>(win(X, tile, ld, row(r0 + q), n, valid), so);
-        y[q] = buf_load<ST>(win(Y, tile, ld, row(r0 + q), n, valid), so);
-        gn[q] = buf_load<float>(win(Gn, tile, ld, row(r0 + q), n, valid), fo);
-        go[q] = buf_load<float>(win(Go, tile, ld, row(r0 + q), n, valid), fo);
-      }
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q) {
-        cur[r0 + q] = fmaf(-alpha, y[q], x[q]);
-        v0[r0 + q] = y[q] + gn[q] - go[q];
-        pin_vgpr(v0[r0 + q]);  // the sum now, not its three operands carried through the rounds
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-      buf_store<ST>(win(X, tile, ld, row(r), n, valid), so, cur[r]);
-      cur[r] = v0[r];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) buf_store<ST>(win(Y, tile, ld, row(r), n, valid), so, cur[r]);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool) {
+      const f4 x = load4<F>(X, off, c, d), y = load4<F>(Y, off, c, d), gn = load4<F>(Gn, off, c, d), go = load4<F>(Go, off, c, d);
+      z[s] = fma4(-alpha, y, x);
+      f4 t = y + gn - go;
+      pin4(t);  // the sum now, not its three operands carried through the rounds
+      v.put(p, s, t);
+    });
+    rounds.init(ra, p, eta);
+    gossip(z, rounds, p, eta, K);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+      if (mine) store4<F>(X, off, c, d, z[s]);
+      z[s] = v.get(p, s);
+    });
+    gossip(z, rounds, p, eta, K);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
   } else {
     // M(Y) first: both outputs need it
-#pragma unroll
-    for (int r0 = 0; r0 < RPT; r0 += kBatch) {
-#pragma unroll
-      for (int r = r0; r < r0 + kBatch; ++r) cur[r] = buf_load<ST>(win(Y, tile, ld, row(r), n, valid), so);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-    float v[RPT];
-#pragma unroll
-    for (int r0 = 0; r0 < RPT; r0 += kBatch) {
-#pragma unroll
-      for (int r = r0; r < r0 + kBatch; ++r) {
-        v[r] = cur[r];
-        cur[r] = buf_load<ST>(win(X, tile, ld, row(r), n, valid), so);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool) { z[s] = load4<F>(Y, off, c, d); });
+    rounds.init(ra, p, eta);
+    gossip(z, rounds, p, eta, K);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool) {
+      v.put(p, s, z[s]);
+      z[s] = load4<F>(X, off, c, d);
+    });
+    gossip(z, rounds, p, eta, K);
+    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+      const f4 gn = load4<F>(Gn, off, c, d), go = load4<F>(Go, off, c, d), my = v.get(p, s);
+      if (mine) {
+        store4<F>(X, off, c, d, fma4(-alpha, my, z[s]));
+        store4<F>(Y, off, c, d, my + gn - go);
       }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-#pragma unroll
-    for (int r0 = 0; r0 < RPT; r0 += kBatch) {
-      float gn[kBatch], go[kBatch];
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q) {
-        gn[q] = buf_load<float>(win(Gn, tile, ld, row(r0 + q), n, valid), fo);
-        go[q] = buf_load<float>(win(Go, tile, ld, row(r0 + q), n, valid), fo);
-      }
-#pragma unroll
-      for (int q = 0; q < kBatch; ++q) {
-        buf_store<ST>(win(X, tile, ld, row(r0 + q), n, valid), so, fmaf(-alpha, v[r0 + q], cur[r0 + q]));
-        buf_store<ST>(win(Y, tile, ld, row(r0 + q), n, valid), so, v[r0 + q] + gn[q] - go[q]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    });
   }
 }
 
-
-template <typename ST, int DEG, bool UNI, int RPT>
-int launch_r(const Shape &s, const uint32_t *table, int mode, void *X, void *Y, const float *Gn, const float *Go,
-             float alpha, int K, float eta, void *stream) {
-  const dim3 grid(ceil_div_i64(s.d, kCols));
-  const size_t lds_bytes = size_t(kWaves) * RPT * kCols * sizeof(float);  // 4 KiB per row of a wavefront
-  auto st = static_cast<hipStream_t>(stream);
-  ST *x = static_cast<ST *>(X), *y = static_cast<ST *>(Y);
-#define DETAG_MODE(M)                                                                                             \
-  fused_generic_kernel<ST, DEG, UNI, M, RPT><<<grid, kThreads, lds_bytes, st>>>(x, y, Gn, Go, s.n, s.d, s.ld, table, \
-                                                                                eta, alpha, K)
+template <typename ST, class R>
+int launch_r(const Shape &s, const Geometry &g, size_t lds, const typename R::Args &ra, int mode, void *X, void *Y,
+             const float *Gn, const float *Go, float alpha, int K, float eta, void *stream) {
+  const dim3 grid(ceil_div_i64(s.d, g.cols));
+  auto go = [&](auto *kernel) -> int {
+    if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
+    kernel<<<grid, g.threads, lds, static_cast<hipStream_t>(stream)>>>(static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go,
+                                                                       s.n, s.d, s.ld, g.lpr_log2(), ra, eta, alpha, K);
+    return hip_rc(hipGetLastError());
+  };
   switch (mode) {
-    case 0: DETAG_MODE(0); break;
-    case 1: DETAG_MODE(1); break;
-    case 2: DETAG_MODE(2); break;
-    default: return hip_rc(hipErrorInvalidValue);
+    case 0: return go(&fused_generic_kernel<ST, 0, R>);
+    case 1: return go(&fused_generic_kernel<ST, 1, R>);
+    case 2: return go(&fused_generic_kernel<ST, 2, R>);
   }
-#undef DETAG_MODE
-  return hip_rc(hipGetLastError());
-}
-
-template <typename ST, int DEG, bool UNI>
-int launch_k(const Shape &s, const uint32_t *table, int mode, void *X, void *Y, const float *Gn, const float *Go,
-             float alpha, int K, float eta, void *stream) {
-#define DETAG_RPT(R) \
-  case R: return launch_r<ST, DEG, UNI, R>(s, table, mode, X, Y, Gn, Go, alpha, K, eta, stream)
-  switch (rows_per_wave(s.n)) {
-    DETAG_RPT(1);
-    DETAG_RPT(2);
-    DETAG_RPT(4);
-    DETAG_RPT(8);
-    DETAG_RPT(16);
-  }
-#undef DETAG_RPT
-  return -1;
-}
-
-template <typename ST>
-int launch_t(const Shape &s, const uint32_t *table, int deg, bool uni, int mode, void *X, void *Y, const float *Gn,
-             const float *Go, float alpha, int K, float eta, void *stream) {
-#define DETAG_CASE(DG)                                                                                   \
-  case DG:                                                                                               \
-    return uni ? launch_k<ST, DG, true>(s, table, mode, X, Y, Gn, Go, alpha, K, eta, stream)              \
-               : launch_k<ST, DG, false>(s, table, mode, X, Y, Gn, Go, alpha, K, eta, stream)
-  switch (deg) {
-    DETAG_CASE(2);
-    DETAG_CASE(4);
-    DETAG_CASE(8);
-  }
-#undef DETAG_CASE
-  return -1;
-}
-
-uint32_t f32_bits(float f) {
-  uint32_t u;
-  static_assert(sizeof u == sizeof f, "");
-  __builtin_memcpy(&u, &f, sizeof u);
-  return u;
+  return hip_rc(hipErrorInvalidValue);
 }
 
 }  // namespace
 
-bool build_ell(const HostW &W, EllHost &out) {
+int launch_fused_generic(const Shape &s, const LdsTable &t, int mode, void *X, void *Y, const float *Gn, const float *Go,
+                         float alpha, int K, float eta, void *stream) {
+  if (K < 1) return -1;
+  return with_rounds(s, t, [&](auto r, const Geometry &g, size_t lds, const auto &ra) {
+    using R = typename decltype(r)::type;
+    return s.bf16 ? launch_r<bf16_t, R>(s, g, lds, ra, mode, X, Y, Gn, Go, alpha, K, eta, stream)
+                  : launch_r<float, R>(s, g, lds, ra, mode, X, Y, Gn, Go, alpha, K, eta, stream);
+  });
+}
+
+bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
   const int n = W.n;
-  if (n > kRowsMax) return false;
   int maxdeg = 0;
-  bool uniform = true;
+  bool one_weight = true, have = false;
+  float weight = 0.f;
   for (int i = 0; i < n; ++i) {
     int cnt = 0;
-    float first = 0.f;
     for (int k = W.rowptr[i]; k < W.rowptr[i + 1]; ++k) {
       if (W.colidx[k] == i) continue;
       const float v = float(W.vals[k]);
-      if (cnt == 0) first = v;
-      else if (v != first) uniform = false;
+      if (!have) weight = v, have = true;
+      else if (v != weight) one_weight = false;
       ++cnt;
     }
-    maxdeg = cnt > maxdeg ? cnt : maxdeg;
+    maxdeg = std::max(maxdeg, cnt);
   }
-  if (maxdeg > 8) return false;
-  out.deg = maxdeg <= 2 ? 2 : maxdeg <= 4 ? 4 : 8;
-  out.uniform = uniform;
-  const int ts = table_stride(out.deg, uniform);
-  const int rpt = rows_per_wave(n), slots = kWaves * rpt;
-  out.table.assign(size_t(slots) * ts, 0u);
-  for (int i = 0; i < slots; ++i) {
-    uint32_t *t = &out.table[size_t((i % kWaves) * rpt + i / kWaves) * ts];
-    const uint32_t own = uint32_t(i) * kCols * 4u;  // byte offset of row i in LDS (< 65536)
-    uint32_t offs[8];
-    float vals[8];
-    for (int k = 0; k < 8; ++k) offs[k] = own, vals[k] = 0.f;  // padding: weight 0 (or a repeat, below), a valid row
-    int cnt = 0;
-    if (i < n)
-      for (int k = W.rowptr[i]; k < W.rowptr[i + 1]; ++k)
-        if (W.colidx[k] != i) offs[cnt] = uint32_t(W.colidx[k]) * kCols * 4u, vals[cnt] = float(W.vals[k]), ++cnt;
-    for (int k = 0; k < out.deg; k += 2) t[k / 2] = offs[k] | (offs[k + 1] << 16);
-    if (uniform) t[out.deg / 2] = f32_bits(vals[0]);  // one weight for the row; padded entries repeat the row itself
-    else
-      for (int k = 0; k < out.deg; ++k) t[out.deg / 2 + k] = f32_bits(vals[k]);
+  out = LdsTableHost{};
+  // a small matrix of more workers than two rows per lane of a 64-column tile hold (n > 128) is better off with the
+  // lists, whose tiles go down to 16 columns: n = 200, d = 4,000, K = 12 16 against 33 us
+  const bool byte_form = n <= kByteRows && maxdeg <= 8 && one_weight &&
+                         (!small_matrix(n, d) || byte_geometry(n, d).slots < kSlotsMax);
+  if (byte_form) {
+    out.bytes_deg = maxdeg <= 2 ? 2 : maxdeg <= 4 ? 4 : 8;
+    out.weight = weight;
+    const int words = out.bytes_deg <= 4 ? 1 : 2;
+    out.byte_table.assign(size_t(kByteRows) * words, 0u);
+    for (int i = 0; i < kByteRows; ++i) {
+      uint8_t nb[8];
+      for (uint8_t &b : nb) b = uint8_t(i);  // a missing neighbour is the row itself: difference zero
+      int cnt = 0;
+      if (i < n)
+        for (int k = W.rowptr[i]; k < W.rowptr[i + 1]; ++k)
+          if (W.colidx[k] != i) nb[cnt++] = uint8_t(W.colidx[k]);
+      for (int k = 0; k < 4 * words; ++k) out.byte_table[size_t(i) * words + k / 4] |= uint32_t(nb[k]) << (8 * (k % 4));
+    }
+    return true;
+  }
+  const Geometry g = csr_geometry(n, d);
+  if (g.cols == 0) return false;
+  const int positions = g.positions(), lpr = g.cols / 4, rows_per_wave = 64 / lpr, waves = g.threads / 64;
+  const int per_slot = g.threads / lpr;
+  // rows by falling degree; slot by slot, every other slot from the last wavefront to the first, so that no wavefront
+  // gets the longest lists of every slot
+  std::vector<int> order(n);
+  std::iota(order.begin(), order.end(), 0);
+  auto degree = [&](int i) { return W.rowptr[i + 1] - W.rowptr[i]; };
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return degree(a) > degree(b); });
+  out.rows.assign(positions, -1);
+  std::vector<int> position(n);
+  int next = 0;
+  for (int s = 0; s < g.slots && next < n; ++s)
+    for (int q = 0; q < waves && next < n; ++q) {
+      const int w = s % 2 ? waves - 1 - q : q;
+      for (int k = 0; k < rows_per_wave && next < n; ++k) {
+        const int p = s * per_slot + w * rows_per_wave + k;
+        out.rows[p] = order[next], position[order[next]] = p, ++next;
+      }
+    }
+  auto offset = [&](int p) { return uint32_t(p) * g.cols * 4u; };
+  for (int w = 0; w < waves; ++w)
+    for (int s = 0; s < g.slots; ++s) {
+      const int p0 = s * per_slot + w * rows_per_wave;
+      std::vector<std::vector<std::pair<uint32_t, float>>> lists(rows_per_wave);
+      size_t pairs = 0;
+      for (int k = 0; k < rows_per_wave; ++k) {
+        const int i = out.rows[p0 + k];
+        if (i >= 0)
+          for (int t = W.rowptr[i]; t < W.rowptr[i + 1]; ++t)
+            if (W.colidx[t] != i) lists[k].push_back({offset(position[W.colidx[t]]), float(W.vals[t])});
+        pairs = std::max(pairs, (lists[k].size() + 1) / 2);
+      }
+      out.groups.push_back(uint32_t(out.pairs.size() / 4)), out.groups.push_back(uint32_t(pairs));
+      out.max_pairs = std::max(out.max_pairs, int(pairs));
+      for (size_t q = 0; q < pairs; ++q)
+        for (int k = 0; k < rows_per_wave; ++k)
+          for (size_t e = 2 * q; e < 2 * q + 2; ++e) {
+            const bool there = e < lists[k].size();
+            out.pairs.push_back(there ? lists[k][e].first : offset(p0 + k));  // or the row itself, weight 0
+            const float v = there ? lists[k][e].second : 0.f;
+            uint32_t bits;
+            __builtin_memcpy(&bits, &v, sizeof bits);
+            out.pairs.push_back(bits);
+          }
+    }
+  if (g.tile_bytes(0) + out.pairs.size() * 4 > kLdsMax) {
+    out = LdsTableHost{};
+    return false;
   }
   return true;
-}
-
-bool fused_generic_available(const HostW &W, const Shape &) {
-  EllHost e;
-  return build_ell(W, e);
-}
-
-int launch_fused_generic(const Shape &s, const HostW &, const DevCsr &w, int mode, void *X, void *Y, const float *Gn,
-                         const float *Go, float alpha, int K, float eta, void *stream) {
-  if (K < 1 || !w.ell_table) return -1;
-  return s.bf16 ? launch_t<bf16_t>(s, w.ell_table, w.ell_deg, w.ell_uniform, mode, X, Y, Gn, Go, alpha, K, eta, stream)
-                : launch_t<float>(s, w.ell_table, w.ell_deg, w.ell_uniform, mode, X, Y, Gn, Go, alpha, K, eta, stream);
 }
 
 }  // namespace detag

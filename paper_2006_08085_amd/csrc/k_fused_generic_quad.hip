@@ -16,137 +16,77 @@ using namespace lds_tile;
 // G updated in place (row by row, the old value read just before the new one is stored).  Same three arrays
 // per lane as the plain ATC phase: the gradient is consumed and stored inside the load loop.  Per element it
 // reads X, Y (state type), G, b (fp32) and writes X, Y, G, where the gradient kernel followed by the phase moves
-// X twice more and the gradient three times.  The counter-based noise shares one Philox block among the four
-// lanes of a quad when a wavefront has at least four rows (see quad_transpose); with fewer rows per wavefront
-// every lane evaluates the block of its own row and keeps one of the four normals.
-template <typename ST, int DEG, bool UNI, int RPT, bool HPW>
-__global__ __launch_bounds__(kThreads, 8) void fused_generic_quadratic_kernel(
+// X twice more and the gradient three times.  A lane's four columns of a row are one Philox block of the
+// counter-based noise.
+template <typename ST, bool HPW, class R>
+__global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadratic_kernel(
     ST *X, ST *Y, float *G, const float *__restrict__ h, const float *__restrict__ b, int n, int64_t d, int64_t ld,
-    const uint32_t *__restrict__ table, float eta, float alpha, int K, float sigma, uint32_t seed_lo, uint32_t seed_hi,
+    int lpr_log2, typename R::Args ra, float eta, float alpha, int K, float sigma, uint32_t seed_lo, uint32_t seed_hi,
     uint32_t step) {
-  extern __shared__ float lds[];  // 16*RPT x 64
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int64_t tile = int64_t(blockIdx.x) * kCols;
-  const uint32_t valid = uint32_t(d - tile < kCols ? d - tile : kCols);
-  const uint32_t so = lane * uint32_t(sizeof(ST)), fo = lane * 4u;
-  const unsigned j = lane & 3u;
-  const uint64_t q = uint64_t(tile + lane) >> 2;  // Philox block = 4 columns; tiles start at multiples of 64
-  constexpr int TS = table_stride(DEG, UNI);
-  RowTab<DEG, UNI> tab[RPT];
-#pragma unroll
-  for (int r = 0; r < RPT; ++r)
-#pragma unroll
-    for (int t = 0; t < TS; ++t) tab[r].w[t] = table[(w * RPT + r) * TS + t];
-  scale_uniform_weights<DEG, UNI, RPT>(tab, 1.f + eta);
-  const float hc = HPW ? 0.f : buf_load<float>(make_rsrc(h + tile, valid * 4u), fo);
-  float cur[RPT], prev[RPT], v0[RPT];
-  auto row = [&](int r) { return w + kWaves * r; };
-  constexpr int kBatch = RPT < 4 ? RPT : 4;
-#pragma unroll
-  for (int r0 = 0; r0 < RPT; r0 += kBatch) {
-    // the batch's noise first, its loads after: generated under the loads, the Philox state and the sixteen
-    // values in flight are live together and the kernel no longer fits two blocks per compute unit without spills
-    float z[4] = {0.f, 0.f, 0.f, 0.f};
+  Place p{threadIdx.x, blockDim.x, lpr_log2};
+  const int64_t first = fused::xcd_tile(blockIdx.x, gridDim.x) << (lpr_log2 + 2);
+  const bool full = first + (int64_t(4) << lpr_log2) <= d;
+  f4 z[R::kSlots];
+  Waiting<R> v;
+  auto rows = [&](auto f) { each_row<R>(ra, p, full, n, ld, first, f); };
+  rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+    // the row's noise first, its loads after: generated under the loads, the Philox state and the values in flight
+    // are live together and the kernel does not fit its registers
+    f4 noise = {0.f, 0.f, 0.f, 0.f};
     if (sigma != 0.f) {
-      if constexpr (kBatch == 4) {  // lane j of a quad: the block of row r0 + j, then a 4x4 transpose
-        normal4(q, uint32_t(w + kWaves * (r0 + int(j))), step, seed_lo, seed_hi, z);
-        quad_transpose(z, j);
-      } else {
+      float t[4];
+      normal4(uint64_t(c) >> 2, uint32_t(R::row(ra, p, s)), step, seed_lo, seed_hi, t);
 #pragma unroll
-        for (int t = 0; t < kBatch; ++t) {
-          float zz[4];
-          normal4(q, uint32_t(row(r0 + t)), step, seed_lo, seed_hi, zz);
-          z[t] = j == 0 ? zz[0] : j == 1 ? zz[1] : j == 2 ? zz[2] : zz[3];
-        }
-      }
+      for (int e = 0; e < 4; ++e) noise[e] = t[e];
     }
     __builtin_amdgcn_sched_barrier(0);
-    float x[kBatch], y[kBatch], go[kBatch], bb[kBatch], hh[HPW ? kBatch : 1];
+    const f4 x = load4<F>(X, off, c, d), bb = load4<F>(b, off, c, d), hh = load4<F>(h, HPW ? off : 0, c, d);
+    f4 g;
 #pragma unroll
-    for (int t = 0; t < kBatch; ++t) {
-      x[t] = buf_load<ST>(win(X, tile, ld, row(r0 + t), n, valid), so);
-      y[t] = buf_load<ST>(win(Y, tile, ld, row(r0 + t), n, valid), so);
-      go[t] = buf_load<float>(win(G, tile, ld, row(r0 + t), n, valid), fo);
-      bb[t] = buf_load<float>(win(b, tile, ld, row(r0 + t), n, valid), fo);
-      if constexpr (HPW) hh[t] = buf_load<float>(win(h, tile, ld, row(r0 + t), n, valid), fo);
-    }
-#pragma unroll
-    for (int t = 0; t < kBatch; ++t) {
-      const float g = fmaf(sigma, z[t], (HPW ? hh[t] : hc) * (x[t] - bb[t]));
-      cur[r0 + t] = fmaf(-alpha, y[t], x[t]);
-      v0[r0 + t] = y[t] + g - go[t];
-      pin_vgpr(v0[r0 + t]);
-      buf_store<float>(win(G, tile, ld, row(r0 + t), n, valid), fo, g);
-    }
+    for (int e = 0; e < 4; ++e) g[e] = fmaf(sigma, noise[e], hh[e] * (x[e] - bb[e]));
     __builtin_amdgcn_sched_barrier(0);
-  }
-  gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) {
-    buf_store<ST>(win(X, tile, ld, row(r), n, valid), so, cur[r]);
-    cur[r] = v0[r];
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  gossip<DEG, UNI, RPT>(cur, prev, lds, w, lane, tab, eta, K);
-#pragma unroll
-  for (int r = 0; r < RPT; ++r) buf_store<ST>(win(Y, tile, ld, row(r), n, valid), so, cur[r]);
-}
-
-template <typename ST, int DEG, bool UNI>
-int launch_q(const Shape &s, const uint32_t *table, void *X, void *Y, float *G, const float *h, bool hpw, const float *b,
-             float alpha, int K, float eta, float sigma, uint64_t seed, uint32_t step, void *stream) {
-  const dim3 grid(ceil_div_i64(s.d, kCols));
-  auto st = static_cast<hipStream_t>(stream);
-  ST *x = static_cast<ST *>(X), *y = static_cast<ST *>(Y);
-  const uint32_t slo = uint32_t(seed & 0xffffffffu), shi = uint32_t(seed >> 32);
-#define DETAG_QUAD(R, HPW)                                                                                          \
-  fused_generic_quadratic_kernel<ST, DEG, UNI, R, HPW>                                                              \
-      <<<grid, kThreads, size_t(kWaves) * R * kCols * sizeof(float), st>>>(x, y, G, h, b, s.n, s.d, s.ld, table, eta, \
-                                                                           alpha, K, sigma, slo, shi, step)
-#define DETAG_RPT(R)                                            \
-  case R:                                                       \
-    if (hpw) DETAG_QUAD(R, true); else DETAG_QUAD(R, false);    \
-    break
-  switch (rows_per_wave(s.n)) {
-    DETAG_RPT(1);
-    DETAG_RPT(2);
-    DETAG_RPT(4);
-    DETAG_RPT(8);
-    DETAG_RPT(16);
-    default: return -1;
-  }
-#undef DETAG_RPT
-#undef DETAG_QUAD
-  return hip_rc(hipGetLastError());
-}
-
-template <typename ST>
-int launch_qt(const Shape &s, const uint32_t *table, int deg, bool uni, void *X, void *Y, float *G, const float *h,
-              bool hpw, const float *b, float alpha, int K, float eta, float sigma, uint64_t seed, uint32_t step,
-              void *stream) {
-#define DETAG_CASE(DG)                                                                                          \
-  case DG:                                                                                                      \
-    return uni ? launch_q<ST, DG, true>(s, table, X, Y, G, h, hpw, b, alpha, K, eta, sigma, seed, step, stream)  \
-               : launch_q<ST, DG, false>(s, table, X, Y, G, h, hpw, b, alpha, K, eta, sigma, seed, step, stream)
-  switch (deg) {
-    DETAG_CASE(2);
-    DETAG_CASE(4);
-    DETAG_CASE(8);
-  }
-#undef DETAG_CASE
-  return -1;
+    const f4 y = load4<F>(Y, off, c, d), go = load4<F>(G, off, c, d);
+    z[s] = fma4(-alpha, y, x);
+    f4 t = y + g - go;
+    pin4(t);
+    v.put(p, s, t);
+    if (mine) store4<F>(G, off, c, d, g);
+  });
+  R rounds;  // set up after the loads: until then its registers are free for them
+  rounds.init(ra, p, eta);
+  gossip(z, rounds, p, eta, K);
+  rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+    if (mine) store4<F>(X, off, c, d, z[s]);
+    z[s] = v.get(p, s);
+  });
+  gossip(z, rounds, p, eta, K);
+  rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
 }
 
 }  // namespace
 
-int launch_fused_generic_quadratic(const Shape &s, const DevCsr &w, void *X, void *Y, float *G, const float *h,
+int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, void *Y, float *G, const float *h,
                                    bool h_per_worker, const float *b, float alpha, int K, float eta, float sigma,
                                    uint64_t seed, uint32_t step, void *stream) {
-  if (K < 1 || !w.ell_table) return -1;
-  return s.bf16 ? launch_qt<bf16_t>(s, w.ell_table, w.ell_deg, w.ell_uniform, X, Y, G, h, h_per_worker, b, alpha, K, eta,
-                                    sigma, seed, step, stream)
-                : launch_qt<float>(s, w.ell_table, w.ell_deg, w.ell_uniform, X, Y, G, h, h_per_worker, b, alpha, K, eta,
-                                   sigma, seed, step, stream);
+  if (K < 1) return -1;
+  return with_rounds(s, t, [&](auto r, const Geometry &g, size_t lds, const auto &ra) {
+    using R = typename decltype(r)::type;
+    auto go = [&](auto *kernel, auto *x, auto *y) -> int {
+      if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
+      kernel<<<dim3(ceil_div_i64(s.d, g.cols)), g.threads, lds, static_cast<hipStream_t>(stream)>>>(
+          x, y, G, h, b, s.n, s.d, s.ld, g.lpr_log2(), ra, eta, alpha, K, sigma, uint32_t(seed & 0xffffffffu),
+          uint32_t(seed >> 32), step);
+      return hip_rc(hipGetLastError());
+    };
+    if (s.bf16) {
+      auto *x = static_cast<bf16_t *>(X), *y = static_cast<bf16_t *>(Y);
+      return h_per_worker ? go(&fused_generic_quadratic_kernel<bf16_t, true, R>, x, y)
+                          : go(&fused_generic_quadratic_kernel<bf16_t, false, R>, x, y);
+    }
+    auto *x = static_cast<float *>(X), *y = static_cast<float *>(Y);
+    return h_per_worker ? go(&fused_generic_quadratic_kernel<float, true, R>, x, y)
+                        : go(&fused_generic_quadratic_kernel<float, false, R>, x, y);
+  });
 }
 
 }  // namespace detag

@@ -1,0 +1,82 @@
+"""The LDS-resident kernels at the edges of their forms: the last matrix that counts as small and the first that does
+not (n * ceil(d/4) = 2^19), ragged widths and odd pitches, worker counts around a full set of rows per lane, one weight
+for the whole matrix and weights of its own, even and odd K, against the fp64 oracle on sampled columns."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2006_08085_amd as D
+from oracle import gossip as OG, noise as ON, objectives as OO, topology as OT
+from workloads import generate as gen
+from tests.gpu_util import DEV, SENTINEL, _built  # noqa: F401
+from tests.util import TOL_BF16, TOL_F32, amax, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _graph(kind, n):
+    if kind == "rr":
+        return gen.edges_random_regular(n, 4, seed=n)
+    if kind == "ring":
+        return gen.edges_ring(n)
+    if kind == "rr8":
+        return gen.edges_random_regular(n, 8, seed=n)
+    rng = np.random.default_rng(n)                       # a path and random edges, at most 8 neighbours
+    e, deg = {(i, i + 1) for i in range(n - 1)}, np.full(n, 2)
+    while len(e) < 2 * n:
+        a, b = sorted(rng.integers(0, n, 2).tolist())
+        if a != b and (a, b) not in e and deg[a] < 8 and deg[b] < 8:
+            e.add((a, b)); deg[a] += 1; deg[b] += 1
+    return np.array(sorted(e), dtype=np.int64)
+
+
+def _matrix(n, d, ld, seed, dtype=torch.float32):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    t = torch.full((n, ld), SENTINEL, device=DEV)
+    t[:, :d].normal_(generator=g)
+    return t.to(dtype)
+
+
+def _cols(t, cols):
+    return t[:, torch.as_tensor(cols, device=DEV)].double().cpu().numpy()
+
+
+@pytest.mark.parametrize("n,kind", [(3, "ring"), (5, "ring"), (8, "irregular"), (9, "rr"), (20, "ring"), (31, "irregular"),
+                                    (64, "rr"), (65, "rr8"), (100, "irregular"), (129, "rr"), (256, "irregular"), (256, "rr")])
+@pytest.mark.parametrize("extra,pad,dtype,K", [(0, 0, "f32", 3), (0, 3, "bf16", 4), (1, 2, "f32", 4), (2, 1, "bf16", 3), (7, 0, "f32", 5)])
+def test_forms_and_edges(n, kind, extra, pad, dtype, K):
+    # d: 4-column groups times n is 2^19 at most for extra = 0 (small: one or two rows per lane), more otherwise (four)
+    d = (1 << 19) // n * 4 + 5 * extra
+    ld = d + pad
+    bf = dtype == "bf16"
+    sd, tol = (torch.bfloat16, TOL_BF16) if bf else (torch.float32, TOL_F32)
+    e = _graph(kind, n)
+    W = OT.mixing_matrix(n, e, "metropolis")
+    topo = D.Topology.ring() if kind == "ring" else D.Topology.from_edges(e, D.DETAG_W_METROPOLIS)
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if bf else D.DETAG_F32)
+    assert ctx.kernel() == D.DETAG_KERNEL_LDS_TILE
+    eta, alpha, sigma, seed = 0.35, 0.2, 0.1, 11
+    rng = np.random.default_rng(5)
+    cols = np.unique(np.concatenate([np.arange(min(d, 40)), np.arange(max(0, d - 300), d), rng.integers(0, d, 60)]))
+    X, Y, Gn, Go, b = (_matrix(n, d, ld, k, sd if k < 2 else torch.float32) for k in range(5))
+    h = torch.rand(ld, device=DEV)
+    x, y, gn, go, bb, hh = (_cols(t, cols) for t in (X, Y, Gn, Go, b, h[None]))
+    S = amax(x, y, gn, go)
+    Z = X.clone()
+    ctx.gossip_accel(Z, K, eta)
+    assert rel_err(_cols(Z, cols), OG.accelerated_gossip(x, W, K, eta), S) < tol
+    for variant, code in (("atc", D.DETAG_VARIANT_ATC), ("alg2", D.DETAG_VARIANT_ALG2)):
+        Xs, Ys = X.clone(), Y.clone()
+        ctx.step(Xs, Ys, Gn, Go, alpha, K, eta, code)
+        xr, yr = OG.detag_step(x, y, gn, go, W, alpha, K, eta, variant)
+        assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol, variant
+    Xs, Ys, G = X.clone(), Y.clone(), Go.clone()
+    ctx.step_quadratic(Xs, Ys, G, h, b, alpha, K, sigma=sigma, seed=seed, step=2, eta=eta)
+    g = OO.grad_quadratic_diag(x, hh[0], bb, ON.normal_noise(seed, 2, n, cols), sigma)
+    xr, yr = OG.detag_step(x, y, g, go, W, alpha, K, eta)
+    assert rel_err(_cols(G, cols), g, amax(g)) < TOL_F32
+    assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol
+    for t in (Z, Xs, Ys, G):
+        assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))   # the padding is never written
+    ctx.close()
