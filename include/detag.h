@@ -181,9 +181,13 @@ detag_status detag_set_path(detag_ctx *ctx, int32_t path /* detag_path */);
  *     0.6 ms.  W with one off-diagonal weight (regular graphs) is the fast
  *     form; with weights of its own a round costs about 1.7 times as much.
  *   DETAG_KERNEL_PER_ROUND  everything else (n > 256, a worker with more than 8
- *     neighbours), or DETAG_PATH_PER_ROUND: one launch per round, 12 B per
- *     element and round (24 + 8*(3K-1) B per element and phase: 208 B at K = 8,
- *     nine times the on-chip families).
+ *     neighbours), or DETAG_PATH_PER_ROUND.  With DETAG_PATH_PER_ROUND one launch
+ *     per round, 12 B per element and round (24 + 8*(3K-1) B per element and
+ *     phase: 208 B at K = 8, nine times the on-chip families).  With
+ *     DETAG_PATH_AUTO detag_gossip_accel and detag_step still run their K
+ *     rounds in one launch where a tile of all workers and their neighbour
+ *     lists fit the LDS of a compute unit (n <= 1024 and, say, 100 neighbours
+ *     each at n = 100); detag_step_quadratic does not exist there.
  *   DETAG_KERNEL_DENSE  only after detag_set_path(DETAG_PATH_DENSE).
  */
 typedef enum {

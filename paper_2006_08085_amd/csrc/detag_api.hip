@@ -23,6 +23,7 @@ struct detag_ctx {
   float *d_vals = nullptr;
   LdsTable lds;                           // neighbour table of the LDS-resident kernels; its arrays in one allocation
   void *d_lds = nullptr;
+  bool has_lds = false;                   // the table exists: a tile of n rows and the lists fit a compute unit
   bool fused_generic = false;             // the LDS-resident family serves this W: n <= 256, at most 8 neighbours
   // per-round path: n x ld fp32 matrices; [0],[1] hold z_r between rounds, [2],[3] the widened copies of bf16 X and Y
   void *scratch[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -169,9 +170,9 @@ hipError_t upload_lds_table(detag_ctx *ctx, const LdsTableHost &t) {
   return hipSuccess;
 }
 
-enum Chosen { kPerRound, kFusedStructured, kFusedGeneric, kDense };
+enum Chosen { kPerRound, kFusedStructured, kFusedGeneric, kOnChipLists, kDense };
 
-detag_status choose_path(const detag_ctx *ctx, Chosen *out) {
+detag_status choose_path(const detag_ctx *ctx, int K, Chosen *out) {
   const bool fs = fused_structured_available(ctx->W), fg = ctx->fused_generic;
   if (ctx->path == DETAG_PATH_PER_ROUND) return *out = kPerRound, DETAG_OK;
   if (ctx->path == DETAG_PATH_DENSE) return *out = kDense, DETAG_OK;
@@ -179,7 +180,12 @@ detag_status choose_path(const detag_ctx *ctx, Chosen *out) {
   if (fg) return *out = kFusedGeneric, DETAG_OK;
   if (ctx->path == DETAG_PATH_FUSED)
     return set_err(ctx, DETAG_EUNSUPPORTED, "no fused kernel for this topology and n");
-  return *out = kPerRound, DETAG_OK;
+  // More workers or neighbours than the LDS family is offered for, but lists and tile fit a compute unit: the rounds of
+  // a phase run there all the same (300 workers, 4 neighbours, d = 100,000: K = 1 450 -> 160 us, K = 8 2050 -> 320 us).
+  // Not for one or two rounds of more than 512 workers on a matrix too small to fill the chip, where reading the
+  // lists is most of the work (1000 workers, d = 1,000, K = 2: 31 us with a launch per round, 47 us so).
+  const bool few = K <= 2 && ctx->shape.n > 512 && int64_t(ctx->shape.n) * ctx->shape.d <= (int64_t(1) << 21);
+  return *out = ctx->has_lds && !few ? kOnChipLists : kPerRound, DETAG_OK;
 }
 
 Shape as_f32(Shape s) { return s.bf16 = false, s; }
@@ -317,7 +323,10 @@ detag_status detag_create(const detag_topology *topo, int32_t n, int64_t d, int6
   LdsTableHost table;
   try {
     st = build_gossip_matrix(topo, n, ctx->W, err);
-    if (st == DETAG_OK) ctx->fused_generic = lds_family_serves(ctx->W) && build_lds_table(ctx->W, d, table);
+    if (st == DETAG_OK) {
+      ctx->has_lds = build_lds_table(ctx->W, d, table);
+      ctx->fused_generic = ctx->has_lds && lds_family_serves(ctx->W);
+    }
   } catch (const std::bad_alloc &) {
     st = DETAG_ENOMEM, err = "out of host memory";
   }
@@ -351,7 +360,7 @@ detag_status detag_create(const detag_topology *topo, int32_t n, int64_t d, int6
     e = hipMemcpy(ctx->d_rowptr, ctx->W.rowptr.data(), (size_t(n) + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ctx->d_colidx, ctx->W.colidx.data(), nnz * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(ctx->d_vals, vals32.data(), nnz * sizeof(float), hipMemcpyHostToDevice);
-  if (e == hipSuccess && ctx->fused_generic) e = upload_lds_table(ctx, table);
+  if (e == hipSuccess && ctx->has_lds) e = upload_lds_table(ctx, table);
   if (e != hipSuccess) {
     const int rc = int(e);
     detag_destroy(ctx);
@@ -427,7 +436,7 @@ detag_status detag_get_kernel(const detag_ctx *ctx, int32_t *kernel) {
   if (!ctx) return set_err(nullptr, DETAG_EINVAL, "ctx is NULL");
   if (!kernel) return set_err(ctx, DETAG_EINVAL, "kernel is NULL");
   Chosen c;
-  if (detag_status st = choose_path(ctx, &c)) return st;
+  if (detag_status st = choose_path(ctx, 1, &c)) return st;
   *kernel = c == kFusedStructured ? DETAG_KERNEL_REGISTER_TILE
           : c == kFusedGeneric    ? DETAG_KERNEL_LDS_TILE
           : c == kDense           ? DETAG_KERNEL_DENSE
@@ -487,13 +496,14 @@ detag_status detag_gossip_accel(detag_ctx *ctx, void *Z_dev, int32_t K, double e
   if (detag_status st = resolve_eta(ctx, eta, &e)) return st;
   if (K == 0) return DETAG_OK;
   Chosen path;
-  if (detag_status st = choose_path(ctx, &path)) return st;
+  if (detag_status st = choose_path(ctx, K, &path)) return st;
   int rc = 0;
   switch (path) {
     case kFusedStructured:
       rc = launch_fused_structured(ctx->shape, ctx->W, 0, Z_dev, nullptr, nullptr, nullptr, 0.f, K, e, stream);
       break;
     case kFusedGeneric:
+    case kOnChipLists:
       rc = launch_fused_generic(ctx->shape, ctx->lds, 0, Z_dev, nullptr, nullptr, nullptr, 0.f, K, e, stream);
       break;
     case kDense: {
@@ -544,13 +554,13 @@ detag_status detag_step(detag_ctx *ctx, void *X_dev, void *Y_dev, const float *G
     return rc ? hip_fail(ctx, "update", rc) : DETAG_OK;
   }
   Chosen path;
-  if (detag_status st = choose_path(ctx, &path)) return st;
+  if (detag_status st = choose_path(ctx, K, &path)) return st;
   const int mode = variant == DETAG_VARIANT_ATC ? 1 : 2;
   if (path == kFusedStructured) {
     const int rc = launch_fused_structured(s, ctx->W, mode, X_dev, Y_dev, Gnew_dev, Gold_dev, a, K, e, stream);
     return rc ? hip_fail(ctx, "fused phase", rc) : DETAG_OK;
   }
-  if (path == kFusedGeneric) {
+  if (path == kFusedGeneric || path == kOnChipLists) {
     const int rc = launch_fused_generic(s, ctx->lds, mode, X_dev, Y_dev, Gnew_dev, Gold_dev, a, K, e, stream);
     return rc ? hip_fail(ctx, "fused phase", rc) : DETAG_OK;
   }
@@ -855,7 +865,7 @@ detag_status detag_step_quadratic(detag_ctx *ctx, void *X_dev, void *Y_dev, floa
   if (detag_status st = resolve_eta(ctx, eta, &e)) return st;
   Chosen path = kPerRound;
   if (K >= 1)
-    if (detag_status st = choose_path(ctx, &path)) return st;
+    if (detag_status st = choose_path(ctx, K, &path)) return st;
   if (path != kFusedStructured && path != kFusedGeneric)
     return set_err(ctx, DETAG_EUNSUPPORTED,
                    "detag_step_quadratic needs K >= 1 and a context whose rounds run on chip (register-resident or "

@@ -184,7 +184,11 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
             out.pairs.push_back(bits);
           }
     }
-  if (g.tile_bytes(0) + out.pairs.size() * 4 > kLdsMax) {
+  // A wavefront walks its longest list alone while the others wait at the barrier: with more than 256 neighbours on a
+  // hub, and enough columns to fill the chip, the one-launch-per-round kernels are the faster ones (star of 300, d =
+  // 200,000, K = 8: 3570 against 3860 us; star of 100 1170 against 480 us)
+  const bool lopsided = out.max_pairs > 128 && !small_matrix(n, d);
+  if (lopsided || g.tile_bytes(0) + out.pairs.size() * 4 > kLdsMax) {
     out = LdsTableHost{};
     return false;
   }

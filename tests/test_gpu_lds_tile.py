@@ -20,7 +20,7 @@ def _graph(kind, n):
     if kind == "ring":
         return gen.edges_ring(n)
     if kind == "rr8":
-        return gen.edges_random_regular(n, 8, seed=n)
+        return np.array(sorted({tuple(sorted((i, (i + s) % n))) for i in range(n) for s in (1, 5, 7, 11)}))
     rng = np.random.default_rng(n)                       # a path and random edges, at most 8 neighbours
     e, deg = {(i, i + 1) for i in range(n - 1)}, np.full(n, 2)
     while len(e) < 2 * n:
@@ -79,4 +79,47 @@ def test_forms_and_edges(n, kind, extra, pad, dtype, K):
     assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol
     for t in (Z, Xs, Ys, G):
         assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))   # the padding is never written
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,kind", [(12, "complete"), (64, "exponential"), (100, "complete"), (257, "rr"), (513, "asym"),
+                                    (1000, "asym"), (1024, "asym"), (1025, "asym")])
+@pytest.mark.parametrize("big,dtype,K", [(False, "f32", 3), (False, "bf16", 2), (True, "f32", 4), (True, "bf16", 3)])
+def test_rounds_on_chip_beyond_the_family(n, kind, big, dtype, K):
+    """More than 256 workers or 8 neighbours on the automatic path (1025 workers: one launch per round): the oracle, and
+    the path with one launch per round."""
+    d = (1 << 19) // n * 4 + 5 if big else 333
+    ld = d + 3
+    bf = dtype == "bf16"
+    sd, tol = (torch.bfloat16, TOL_BF16) if bf else (torch.float32, TOL_F32)
+    if kind == "complete":
+        e = np.array([(i, j) for i in range(n) for j in range(i + 1, n)])
+    elif kind == "exponential":
+        e = np.array(sorted({tuple(sorted((i, (i + s) % n))) for i in range(n) for s in (1, 2, 4, 8, 16, 32)}))
+    elif kind == "rr":
+        e = _graph(kind, n)
+    if kind == "asym":  # three neighbours with weights of their own (and no eigenvalues to compute at creation)
+        W = sum(w * np.roll(np.eye(n), s, axis=1) for w, s in ((0.5, 0), (0.25, 1), (0.15, 7), (0.1, 200)))
+        topo = D.Topology.from_dense(W)
+    else:
+        W, topo = OT.mixing_matrix(n, e, "metropolis"), D.Topology.from_edges(e, D.DETAG_W_METROPOLIS)
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if bf else D.DETAG_F32)
+    assert ctx.kernel() == D.DETAG_KERNEL_PER_ROUND and not ctx.has_fused()
+    eta, alpha = 0.35, 0.2
+    rng = np.random.default_rng(5)
+    cols = np.unique(np.concatenate([np.arange(20), np.arange(d - 40, d), rng.integers(0, d, 20)]))
+    X, Y, Gn, Go = (_matrix(n, d, ld, k, sd if k < 2 else torch.float32) for k in range(4))
+    x, y, gn, go = (_cols(t, cols) for t in (X, Y, Gn, Go))
+    S = amax(x, y, gn, go)
+    for path in (D.DETAG_PATH_AUTO, D.DETAG_PATH_PER_ROUND):
+        ctx.set_path(path)
+        Z = X.clone()
+        ctx.gossip_accel(Z, K, eta)
+        assert rel_err(_cols(Z, cols), OG.accelerated_gossip(x, W, K, eta), S) < tol
+        for variant, code in (("atc", D.DETAG_VARIANT_ATC), ("alg2", D.DETAG_VARIANT_ALG2)):
+            Xs, Ys = X.clone(), Y.clone()
+            ctx.step(Xs, Ys, Gn, Go, alpha, K, eta, code)
+            xr, yr = OG.detag_step(x, y, gn, go, W, alpha, K, eta, variant)
+            assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol, (path, variant)
+            assert torch.equal(Xs[:, d:], torch.full_like(Xs[:, d:], SENTINEL))
     ctx.close()
