@@ -1,292 +1,325 @@
 // Mini-batch gradient of multinomial logistic regression, every worker on its
 // own batch (the gradient query of Algorithm 2 for the label-sorted-shard
-// workload).  Both contractions run on the bf16 matrix cores
-// (v_mfma_f32_32x32x16_bf16, fp32 accumulate):
+// workload), in two launches:
 //
 //   logits[s,c] = sum_f feat[s,f] * Wt[c,f] + bias[c]        (B x F) . (F x C)
 //   dW[c,f]     = sum_s delta[s,c] * feat[s,f]                (C x B) . (B x F)
 //
-// The features are bf16 data.  The fp32 operands (weights, softmax residuals
-// delta) are split exactly into three bf16 terms w = hi + mid + lo; the three
-// terms of class c sit in rows c, C+c, 2C+c of the 32-row MFMA tile (3C <= 32)
-// and are summed after the contraction, so the products carry every bit of the
-// fp32 operand and no rounding point has to be mirrored by a reference.
-// Each fp32 operand is split once (the weights by a small kernel of their own,
-// the residuals where they are produced) into bf16 arrays the contractions load
-// directly: split inside the contraction loops, the same values were split by
-// every block that used them, and that arithmetic was 40 % of the run time.
+// The features are bf16 data, weights and residuals fp32.  The batch of 32 workers x 128 samples x 3072 features is 25 MB,
+// read by both launches (the second time mostly from the memory-side cache): what bounds them is how many of those bytes
+// are in flight and how long the chain index - row - sum - softmax is, not arithmetic.  So both launches give every
+// compute unit at least one block, and a wavefront requests all the feature bytes it needs before it uses the first.
 //
-// MFMA 32x32x16 operand layout (lane l, m = l % 32, g = l / 32):
-//   A: row m, k = 8g..8g+7      B: column m, k = 8g..8g+7
-//   D: column m, register r -> row 8*(r/4) + 4g + r%4
+//   softmax_logits_kernel  block = one worker x one chunk of up to 384 features x the whole batch, one wavefront per 16
+//     samples.  The products run on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulate); the chunk's
+//     weights are split exactly into three bf16 terms w = hi + mid + lo on the way into LDS, once per block, so the
+//     products carry every bit of the fp32 weights.  Writes the chunk's part of the logits.
+//   softmax_grad_kernel    the same blocks, a wavefront per 32 features.  Workgroups go to the eight XCDs in turn, so a
+//     block finds in its XCD's L2 what the same block of the first launch read (25 MB spread over 8 x 4 MB).  Every
+//     block adds up the parts of the logits and takes the softmax itself (10 x 128 values, while its feature rows
+//     arrive): a launch in between, or a ticket for the last block, costs more.  The residuals are split into three
+//     bf16 terms in LDS; a wavefront transposes its features through an LDS area of its own, 64 samples at a time, and
+//     multiplies on the matrix cores.  (The products in fp32 on the vector ALUs, samples shared among the wavefronts
+//     and summed in LDS at the end, took 16 to 17 us: 4.9 us of multiplications and a 3 us tail.)
+// The times at the two kernels are for 32 workers, 128 samples, 3072 features and 10 classes; with the phase after them
+// the call takes 30.3 us, 47.3 before.
+//
+// MFMA 16x16x32 operand layout (lane l, m = l % 16, q = l / 16):
+//   A: row m, k = 8q..8q+7      B: column m, k = 8q..8q+7
+//   D: column m, register r -> row 4q + r
 #include "dev_common.hpp"
 #include "detag_internal.h"
 
 namespace detag {
 namespace {
 
-constexpr int kLogitWaves = 16, kLogitThreads = 64 * kLogitWaves;  // logits: 16 wavefronts split F
-constexpr int kGradThreads = 256;                                  // weight gradient: 4 wavefronts x 32 columns
-constexpr int kStage = 128;                                        // samples staged in LDS at a time
-constexpr int kStagePitch = 136;                                   // bf16 per staged row: 272 B, 16-byte aligned,
-                                                                   // and 8 rows apart land 32 banks apart
+constexpr int kClassesMax = 10, kSamplesMax = 256;
+constexpr int kChunkMax = 384, kStepsMax = kChunkMax / 32;  // features of a logits block, MFMA steps of 32
+constexpr int kWeightPitch = kChunkMax + 8;  // bf16 per weight row in LDS: 16 rows start in 16 different groups of 4 banks
+constexpr int kGradWaves = kChunkMax / 32, kGradThreads = 64 * kGradWaves;
+constexpr int kWaveCols = 32;     // features of a wavefront
+constexpr int kStage = 64;        // samples a wavefront transposes at a time
+constexpr int kStagePitch = 36;   // bf16 per staged row, 72 B: rows 8 apart start 64 B apart in the banks
+constexpr int kHeld = 2;          // stages whose rows are requested together
+constexpr int kDeltaPitch = kSamplesMax + 8;  // bf16 per class and term: 16 classes start in 16 groups of 4 banks
+constexpr int kLanesClasses = 12;  // classes four lanes of a sample cover
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ uint16_t bf16_part(float w, int part) {
-  // exact three-way split: w = hi + mid + lo, each a bf16
-  const uint16_t hi = bf16_bits_rne(w);
-  if (part == 0) return hi;
-  const float r1 = w - __uint_as_float(uint32_t(hi) << 16);
-  const uint16_t mid = bf16_bits_rne(r1);
-  if (part == 1) return mid;
-  const float r2 = r1 - __uint_as_float(uint32_t(mid) << 16);
-  return bf16_bits_rne(r2);
-}
-
-__device__ __forceinline__ int d_row(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
-
-// Wsplit[i][p*C + c][f] = term p of X[i][c*F + f].  One thread = 8 consecutive f of one (i, c).
-template <bool VEC>
-__global__ __launch_bounds__(256) void softmax_split_kernel(int64_t ld, const float *__restrict__ X, int n, int F, int C,
-                                                            uint16_t *__restrict__ wsplit) {
-  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  const int per_row = F / 8;
-  if (t >= int64_t(n) * C * per_row) return;
-  const int f = int(t % per_row) * 8, c = int((t / per_row) % C), i = int(t / (int64_t(per_row) * C));
-  const float *src = X + int64_t(i) * ld + int64_t(c) * F + f;
-  float v[8];
-  if constexpr (VEC) {
-    const float4 a = *reinterpret_cast<const float4 *>(src), b = *reinterpret_cast<const float4 *>(src + 4);
-    v[0] = a.x, v[1] = a.y, v[2] = a.z, v[3] = a.w, v[4] = b.x, v[5] = b.y, v[6] = b.z, v[7] = b.w;
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = src[j];
-  }
+// The exact three-way split w = hi + mid + lo, each a bf16.
+__device__ __forceinline__ void bf16_split(float w, uint16_t (&t)[3]) {
 #pragma unroll
   for (int p = 0; p < 3; ++p) {
-    u16x8 o;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) o[j] = bf16_part(v[j], p);
-    *reinterpret_cast<u16x8 *>(wsplit + (int64_t(i) * 3 * C + p * C + c) * F + f) = o;
+    t[p] = bf16_bits_rne(w);
+    w -= __uint_as_float(uint32_t(t[p]) << 16);
   }
 }
 
-// grid (B/32, n).  One block = 32 samples of one worker; its 16 wavefronts split F in steps of 16 features,
-// six steps' operands in flight at a time.  Writes the residuals delta[i][c][s] = (p_c - y_c)/B in fp32 and
-// their three bf16 terms dsplit[i][p*C + c][s].
-__global__ __launch_bounds__(kLogitThreads) void softmax_logits_kernel(int64_t ld, const float *__restrict__ X,
-                                                                       const uint16_t *__restrict__ wsplit,
-                                                                       const uint16_t *__restrict__ feat,
-                                                                       const int32_t *__restrict__ labels,
-                                                                       const int32_t *__restrict__ batch, int S, int F,
-                                                                       int C, int B, float *__restrict__ delta,
-                                                                       uint16_t *__restrict__ dsplit,
-                                                                       float *__restrict__ loss_part) {
-  __shared__ float part[kLogitWaves][30][33];  // rows 3C <= 30 of every wavefront's tile
-  const int i = blockIdx.y, sb = blockIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 31, g = lane >> 5;
-  const bool row_ok = m < 3 * C;
-  int idx = batch[int64_t(i) * B + sb * 32 + m];
-  idx = idx < 0 ? 0 : idx >= S ? S - 1 : idx;
-  const uint16_t *wrow = wsplit + (int64_t(i) * 3 * C + (row_ok ? m : 0)) * F + 8 * g;
-  const uint16_t *frow = feat + (int64_t(i) * S + idx) * F + 8 * g;
-  f32x16 acc;
+__device__ __forceinline__ int clamped(int v, int n) { return v < 0 ? 0 : v >= n ? n - 1 : v; }
+
+// grid (chunks, n), B/16 wavefronts.  part[i][chunk][c][s] = sum over the chunk's features.
+// 32 workers x 8 chunks: 9.7 us (formerly a splitting kernel, 5.7 us, and 128 blocks that split the features over 16
+// wavefronts and summed in LDS, 20.7 us).
+__global__ __launch_bounds__(64 * kSamplesMax / 16) void softmax_logits_kernel(
+    int64_t ld, const float *__restrict__ X, const uint16_t *__restrict__ feat, const int32_t *__restrict__ batch, int S, int F,
+    int C, int B, int chunk, float *__restrict__ part) {
+  __shared__ __attribute__((aligned(16))) uint16_t weight[3][kClassesMax][kWeightPitch];
+  const int i = blockIdx.y, f0 = blockIdx.x * chunk, nf = F - f0 < chunk ? F - f0 : chunk, steps = nf / 32;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+  const int idx = clamped(batch[int64_t(i) * B + wave * 16 + m], S);
+  const uint16_t *frow = feat + (int64_t(i) * S + idx) * F + f0 + 8 * q;
+  u16x8 fv[kStepsMax];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  const int steps = F / 16;
-  constexpr int U = 6;
-  for (int ks = wave; ks < steps; ks += U * kLogitWaves) {
-    u16x8 wv[U], fv[U];
+  for (int st = 0; st < kStepsMax; ++st)
+    if (st < steps) fv[st] = *reinterpret_cast<const u16x8 *>(frow + 32 * st);  // uniform condition
+  for (int k = threadIdx.x * 4; k < C * nf; k += blockDim.x * 4) {
+    const int c = k / nf, f = k % nf;  // nf is a multiple of 32: the four stay in a row
+    const f32x4 w = *reinterpret_cast<const f32x4_any *>(X + int64_t(i) * ld + int64_t(c) * F + f0 + f);
+    u16x4 t[3];
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (ks + u * kLogitWaves < steps) {  // wavefront-uniform
-        const int k0 = (ks + u * kLogitWaves) * 16;
-        wv[u] = *reinterpret_cast<const u16x8 *>(wrow + k0);
-        fv[u] = *reinterpret_cast<const u16x8 *>(frow + k0);
-      }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (ks + u * kLogitWaves < steps) {
-        if (!row_ok) wv[u] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};  // rows past 3C of the tile
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv[u]),
-                                                      __builtin_bit_cast(bf16x8, fv[u]), acc, 0, 0, 0);
-      }
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if (d_row(r, g) < 30) part[wave][d_row(r, g)][m] = acc[r];
-  __syncthreads();
-  // logits[c][s] = bias[c] + the three split terms of class c summed over the wavefronts (fixed order):
-  // one thread per (class, sample), result parked in wavefront 0's slice of `part`
-  float lsum = 0.f;
-  const int lc = threadIdx.x >> 5, ls = threadIdx.x & 31;
-  if (lc < C) {
-    for (int w = 0; w < kLogitWaves; ++w) lsum += part[w][lc][ls] + part[w][C + lc][ls] + part[w][2 * C + lc][ls];
-    lsum += X[int64_t(i) * ld + int64_t(C) * F + lc];
-  }
-  __syncthreads();
-  if (lc < C) part[0][lc][ls] = lsum;
-  __syncthreads();
-  if (threadIdx.x < 32) {
-    const int s = sb * 32 + threadIdx.x;
-    int y = labels[int64_t(i) * S + idx];  // idx is this lane's sample (m == threadIdx.x here)
-    y = y < 0 ? 0 : y >= C ? C - 1 : y;
-    float logit[10];
-    float mx = -3.0e38f;
-#pragma unroll
-    for (int cc = 0; cc < 10; ++cc) {
-      float v = 0.f;
-      if (cc < C) {
-        v = part[0][cc][threadIdx.x];
-        mx = fmaxf(mx, v);
-      }
-      logit[cc] = v;
+    for (int e = 0; e < 4; ++e) {
+      uint16_t s[3];
+      bf16_split(w[e], s);
+      t[0][e] = s[0], t[1][e] = s[1], t[2][e] = s[2];
     }
-    float sum = 0.f;
 #pragma unroll
-    for (int cc = 0; cc < 10; ++cc)
-      if (cc < C) {
-        logit[cc] = expf(logit[cc] - mx);
-        sum += logit[cc];
-      }
-    const float inv = 1.f / sum, invB = 1.f / float(B);
-    float my_loss = 0.f;
-#pragma unroll
-    for (int cc = 0; cc < 10; ++cc)
-      if (cc < C) {
-        const float pr = logit[cc] * inv;
-        if (cc == y) my_loss = -logf(pr);
-        const float dl = (pr - (cc == y ? 1.f : 0.f)) * invB;
-        delta[(int64_t(i) * C + cc) * B + s] = dl;
-#pragma unroll
-        for (int pp = 0; pp < 3; ++pp) dsplit[(int64_t(i) * 3 * C + pp * C + cc) * B + s] = bf16_part(dl, pp);
-      }
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) my_loss += __shfl_down(my_loss, o, 64);
-    if (threadIdx.x == 0) loss_part[int64_t(i) * (B / 32) + sb] = my_loss;
+    for (int p = 0; p < 3; ++p) *reinterpret_cast<u16x4 *>(&weight[p][c][f]) = t[p];
   }
+  __syncthreads();
+  const int row = m < C ? m : C - 1;  // rows past C of the tile repeat the last class and are not stored
+  // the upper term and the two small ones in accumulators of their own: added to one, the small terms would triple the
+  // roundings at the magnitude of the sum
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f}, low = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int st = 0; st < kStepsMax; ++st)
+    if (st < steps) {
+      auto product = [&](int p, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8 *>(&weight[p][row][32 * st + 8 * q])),
+            __builtin_bit_cast(bf16x8, fv[st]), c, 0, 0, 0);
+      };
+      low = product(2, low);
+      acc = product(0, acc);
+      low = product(1, low);
+    }
+  acc += low;
+  float *out = part + (int64_t(i) * gridDim.x + blockIdx.x) * C * B + wave * 16 + m;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (4 * q + r < C) out[int64_t(4 * q + r) * B] = acc[r];
 }
 
-// grid (ceil(F/128), n).  One block = 128 feature columns of one worker, one wavefront = 32 of them; K runs
-// over the B samples.  The batch's rows of those columns are gathered into LDS with 16-byte row loads (a
-// sample's 128 columns are 256 contiguous bytes) and read back column-wise, 8 samples per lane, which is the
-// operand layout the MFMA wants; reading them column-wise from memory would be 2-byte accesses.
-__global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(int64_t ld, const uint16_t *__restrict__ feat,
-                                                                    const int32_t *__restrict__ batch, int S, int F,
-                                                                    int C, int B, const float *__restrict__ delta,
-                                                                    const uint16_t *__restrict__ dsplit,
-                                                                    const float *__restrict__ loss_part,
-                                                                    float *__restrict__ G, float *__restrict__ loss) {
-  __shared__ __attribute__((aligned(16))) uint16_t stage[kStage][kStagePitch];
-  __shared__ float tile[4][30][33];
-  const int i = blockIdx.y;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 31, g = lane >> 5;
-  const int fc0 = blockIdx.x * 128, f0 = fc0 + wave * 32;
-  const bool cols_ok = f0 < F;  // F % 32 == 0: a wavefront's 32 columns are all in or all out
-  const bool row_ok = m < 3 * C;
-  const int piece = threadIdx.x & 15, prow = threadIdx.x >> 4;  // staging: 16 pieces of 8 columns x 16 rows a pass
-  const bool piece_ok = fc0 + 8 * piece < F;
-  f32x16 acc;
+// grid (chunks, n).  32 workers x 8 chunks: 12.2 us (15.6 us with column groups that do not match the first launch's,
+// whose features come from beyond the L2; 17 us with 256 features per block multiplied on the vector ALUs) (formerly 13.1 us with 128 features per block, the residuals split by
+// the launch before).
+__global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
+    int64_t ld, const float *__restrict__ X, const uint16_t *__restrict__ feat, const int32_t *__restrict__ labels,
+    const int32_t *__restrict__ batch, int S, int F, int C, int B, int chunk, const float *__restrict__ part,
+    float *__restrict__ G, float *__restrict__ loss) {
+  __shared__ __attribute__((aligned(16))) uint16_t delta[3][kClassesMax][kDeltaPitch];
+  __shared__ __attribute__((aligned(16))) uint16_t stages[kGradWaves][kStage][kStagePitch];
+  __shared__ float logits[kClassesMax * kSamplesMax], sample_loss[kSamplesMax];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
+  const int i = blockIdx.y, f0 = blockIdx.x * chunk + wave * kWaveCols, chunks = gridDim.x;
+  const bool cols_ok = wave * kWaveCols < chunk && f0 < F;  // F % 32 == 0: a wavefront's columns are all in or all out
+  const int32_t *rows = batch + int64_t(i) * B;
+  // a stage's rows: four lanes to a row of 64 B, sixteen rows an instruction
+  u16x8 v[kHeld][kStage / 16];
+  auto fetch = [&](int from) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int s0 = 0; s0 < B; s0 += kStage) {
-    const int ns = B - s0 < kStage ? B - s0 : kStage;  // a multiple of 32
-    // this lane's residuals for every step of the stage, fetched together with the feature rows
-    u16x8 dv[kStage / 16];
-    const uint16_t *drow = dsplit + (int64_t(i) * 3 * C + (row_ok ? m : 0)) * B + s0 + 8 * g;
+    for (int h = 0; h < kHeld; ++h)
 #pragma unroll
-    for (int st = 0; st < kStage / 16; ++st)
-      if (cols_ok && st * 16 < ns) dv[st] = *reinterpret_cast<const u16x8 *>(drow + st * 16);
-    u16x8 rows[kStage / 16];
+      for (int k = 0; k < kStage / 16; ++k) {
+        const int s = from + h * kStage + k * 16;  // uniform; B is a multiple of 32
+        if (cols_ok && s < B)
+          v[h][k] = *reinterpret_cast<const u16x8 *>(
+              feat + (int64_t(i) * S + clamped(rows[s + (lane >> 2)], S)) * F + f0 + (lane & 3) * 8);
+      }
+  };
+  // Memory answers a wavefront in the order it asked: the parts of the logits first, the labels, then the feature rows,
+  // which arrive under the softmax.  This thread's (class, sample) pairs:
+  constexpr int kPairs = (kClassesMax * kSamplesMax + kGradThreads - 1) / kGradThreads;
+  constexpr int kPasses = (kSamplesMax * 4 + kGradThreads - 1) / kGradThreads;
+  float sums[kPairs];
+  // four lanes share a sample: lane j takes classes j, j + 4, j + 8
+  int y[kPasses];
 #pragma unroll
-    for (int ps = 0; ps < kStage / 16; ++ps) {
-      const int sr = ps * 16 + prow;
-      if (sr < ns && piece_ok) {
-        int idx = batch[int64_t(i) * B + s0 + sr];
-        idx = idx < 0 ? 0 : idx >= S ? S - 1 : idx;
-        rows[ps] = *reinterpret_cast<const u16x8 *>(feat + (int64_t(i) * S + idx) * F + fc0 + 8 * piece);
+  for (int j = 0; j < kPairs; ++j) sums[j] = 0.f;
+  for (int q0 = 0; q0 < chunks; q0 += 8) {
+    float t[kPairs][8];
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+      const int k = int(threadIdx.x) + j * kGradThreads;
+      if (j * kGradThreads < C * B) {  // uniform
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          t[j][q] = k < C * B && q0 + q < chunks ? part[(int64_t(i) * chunks + q0 + q) * C * B + k] : 0.f;
       }
     }
+    if (q0 + 8 >= chunks) {
 #pragma unroll
-    for (int ps = 0; ps < kStage / 16; ++ps) {
-      const int sr = ps * 16 + prow;
-      if (sr < ns && piece_ok) *reinterpret_cast<u16x8 *>(&stage[sr][8 * piece]) = rows[ps];
+      for (int r = 0; r < kPasses; ++r) {
+        const int s = int(threadIdx.x) / 4 + r * (kGradThreads / 4);
+        y[r] = s < B ? clamped(labels[int64_t(i) * S + clamped(rows[s], S)], C) : 0;
+      }
+      fetch(0);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    __syncthreads();
-    if (cols_ok) {
 #pragma unroll
-      for (int st = 0; st < kStage / 16; ++st)
-        if (st * 16 < ns) {  // block-uniform
-          u16x8 b;
+    for (int j = 0; j < kPairs; ++j)
+      if (j * kGradThreads < C * B) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j) b[j] = stage[st * 16 + 8 * g + j][wave * 32 + m];
-          if (!row_ok) dv[st] = u16x8{0, 0, 0, 0, 0, 0, 0, 0};  // rows past 3C of the tile
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dv[st]),
-                                                        __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+        for (int q = 0; q < 8; ++q) sums[j] += t[j][q];
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < kPairs; ++j) {
+    const int k = int(threadIdx.x) + j * kGradThreads;
+    if (k < C * B) {
+      const int c = k / B;
+      logits[c * kSamplesMax + k % B] = sums[j] + X[int64_t(i) * ld + int64_t(C) * F + c];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < kPasses; ++r) {
+    const int s = int(threadIdx.x) / 4 + r * (kGradThreads / 4), j = threadIdx.x & 3;
+    if (s < B) {  // the four lanes of a sample together
+      float e[kLanesClasses / 4], mx = -__builtin_inff();
+#pragma unroll
+      for (int k = 0; k < kLanesClasses / 4; ++k) {
+        const int c = j + 4 * k;
+        e[k] = c < C ? logits[c * kSamplesMax + s] : -__builtin_inff();
+        mx = fmaxf(mx, e[k]);
+      }
+#pragma unroll
+      for (int o = 1; o < 4; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+      float sum = 0.f, of_y = 0.f;
+#pragma unroll
+      for (int k = 0; k < kLanesClasses / 4; ++k) {
+        e[k] = j + 4 * k < C ? expf(e[k] - mx) : 0.f;
+        sum += e[k];
+        if (j + 4 * k == y[r]) of_y = e[k];
+      }
+#pragma unroll
+      for (int o = 1; o < 4; o <<= 1) sum += __shfl_xor(sum, o, 64), of_y += __shfl_xor(of_y, o, 64);
+      const float inv = 1.f / sum, invB = 1.f / float(B);
+#pragma unroll
+      for (int k = 0; k < kLanesClasses / 4; ++k) {
+        const int c = j + 4 * k;
+        if (c < C) {
+          const float dl = (e[k] * inv - (c == y[r] ? 1.f : 0.f)) * invB;
+          uint16_t t[3];
+          bf16_split(dl, t);
+#pragma unroll
+          for (int p = 0; p < 3; ++p) delta[p][c][s] = t[p];
+          logits[c * kSamplesMax + s] = dl;  // for the bias gradient; only these four lanes read the sample's logits
         }
+      }
+      if (j == 0) sample_loss[s] = -logf(of_y * inv);
     }
-    __syncthreads();
   }
-#pragma unroll
-  for (int r = 0; r < 16; ++r)
-    if (d_row(r, g) < 30) tile[wave][d_row(r, g)][m] = acc[r];
   __syncthreads();
-  if (cols_ok)
-    for (int cc = g; cc < C; cc += 2)
-      G[int64_t(i) * ld + int64_t(cc) * F + f0 + m] = tile[wave][cc][m] + tile[wave][C + cc][m] + tile[wave][2 * C + cc][m];
-  if (blockIdx.x == 0) {
-    // bias gradient: sum over the batch of delta (already divided by B); wavefront w takes classes w, w+4, ...
-    for (int cc = wave; cc < C; cc += 4) {
-      const float *dr = delta + (int64_t(i) * C + cc) * B;
-      float s = 0.f;
-      for (int k = lane; k < B; k += 64) s += dr[k];
+  if (cols_ok) {
+    f32x4 acc[2], low[2];
+    acc[0] = acc[1] = low[0] = low[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int row = m < C ? m : C - 1;  // rows past C of the tile repeat the last class and are not stored
+    uint16_t(&stage)[kStage][kStagePitch] = stages[wave];
+    for (int from = 0; from < B; from += kHeld * kStage) {
+      if (from > 0) fetch(from);
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-      if (lane == 0) G[int64_t(i) * ld + int64_t(C) * F + cc] = s;
+      for (int h = 0; h < kHeld; ++h) {
+        const int s0 = from + h * kStage;
+        if (s0 >= B) break;
+        // LDS serves a wavefront in order: the rows are written before they are read, and read before the next stage's
+#pragma unroll
+        for (int k = 0; k < kStage / 16; ++k)
+          if (s0 + k * 16 < B) {
+            u16x4 *to = reinterpret_cast<u16x4 *>(&stage[k * 16 + (lane >> 2)][(lane & 3) * 8]);
+            to[0] = u16x4{v[h][k][0], v[h][k][1], v[h][k][2], v[h][k][3]};
+            to[1] = u16x4{v[h][k][4], v[h][k][5], v[h][k][6], v[h][k][7]};
+          }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int st = 0; st < kStage / 32; ++st)
+          if (s0 + st * 32 < B) {
+            u16x8 a[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[p] = *reinterpret_cast<const u16x8 *>(&delta[p][row][s0 + st * 32 + 8 * q]);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              u16x8 x;
+#pragma unroll
+              for (int j = 0; j < 8; ++j) x[j] = stage[st * 32 + 8 * q + j][t * 16 + m];
+              auto product = [&](int p, f32x4 c) {
+                return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[p]), __builtin_bit_cast(bf16x8, x), c,
+                                                               0, 0, 0);
+              };
+              low[t] = product(2, low[t]);
+              acc[t] = product(0, acc[t]);
+              low[t] = product(1, low[t]);
+            }
+          }
+        __builtin_amdgcn_wave_barrier();
+      }
     }
-    if (threadIdx.x == 64 && loss) {
-      float s = 0.f;
-      for (int k = 0; k < B / 32; ++k) s += loss_part[int64_t(i) * (B / 32) + k];
-      loss[i] = s / float(B);
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (4 * q + r < C) G[int64_t(i) * ld + int64_t(4 * q + r) * F + f0 + t * 16 + m] = acc[t][r] + low[t][r];
+  }
+  if (blockIdx.x == 0) {
+    // bias gradient: sum over the batch of delta (already divided by B); wavefront w takes classes w, w+8
+    for (int c = wave; c < C; c += kGradWaves) {
+      float sum = 0.f;
+      for (int s = threadIdx.x & 63; s < B; s += 64) sum += logits[c * kSamplesMax + s];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
+      if ((threadIdx.x & 63) == 0) G[int64_t(i) * ld + int64_t(C) * F + c] = sum;
+    }
+    if (wave == kGradWaves - 1 && loss) {
+      float sum = 0.f;
+      for (int s = threadIdx.x & 63; s < B; s += 64) sum += sample_loss[s];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
+      if ((threadIdx.x & 63) == 0) loss[i] = sum / float(B);
     }
   }
 }
 
-}  // namespace
-
-namespace {
-// scratch layout (floats): delta n*C*B | loss_part n*(B/32) rounded up to 4 | dsplit n*3C*B bf16 | wsplit n*3C*F bf16
-int64_t round4(int64_t x) { return (x + 3) / 4 * 4; }
-}  // namespace
-
-int64_t softmax_scratch_floats(int n, int C, int B, int F) {
-  return int64_t(n) * C * B + round4(int64_t(n) * (B / 32)) + int64_t(n) * 3 * C * B / 2 + int64_t(n) * 3 * C * F / 2;
+// Features per logits block: enough chunks that n workers make 256 blocks, at most 16 (every gradient block adds the
+// parts up), a multiple of 32.
+int logits_chunk(int n, int F) {
+  int chunks = (256 + n - 1) / n;
+  chunks = chunks > 16 ? 16 : chunks;
+  int chunk = ((F + chunks - 1) / chunks + 31) / 32 * 32;
+  return chunk > kChunkMax ? kChunkMax : chunk;
 }
+int logits_chunks(int n, int F) {
+  const int chunk = logits_chunk(n, F);
+  return (F + chunk - 1) / chunk;
+}
+
+}  // namespace
+
+// The parts of the logits, n x chunks x C x B.
+int64_t softmax_scratch_floats(int n, int C, int B, int F) { return int64_t(n) * logits_chunks(n, F) * C * B; }
 
 int launch_grad_softmax(const Shape &s, const void *X, const uint16_t *feat, const int32_t *labels,
                         const int32_t *batch, int S, int F, int C, int B, float *scratch, float *G, float *loss,
                         void *stream) {
   auto st = static_cast<hipStream_t>(stream);
-  float *delta = scratch, *loss_part = delta + int64_t(s.n) * C * B;
-  uint16_t *dsplit = reinterpret_cast<uint16_t *>(loss_part + round4(int64_t(s.n) * (B / 32)));
-  uint16_t *wsplit = dsplit + int64_t(s.n) * 3 * C * B;
   const float *x = static_cast<const float *>(X);
-  // weight rows start at X + i*ld + c*F + 8k: 16-byte aligned iff X is and ld, F are multiples of 4
-  const bool vec = s.ld % 4 == 0 && F % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
-  const int split_blocks = int((int64_t(s.n) * C * (F / 8) + 255) / 256);
-  if (vec) softmax_split_kernel<true><<<split_blocks, 256, 0, st>>>(s.ld, x, s.n, F, C, wsplit);
-  else softmax_split_kernel<false><<<split_blocks, 256, 0, st>>>(s.ld, x, s.n, F, C, wsplit);
-  int rc = hip_rc(hipGetLastError());
-  if (rc) return rc;
-  softmax_logits_kernel<<<dim3(B / 32, s.n), kLogitThreads, 0, st>>>(s.ld, x, wsplit, feat, labels, batch, S, F, C, B,
-                                                                     delta, dsplit, loss_part);
-  rc = hip_rc(hipGetLastError());
-  if (rc) return rc;
-  softmax_grad_kernel<<<dim3((F + 127) / 128, s.n), kGradThreads, 0, st>>>(s.ld, feat, batch, S, F, C, B, delta, dsplit,
-                                                                           loss_part, G, loss);
+  const int chunk = logits_chunk(s.n, F), chunks = logits_chunks(s.n, F);
+  softmax_logits_kernel<<<dim3(chunks, s.n), 64 * (B / 16), 0, st>>>(s.ld, x, feat, batch, S, F, C, B, chunk, scratch);
+  if (int rc = hip_rc(hipGetLastError())) return rc;
+  softmax_grad_kernel<<<dim3(chunks, s.n), kGradThreads, 0, st>>>(s.ld, x, feat, labels, batch, S, F, C, B, chunk, scratch, G,
+                                                                  loss);
   return hip_rc(hipGetLastError());
 }
 
