@@ -11,6 +11,11 @@ namespace fused {
 
 constexpr int kThreads = 256;
 
+// Threads of a block.  No two wavefronts of a block work together, so its size only decides how columns spread over the
+// chip: up to 32,768 columns make 128 blocks of 256 threads or fewer, which leaves half the compute units idle, and take
+// one wavefront per block (step of 64 workers on a ring, d = 30,000, K = 2 10.0 -> 8.6 us, of 32 workers 5.8 -> 5.4 us).
+inline int block_threads(int64_t d) { return d <= 32768 ? 64 : kThreads; }
+
 // Workgroups are handed to the eight XCDs (each with its own L2) round-robin by their index.  Mapping index b
 // to column tile (b % 8) * (tiles / 8) + b / 8 gives every XCD one contiguous eighth of the columns instead of
 // every eighth tile, so the lines one L2 holds are neighbours in memory.  The tiles past a multiple of eight

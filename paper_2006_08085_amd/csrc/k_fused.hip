@@ -32,8 +32,8 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
     float alpha, int K) {
   constexpr int N = T::n;
   constexpr int D = kRowsAhead < N ? kRowsAhead : N;
-  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * kThreads;
-  const uint32_t valid = uint32_t(d - tile < kThreads ? d - tile : kThreads);
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
+  const uint32_t valid = uint32_t(d - tile < blockDim.x ? d - tile : blockDim.x);
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST));  // lane byte offset in a state row
   const uint32_t go4 = threadIdx.x * 4u;                   // ... in an fp32 row
   float u[N], p[N];
@@ -142,8 +142,8 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 0)) void structured_
     const ST *cur, const ST *prev, ST *out, int64_t d, int64_t ld, Coef c) {
   constexpr int N = T::n;
   constexpr int D = kRowsAhead < N ? kRowsAhead : N;
-  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * kThreads;
-  const uint32_t valid = uint32_t(d - tile < kThreads ? d - tile : kThreads);
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
+  const uint32_t valid = uint32_t(d - tile < blockDim.x ? d - tile : blockDim.x);
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST));
   float u[N], lp[N];
 #pragma unroll
@@ -164,14 +164,15 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 0)) void structured_
 template <class T, typename ST>
 int launch_t(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, const Coef &c,
              float alpha, int K, void *stream) {
-  const dim3 grid(ceil_div_i64(s.d, kThreads));
+  const int threads = block_threads(s.d);
+  const dim3 grid(ceil_div_i64(s.d, threads));
   auto st = static_cast<hipStream_t>(stream);
   ST *x = static_cast<ST *>(X), *y = static_cast<ST *>(Y);
   switch (mode) {
-    case 0: fused_structured_kernel<T, ST, 0><<<grid, kThreads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
-    case 1: fused_structured_kernel<T, ST, 1><<<grid, kThreads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
-    case 3: fused_structured_kernel<T, ST, 3><<<grid, kThreads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
-    default: fused_structured_kernel<T, ST, 2><<<grid, kThreads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
+    case 0: fused_structured_kernel<T, ST, 0><<<grid, threads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
+    case 1: fused_structured_kernel<T, ST, 1><<<grid, threads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
+    case 3: fused_structured_kernel<T, ST, 3><<<grid, threads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
+    default: fused_structured_kernel<T, ST, 2><<<grid, threads, 0, st>>>(x, y, Gn, Go, s.d, s.ld, c, alpha, K); break;
   }
   return hip_rc(hipGetLastError());
 }
@@ -199,15 +200,16 @@ int launch_fused_structured(const Shape &s, const HostW &W, int mode, void *X, v
 int launch_structured_round(const Shape &s, const HostW &W, const void *cur, const void *prev, void *out, float eta,
                             void *stream) {
   const Coef c = make_coef(W, eta);
-  const dim3 grid(ceil_div_i64(s.d, kThreads));
+  const int threads = block_threads(s.d);
+  const dim3 grid(ceil_div_i64(s.d, threads));
   auto st = static_cast<hipStream_t>(stream);
   return with_pattern(W, [&](auto t) {
     using T = decltype(t);
     if (s.bf16)
-      structured_round_kernel<T, bf16_t><<<grid, kThreads, 0, st>>>(
+      structured_round_kernel<T, bf16_t><<<grid, threads, 0, st>>>(
           static_cast<const bf16_t *>(cur), static_cast<const bf16_t *>(prev), static_cast<bf16_t *>(out), s.d, s.ld, c);
     else
-      structured_round_kernel<T, float><<<grid, kThreads, 0, st>>>(
+      structured_round_kernel<T, float><<<grid, threads, 0, st>>>(
           static_cast<const float *>(cur), static_cast<const float *>(prev), static_cast<float *>(out), s.d, s.ld, c);
     return hip_rc(hipGetLastError());
   });

@@ -52,8 +52,8 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
   constexpr int NR = N - NL;
   constexpr int D = kRowsAhead < N ? kRowsAhead : N;
   __shared__ float vl[NL > 0 ? NL * kThreads : 1];
-  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * kThreads;
-  const uint32_t valid = uint32_t(d - tile < kThreads ? d - tile : kThreads);
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
+  const uint32_t valid = uint32_t(d - tile < blockDim.x ? d - tile : blockDim.x);
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST)), fo = threadIdx.x * 4u;
   const unsigned j = threadIdx.x & 3u;
   const uint64_t q = uint64_t(tile + threadIdx.x) >> 2;
@@ -134,8 +134,8 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
   static_assert(N % 4 == 0, "rows are processed in groups of four");
   constexpr int D = kRowsAhead < N ? kRowsAhead : N;
   __shared__ float gl[N * kThreads];
-  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * kThreads;
-  const uint32_t valid = uint32_t(d - tile < kThreads ? d - tile : kThreads);
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
+  const uint32_t valid = uint32_t(d - tile < blockDim.x ? d - tile : blockDim.x);
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST)), fo = threadIdx.x * 4u;
   const unsigned j = threadIdx.x & 3u;
   const uint64_t q = uint64_t(tile + threadIdx.x) >> 2;
@@ -202,11 +202,12 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
 template <class T>
 int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float *h, bool hpw, const float *b,
              const Coef &c, float alpha, int K, float sigma, uint64_t seed, uint32_t step, void *stream) {
-  const dim3 grid(ceil_div_i64(s.d, kThreads));
+  const int threads = block_threads(s.d);
+  const dim3 grid(ceil_div_i64(s.d, threads));
   auto st = static_cast<hipStream_t>(stream);
   const uint32_t slo = uint32_t(seed & 0xffffffffu), shi = uint32_t(seed >> 32);
 #define DETAG_QUAD(KERNEL, ST, HPW)                                                                              \
-  KERNEL<T, ST, HPW><<<grid, kThreads, 0, st>>>(static_cast<ST *>(X), static_cast<ST *>(Y), G, h, b, s.d, s.ld, c, \
+  KERNEL<T, ST, HPW><<<grid, threads, 0, st>>>(static_cast<ST *>(X), static_cast<ST *>(Y), G, h, b, s.d, s.ld, c, \
                                                 alpha, K, sigma, slo, shi, step)
 #define DETAG_QUAD_ST(KERNEL)                                                            \
   if (s.bf16) {                                                                          \
