@@ -14,15 +14,16 @@ namespace detag {
 namespace {
 
 constexpr int kThreads = 256;
-typedef float vf4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t vu2_t __attribute__((ext_vector_type(2)));
+// four columns are one access wherever the row starts (see k_stream.hip)
+typedef float vf4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned short vu4_t __attribute__((ext_vector_type(4), aligned(2)));
 
 // A block works on kGradRows consecutive worker rows of its 1024 columns, so that a shared curvature vector is
 // read once per kGradRows rows instead of once per row (read per row it is a fourth stream: measured 1.33 x the
 // bytes of X, b and G on 64 x 11.2 M).
 constexpr int kGradRows = 4;
 
-template <typename ST, bool VEC>
+template <typename ST>
 __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t d, int64_t ld, const ST *__restrict__ X,
                                                                   const float *__restrict__ h, int64_t h_row_stride,
                                                                   const float *__restrict__ b,
@@ -34,11 +35,11 @@ __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t
   if (c0 >= d) return;
   const int i0 = blockIdx.y * kGradRows;
   const int valid = int(d - c0 < 4 ? d - c0 : 4);
-  const bool wide = VEC && valid == 4;
+  const bool wide = valid == 4;
   float hs[4] = {0.f, 0.f, 0.f, 0.f};
   if (h_row_stride == 0) {  // shared by the workers: read once, cached (other blocks read it too)
     if (wide) {
-      const float4 th = *reinterpret_cast<const float4 *>(h + c0);
+      const vf4_t th = *reinterpret_cast<const vf4_t *>(h + c0);
       hs[0] = th.x, hs[1] = th.y, hs[2] = th.z, hs[3] = th.w;
     } else {
 #pragma unroll
@@ -57,9 +58,9 @@ __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t
         const vf4_t t = __builtin_nontemporal_load(reinterpret_cast<const vf4_t *>(X + off));
         x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
       } else {
-        const vu2_t t = __builtin_nontemporal_load(reinterpret_cast<const vu2_t *>(X + off));
-        x[0] = __uint_as_float(t.x << 16), x[1] = __uint_as_float(t.x & 0xffff0000u);
-        x[2] = __uint_as_float(t.y << 16), x[3] = __uint_as_float(t.y & 0xffff0000u);
+        const vu4_t t = __builtin_nontemporal_load(reinterpret_cast<const vu4_t *>(X + off));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(uint32_t(t[e]) << 16);
       }
       const vf4_t tb = __builtin_nontemporal_load(reinterpret_cast<const vf4_t *>(b + off));
       bv[0] = tb.x, bv[1] = tb.y, bv[2] = tb.z, bv[3] = tb.w;
@@ -134,8 +135,6 @@ __global__ __launch_bounds__(kThreads) void lstsq_grad_kernel(int m, int64_t d, 
   G[int64_t(i) * ld + c] = acc;
 }
 
-bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
 }  // namespace
 
 int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_per_worker, const float *b,
@@ -144,17 +143,12 @@ int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_p
   const dim3 grid(ceil_div_i64(blocks4, kThreads), (s.n + kGradRows - 1) / kGradRows);
   auto st = static_cast<hipStream_t>(stream);
   const int64_t hstride = h_per_worker ? s.ld : 0;
-  const bool vec = s.ld % 4 == 0 && aligned16(h) && aligned16(b) && aligned16(G) && (!noise || aligned16(noise)) &&
-                   (reinterpret_cast<uintptr_t>(X) & (s.bf16 ? 7 : 15)) == 0;
   const uint32_t slo = uint32_t(seed & 0xffffffffu), shi = uint32_t(seed >> 32);
-#define DETAG_LAUNCH(ST, V)                                                                                     \
-  grad_quadratic_kernel<ST, V><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, static_cast<const ST *>(X), h, hstride, b, \
-                                                          noise, sigma, slo, shi, step, G)
-  if (s.bf16) {
-    if (vec) DETAG_LAUNCH(bf16_t, true); else DETAG_LAUNCH(bf16_t, false);
-  } else {
-    if (vec) DETAG_LAUNCH(float, true); else DETAG_LAUNCH(float, false);
-  }
+#define DETAG_LAUNCH(ST)                                                                                        \
+  grad_quadratic_kernel<ST><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, static_cast<const ST *>(X), h, hstride, b, noise, \
+                                                       sigma, slo, shi, step, G)
+  if (s.bf16) DETAG_LAUNCH(bf16_t);
+  else DETAG_LAUNCH(float);
 #undef DETAG_LAUNCH
   return hip_rc(hipGetLastError());
 }

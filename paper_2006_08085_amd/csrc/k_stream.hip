@@ -18,8 +18,12 @@ constexpr int kThreads = 256;
 // Streamed data (touched once per kernel) goes through non-temporal accesses: on the 64 x 11.2 M fp32 matrices the
 // update-and-track pass takes 2.78 ms with them against 3.14 ms without (0.77 against 0.68 of HBM peak), the
 // tracker update 1.75 against 2.06 ms.  Rows that neighbours read again within a kernel (NT = false) stay cached.
-typedef float vf4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t vu2_t __attribute__((ext_vector_type(2)));
+// Four columns are one access wherever the row starts: memory needs element alignment only, so an odd pitch or a shifted
+// base takes the same path (detag_grad_quadratic_diag on 100 x 300,007 with pitch d and per-worker curvature: 148 us one column at a time, 90 us
+// so).
+typedef float vf4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned short vu4_t __attribute__((ext_vector_type(4), aligned(2)));
+constexpr int VEC = 4;
 
 template <bool NT>
 __device__ __forceinline__ float load_one(const float *p) { return NT ? __builtin_nontemporal_load(p) : *p; }
@@ -30,42 +34,39 @@ __device__ __forceinline__ float load_one(const bf16_t *p) {
 __device__ __forceinline__ void store_one(float *p, float v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void store_one(bf16_t *p, float v) { __builtin_nontemporal_store(bf16_bits_rne(v), &p->bits); }
 
-template <typename ST, int VEC, bool NT = true>
+template <typename ST, bool NT = true>
 __device__ __forceinline__ void load_vec(const ST *p, int valid, float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    if (valid >= 4) {
-      if constexpr (sizeof(ST) == 4) {
-        const vf4_t *q = reinterpret_cast<const vf4_t *>(p);
-        const vf4_t t = NT ? __builtin_nontemporal_load(q) : *q;
-        v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
-      } else {
-        const vu2_t *q = reinterpret_cast<const vu2_t *>(p);
-        const vu2_t t = NT ? __builtin_nontemporal_load(q) : *q;
-        v[0] = __uint_as_float(t.x << 16), v[1] = __uint_as_float(t.x & 0xffff0000u);
-        v[2] = __uint_as_float(t.y << 16), v[3] = __uint_as_float(t.y & 0xffff0000u);
-      }
-      return;
+  if (valid >= 4) {
+    if constexpr (sizeof(ST) == 4) {
+      const vf4_t *q = reinterpret_cast<const vf4_t *>(p);
+      const vf4_t t = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v[e] = t[e];
+    } else {
+      const vu4_t *q = reinterpret_cast<const vu4_t *>(p);
+      const vu4_t t = NT ? __builtin_nontemporal_load(q) : *q;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
     }
+    return;
   }
 #pragma unroll
   for (int e = 0; e < VEC; ++e) v[e] = e < valid ? load_one<NT>(p + e) : 0.f;
 }
 
-template <typename ST, int VEC>
+template <typename ST>
 __device__ __forceinline__ void store_vec(ST *p, int valid, const float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    if (valid >= 4) {
-      if constexpr (sizeof(ST) == 4) {
-        const vf4_t t = {v[0], v[1], v[2], v[3]};
-        __builtin_nontemporal_store(t, reinterpret_cast<vf4_t *>(p));
-      } else {
-        vu2_t t;
-        t.x = uint32_t(bf16_bits_rne(v[0])) | (uint32_t(bf16_bits_rne(v[1])) << 16);
-        t.y = uint32_t(bf16_bits_rne(v[2])) | (uint32_t(bf16_bits_rne(v[3])) << 16);
-        __builtin_nontemporal_store(t, reinterpret_cast<vu2_t *>(p));
-      }
-      return;
+  if (valid >= 4) {
+    if constexpr (sizeof(ST) == 4) {
+      const vf4_t t = {v[0], v[1], v[2], v[3]};
+      __builtin_nontemporal_store(t, reinterpret_cast<vf4_t *>(p));
+    } else {
+      vu4_t t;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) t[e] = bf16_bits_rne(v[e]);
+      __builtin_nontemporal_store(t, reinterpret_cast<vu4_t *>(p));
     }
+    return;
   }
 #pragma unroll
   for (int e = 0; e < VEC; ++e)
@@ -79,7 +80,7 @@ __device__ __forceinline__ void store_vec(ST *p, int valid, const float (&v)[VEC
 // the worker mean does not drift over many rounds; and the increment is formed at its own (small) magnitude,
 // so the only rounding at the magnitude of the state is the last add.
 // With HAS_G: out[i,:] = cur[i,:] + sum_k ... - alpha * G[i,:] (D-PSGD) and prev is not read.
-template <typename ST, int VEC, bool HAS_G>
+template <typename ST, bool HAS_G>
 __global__ __launch_bounds__(kThreads) void gossip_round_kernel(int n, int64_t d, int64_t ld,
                                                                 const int32_t *__restrict__ rowptr,
                                                                 const int32_t *__restrict__ colidx,
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(kThreads) void gossip_round_kernel(int n, int64_t d
   const int r1 = r0 + rows_per_group < n ? r0 + rows_per_group : n;
   for (int i = r0; i < r1; ++i) {
     float own[VEC], acc[VEC];
-    load_vec<ST, VEC, false>(cur + int64_t(i) * ld + c0, valid, own);
+    load_vec<ST, false>(cur + int64_t(i) * ld + c0, valid, own);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = 0.f;
     const int k1 = rowptr[i + 1];
@@ -103,23 +104,23 @@ __global__ __launch_bounds__(kThreads) void gossip_round_kernel(int n, int64_t d
       if (j == i) continue;  // the diagonal entry contributes a zero difference
       const float w = vals[k];
       float v[VEC];
-      load_vec<ST, VEC, false>(cur + int64_t(j) * ld + c0, valid, v);
+      load_vec<ST, false>(cur + int64_t(j) * ld + c0, valid, v);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) acc[e] = fmaf(w, v[e] - own[e], acc[e]);
     }
     float o[VEC];
     if constexpr (HAS_G) {
       float g[VEC];
-      load_vec<float, VEC>(G + int64_t(i) * ld + c0, valid, g);
+      load_vec<float>(G + int64_t(i) * ld + c0, valid, g);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) o[e] = own[e] + fmaf(-alpha, g[e], c_mix * acc[e]);
     } else {
       float p[VEC];
-      load_vec<ST, VEC>(prev + int64_t(i) * ld + c0, valid, p);
+      load_vec<ST>(prev + int64_t(i) * ld + c0, valid, p);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) o[e] = own[e] + fmaf(c_mix, acc[e], eta * (own[e] - p[e]));
     }
-    store_vec<ST, VEC>(out + int64_t(i) * ld + c0, valid, o);
+    store_vec<ST>(out + int64_t(i) * ld + c0, valid, o);
   }
 }
 
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void gossip_round_tile_kernel(int 
 }
 
 // mode 0: Y += Gn - Go.   mode 1: X -= alpha*Y (Y before the update); Y += Gn - Go.
-template <typename ST, int VEC, int MODE>
+template <typename ST, int MODE>
 __global__ __launch_bounds__(kThreads) void elementwise_kernel(int64_t d, int64_t ld, ST *X, ST *Y,
                                                                const float *__restrict__ Gn,
                                                                const float *__restrict__ Go, float alpha) {
@@ -202,24 +203,24 @@ __global__ __launch_bounds__(kThreads) void elementwise_kernel(int64_t d, int64_
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float y[VEC], gn[VEC], go[VEC];
-  load_vec<ST, VEC>(Y + off, valid, y);
-  load_vec<float, VEC>(Gn + off, valid, gn);
-  load_vec<float, VEC>(Go + off, valid, go);
+  load_vec<ST>(Y + off, valid, y);
+  load_vec<float>(Gn + off, valid, gn);
+  load_vec<float>(Go + off, valid, go);
   if constexpr (MODE == 1) {
     float x[VEC];
-    load_vec<ST, VEC>(X + off, valid, x);
+    load_vec<ST>(X + off, valid, x);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) x[e] = fmaf(-alpha, y[e], x[e]);
-    store_vec<ST, VEC>(X + off, valid, x);
+    store_vec<ST>(X + off, valid, x);
   }
 #pragma unroll
   for (int e = 0; e < VEC; ++e) y[e] = y[e] + gn[e] - go[e];
-  store_vec<ST, VEC>(Y + off, valid, y);
+  store_vec<ST>(Y + off, valid, y);
 }
 
 // out[i,:] = sum_k vals[k] * cur[col[k],:] for a general sparse matrix (rows need not sum to one, may be empty):
 // the factor matrices of the exact average consensus (Lemma 1).
-template <typename ST, int VEC>
+template <typename ST>
 __global__ __launch_bounds__(kThreads) void spmm_kernel(int n, int64_t d, int64_t ld, const int32_t *__restrict__ rowptr,
                                                         const int32_t *__restrict__ colidx,
                                                         const float *__restrict__ vals, const ST *__restrict__ cur,
@@ -237,16 +238,16 @@ __global__ __launch_bounds__(kThreads) void spmm_kernel(int n, int64_t d, int64_
     for (int k = rowptr[i]; k < k1; ++k) {
       const float w = vals[k];
       float v[VEC];
-      load_vec<ST, VEC, false>(cur + int64_t(colidx[k]) * ld + c0, valid, v);
+      load_vec<ST, false>(cur + int64_t(colidx[k]) * ld + c0, valid, v);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) acc[e] = fmaf(w, v[e], acc[e]);
     }
-    store_vec<ST, VEC>(out + int64_t(i) * ld + c0, valid, acc);
+    store_vec<ST>(out + int64_t(i) * ld + c0, valid, acc);
   }
 }
 
 // End of a round of Algorithm 1: X = Xt - scale*G; Xt = X; G = 0.
-template <typename ST, int VEC>
+template <typename ST>
 __global__ __launch_bounds__(kThreads) void defacto_update_kernel(int64_t d, int64_t ld, ST *X, ST *Xt, float *G,
                                                                   float scale) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -254,20 +255,19 @@ __global__ __launch_bounds__(kThreads) void defacto_update_kernel(int64_t d, int
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float x[VEC], g[VEC];
-  load_vec<ST, VEC>(Xt + off, valid, x);
-  load_vec<float, VEC>(G + off, valid, g);
+  load_vec<ST>(Xt + off, valid, x);
+  load_vec<float>(G + off, valid, g);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
     x[e] = fmaf(-scale, g[e], x[e]);
     g[e] = 0.f;
   }
-  store_vec<ST, VEC>(X + off, valid, x);
-  if (Xt != X) store_vec<ST, VEC>(Xt + off, valid, x);
-  store_vec<float, VEC>(G + off, valid, g);
+  store_vec<ST>(X + off, valid, x);
+  if (Xt != X) store_vec<ST>(Xt + off, valid, x);
+  store_vec<float>(G + off, valid, g);
 }
 
 // Gacc += scale * g
-template <int VEC>
 __global__ __launch_bounds__(kThreads) void accumulate_kernel(int64_t d, int64_t ld, float *Gacc,
                                                               const float *__restrict__ g, float scale) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -275,15 +275,15 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(int64_t d, int64_t
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float a[VEC], x[VEC];
-  load_vec<float, VEC>(Gacc + off, valid, a);
-  load_vec<float, VEC>(g + off, valid, x);
+  load_vec<float>(Gacc + off, valid, a);
+  load_vec<float>(g + off, valid, x);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) a[e] = fmaf(scale, x[e], a[e]);
-  store_vec<float, VEC>(Gacc + off, valid, a);
+  store_vec<float>(Gacc + off, valid, a);
 }
 
 // End of a phase of Algorithm 2: X = Xt - alpha*Y; Y += Gk - Gkm1; Xt = X; Gkm1 = 0.
-template <typename ST, int VEC>
+template <typename ST>
 __global__ __launch_bounds__(kThreads) void phase_end_kernel(int64_t d, int64_t ld, ST *X, ST *Xt, ST *Y,
                                                              const float *__restrict__ Gk, float *Gkm1, float alpha) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -291,24 +291,24 @@ __global__ __launch_bounds__(kThreads) void phase_end_kernel(int64_t d, int64_t 
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float x[VEC], y[VEC], gk[VEC], gm[VEC];
-  load_vec<ST, VEC>(Xt + off, valid, x);
-  load_vec<ST, VEC>(Y + off, valid, y);
-  load_vec<float, VEC>(Gk + off, valid, gk);
-  load_vec<float, VEC>(Gkm1 + off, valid, gm);
+  load_vec<ST>(Xt + off, valid, x);
+  load_vec<ST>(Y + off, valid, y);
+  load_vec<float>(Gk + off, valid, gk);
+  load_vec<float>(Gkm1 + off, valid, gm);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
     x[e] = fmaf(-alpha, y[e], x[e]);
     y[e] = y[e] + gk[e] - gm[e];
     gm[e] = 0.f;
   }
-  store_vec<ST, VEC>(X + off, valid, x);
-  if (Xt != X) store_vec<ST, VEC>(Xt + off, valid, x);
-  store_vec<ST, VEC>(Y + off, valid, y);
-  store_vec<float, VEC>(Gkm1 + off, valid, gm);
+  store_vec<ST>(X + off, valid, x);
+  if (Xt != X) store_vec<ST>(Xt + off, valid, x);
+  store_vec<ST>(Y + off, valid, y);
+  store_vec<float>(Gkm1 + off, valid, gm);
 }
 
 // dst = src with a change of storage type (bf16 -> fp32 exact, fp32 -> bf16 round to nearest even)
-template <typename TS, typename TD, int VEC>
+template <typename TS, typename TD>
 __global__ __launch_bounds__(kThreads) void convert_kernel(int64_t d, int64_t ld, const TS *__restrict__ src,
                                                            TD *__restrict__ dst) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -316,19 +316,8 @@ __global__ __launch_bounds__(kThreads) void convert_kernel(int64_t d, int64_t ld
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float x[VEC];
-  load_vec<TS, VEC>(src + off, valid, x);
-  store_vec<TD, VEC>(dst + off, valid, x);
-}
-
-// 16-byte accesses need every row start 16-byte aligned (8 bytes for bf16 vectors of four).
-bool vec_ok(const Shape &s, std::initializer_list<const void *> state_ptrs, std::initializer_list<const void *> f32_ptrs) {
-  if (s.ld % 4) return false;
-  const uintptr_t smask = s.bf16 ? 7 : 15;
-  for (const void *p : state_ptrs)
-    if (p && (reinterpret_cast<uintptr_t>(p) & smask)) return false;
-  for (const void *p : f32_ptrs)
-    if (p && (reinterpret_cast<uintptr_t>(p) & 15)) return false;
-  return true;
+  load_vec<TS>(src + off, valid, x);
+  store_vec<TD>(dst + off, valid, x);
 }
 
 int rows_per_group_for(const Shape &s, int col_blocks) {
@@ -357,17 +346,11 @@ int launch_round_t(const Shape &s, const DevCsr &w, const void *cur, const void 
 #undef DETAG_TILE_GO
     return hip_rc(hipGetLastError());
   }
-  const bool vec = vec_ok(s, {cur, prev, out}, {G});
-  const int per_block = kThreads * (vec ? 4 : 1);
+  const int per_block = kThreads * VEC;
   const int col_blocks = ceil_div_i64(s.d, per_block);
   const int rpg = rows_per_group_for(s, col_blocks);
   dim3 grid(col_blocks, (s.n + rpg - 1) / rpg);
-  if (vec)
-    gossip_round_kernel<ST, 4, HAS_G><<<grid, kThreads, 0, st>>>(
-        s.n, s.d, s.ld, w.rowptr, w.colidx, w.vals, static_cast<const ST *>(cur), static_cast<const ST *>(prev),
-        static_cast<ST *>(out), G, c_mix, eta, alpha, rpg);
-  else
-    gossip_round_kernel<ST, 1, HAS_G><<<grid, kThreads, 0, st>>>(
+  gossip_round_kernel<ST, HAS_G><<<grid, kThreads, 0, st>>>(
         s.n, s.d, s.ld, w.rowptr, w.colidx, w.vals, static_cast<const ST *>(cur), static_cast<const ST *>(prev),
         static_cast<ST *>(out), G, c_mix, eta, alpha, rpg);
   return hip_rc(hipGetLastError());
@@ -376,30 +359,19 @@ int launch_round_t(const Shape &s, const DevCsr &w, const void *cur, const void 
 template <typename ST, int MODE>
 int launch_elementwise_t(const Shape &s, void *X, void *Y, const float *Gn, const float *Go, float alpha,
                          void *stream) {
-  const bool vec = vec_ok(s, {X, Y}, {Gn, Go});
-  const int per_block = kThreads * (vec ? 4 : 1);
+  const int per_block = kThreads * VEC;
   dim3 grid(ceil_div_i64(s.d, per_block), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  if (vec)
-    elementwise_kernel<ST, 4, MODE><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X),
-                                                                static_cast<ST *>(Y), Gn, Go, alpha);
-  else
-    elementwise_kernel<ST, 1, MODE><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X),
+  elementwise_kernel<ST, MODE><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X),
                                                                 static_cast<ST *>(Y), Gn, Go, alpha);
   return hip_rc(hipGetLastError());
 }
 
 template <typename TS, typename TD>
 int launch_convert_t(const Shape &s, const void *src, void *dst, void *stream) {
-  const bool vec = s.ld % 4 == 0 && (reinterpret_cast<uintptr_t>(src) % (4 * sizeof(TS))) == 0 &&
-                   (reinterpret_cast<uintptr_t>(dst) % (4 * sizeof(TD))) == 0;
-  dim3 grid(ceil_div_i64(s.d, kThreads * (vec ? 4 : 1)), s.n);
+  dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  if (vec)
-    convert_kernel<TS, TD, 4><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<const TS *>(src),
-                                                         static_cast<TD *>(dst));
-  else
-    convert_kernel<TS, TD, 1><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<const TS *>(src),
+  convert_kernel<TS, TD><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<const TS *>(src),
                                                          static_cast<TD *>(dst));
   return hip_rc(hipGetLastError());
 }
@@ -408,16 +380,11 @@ int launch_convert_t(const Shape &s, const void *src, void *dst, void *stream) {
 
 template <typename ST>
 int launch_spmm_t(const Shape &s, const DevCsr &a, const void *cur, void *out, void *stream) {
-  const bool vec = vec_ok(s, {cur, out}, {});
-  const int col_blocks = ceil_div_i64(s.d, kThreads * (vec ? 4 : 1));
+  const int col_blocks = ceil_div_i64(s.d, kThreads * VEC);
   const int rpg = rows_per_group_for(s, col_blocks);
   dim3 grid(col_blocks, (s.n + rpg - 1) / rpg);
   auto st = static_cast<hipStream_t>(stream);
-  if (vec)
-    spmm_kernel<ST, 4><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, a.rowptr, a.colidx, a.vals,
-                                                  static_cast<const ST *>(cur), static_cast<ST *>(out), rpg);
-  else
-    spmm_kernel<ST, 1><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, a.rowptr, a.colidx, a.vals,
+  spmm_kernel<ST><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, a.rowptr, a.colidx, a.vals,
                                                   static_cast<const ST *>(cur), static_cast<ST *>(out), rpg);
   return hip_rc(hipGetLastError());
 }
@@ -428,14 +395,9 @@ int launch_spmm(const Shape &s, const DevCsr &a, const void *cur, void *out, voi
 
 template <typename ST>
 int launch_defacto_update_t(const Shape &s, void *X, void *Xt, float *G, float scale, void *stream) {
-  const bool vec = vec_ok(s, {X, Xt}, {G});
-  dim3 grid(ceil_div_i64(s.d, kThreads * (vec ? 4 : 1)), s.n);
+  dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  if (vec)
-    defacto_update_kernel<ST, 4><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt), G,
-                                                            scale);
-  else
-    defacto_update_kernel<ST, 1><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt), G,
+  defacto_update_kernel<ST><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt), G,
                                                             scale);
   return hip_rc(hipGetLastError());
 }
@@ -446,25 +408,18 @@ int launch_defacto_update(const Shape &s, void *X, void *Xt, float *G, float sca
 }
 
 int launch_accumulate(const Shape &s, float *Gacc, const float *g, float scale, void *stream) {
-  const bool vec = vec_ok(s, {}, {Gacc, g});
-  dim3 grid(ceil_div_i64(s.d, kThreads * (vec ? 4 : 1)), s.n);
+  dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  if (vec) accumulate_kernel<4><<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale);
-  else accumulate_kernel<1><<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale);
+  accumulate_kernel<<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale);
   return hip_rc(hipGetLastError());
 }
 
 template <typename ST>
 int launch_phase_end_t(const Shape &s, void *X, void *Xt, void *Y, const float *Gk, float *Gkm1, float alpha,
                        void *stream) {
-  const bool vec = vec_ok(s, {X, Xt, Y}, {Gk, Gkm1});
-  dim3 grid(ceil_div_i64(s.d, kThreads * (vec ? 4 : 1)), s.n);
+  dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  if (vec)
-    phase_end_kernel<ST, 4><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt),
-                                                       static_cast<ST *>(Y), Gk, Gkm1, alpha);
-  else
-    phase_end_kernel<ST, 1><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt),
+  phase_end_kernel<ST><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt),
                                                        static_cast<ST *>(Y), Gk, Gkm1, alpha);
   return hip_rc(hipGetLastError());
 }
