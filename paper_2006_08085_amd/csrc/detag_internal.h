@@ -141,6 +141,7 @@ int launch_fused_quadratic(const Shape &s, const HostW &W, bool alg2, void *X, v
 int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, void *Y, float *G, const float *h,
                                    bool h_per_worker, const float *b, float alpha, int K, float eta, float sigma,
                                    uint64_t seed, uint32_t step, void *stream);
+// mode as above, and 3 = D-PSGD (X <- W^T X - alpha*Gn; eta = 0, K = 1).
 int launch_fused_generic(const Shape &s, const LdsTable &t, int mode, void *X, void *Y, const float *Gn, const float *Go,
                          float alpha, int K, float eta, void *stream);
 

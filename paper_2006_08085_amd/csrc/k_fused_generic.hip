@@ -16,6 +16,7 @@ using namespace lds_tile;
 
 // mode 0: Z <- M(Z) on X.  mode 1 (ATC): X <- M(X - alpha*Y), Y <- M(Y + Gn - Go).
 // mode 2 (ALG2): X <- M(X) - alpha*M(Y), Y <- M(Y) + Gn - Go.
+// mode 3 (D-PSGD): X <- W^T X - alpha*Gn, one plain round (called with eta = 0).
 template <typename ST, int MODE, class R>
 __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(ST *X, ST *Y, const float *__restrict__ Gn,
                                                                        const float *__restrict__ Go, int n, int64_t d,
@@ -50,6 +51,19 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     });
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
+  } else if constexpr (MODE == 3) {
+    f4 g[R::kSlots];
+    rows([&](auto F, int s, int64_t off, int64_t c, bool) {
+      z[s] = load4<F>(X, off, c, d), g[s] = load4<F>(Gn, off, c, d);
+      lds_write(p.own(s), z[s]);
+    });
+    rounds.init(ra, p, eta);
+    __syncthreads();
+    const float w = rounds.scale();
+    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+      const f4 mixed = fma4(w, rounds.template diff_sum<0u>(s, z[s]), z[s]);
+      if (mine) store4<F>(X, off, c, d, fma4(-alpha, g[s], mixed));
+    });
   } else {
     // M(Y) first: both outputs need it
     rows([&](auto F, int s, int64_t off, int64_t c, bool) { z[s] = load4<F>(Y, off, c, d); });
@@ -84,6 +98,7 @@ int launch_r(const Shape &s, const Geometry &g, size_t lds, const typename R::Ar
     case 0: return go(&fused_generic_kernel<ST, 0, R>);
     case 1: return go(&fused_generic_kernel<ST, 1, R>);
     case 2: return go(&fused_generic_kernel<ST, 2, R>);
+    case 3: return go(&fused_generic_kernel<ST, 3, R>);
   }
   return hip_rc(hipErrorInvalidValue);
 }

@@ -19,8 +19,8 @@ constexpr int kThreads = 256;
 // update-and-track pass takes 2.78 ms with them against 3.14 ms without (0.77 against 0.68 of HBM peak), the
 // tracker update 1.75 against 2.06 ms.  Rows that neighbours read again within a kernel (NT = false) stay cached.
 // Four columns are one access wherever the row starts: memory needs element alignment only, so an odd pitch or a shifted
-// base takes the same path (detag_grad_quadratic_diag on 100 x 300,007 with pitch d and per-worker curvature: 148 us one column at a time, 90 us
-// so).
+// base takes the same path (quadratic gradient of 100 workers, d = 300,007, pitch d, per-worker curvature: 148 us one
+// column at a time, 90 us so).
 typedef float vf4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short vu4_t __attribute__((ext_vector_type(4), aligned(2)));
 constexpr int VEC = 4;

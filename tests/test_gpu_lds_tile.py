@@ -77,7 +77,10 @@ def test_forms_and_edges(n, kind, extra, pad, dtype, K):
     xr, yr = OG.detag_step(x, y, g, go, W, alpha, K, eta)
     assert rel_err(_cols(G, cols), g, amax(g)) < TOL_F32
     assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol
-    for t in (Z, Xs, Ys, G):
+    Xp = X.clone()
+    ctx.dpsgd_step(Xp, Gn, alpha)
+    assert rel_err(_cols(Xp, cols), OG.dpsgd_step(x, gn, W, alpha), S) < tol
+    for t in (Z, Xs, Ys, G, Xp):
         assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))   # the padding is never written
     ctx.close()
 
@@ -113,9 +116,11 @@ def test_rounds_on_chip_beyond_the_family(n, kind, big, dtype, K):
     S = amax(x, y, gn, go)
     for path in (D.DETAG_PATH_AUTO, D.DETAG_PATH_PER_ROUND):
         ctx.set_path(path)
-        Z = X.clone()
+        Z, Xp = X.clone(), X.clone()
         ctx.gossip_accel(Z, K, eta)
         assert rel_err(_cols(Z, cols), OG.accelerated_gossip(x, W, K, eta), S) < tol
+        ctx.dpsgd_step(Xp, Gn, alpha)
+        assert rel_err(_cols(Xp, cols), OG.dpsgd_step(x, gn, W, alpha), S) < tol
         for variant, code in (("atc", D.DETAG_VARIANT_ATC), ("alg2", D.DETAG_VARIANT_ALG2)):
             Xs, Ys = X.clone(), Y.clone()
             ctx.step(Xs, Ys, Gn, Go, alpha, K, eta, code)
