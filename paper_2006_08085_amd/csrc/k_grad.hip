@@ -101,38 +101,88 @@ __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t
   }
 }
 
-// resid[i*m + r] = A_i[r,:] . x_i - b_i[r]; one wavefront per (i, r).
-template <typename ST>
-__global__ __launch_bounds__(kThreads) void lstsq_resid_kernel(int n, int m, int64_t d, int64_t ld,
-                                                               const ST *__restrict__ X, const float *__restrict__ A,
-                                                               const float *__restrict__ b,
-                                                               float *__restrict__ resid) {
-  const int64_t row = int64_t(blockIdx.x) * (kThreads / 64) + (threadIdx.x >> 6);  // = i*m + r
-  if (row >= int64_t(n) * m) return;
-  const int i = int(row / m);
-  const int lane = threadIdx.x & 63;
-  const float *a = A + row * d;
-  const ST *x = X + int64_t(i) * ld;
-  float acc = 0.f;
-  for (int64_t c = lane; c < d; c += 64) acc = fmaf(a[c], to_f32(x[c]), acc);
+__device__ __forceinline__ vf4_t load4(const float *p) { return *reinterpret_cast<const vf4_t *>(p); }
+__device__ __forceinline__ vf4_t load4(const bf16_t *p) {
+  const vu4_t t = *reinterpret_cast<const vu4_t *>(p);
+  vf4_t v;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
-  if (lane == 0) resid[row] = acc - b[row];
+  for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
+  return v;
 }
 
-// G[i,c] = sum_r A_i[r,c] * resid[i,r]; one lane per column.
-__global__ __launch_bounds__(kThreads) void lstsq_grad_kernel(int m, int64_t d, int64_t ld,
-                                                              const float *__restrict__ A,
-                                                              const float *__restrict__ resid,
-                                                              float *__restrict__ G) {
-  const int64_t c = int64_t(blockIdx.x) * kThreads + threadIdx.x;
-  if (c >= d) return;
-  const int i = blockIdx.y;
-  const float *a = A + int64_t(i) * m * d + c;
-  const float *r = resid + int64_t(i) * m;
-  float acc = 0.f;
-  for (int k = 0; k < m; ++k) acc = fmaf(a[int64_t(k) * d], r[k], acc);
-  G[int64_t(i) * ld + c] = acc;
+// resid[i*m + r] = A_i[r,:] . x_i - b_i[r]; one block of one wavefront per (i, r), which spreads a few hundred rows over
+// all compute units.  Four 16-byte pieces of the row and of x are in flight per lane, each with a sum of its own.
+template <typename ST>
+__global__ __launch_bounds__(64) void lstsq_resid_kernel(int m, int64_t d, int64_t ld, const ST *__restrict__ X,
+                                                         const float *__restrict__ A, const float *__restrict__ b,
+                                                         float *__restrict__ resid) {
+  constexpr int kPieces = 4;
+  const int64_t row = blockIdx.x;  // = i*m + r
+  const int lane = threadIdx.x;
+  const float *a = A + row * d;
+  const ST *x = X + row / m * ld;
+  float acc[kPieces] = {0.f, 0.f, 0.f, 0.f};
+  int64_t c = lane * 4;
+  for (; c - lane * 4 + kPieces * 256 <= d; c += kPieces * 256) {
+    vf4_t av[kPieces], xv[kPieces];
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) av[k] = load4(a + c + 256 * k), xv[k] = load4(x + c + 256 * k);
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[k] = fmaf(av[k][e], xv[k][e], acc[k]);
+  }
+  for (int64_t t = c - lane * 3; t < d; t += 64) acc[0] = fmaf(a[t], to_f32(x[t]), acc[0]);  // the last d % 1024 columns
+  float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
+  if (lane == 0) resid[row] = sum - b[row];
+}
+
+// G[i,c] = sum_r A_i[r,c] * resid[i,r].  A block owns 4 * LANES columns of one worker; LANES lanes side by side take a
+// row, so its 16 wavefronts walk 1024 / LANES rows at a time and add their parts up at the end.  With 16 lanes (64
+// columns) a small problem makes enough blocks and a row of 64 samples is one step; with 64 lanes a wavefront reads 1 KiB
+// of a row.
+constexpr int kSumThreads = 1024;
+template <int LANES>
+__global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int m, int64_t d, int64_t ld, const float *__restrict__ A,
+                                                                 const float *__restrict__ resid, float *__restrict__ G) {
+  constexpr int kRows = kSumThreads / LANES, kCols = 4 * LANES, kWaves = kSumThreads / 64;
+  __shared__ float part[kWaves][kCols];
+  const int i = blockIdx.y, lane = threadIdx.x % LANES, r0 = threadIdx.x / LANES;
+  const int64_t c = int64_t(blockIdx.x) * kCols + 4 * lane;
+  const float *a = A + int64_t(i) * m * d;
+  const float *res = resid + int64_t(i) * m;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  if (c + 4 <= d) {
+#pragma unroll 4
+    for (int r = r0; r < m; r += kRows) {
+      const vf4_t v = load4(a + int64_t(r) * d + c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(v[e], res[r], acc[e]);
+    }
+  } else {
+    for (int r = r0; r < m; r += kRows)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c + e < d) acc[e] = fmaf(a[int64_t(r) * d + c + e], res[r], acc[e]);
+  }
+#pragma unroll
+  for (int o = LANES; o < 64; o <<= 1)  // rows of one wavefront
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o, 64);
+  if ((threadIdx.x & 63) < LANES) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) part[threadIdx.x >> 6][4 * lane + e] = acc[e];
+  }
+  __syncthreads();
+  if (threadIdx.x < kCols) {
+    const int64_t col = int64_t(blockIdx.x) * kCols + threadIdx.x;
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) sum += part[w][threadIdx.x];
+    if (col < d) G[int64_t(i) * ld + col] = sum;
+  }
 }
 
 }  // namespace
@@ -156,15 +206,16 @@ int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_p
 int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float *b, int m, float *resid, float *G,
                       void *stream) {
   auto st = static_cast<hipStream_t>(stream);
-  const int64_t rows = int64_t(s.n) * m;
-  const dim3 g1(ceil_div_i64(rows, kThreads / 64));
-  if (s.bf16)
-    lstsq_resid_kernel<bf16_t><<<g1, kThreads, 0, st>>>(s.n, m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, resid);
-  else
-    lstsq_resid_kernel<float><<<g1, kThreads, 0, st>>>(s.n, m, s.d, s.ld, static_cast<const float *>(X), A, b, resid);
+  const dim3 g1(uint32_t(int64_t(s.n) * m));
+  if (s.bf16) lstsq_resid_kernel<bf16_t><<<g1, 64, 0, st>>>(m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, resid);
+  else lstsq_resid_kernel<float><<<g1, 64, 0, st>>>(m, s.d, s.ld, static_cast<const float *>(X), A, b, resid);
   int rc = hip_rc(hipGetLastError());
   if (rc) return rc;
-  lstsq_grad_kernel<<<dim3(ceil_div_i64(s.d, kThreads), s.n), kThreads, 0, st>>>(m, s.d, s.ld, A, resid, G);
+  // 64 columns per block until blocks of 256 columns alone make two per compute unit
+  if (int64_t(ceil_div_i64(s.d, 256)) * s.n < 512)
+    lstsq_grad_kernel<16><<<dim3(ceil_div_i64(s.d, 64), s.n), kSumThreads, 0, st>>>(m, s.d, s.ld, A, resid, G);
+  else
+    lstsq_grad_kernel<64><<<dim3(ceil_div_i64(s.d, 256), s.n), kSumThreads, 0, st>>>(m, s.d, s.ld, A, resid, G);
   return hip_rc(hipGetLastError());
 }
 

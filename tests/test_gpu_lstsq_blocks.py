@@ -1,0 +1,34 @@
+"""Least-squares gradient at the edges of its blocks: rows of less than one 16-byte piece per lane, around 1024 columns,
+sample counts around a block's rows, both widths of the column blocks, odd pitches."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2006_08085_amd as D
+from oracle import objectives as OO
+from workloads import generate as gen
+from tests.gpu_util import DEV, _built, padding_ok, to_dev, to_host  # noqa: F401
+from tests.util import TOL_F32, amax, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,d,m,pad", [(1, 1, 1, 0), (3, 5, 2, 1), (2, 255, 63, 0), (2, 1023, 65, 2), (4, 1025, 64, 0), (5, 2050, 7, 3),
+                                       (16, 8193, 130, 1), (64, 2049, 3, 0)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_blocks(n, d, m, pad, dtype):
+    ld = d + pad
+    X = gen.state(n, d, seed=1)
+    if dtype == "bf16":
+        X = OO.round_bf16(X)
+    A, b = gen.lstsq_problem(n, m, d, seed=2, shift=0.5)
+    topo = D.Topology.ring() if n > 1 else D.Topology.from_dense(np.ones((1, 1)))
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32)
+    G = to_dev(np.zeros((n, d)), ld)
+    ctx.grad_lstsq(to_dev(X, ld, torch.bfloat16 if dtype == "bf16" else torch.float32), torch.from_numpy(A).to(DEV),
+                   torch.from_numpy(b).to(DEV), G)
+    ref = OO.grad_lstsq(X, A, b)
+    # residuals are sums of d products of size |A| |x|, entries of G sums of m products of those
+    S = max(amax(ref), amax(A) * np.sqrt(d) * amax(A) * amax(X))
+    assert rel_err(to_host(G, d), ref, S) < TOL_F32
+    assert padding_ok(G, d)
