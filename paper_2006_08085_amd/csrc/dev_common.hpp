@@ -54,32 +54,27 @@ __device__ __forceinline__ rsrc_t row_of(const E *base, int64_t tile, int64_t ld
   return make_rsrc(base + tile + int64_t(i) * ld, valid * uint32_t(sizeof(E)));
 }
 
-// Cache-policy bits of the buffer instructions on gfx950 (the `aux` operand):
-// bit 0 = sc0, bit 1 = nt, bit 4 = sc1.  State tiles are touched exactly once
-// per kernel, so they are streamed with nt (non-temporal).
-constexpr int kAuxLoad = 2, kAuxStore = 2;
-
-template <typename ST>
-__device__ __forceinline__ float buf_load(rsrc_t r, uint32_t byte_off);
-template <>
-__device__ __forceinline__ float buf_load<float>(rsrc_t r, uint32_t byte_off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, int(byte_off), 0, kAuxLoad));
-}
-template <>
-__device__ __forceinline__ float buf_load<bf16_t>(rsrc_t r, uint32_t byte_off) {
-  const uint16_t h = uint16_t(__builtin_amdgcn_raw_buffer_load_b16(r, int(byte_off), 0, kAuxLoad));
-  return __uint_as_float(uint32_t(h) << 16);
+// Cache-policy bits of the buffer instructions on gfx950 (the `aux` operand): bit 0 = sc0, bit 1 = nt, bit 4 = sc1.
+// NT: state tiles are touched exactly once per kernel, so a matrix that no cache holds until the next call is streamed
+// (non-temporal).
+template <typename ST, bool NT = true>
+__device__ __forceinline__ float buf_load(rsrc_t r, uint32_t byte_off) {
+  constexpr int aux = NT ? 2 : 0;
+  if constexpr (sizeof(ST) == 4) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, int(byte_off), 0, aux));
+  } else {
+    const uint16_t h = uint16_t(__builtin_amdgcn_raw_buffer_load_b16(r, int(byte_off), 0, aux));
+    return __uint_as_float(uint32_t(h) << 16);
+  }
 }
 
-template <typename ST>
-__device__ __forceinline__ void buf_store(rsrc_t r, uint32_t byte_off, float v);
-template <>
-__device__ __forceinline__ void buf_store<float>(rsrc_t r, uint32_t byte_off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, int(byte_off), 0, kAuxStore);
-}
-template <>
-__device__ __forceinline__ void buf_store<bf16_t>(rsrc_t r, uint32_t byte_off, float v) {
-  __builtin_amdgcn_raw_buffer_store_b16(short(bf16_bits_rne(v)), r, int(byte_off), 0, kAuxStore);
+template <typename ST, bool NT = true>
+__device__ __forceinline__ void buf_store(rsrc_t r, uint32_t byte_off, float v) {
+  constexpr int aux = NT ? 2 : 0;
+  if constexpr (sizeof(ST) == 4)
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, int(byte_off), 0, aux);
+  else
+    __builtin_amdgcn_raw_buffer_store_b16(short(bf16_bits_rne(v)), r, int(byte_off), 0, aux);
 }
 
 // Hides a uniform pointer's value from the optimiser (it stays in scalar

@@ -3,6 +3,8 @@
 // registers.
 #pragma once
 
+#include <type_traits>
+
 #include "detag_internal.h"
 #include "dev_common.hpp"
 
@@ -24,6 +26,12 @@ __device__ __forceinline__ int64_t xcd_tile(uint32_t b, uint32_t tiles) {
   const uint32_t per = tiles / 8u;
   return b < per * 8u ? int64_t(b % 8u) * per + b / 8u : int64_t(b);
 }
+
+// Whether a call whose matrices take `per_element` bytes per element streams past the caches.  The memory-side cache holds
+// 256 MB and a program has other matrices too: up to 80 MB a call's matrices are left to the caches, where the next call
+// finds them (gradient-fused step, ring of 16: d = 272,474 (70 MB) 22 -> 19 us, three states in turn as well; d =
+// 500,000 (128 MB) 43 -> 35 us with one state but 44 -> 46 us with three in turn).
+inline bool streams(const Shape &s, int per_element) { return int64_t(s.n) * s.ld * per_element > (int64_t(80) << 20); }
 
 template <int N>
 struct Ring {
