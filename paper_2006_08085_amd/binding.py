@@ -39,6 +39,20 @@ EXPORTS = ["detag_create", "detag_destroy", "detag_get_spectrum", "detag_get_csr
            "detag_grad_softmax_bf16", "detag_last_error", "detag_version"]
 
 
+class _Torch:
+    """The torch module, imported when a tensor is first handled (the host entry points work without it).  What was looked
+    up once is an ordinary attribute afterwards."""
+
+    def __getattr__(self, name):
+        import torch as module
+        value = getattr(module, name)
+        setattr(self, name, value)
+        return value
+
+
+_torch = _Torch()
+
+
 class DetagError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"{_STATUS_NAMES[status] if 0 <= status < len(_STATUS_NAMES) else status}: {message}")
@@ -270,6 +284,7 @@ class Context:
     def __init__(self, handle: int, n: int, d: int, ld: int, dtype: int):
         self._h = C.c_void_p(handle)
         self.n, self.d, self.ld, self.dtype = n, d, ld, dtype
+        self._strides = (ld, 1)
 
     def close(self):
         if self._h:
@@ -288,24 +303,31 @@ class Context:
             raise DetagError(status, lib().detag_last_error(self._h).decode())
 
     def _state(self, t, name="state"):
-        import torch
-        want = torch.bfloat16 if self.dtype == DETAG_BF16 else torch.float32
-        return self._mat(t, want, name)
+        return self._mat(t, _torch.bfloat16 if self.dtype == DETAG_BF16 else _torch.float32, name)
+
+    def _f32(self, t, name):
+        return self._mat(t, _torch.float32, name)
 
     def _mat(self, t, want_dtype, name):
+        # the whole check in as few tensor queries as it takes: a small step is a few microseconds on the GPU
+        if t.is_cuda and t.dtype is want_dtype and t.stride() == self._strides:
+            shape = t.shape
+            if shape[0] == self.n and shape[1] >= self.d:
+                return t.data_ptr()
+        return self._refuse(t, want_dtype, name)
+
+    def _refuse(self, t, want_dtype, name):
         if not t.is_cuda:
             raise ValueError(f"{name} must be a GPU tensor")
         if t.dtype != want_dtype:
             raise ValueError(f"{name} must be {want_dtype}, got {t.dtype}")
-        if t.dim() != 2 or t.shape[0] != self.n or t.shape[1] < self.d or t.stride(1) != 1 or t.stride(0) != self.ld:
-            raise ValueError(f"{name} must be an n x ld row-major matrix with pitch {self.ld} (n={self.n}, d={self.d}); "
-                             f"got shape {tuple(t.shape)} strides {t.stride()}")
-        return C.c_void_p(t.data_ptr())
+        raise ValueError(f"{name} must be an n x ld row-major matrix with pitch {self.ld} (n={self.n}, d={self.d}); "
+                         f"got shape {tuple(t.shape)} strides {t.stride()}")
 
     @staticmethod
     def _stream():
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        # the current stream of the current device, without building the Stream object around it
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
 
     # -- queries -------------------------------------------------------------
     def spectrum(self):
@@ -365,19 +387,16 @@ class Context:
         self._check(lib().detag_gossip_accel(self._h, self._state(Z, "Z"), K, eta, self._stream()))
 
     def track(self, Y, G_new, G_old):
-        import torch
-        self._check(lib().detag_track(self._h, self._state(Y, "Y"), self._mat(G_new, torch.float32, "G_new"),
-                                      self._mat(G_old, torch.float32, "G_old"), self._stream()))
+        self._check(lib().detag_track(self._h, self._state(Y, "Y"), self._f32(G_new, "G_new"),
+                                      self._f32(G_old, "G_old"), self._stream()))
 
     def step(self, X, Y, G_new, G_old, alpha: float, K: int, eta: float = -1.0, variant: int = DETAG_VARIANT_ATC):
-        import torch
         self._check(lib().detag_step(self._h, self._state(X, "X"), self._state(Y, "Y"),
-                                     self._mat(G_new, torch.float32, "G_new"), self._mat(G_old, torch.float32, "G_old"),
+                                     self._f32(G_new, "G_new"), self._f32(G_old, "G_old"),
                                      alpha, K, eta, variant, self._stream()))
 
     def dpsgd_step(self, X, G, alpha: float):
-        import torch
-        self._check(lib().detag_dpsgd_step(self._h, self._state(X, "X"), self._mat(G, torch.float32, "G"), alpha,
+        self._check(lib().detag_dpsgd_step(self._h, self._state(X, "X"), self._f32(G, "G"), alpha,
                                            self._stream()))
 
     # -- Algorithm 2 iteration by iteration ---------------------------------------
@@ -386,112 +405,102 @@ class Context:
                                              self._state(Z_out, "Z_out"), eta, self._stream()))
 
     def accumulate(self, G_acc, g, scale: float = 1.0):
-        import torch
-        self._check(lib().detag_accumulate(self._h, self._mat(G_acc, torch.float32, "G_acc"),
-                                           self._mat(g, torch.float32, "g"), scale, self._stream()))
+        self._check(lib().detag_accumulate(self._h, self._f32(G_acc, "G_acc"),
+                                           self._f32(g, "g"), scale, self._stream()))
 
     def phase_end(self, X, X_tilde, Y, G_k, G_km1, alpha: float):
-        import torch
         self._check(lib().detag_phase_end(self._h, self._state(X, "X"), self._state(X_tilde, "X_tilde"),
-                                          self._state(Y, "Y"), self._mat(G_k, torch.float32, "G_k"),
-                                          self._mat(G_km1, torch.float32, "G_km1"), alpha, self._stream()))
+                                          self._state(Y, "Y"), self._f32(G_k, "G_k"),
+                                          self._f32(G_km1, "G_km1"), alpha, self._stream()))
 
     def defacto_update(self, X, X_tilde, G, scale: float):
-        import torch
         self._check(lib().detag_defacto_update(self._h, self._state(X, "X"), self._state(X_tilde, "X_tilde"),
-                                               self._mat(G, torch.float32, "G"), scale, self._stream()))
+                                               self._f32(G, "G"), scale, self._stream()))
 
     # -- diagnostics -----------------------------------------------------------
     def mean(self, X, out=None):
-        import torch
         if out is None:
-            out = torch.empty(self.d, dtype=torch.float32, device=X.device)
-        if out.dtype != torch.float32 or out.numel() < self.d or not out.is_contiguous():
+            out = _torch.empty(self.d, dtype=_torch.float32, device=X.device)
+        if out.dtype != _torch.float32 or out.numel() < self.d or not out.is_contiguous():
             raise ValueError("out must be a contiguous float32 vector of length >= d")
-        self._check(lib().detag_mean(self._h, self._state(X, "X"), C.c_void_p(out.data_ptr()), self._stream()))
+        self._check(lib().detag_mean(self._h, self._state(X, "X"), out.data_ptr(), self._stream()))
         return out
 
     def consensus_error(self, X, out=None):
-        import torch
         if out is None:
-            out = torch.empty(1, dtype=torch.float64, device=X.device)
-        self._check(lib().detag_consensus_error(self._h, self._state(X, "X"), C.c_void_p(out.data_ptr()),
+            out = _torch.empty(1, dtype=_torch.float64, device=X.device)
+        self._check(lib().detag_consensus_error(self._h, self._state(X, "X"), out.data_ptr(),
                                                 self._stream()))
         return out
 
     def consensus_error_static(self, X, out):
         """detag_consensus_error_static: `out` (one float64 on the GPU) is required, since this call is for
         callers that may not allocate."""
-        import torch
-        if out.dtype != torch.float64 or not out.is_cuda or out.numel() < 1:
+        if out.dtype != _torch.float64 or not out.is_cuda or out.numel() < 1:
             raise ValueError("out must be a float64 GPU tensor with at least one element")
-        self._check(lib().detag_consensus_error_static(self._h, self._state(X, "X"), C.c_void_p(out.data_ptr()),
+        self._check(lib().detag_consensus_error_static(self._h, self._state(X, "X"), out.data_ptr(),
                                                        self._stream()))
         return out
 
     # -- gradients ---------------------------------------------------------------
     def grad_quadratic_diag(self, X, h, b, G, noise=None, sigma: float = 0.0, seed: int = 0, step: int = 0):
-        import torch
         per_worker = 1 if h.dim() == 2 else 0
         if per_worker:
-            hp = self._mat(h, torch.float32, "h")
+            hp = self._f32(h, "h")
         else:
-            if h.dtype != torch.float32 or not h.is_cuda or h.numel() < self.d or not h.is_contiguous():
+            if h.dtype != _torch.float32 or not h.is_cuda or h.numel() < self.d or not h.is_contiguous():
                 raise ValueError("h must be a contiguous float32 GPU vector of length >= d")
-            hp = C.c_void_p(h.data_ptr())
-        npz = None if noise is None else self._mat(noise, torch.float32, "noise")
+            hp = h.data_ptr()
+        npz = None if noise is None else self._f32(noise, "noise")
         self._check(lib().detag_grad_quadratic_diag(self._h, self._state(X, "X"), hp, per_worker,
-                                                    self._mat(b, torch.float32, "b"), npz, sigma, seed, step,
-                                                    self._mat(G, torch.float32, "G"), self._stream()))
+                                                    self._f32(b, "b"), npz, sigma, seed, step,
+                                                    self._f32(G, "G"), self._stream()))
 
     def step_quadratic(self, X, Y, G, h, b, alpha: float, K: int, sigma: float = 0.0, seed: int = 0, step: int = 0,
                        eta: float = -1.0, variant: int = DETAG_VARIANT_ATC):
         """h: a float32 vector of length >= d shared by the workers, or an n x ld matrix with one row per worker."""
-        import torch
         per_worker = 1 if h.dim() == 2 else 0
         if per_worker:
-            hp = self._mat(h, torch.float32, "h")
+            hp = self._f32(h, "h")
         else:
-            if h.dtype != torch.float32 or not h.is_cuda or h.dim() != 1 or h.numel() < self.d or not h.is_contiguous():
+            if h.dtype != _torch.float32 or not h.is_cuda or h.dim() != 1 or h.numel() < self.d or not h.is_contiguous():
                 raise ValueError("h must be a contiguous float32 GPU vector of length >= d")
-            hp = C.c_void_p(h.data_ptr())
+            hp = h.data_ptr()
         self._check(lib().detag_step_quadratic(self._h, self._state(X, "X"), self._state(Y, "Y"),
-                                               self._mat(G, torch.float32, "G"), hp, per_worker,
-                                               self._mat(b, torch.float32, "b"), sigma, seed, step, alpha, K, eta,
+                                               self._f32(G, "G"), hp, per_worker,
+                                               self._f32(b, "b"), sigma, seed, step, alpha, K, eta,
                                                variant, self._stream()))
 
     def grad_lstsq(self, X, A, b, G):
-        import torch
-        if A.dtype != torch.float32 or not A.is_cuda or not A.is_contiguous() or A.dim() != 3 \
+        if A.dtype != _torch.float32 or not A.is_cuda or not A.is_contiguous() or A.dim() != 3 \
                 or A.shape[0] != self.n or A.shape[2] != self.d:
             raise ValueError("A must be a contiguous float32 GPU tensor of shape (n, m, d)")
         m = A.shape[1]
-        if b.dtype != torch.float32 or not b.is_cuda or not b.is_contiguous() or tuple(b.shape) != (self.n, m):
+        if b.dtype != _torch.float32 or not b.is_cuda or not b.is_contiguous() or tuple(b.shape) != (self.n, m):
             raise ValueError("b must be a contiguous float32 GPU tensor of shape (n, m)")
-        self._check(lib().detag_grad_lstsq(self._h, self._state(X, "X"), C.c_void_p(A.data_ptr()),
-                                           C.c_void_p(b.data_ptr()), m, self._mat(G, torch.float32, "G"),
+        self._check(lib().detag_grad_lstsq(self._h, self._state(X, "X"), A.data_ptr(),
+                                           b.data_ptr(), m, self._f32(G, "G"),
                                            self._stream()))
 
     def grad_softmax_bf16(self, X, feats, labels, batch, C_classes: int, G, loss=None):
-        import torch
-        if feats.dtype != torch.bfloat16 or not feats.is_cuda or not feats.is_contiguous() or feats.dim() != 3 \
+        if feats.dtype != _torch.bfloat16 or not feats.is_cuda or not feats.is_contiguous() or feats.dim() != 3 \
                 or feats.shape[0] != self.n:
             raise ValueError("feats must be a contiguous bfloat16 GPU tensor of shape (n, S, F)")
         S, F = feats.shape[1], feats.shape[2]
-        if labels.dtype != torch.int32 or not labels.is_cuda or not labels.is_contiguous() or tuple(labels.shape) != (self.n, S):
+        if labels.dtype != _torch.int32 or not labels.is_cuda or not labels.is_contiguous() or tuple(labels.shape) != (self.n, S):
             raise ValueError("labels must be a contiguous int32 GPU tensor of shape (n, S)")
-        if batch.dtype != torch.int32 or not batch.is_cuda or not batch.is_contiguous() or batch.dim() != 2 \
+        if batch.dtype != _torch.int32 or not batch.is_cuda or not batch.is_contiguous() or batch.dim() != 2 \
                 or batch.shape[0] != self.n:
             raise ValueError("batch must be a contiguous int32 GPU tensor of shape (n, B)")
         B = batch.shape[1]
         lp = None
         if loss is not None:
-            if loss.dtype != torch.float32 or not loss.is_cuda or loss.numel() < self.n or not loss.is_contiguous():
+            if loss.dtype != _torch.float32 or not loss.is_cuda or loss.numel() < self.n or not loss.is_contiguous():
                 raise ValueError("loss must be a contiguous float32 GPU vector of length >= n")
-            lp = C.c_void_p(loss.data_ptr())
-        self._check(lib().detag_grad_softmax_bf16(self._h, self._state(X, "X"), C.c_void_p(feats.data_ptr()),
-                                                  C.c_void_p(labels.data_ptr()), C.c_void_p(batch.data_ptr()),
-                                                  S, F, C_classes, B, self._mat(G, torch.float32, "G"), lp,
+            lp = loss.data_ptr()
+        self._check(lib().detag_grad_softmax_bf16(self._h, self._state(X, "X"), feats.data_ptr(),
+                                                  labels.data_ptr(), batch.data_ptr(),
+                                                  S, F, C_classes, B, self._f32(G, "G"), lp,
                                                   self._stream()))
 
 
