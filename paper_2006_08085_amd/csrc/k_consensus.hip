@@ -23,6 +23,7 @@
 // No wavefront waits for another: there is no barrier.
 #include "detag_internal.h"
 #include "dev_common.hpp"
+#include "fused_common.hpp"
 
 namespace detag {
 namespace {
@@ -119,7 +120,8 @@ __global__ __launch_bounds__(256) void factor_sequence_kernel(ST *Z, int n, int6
                                                               const BatchWords *__restrict__ table, int batches) {
   extern __shared__ float smem[];  // one n x 64 tile per wavefront
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int64_t tile = (int64_t(blockIdx.x) * (blockDim.x >> 6) + w) * kCols;
+  // neighbouring tiles on one XCD (64 x 3,000,000 542 -> 493 us, odd pitch 64 x 300,007 68 -> 59 us)
+  const int64_t tile = (fused::xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + w) * kCols;
   if (tile >= d) return;  // no barrier anywhere below
   float *tile_f = smem + size_t(w) * n * kCols;
   char *mine = reinterpret_cast<char *>(tile_f + lane);

@@ -31,6 +31,7 @@
 // A: row m, k = 8g..8g+7;  B: column m, k = 8g..8g+7;  D: column m, register r -> row 8*(r/4) + 4g + r%4.
 #include "detag_internal.h"
 #include "dev_common.hpp"
+#include "fused_common.hpp"
 
 namespace detag {
 namespace {
@@ -278,7 +279,8 @@ __global__ __launch_bounds__(kThreads, TP >= 3 ? 2 : 3) void dense_phase_kernel(
                                                                   float alpha) {
   extern __shared__ uint16_t stage[];  // TU terms of one unit of the 64-column tile; afterwards the output scratch
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int64_t tile = int64_t(blockIdx.x) * kCols;
+  // neighbouring tiles on one XCD: where the pitch is odd they share cache lines (64 x 1,000,003 fp32: 616 -> 490 us)
+  const int64_t tile = fused::xcd_tile(blockIdx.x, gridDim.x) * kCols;
   const uint32_t valid = uint32_t(d - tile < kCols ? d - tile : kCols);
   const bool rows_mine = 64 * w < n;  // wavefront-uniform: this wavefront has output rows
   const uint32_t so = lane * uint32_t(sizeof(ST)), fo = lane * 4u;
