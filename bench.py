@@ -30,7 +30,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published peak
-LDS_PEAK_GBS = 256 * 128 * 2.4  # 256 compute units x 128 B per clock x 2.4 GHz = 78,643 GB/s
+LDS_PEAK_GBS = 256 * 256 * 2.4  # 256 compute units x 256 B per clock (16-byte reads) x 2.4 GHz = 157,286 GB/s
 PHASE_BYTES_PER_ELEMENT = 24   # detag_step, fp32: read X, Y, G_new, G_old; write X, Y (independent of K)
 FUSED_BYTES_PER_ELEMENT = 28   # detag_step_quadratic, fp32: read X, Y, G, b; write X, Y, G
 DPSGD_BYTES_PER_ELEMENT = 12   # detag_dpsgd_step, fp32: read X, G; write X
@@ -275,6 +275,7 @@ def main():
         bpe = 2 * sb + 4
         staged = n <= 256 and n * ld * sb >= (128 << 20)      # the launcher's rule for the LDS-staged round kernel
         kernel = (("fused_structured_kernel, D-PSGD mode" if structured and not per_round else
+                   "fused_generic_kernel, D-PSGD mode" if not per_round else
                    "gossip_round_tile_kernel, in place" if staged else "copy + gossip_round_kernel")
                   + " (detag_dpsgd_step)")
     elif fused:
@@ -282,7 +283,7 @@ def main():
         kernel = ("fused_generic_quadratic_kernel" if not structured else "fused_quadratic_alg2_kernel"
                   if args.variant == "alg2" else "fused_quadratic_kernel") + " (detag_step_quadratic)"
         if not structured:
-            note = "this kernel keeps all rows of a tile in LDS and is bound by LDS bandwidth and VALU issue, not by HBM"
+            note = "this kernel keeps all rows of a tile in LDS and is bound by LDS bandwidth and VALU issue, partly by HBM"
     elif per_round:
         bpe = 24 + 2 * rounds_bytes
         kernel = "elementwise_kernel + %s x%d (detag_step, one launch per round)" % (
@@ -295,7 +296,7 @@ def main():
         if args.dense:
             note = "bound by the latency of its staging loads and by instruction issue, not yet by HBM or the matrix cores"
         elif not structured:
-            note = "this kernel keeps all rows of a tile in LDS and is bound by LDS bandwidth and VALU issue, not by HBM"
+            note = "this kernel keeps all rows of a tile in LDS and is bound by LDS bandwidth and VALU issue, partly by HBM"
     if not bf16 and what == "step" and not per_round:
         assert bpe == (DPSGD_BYTES_PER_ELEMENT if alg == "dpsgd" else FUSED_BYTES_PER_ELEMENT if fused
                        else PHASE_BYTES_PER_ELEMENT)
@@ -350,7 +351,8 @@ def main():
                                 "lds_bytes_per_launch": lds_bytes, "hbm_achieved": achieved, "hbm_peak": HBM_PEAK_GBS,
                                 "hbm_frac": achieved / HBM_PEAK_GBS,
                                 "note": "the rounds run out of LDS: achieved/peak are LDS bytes over the whole kernel "
-                                        "against 256 CUs x 128 B/clk x 2.4 GHz; hbm_* give the HBM side of the same launch"})
+                                        "against 256 CUs x 256 B/clk x 2.4 GHz (the rate of 16-byte reads; four of them to one "
+                                        "write were measured at 106.7 TB/s); hbm_* give the HBM side of the same launch"})
         out["roofline"].pop("bar", None)
     if what == "diag":
         ce_ms = sum(e[1].elapsed_time(e[2]) for e in evs) / args.steps
