@@ -261,10 +261,13 @@ struct ListRounds {
       pairs[s] = int(a.groups[2 * (wave * S + s) + 1]);
 #pragma unroll
       for (int q = 0; q < kListPairs; ++q) {
-        f4 e = {__uint_as_float(0u), 0.f, __uint_as_float(0u), 0.f};
-        if (q < pairs[s]) e = a.pairs[first + q * rows_per_wave + in_wave];
-        at[s][2 * q] = __float_as_uint(e[0]) + col_bytes, weight[s][2 * q] = e[1];
-        at[s][2 * q + 1] = __float_as_uint(e[2]) + col_bytes, weight[s][2 * q + 1] = e[3];
+        // past the end of the list: the row itself with weight 0, so that nobody else's infinity gets in
+        at[s][2 * q] = at[s][2 * q + 1] = p.own(s), weight[s][2 * q] = weight[s][2 * q + 1] = 0.f;
+        if (q < pairs[s]) {
+          const f4 e = a.pairs[first + q * rows_per_wave + in_wave];
+          at[s][2 * q] = __float_as_uint(e[0]) + col_bytes, weight[s][2 * q] = e[1];
+          at[s][2 * q + 1] = __float_as_uint(e[2]) + col_bytes, weight[s][2 * q + 1] = e[3];
+        }
       }
     }
     cm = 1.f + eta;

@@ -128,3 +128,25 @@ def test_rounds_on_chip_beyond_the_family(n, kind, big, dtype, K):
             assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol, (path, variant)
             assert torch.equal(Xs[:, d:], torch.full_like(Xs[:, d:], SENTINEL))
     ctx.close()
+
+
+@pytest.mark.parametrize("n,kind", [(7, "ring"), (12, "irregular"), (31, "irregular"), (100, "irregular"), (64, "rr"), (257, "irregular")])
+@pytest.mark.parametrize("big", [False, True])
+def test_an_infinity_reaches_only_its_neighbours(n, kind, big):
+    """Padding of the neighbour tables must not name anybody else's row: after one round the columns of every worker that
+    neither holds the infinity nor has it as a neighbour are what they are without it."""
+    d = (1 << 19) // n * 4 + 8 if big else 200
+    e = _graph(kind, n)
+    W = OT.mixing_matrix(n, e, "metropolis")
+    ctx = D.detag_create(D.Topology.from_edges(e, D.DETAG_W_METROPOLIS), n, d)
+    Z = _matrix(n, d, d, 1)
+    clean = Z.clone()
+    ctx.gossip_accel(clean, 1, 0.3)
+    for worker in (0, n // 2, int(np.argmax((W != 0).sum(1)))):
+        bad = Z.clone()
+        bad[worker, 5] = float("inf")
+        ctx.gossip_accel(bad, 1, 0.3)
+        untouched = torch.as_tensor(np.flatnonzero(W[worker] == 0), device=DEV)
+        assert torch.equal(bad[untouched], clean[untouched])
+        bad[:, 5] = clean[:, 5]
+        assert torch.equal(bad, clean)
