@@ -165,13 +165,14 @@ struct ByteRounds {
   }
   __device__ __forceinline__ static int row(const Args &, const Place &p, int s) { return int(p.pos(s)); }
 
+  __device__ __forceinline__ uint32_t address(int s, int k) const {
+    return __builtin_amdgcn_perm(w[s][k / 4], low, 0x0c0c0000u | (4u + (k & 3)) << 8);
+  }
   // sum_j (z_j - z_i) on the tile at offset IN: the neighbours pairwise, so that DEG equal values sum exactly and
   // cancel DEG * z exactly
   template <uint32_t IN>
   __device__ __forceinline__ f4 diff_sum(int s, f4 z) const {
-    auto nb = [&](int k) {
-      return lds_read(__builtin_amdgcn_perm(w[s][k / 4], low, 0x0c0c0000u | (4u + (k & 3)) << 8) + IN);
-    };
+    auto nb = [&](int k) { return lds_read(address(s, k) + IN); };
     f4 sum;
     if constexpr (DEG == 2) sum = nb(0) + nb(1);
     else if constexpr (DEG == 4) sum = (nb(0) + nb(2)) + (nb(1) + nb(3));
@@ -179,6 +180,14 @@ struct ByteRounds {
     return fma4(-float(DEG), z, sum);
   }
   __device__ __forceinline__ float scale() const { return b; }
+  // sum_j W_ji (z_j - z_i) of a plain round (eta = 0) on the tile at offset 0, term by term in the order of the list.  The
+  // pairwise sum above rounds at DEG times the magnitude of z: not where its result is the step itself.
+  __device__ __forceinline__ f4 plain(int s, f4 z) const {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < DEG; ++k) acc = fma4(b, lds_read(address(s, k)) - z, acc);
+    return acc;
+  }
   // The table's registers are made opaque once per round: otherwise the addresses, 4 DEG of them, are computed ahead
   // of the round loop and kept, in four times the registers.
   __device__ __forceinline__ void keep_packed() {
@@ -238,6 +247,7 @@ struct CsrRounds {
     return acc;
   }
   __device__ __forceinline__ float scale() const { return cm; }
+  __device__ __forceinline__ f4 plain(int s, f4 z) const { return diff_sum<0u>(s, z); }  // as in ByteRounds
   __device__ __forceinline__ void keep_packed() { asm volatile("" : "+v"(list), "+v"(col_bytes)); }
 };
 
@@ -291,6 +301,7 @@ struct ListRounds {
     return acc;
   }
   __device__ __forceinline__ float scale() const { return cm; }
+  __device__ __forceinline__ f4 plain(int s, f4 z) const { return diff_sum<0u>(s, z); }  // as in ByteRounds
   __device__ __forceinline__ void keep_packed() {}
 };
 

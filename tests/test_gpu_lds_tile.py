@@ -150,3 +150,33 @@ def test_an_infinity_reaches_only_its_neighbours(n, kind, big):
         assert torch.equal(bad[untouched], clean[untouched])
         bad[:, 5] = clean[:, 5]
         assert torch.equal(bad, clean)
+
+
+@pytest.mark.parametrize("n,kind", [(1, "alone"), (2, "ring"), (7, "ring"), (12, "rr"), (31, "irregular"), (64, "rr8"), (100, "irregular"),
+                                    (129, "rr"), (256, "irregular"), (256, "rr"), (300, "rr"), (512, "asym")])
+@pytest.mark.parametrize("big,dtype", [(False, "f32"), (True, "f32"), (False, "bf16")])
+def test_dpsgd_is_the_step_of_one_launch_per_round(n, kind, big, dtype):
+    """The same sum in the same order with the same roundings, so the same bits: workers close to each other (where a sum
+    of neighbours instead of differences loses digits), values whose sum overflows, infinities."""
+    d = min(1 << 17, (1 << 19) // n * 4) + 5 if big else 333
+    sd = torch.bfloat16 if dtype == "bf16" else torch.float32
+    if kind == "alone":
+        topo = D.Topology.from_dense(np.ones((1, 1)))
+    elif kind == "asym":
+        topo = D.Topology.from_dense(sum(w * np.roll(np.eye(n), s, axis=1) for w, s in ((0.5, 0), (0.25, 1), (0.15, 7), (0.1, 200))))
+    else:
+        topo = D.Topology.ring() if kind == "ring" else D.Topology.from_edges(_graph(kind, n), D.DETAG_W_METROPOLIS)
+    ctx = D.detag_create(topo, n, d, d, D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32)
+    G = _matrix(n, d, d, 2)
+    X = (1.0 + 1e-3 * _matrix(n, d, d, 1)).to(sd)
+    X[:, 7] *= 1.5e38
+    X[n // 2, 11] = float("inf")
+    out = []
+    for path in (D.DETAG_PATH_AUTO, D.DETAG_PATH_PER_ROUND):
+        ctx.set_path(path)
+        out.append(X.clone())
+        ctx.dpsgd_step(out[-1], G, 0.1)
+    got, want = out
+    assert torch.isfinite(want[:, 7]).all()
+    assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.nan_to_num(1.0), want.nan_to_num(1.0))
+    ctx.close()
