@@ -6,6 +6,8 @@
 //     column) with Philox-4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11) and the
 //     Box-Muller transform.  A thread owns the four columns of one Philox block.
 //   least squares: G_i = A_i^T (A_i x_i - b_i), two small passes.
+#include <algorithm>
+
 #include "detag_internal.h"
 #include "dev_common.hpp"
 #include "noise_dev.hpp"
@@ -14,6 +16,9 @@ namespace detag {
 namespace {
 
 constexpr int kThreads = 256;
+// A grid counts its threads in 32 bits, and the runtime launches what is left of a larger number without an error: the
+// least-squares kernels, which take many threads per row or column, go in pieces of at most this many.
+constexpr int64_t kThreadsPerLaunch = int64_t(1) << 31;
 // four columns are one access wherever the row starts (see k_stream.hip)
 typedef float vf4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short vu4_t __attribute__((ext_vector_type(4), aligned(2)));
@@ -113,11 +118,11 @@ __device__ __forceinline__ vf4_t load4(const bf16_t *p) {
 // resid[i*m + r] = A_i[r,:] . x_i - b_i[r]; one block of one wavefront per (i, r), which spreads a few hundred rows over
 // all compute units.  Four 16-byte pieces of the row and of x are in flight per lane, each with a sum of its own.
 template <typename ST>
-__global__ __launch_bounds__(64) void lstsq_resid_kernel(int m, int64_t d, int64_t ld, const ST *__restrict__ X,
+__global__ __launch_bounds__(64) void lstsq_resid_kernel(int64_t first_row, int m, int64_t d, int64_t ld, const ST *__restrict__ X,
                                                          const float *__restrict__ A, const float *__restrict__ b,
                                                          float *__restrict__ resid) {
   constexpr int kPieces = 4;
-  const int64_t row = blockIdx.x;  // = i*m + r
+  const int64_t row = first_row + blockIdx.x;  // = i*m + r
   const int lane = threadIdx.x;
   const float *a = A + row * d;
   const ST *x = X + row / m * ld;
@@ -206,11 +211,15 @@ int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_p
 int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float *b, int m, float *resid, float *G,
                       void *stream) {
   auto st = static_cast<hipStream_t>(stream);
-  const dim3 g1(uint32_t(int64_t(s.n) * m));
-  if (s.bf16) lstsq_resid_kernel<bf16_t><<<g1, 64, 0, st>>>(m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, resid);
-  else lstsq_resid_kernel<float><<<g1, 64, 0, st>>>(m, s.d, s.ld, static_cast<const float *>(X), A, b, resid);
-  int rc = hip_rc(hipGetLastError());
-  if (rc) return rc;
+  const int64_t rows = int64_t(s.n) * m;
+  for (int64_t first = 0; first < rows; first += kThreadsPerLaunch / 64) {
+    const dim3 grid(uint32_t(std::min(rows - first, kThreadsPerLaunch / 64)));
+    if (s.bf16)
+      lstsq_resid_kernel<bf16_t><<<grid, 64, 0, st>>>(first, m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, resid);
+    else
+      lstsq_resid_kernel<float><<<grid, 64, 0, st>>>(first, m, s.d, s.ld, static_cast<const float *>(X), A, b, resid);
+    if (int rc = hip_rc(hipGetLastError())) return rc;
+  }
   // 64 columns per block until blocks of 256 columns alone make two per compute unit
   if (int64_t(ceil_div_i64(s.d, 256)) * s.n < 512)
     lstsq_grad_kernel<16><<<dim3(ceil_div_i64(s.d, 64), s.n), kSumThreads, 0, st>>>(m, s.d, s.ld, A, resid, G);

@@ -32,3 +32,16 @@ def test_blocks(n, d, m, pad, dtype):
     S = max(amax(ref), amax(A) * np.sqrt(d) * amax(A) * amax(X))
     assert rel_err(to_host(G, d), ref, S) < TOL_F32
     assert padding_ok(G, d)
+
+
+def _alone(d):
+    return D.detag_create(D.Topology.from_dense(np.ones((1, 1))), 1, d, d)
+
+
+def test_more_rows_than_a_launch_has_threads_for():
+    m = (1 << 26) + 8                                   # a wavefront per row: 2^32 threads and some
+    A, b = torch.zeros(1, m, 1, device=DEV), torch.full((1, m), -1.0, device=DEV)
+    A[0, :3, 0], A[0, -1, 0] = 1.0, 3.0
+    X, G = torch.ones(1, 1, device=DEV), torch.zeros(1, 1, device=DEV)
+    _alone(1).grad_lstsq(X, A, b, G)
+    assert G.item() == 3 * 1.0 * 2.0 + 3.0 * 4.0        # A^T (A x - b), exact in fp32
