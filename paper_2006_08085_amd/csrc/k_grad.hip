@@ -150,12 +150,13 @@ __global__ __launch_bounds__(64) void lstsq_resid_kernel(int64_t first_row, int 
 // of a row.
 constexpr int kSumThreads = 1024;
 template <int LANES>
-__global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int m, int64_t d, int64_t ld, const float *__restrict__ A,
-                                                                 const float *__restrict__ resid, float *__restrict__ G) {
+__global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_col, int m, int64_t d, int64_t ld,
+                                                                 const float *__restrict__ A, const float *__restrict__ resid,
+                                                                 float *__restrict__ G) {
   constexpr int kRows = kSumThreads / LANES, kCols = 4 * LANES, kWaves = kSumThreads / 64;
   __shared__ float part[kWaves][kCols];
   const int i = blockIdx.y, lane = threadIdx.x % LANES, r0 = threadIdx.x / LANES;
-  const int64_t c = int64_t(blockIdx.x) * kCols + 4 * lane;
+  const int64_t c0 = first_col + int64_t(blockIdx.x) * kCols, c = c0 + 4 * lane;
   const float *a = A + int64_t(i) * m * d;
   const float *res = resid + int64_t(i) * m;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
@@ -182,7 +183,7 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int m, int64_t 
   }
   __syncthreads();
   if (threadIdx.x < kCols) {
-    const int64_t col = int64_t(blockIdx.x) * kCols + threadIdx.x;
+    const int64_t col = c0 + threadIdx.x;
     float sum = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) sum += part[w][threadIdx.x];
@@ -221,11 +222,17 @@ int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float
     if (int rc = hip_rc(hipGetLastError())) return rc;
   }
   // 64 columns per block until blocks of 256 columns alone make two per compute unit
-  if (int64_t(ceil_div_i64(s.d, 256)) * s.n < 512)
-    lstsq_grad_kernel<16><<<dim3(ceil_div_i64(s.d, 64), s.n), kSumThreads, 0, st>>>(m, s.d, s.ld, A, resid, G);
-  else
-    lstsq_grad_kernel<64><<<dim3(ceil_div_i64(s.d, 256), s.n), kSumThreads, 0, st>>>(m, s.d, s.ld, A, resid, G);
-  return hip_rc(hipGetLastError());
+  if (int64_t(ceil_div_i64(s.d, 256)) * s.n < 512) {
+    lstsq_grad_kernel<16><<<dim3(ceil_div_i64(s.d, 64), s.n), kSumThreads, 0, st>>>(0, m, s.d, s.ld, A, resid, G);
+    return hip_rc(hipGetLastError());
+  }
+  constexpr int64_t kPiece = kThreadsPerLaunch / kSumThreads * 256;  // columns
+  for (int64_t first = 0; first < s.d; first += kPiece) {
+    const dim3 grid(ceil_div_i64(std::min(s.d - first, kPiece), 256), s.n);
+    lstsq_grad_kernel<64><<<grid, kSumThreads, 0, st>>>(first, m, s.d, s.ld, A, resid, G);
+    if (int rc = hip_rc(hipGetLastError())) return rc;
+  }
+  return 0;
 }
 
 }  // namespace detag

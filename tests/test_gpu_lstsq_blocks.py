@@ -7,7 +7,7 @@ import torch
 import paper_2006_08085_amd as D
 from oracle import objectives as OO
 from workloads import generate as gen
-from tests.gpu_util import DEV, _built, padding_ok, to_dev, to_host  # noqa: F401
+from tests.gpu_util import DEV, SENTINEL, _built, padding_ok, to_dev, to_host  # noqa: F401
 from tests.util import TOL_F32, amax, rel_err
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +45,13 @@ def test_more_rows_than_a_launch_has_threads_for():
     X, G = torch.ones(1, 1, device=DEV), torch.zeros(1, 1, device=DEV)
     _alone(1).grad_lstsq(X, A, b, G)
     assert G.item() == 3 * 1.0 * 2.0 + 3.0 * 4.0        # A^T (A x - b), exact in fp32
+
+
+def test_more_columns_than_a_launch_has_threads_for():
+    d = (1 << 30) + 3                                   # four threads per column: 2^32 and some
+    A, b = torch.zeros(1, 1, d, device=DEV), torch.full((1, 1), -2.0, device=DEV)
+    A[0, 0, -2:] = torch.tensor([3.0, 4.0], device=DEV)
+    A[0, 0, 1 << 29] = 5.0
+    X, G = torch.zeros(1, d, device=DEV), torch.full((1, d), SENTINEL, device=DEV)
+    _alone(d).grad_lstsq(X, A, b, G)
+    assert torch.equal(G, 2.0 * A[0])                   # A^T (A x - b), exact in fp32
