@@ -92,6 +92,10 @@ __device__ __forceinline__ P *launder_uniform(P *p) {
 // use v yet and carries the three operands instead of the one result.
 __device__ __forceinline__ void pin_vgpr(float &v) { asm volatile("" : "+v"(v)); }
 
+// A grid counts its threads in 32 bits, and the runtime launches what is left of a larger number without an error: kernels
+// that take many threads per row or column go in pieces of at most this many.
+constexpr int64_t kThreadsPerLaunch = int64_t(1) << 31;
+
 inline int hip_rc(hipError_t e) { return static_cast<int>(e); }
 
 inline int ceil_div_i64(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }

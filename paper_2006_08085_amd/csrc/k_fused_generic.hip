@@ -89,12 +89,18 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
 template <typename ST, class R>
 int launch_r(const Shape &s, const Geometry &g, size_t lds, const typename R::Args &ra, int mode, void *X, void *Y,
              const float *Gn, const float *Go, float alpha, int K, float eta, void *stream) {
-  const dim3 grid(ceil_div_i64(s.d, g.cols));
+  // a lane has 16 elements of a large matrix: 2^36 of them (one bf16 matrix of 137 GB) are 2^32 threads
+  const int64_t piece = kThreadsPerLaunch / g.threads * g.cols;  // columns
   auto go = [&](auto *kernel) -> int {
     if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
-    kernel<<<grid, g.threads, lds, static_cast<hipStream_t>(stream)>>>(static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go,
-                                                                       s.n, s.d, s.ld, g.lpr_log2(), ra, eta, alpha, K);
-    return hip_rc(hipGetLastError());
+    for (int64_t first = 0; first < s.d; first += piece) {
+      auto at = [&](auto *p) { return p ? p + first : p; };
+      const int64_t d = std::min(s.d - first, piece);
+      kernel<<<dim3(ceil_div_i64(d, g.cols)), g.threads, lds, static_cast<hipStream_t>(stream)>>>(
+          at(static_cast<ST *>(X)), at(static_cast<ST *>(Y)), at(Gn), at(Go), s.n, d, s.ld, g.lpr_log2(), ra, eta, alpha, K);
+      if (int rc = hip_rc(hipGetLastError())) return rc;
+    }
+    return 0;
   };
   switch (mode) {
     case 0: return go(&fused_generic_kernel<ST, 0, R>);

@@ -16,9 +16,6 @@ namespace detag {
 namespace {
 
 constexpr int kThreads = 256;
-// A grid counts its threads in 32 bits, and the runtime launches what is left of a larger number without an error: the
-// least-squares kernels, which take many threads per row or column, go in pieces of at most this many.
-constexpr int64_t kThreadsPerLaunch = int64_t(1) << 31;
 // four columns are one access wherever the row starts (see k_stream.hip)
 typedef float vf4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short vu4_t __attribute__((ext_vector_type(4), aligned(2)));

@@ -180,3 +180,27 @@ def test_dpsgd_is_the_step_of_one_launch_per_round(n, kind, big, dtype):
     assert torch.isfinite(want[:, 7]).all()
     assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.nan_to_num(1.0), want.nan_to_num(1.0))
     ctx.close()
+
+
+def test_more_elements_than_a_launch_has_threads_for():
+    """2^36 elements and some in one bf16 matrix (137 GB) of more workers than the family serves: a lane has 16 of them, a
+    grid counts 2^32 threads."""
+    n, K, eta = 512, 2, 0.3
+    d = (1 << 27) + 40
+    if torch.cuda.mem_get_info()[0] < 2 * n * d + (8 << 30):
+        pytest.skip("needs 146 GB of free GPU memory")
+    W = sum(w * np.roll(np.eye(n), s, axis=1) for w, s in ((0.5, 0), (0.25, 1), (0.15, 7), (0.1, 200)))
+    ctx = D.detag_create(D.Topology.from_dense(W), n, d, d, D.DETAG_BF16)
+    Z = torch.zeros((n, d), dtype=torch.bfloat16, device=DEV)
+    cols = np.concatenate([np.arange(40), (1 << 26) + np.arange(-20, 20), np.arange(d - 60, d)])
+    at = torch.as_tensor(cols, device=DEV)
+    Z[:, at] = _matrix(n, len(cols), len(cols), 1).to(torch.bfloat16)
+    z = _cols(Z, cols)
+    ctx.gossip_accel(Z, K, eta)
+    got = _cols(Z, cols)
+    Z[:, at] = 0
+    rest = max(Z[i].abs().max().item() for i in range(0, n, 73))
+    del Z
+    torch.cuda.empty_cache()
+    ctx.close()
+    assert rel_err(got, OG.accelerated_gossip(z, W, K, eta), amax(z)) < TOL_BF16 and rest == 0
