@@ -468,10 +468,11 @@ inline Geometry csr_geometry(int n, int64_t d) {
   return g;
 }
 
-// A launch that asks for more LDS than the default limit has to raise it for its kernel first.
+// A launch that asks for more LDS than the default limit raises it for its kernel first, always to the same value: the
+// limit is the process's, and contexts on other host threads launch the same kernel with lists of another length.
 inline int allow_lds(const void *kernel, size_t bytes) {
   if (bytes <= 65536) return 0;
-  return hip_rc(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)));
+  return hip_rc(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsMax)));
 }
 
 template <class R>
