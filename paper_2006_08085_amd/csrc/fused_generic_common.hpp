@@ -118,7 +118,7 @@ __device__ __forceinline__ void pin4(f4 &v) {
   }
 }
 
-// The tile starts at LDS offset 0: the kernels have no other LDS.  Addressed as numbers, an access costs no addition of
+// The tile starts at LDS offset 0: the kernels have no other LDS (tests/test_kernel_metadata.py).  Addressed as numbers, an access costs no addition of
 // a base that is zero.
 typedef __attribute__((address_space(3))) f4 lds_f4;
 __device__ __forceinline__ f4 lds_read(uint32_t off) { return *reinterpret_cast<const lds_f4 *>(off); }
