@@ -31,3 +31,9 @@ def test_chunks_and_stages(n, S, F, C, B, pad):
     assert rel_err(to_host(G, d), ref, amax(ref)) < TOL_F32
     assert np.abs(loss.cpu().numpy() - lref).max() < 1e-5 * np.abs(lref).max()
     assert padding_ok(G, d)
+
+
+@pytest.mark.parametrize("n,S,F,C,B,pad", [(2, 70, 6144, 3, 64, 0), (2, 70, 6176, 3, 64, 1), (1, 300, 16416, 10, 256, 0), (20, 40, 9216, 7, 32, 2)])
+def test_as_many_chunks_as_are_added_up_and_more(n, S, F, C, B, pad):
+    """16, 17, 43 and 24 chunks: from 17 on a launch of its own adds their parts of the logits up."""
+    test_chunks_and_stages(n, S, F, C, B, pad)
