@@ -55,50 +55,61 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short u4_any __attribute__((ext_vector_type(4), aligned(2)));
 
-// Four adjacent columns of a row from column c on.  FULL: the block's columns all exist.  Otherwise columns past the
-// last one repeat it: they are computed and never stored.
-template <bool FULL>
-__device__ __forceinline__ f4 load4(const float *base, int64_t row_off, int64_t c, int64_t d) {
-  if constexpr (FULL) return __builtin_nontemporal_load(reinterpret_cast<const f4_any *>(base + (row_off + c)));
+__device__ __forceinline__ f4 load4(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const f4_any *>(p)); }
+__device__ __forceinline__ f4 load4(const bf16_t *p) {
+  const u4_any t = __builtin_nontemporal_load(reinterpret_cast<const u4_any *>(p));
   f4 v;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = base[row_off + (c + e < d ? c + e : d - 1)];
+  for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
   return v;
 }
-template <bool FULL>
-__device__ __forceinline__ f4 load4(const bf16_t *base, int64_t row_off, int64_t c, int64_t d) {
-  f4 v;
-  if constexpr (FULL) {
-    const u4_any t = __builtin_nontemporal_load(reinterpret_cast<const u4_any *>(base + (row_off + c)));
+__device__ __forceinline__ void store4(float *p, f4 v) { __builtin_nontemporal_store(f4_any(v), reinterpret_cast<f4_any *>(p)); }
+__device__ __forceinline__ void store4(bf16_t *p, f4 v) {
+  u4_any t;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
-  } else {
+  for (int e = 0; e < 4; ++e) t[e] = bf16_bits_rne(v[e]);
+  __builtin_nontemporal_store(t, reinterpret_cast<u4_any *>(p));
+}
+
+// The columns of a block: all exist; the rows end after four of them or more; after fewer than four.
+enum Tile : int { kWhole, kCut, kNarrow };
+
+// The four columns of a lane.  Columns are independent, so in a cut tile a lane whose columns do not all exist takes the
+// row's last four instead (at = d - 4): those before its own are computed once more and not stored, a lane past the end
+// stores none.  The accesses are those of a whole tile.  One by one, with a 64-bit address for each column, the cut tile
+// was so much code that fetching it took longer than the rest of a small call (1000 workers on a ring, d = 300, K = 4
+// 51 us, 23 us so; 256 workers, 4-regular, d = 3,915, K = 1 14.9 and 8.0 us).  A narrow tile is read one by one: its row's
+// last four columns lie in lines of the tile before (d = 3,906 8.4 us, 10.9 us the other way).
+// CUT = false: cut tiles are treated like narrow ones.  One register decides for all of a block's loads and stores.
+template <bool CUT>
+__device__ __forceinline__ int tile_kind(int64_t first, int lpr_log2, int64_t d) {
+  const int64_t left = d - first;
+  const bool whole = left >= int64_t(4) << lpr_log2;
+  if constexpr (!CUT) return whole ? kWhole : kNarrow;
+  return whole ? kWhole : left >= 4 ? kCut : kNarrow;
+}
+
+struct Columns {
+  int64_t at;  // the first of them
+  int skip;    // how many of them belong to the lane before; 4 or more: none is the lane's
+};
+
+template <int TILE, class ST>
+__device__ __forceinline__ f4 load4(const ST *base, int64_t row_off, const Columns &c, int64_t d) {
+  if constexpr (TILE != kNarrow) return load4(base + (row_off + c.at));
+  f4 v;  // columns past the last repeat it
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = to_f32(base[row_off + (c + e < d ? c + e : d - 1)]);
-  }
+  for (int e = 0; e < 4; ++e) v[e] = to_f32(base[row_off + (c.at + e < d ? c.at + e : d - 1)]);
   return v;
 }
-template <bool FULL>
-__device__ __forceinline__ void store4(float *base, int64_t row_off, int64_t c, int64_t d, f4 v) {
-  if constexpr (FULL) {
-    __builtin_nontemporal_store(f4_any(v), reinterpret_cast<f4_any *>(base + (row_off + c)));
+template <int TILE, class ST>
+__device__ __forceinline__ void store4(ST *base, int64_t row_off, const Columns &c, int64_t d, f4 v) {
+  if (TILE == kWhole || (TILE == kCut && c.skip == 0)) {
+    store4(base + (row_off + c.at), v);
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (c + e < d) base[row_off + c + e] = v[e];
-  }
-}
-template <bool FULL>
-__device__ __forceinline__ void store4(bf16_t *base, int64_t row_off, int64_t c, int64_t d, f4 v) {
-  if constexpr (FULL) {
-    u4_any t;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) t[e] = bf16_bits_rne(v[e]);
-    __builtin_nontemporal_store(t, reinterpret_cast<u4_any *>(base + (row_off + c)));
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (c + e < d) base[row_off + c + e].bits = bf16_bits_rne(v[e]);
+    for (int e = TILE == kCut; e < 4; ++e)
+      if (e >= c.skip && (TILE == kCut || c.at + e < d)) base[row_off + c.at + e] = from_f32<ST>(v[e]);
   }
 }
 
@@ -138,6 +149,12 @@ struct Place {
 // Blocks of S < 4 hold two tiles; the second one starts here (a compile-time distance, so that it costs no address).
 constexpr uint32_t second_tile(int S) { return uint32_t(S) * kThreadsMax * 16u; }
 
+// A small matrix is a chain of memory latencies: the table of its S < 4 rows per lane is requested ahead of the state
+// (13 irregular workers, d = 7,692, K = 4 7.3 -> 6.7 us).  With S = 4 its registers are free for the first loads and it
+// comes after them.
+template <int S>
+constexpr bool kFetchFirst = S < kSlotsMax;
+
 template <int DEG, int S>
 struct ByteRounds {
   static constexpr int kSlots = S, kWords = DEG <= 4 ? 1 : DEG / 4;
@@ -151,7 +168,14 @@ struct ByteRounds {
   uint32_t low;  // low byte of the lane's column offset
   float b;
 
+  __device__ __forceinline__ void fetch(const Args &a, const Place &p) {
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int q = 0; q < kWords; ++q) w[s][q] = a.table[p.pos(s) * kWords + q];
+  }
   __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
+    if constexpr (!kFetchFirst<S>) fetch(a, p);
     // row r starts at r * cols * 4 bytes and the columns add up to cols * 4 - 1: the neighbour's byte becomes bits 8..15
     // of the address of the lane's columns in that row (cols is 64, 128 or 256; n * cols <= 16384)
     const uint32_t byte_col = p.col() * 4u, scale = 1u << (p.lpr_log2 - 4);
@@ -159,11 +183,10 @@ struct ByteRounds {
 #pragma unroll
     for (int s = 0; s < S; ++s)
 #pragma unroll
-      for (int q = 0; q < kWords; ++q)
-        w[s][q] = a.table[p.pos(s) * kWords + q] * scale + (byte_col >> 8) * 0x01010101u;
+      for (int q = 0; q < kWords; ++q) w[s][q] = w[s][q] * scale + (byte_col >> 8) * 0x01010101u;
     b = (1.f + eta) * a.weight;
   }
-  __device__ __forceinline__ static int row(const Args &, const Place &p, int s) { return int(p.pos(s)); }
+  __device__ __forceinline__ int row(const Args &, const Place &p, int s) const { return int(p.pos(s)); }
 
   __device__ __forceinline__ uint32_t address(int s, int k) const {
     return __builtin_amdgcn_perm(w[s][k / 4], low, 0x0c0c0000u | (4u + (k & 3)) << 8);
@@ -221,6 +244,7 @@ struct CsrRounds {
   uint32_t col_bytes, step;
   float cm;
 
+  __device__ __forceinline__ void fetch(const Args &, const Place &) {}
   __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
     for (int k = int(p.tid); k < a.pair_count; k += int(p.threads)) lds_write(a.tile_bytes + 16u * k, a.pairs[k]);
     const uint32_t wave = __builtin_amdgcn_readfirstlane(p.tid >> 6), rows_per_wave = 64u >> p.lpr_log2;
@@ -231,7 +255,7 @@ struct CsrRounds {
     col_bytes = p.col() * 4u;
     cm = 1.f + eta;
   }
-  __device__ __forceinline__ static int row(const Args &a, const Place &p, int s) { return a.rows[p.pos(s)]; }
+  __device__ __forceinline__ int row(const Args &a, const Place &p, int s) const { return a.rows[p.pos(s)]; }
 
   // sum_j W_ji (z_j - z_i); lists are padded to an even length with the row itself, weight 0
   template <uint32_t IN>
@@ -257,32 +281,44 @@ template <int S>
 struct ListRounds {
   static constexpr int kSlots = S, kWaves = 4, kParked = 0;
   using Args = ListArgs;
+  f4 list[S][kListPairs];
   uint32_t at[S][2 * kListPairs];
   float weight[S][2 * kListPairs];
-  int pairs[S];  // uniform in a wavefront
+  int rows[S], pairs[S];  // pairs: uniform in a wavefront
   float cm;
 
-  __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
+  __device__ __forceinline__ void fetch(const Args &a, const Place &p) {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(p.tid >> 6), rows_per_wave = 64u >> p.lpr_log2;
-    const uint32_t in_wave = (p.tid & 63u) >> p.lpr_log2, col_bytes = p.col() * 4u;
+    const uint32_t in_wave = (p.tid & 63u) >> p.lpr_log2;
+    uint32_t first[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const uint32_t first = a.groups[2 * (wave * S + s)];
-      pairs[s] = int(a.groups[2 * (wave * S + s) + 1]);
+      rows[s] = a.rows[p.pos(s)];
+      first[s] = a.groups[2 * (wave * S + s)], pairs[s] = int(a.groups[2 * (wave * S + s) + 1]);
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int q = 0; q < kListPairs; ++q)
+        if (q < pairs[s]) list[s][q] = a.pairs[first[s] + q * rows_per_wave + in_wave];
+  }
+  __device__ __forceinline__ void init(const Args &, const Place &p, float eta) {
+    const uint32_t col_bytes = p.col() * 4u;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
 #pragma unroll
       for (int q = 0; q < kListPairs; ++q) {
         // past the end of the list: the row itself with weight 0, so that nobody else's infinity gets in
         at[s][2 * q] = at[s][2 * q + 1] = p.own(s), weight[s][2 * q] = weight[s][2 * q + 1] = 0.f;
         if (q < pairs[s]) {
-          const f4 e = a.pairs[first + q * rows_per_wave + in_wave];
+          const f4 e = list[s][q];
           at[s][2 * q] = __float_as_uint(e[0]) + col_bytes, weight[s][2 * q] = e[1];
           at[s][2 * q + 1] = __float_as_uint(e[2]) + col_bytes, weight[s][2 * q + 1] = e[3];
         }
       }
-    }
     cm = 1.f + eta;
   }
-  __device__ __forceinline__ static int row(const Args &a, const Place &p, int s) { return a.rows[p.pos(s)]; }
+  __device__ __forceinline__ int row(const Args &, const Place &, int s) const { return rows[s]; }
 
   template <uint32_t IN>
   __device__ __forceinline__ f4 diff_sum(int s, f4 z) const {
@@ -374,25 +410,28 @@ __device__ __forceinline__ void gossip(f4 (&z)[R::kSlots], R &rounds, Place &p, 
   p.forget();
 }
 
-// Calls f(full, s, row offset, column, mine) for the lane's rows in turn, with the scheduler fenced in between: left
-// alone, the compiler issues every row's loads at once and spills.  `full` is a compile-time truth value.  A position
-// past the last row reads row 0 and must not store (mine = false); no list names it.
-template <class R, class F>
-__device__ __forceinline__ void each_row(const typename R::Args &ra, Place &p, bool full, int n, int64_t ld,
-                                         int64_t first, F &&f) {
-  auto go = [&](auto is_full) {
+// Calls f(tile, s, row offset, columns, mine) for the lane's rows in turn, with the scheduler fenced in between: left
+// alone, the compiler issues every row's loads at once and spills.  `tile` is a compile-time value of Tile.  A position
+// past the last row reads row 0 and must not store (mine = false); no list names it.  CUT as above.
+template <class R, bool CUT, class F>
+__device__ __forceinline__ void each_row(const R &rounds, const typename R::Args &ra, Place &p, int tile, int n, int64_t d,
+                                         int64_t ld, int64_t first, F &&f) {
+  auto go = [&](auto of) {
 #pragma unroll
     for (int s = 0; s < R::kSlots; ++s) {
       p.forget();
-      const int64_t c = first + p.col();
-      const int row = R::row(ra, p, s);
+      Columns c{first + p.col(), 0};
+      if (of == kCut && c.at > d - 4) c = Columns{d - 4, int(c.at - (d - 4))};
+      const int row = rounds.row(ra, p, s);
       const bool mine = row >= 0 && row < n;
-      f(is_full, s, int64_t(mine ? row : 0) * ld, c, mine);
+      f(of, s, int64_t(mine ? row : 0) * ld, c, mine);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  if (full) go(std::true_type{});
-  else go(std::false_type{});
+  if (__builtin_expect(tile == kWhole, 1)) return go(std::integral_constant<int, kWhole>{});
+  if constexpr (CUT)
+    if (tile == kCut) return go(std::integral_constant<int, kCut>{});
+  go(std::integral_constant<int, kNarrow>{});
 }
 
 // Columns, rows per lane and threads of a block.  A tile takes 16 bytes per lane and row: 64 KiB at most.

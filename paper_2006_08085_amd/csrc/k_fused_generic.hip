@@ -24,19 +24,20 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
                                                                        float eta, float alpha, int K) {
   Place p{threadIdx.x, blockDim.x, lpr_log2};
   const int64_t first = fused::xcd_tile(blockIdx.x, gridDim.x) << (lpr_log2 + 2);
-  const bool full = first + (int64_t(4) << lpr_log2) <= d;
+  const int tile = tile_kind<true>(first, lpr_log2, d);
   f4 z[R::kSlots];
   Waiting<R> v;
-  auto rows = [&](auto f) { each_row<R>(ra, p, full, n, ld, first, f); };
   R rounds;  // set up after the first loads: until then its registers are free for them
+  auto rows = [&](auto f) { each_row<R, true>(rounds, ra, p, tile, n, d, ld, first, f); };
+  if constexpr (kFetchFirst<R::kSlots>) rounds.fetch(ra, p);
   if constexpr (MODE == 0) {
-    rows([&](auto F, int s, int64_t off, int64_t c, bool) { z[s] = load4<F>(X, off, c, d); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F>(X, off, c, d); });
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(X, off, c, d, z[s]); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F>(X, off, c, d, z[s]); });
   } else if constexpr (MODE == 1) {
     // every input is read once: the second gossip's input Y + Gn - Go waits in registers under the first
-    rows([&](auto F, int s, int64_t off, int64_t c, bool) {
+    rows([&](auto F, int s, int64_t off, Columns c, bool) {
       const f4 x = load4<F>(X, off, c, d), y = load4<F>(Y, off, c, d), gn = load4<F>(Gn, off, c, d), go = load4<F>(Go, off, c, d);
       z[s] = fma4(-alpha, y, x);
       f4 t = y + gn - go;
@@ -45,21 +46,21 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     });
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
       if (mine) store4<F>(X, off, c, d, z[s]);
       z[s] = v.get(p, s);
     });
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
   } else if constexpr (MODE == 3) {
     f4 g[R::kSlots];
-    rows([&](auto F, int s, int64_t off, int64_t c, bool) {
+    rows([&](auto F, int s, int64_t off, Columns c, bool) {
       z[s] = load4<F>(X, off, c, d), g[s] = load4<F>(Gn, off, c, d);
       lds_write(p.own(s), z[s]);
     });
     rounds.init(ra, p, eta);
     __syncthreads();
-    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
       // the increment at its own magnitude and one rounding at that of z, as in the kernel with one launch per round and
       // bit for bit its result (mixed first and -alpha*g added to that: 1.4 to 1.8 times the error against 64 bits); the
       // padded list of a worker without neighbours names itself and is left out
@@ -68,15 +69,15 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     });
   } else {
     // M(Y) first: both outputs need it
-    rows([&](auto F, int s, int64_t off, int64_t c, bool) { z[s] = load4<F>(Y, off, c, d); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F>(Y, off, c, d); });
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, int64_t c, bool) {
+    rows([&](auto F, int s, int64_t off, Columns c, bool) {
       v.put(p, s, z[s]);
       z[s] = load4<F>(X, off, c, d);
     });
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
       const f4 gn = load4<F>(Gn, off, c, d), go = load4<F>(Go, off, c, d), my = v.get(p, s);
       if (mine) {
         store4<F>(X, off, c, d, fma4(-alpha, my, z[s]));

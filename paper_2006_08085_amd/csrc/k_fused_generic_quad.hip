@@ -25,19 +25,24 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadrati
     uint32_t step) {
   Place p{threadIdx.x, blockDim.x, lpr_log2};
   const int64_t first = fused::xcd_tile(blockIdx.x, gridDim.x) << (lpr_log2 + 2);
-  const bool full = first + (int64_t(4) << lpr_log2) <= d;
+  // within 64 registers the third form of the loads costs the others a spill (n = 256, d = 1 M, bf16, K = 4 1167 -> 1189 us)
+  constexpr bool kCutTiles = R::kParked == 0;
+  const int tile = tile_kind<kCutTiles>(first, lpr_log2, d);
   f4 z[R::kSlots];
   Waiting<R> v;
-  auto rows = [&](auto f) { each_row<R>(ra, p, full, n, ld, first, f); };
-  rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+  R rounds;  // set up after the loads: until then its registers are free for them
+  auto rows = [&](auto f) { each_row<R, kCutTiles>(rounds, ra, p, tile, n, d, ld, first, f); };
+  if constexpr (kFetchFirst<R::kSlots>) rounds.fetch(ra, p);
+  rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
     // the row's noise first, its loads after: generated under the loads, the Philox state and the values in flight
     // are live together and the kernel does not fit its registers
     f4 noise = {0.f, 0.f, 0.f, 0.f};
     if (sigma != 0.f) {
       float t[4];
-      normal4(uint64_t(c) >> 2, uint32_t(R::row(ra, p, s)), step, seed_lo, seed_hi, t);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) noise[e] = t[e];
+      normal4(uint64_t(c.at + c.skip) >> 2, uint32_t(rounds.row(ra, p, s)), step, seed_lo, seed_hi, t);
+      noise = f4{t[0], t[1], t[2], t[3]};
+      if (F == kCut && c.skip > 0)  // the block of the lane's own columns, moved to where they are
+        noise = f4{t[0], c.skip == 1 ? t[0] : t[1], c.skip == 1 ? t[1] : t[0], c.skip == 1 ? t[2] : c.skip == 2 ? t[1] : t[0]};
     }
     __builtin_amdgcn_sched_barrier(0);
     const f4 x = load4<F>(X, off, c, d), bb = load4<F>(b, off, c, d), hh = load4<F>(h, HPW ? off : 0, c, d);
@@ -52,15 +57,14 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadrati
     v.put(p, s, t);
     if (mine) store4<F>(G, off, c, d, g);
   });
-  R rounds;  // set up after the loads: until then its registers are free for them
   rounds.init(ra, p, eta);
   gossip(z, rounds, p, eta, K);
-  rows([&](auto F, int s, int64_t off, int64_t c, bool mine) {
+  rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
     if (mine) store4<F>(X, off, c, d, z[s]);
     z[s] = v.get(p, s);
   });
   gossip(z, rounds, p, eta, K);
-  rows([&](auto F, int s, int64_t off, int64_t c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
+  rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
 }
 
 }  // namespace

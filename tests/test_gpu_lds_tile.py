@@ -204,3 +204,38 @@ def test_more_elements_than_a_launch_has_threads_for():
     torch.cuda.empty_cache()
     ctx.close()
     assert rel_err(got, OG.accelerated_gossip(z, W, K, eta), amax(z)) < TOL_BF16 and rest == 0
+
+
+@pytest.mark.parametrize("n,kind", [(7, "ring"), (13, "irregular"), (64, "rr8"), (100, "irregular"), (200, "rr"), (300, "rr")])
+@pytest.mark.parametrize("big,dtype", [(False, "f32"), (True, "f32"), (False, "bf16"), (True, "bf16")])
+def test_where_the_rows_end_in_a_tile(n, kind, big, dtype):
+    """Columns are independent: whatever number of columns the last tile has, each comes out as in a wider matrix, bit for
+    bit, and nothing is written behind them."""
+    base = (1 << 19) // n * 4 + 256 if big else 256
+    ld, K, eta, alpha, sigma = base + 256, 3, 0.35, 0.2, 0.1
+    sd = torch.bfloat16 if dtype == "bf16" else torch.float32
+    topo = D.Topology.ring() if kind == "ring" else D.Topology.from_edges(_graph(kind, n), D.DETAG_W_METROPOLIS)
+    state = [_matrix(n, ld, ld, k, sd if k < 2 else torch.float32) for k in range(5)]
+    h = torch.rand(ld, device=DEV)
+
+    def run(d):
+        ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32)
+        X, Y, Gn, Go, b = state
+        out = [X.clone() for _ in range(8)]
+        ctx.gossip_accel(out[0], K, eta)
+        ctx.dpsgd_step(out[1], Gn, alpha)
+        out[3].copy_(Y), out[5].copy_(Y), out[7].copy_(Y)
+        ctx.step(out[2], out[3], Gn, Go, alpha, K, eta, D.DETAG_VARIANT_ATC)
+        ctx.step(out[4], out[5], Gn, Go, alpha, K, eta, D.DETAG_VARIANT_ALG2)
+        G = Go.clone()
+        if n <= 256:
+            ctx.step_quadratic(out[6], out[7], G, h, b, alpha, K, sigma=sigma, seed=3, step=1, eta=eta)
+        ctx.close()
+        return out + [G]
+
+    whole = run(base + 256)
+    for more in (0, 1, 2, 3, 4, 5, 6, 7, 31, 33, 62, 130, 255):
+        d = base + more
+        before = [state[0], state[0], state[0], state[1], state[0], state[1], state[0], state[1], state[3]]
+        for got, want, old in zip(run(d), whole, before):
+            assert torch.equal(got[:, :d], want[:, :d]) and torch.equal(got[:, d:], old[:, d:]), more
