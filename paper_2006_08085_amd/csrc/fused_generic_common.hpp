@@ -72,7 +72,7 @@ __device__ __forceinline__ void store4(bf16_t *p, f4 v) {
 }
 
 // The columns of a block: all exist; the rows end after four of them or more; after fewer than four.
-enum Tile : int { kWhole, kCut, kNarrow };
+enum Tile : int { kNarrow, kCut, kWhole };
 
 // The four columns of a lane.  Columns are independent, so in a cut tile a lane whose columns do not all exist takes the
 // row's last four instead (at = d - 4): those before its own are computed once more and not stored, a lane past the end
@@ -80,12 +80,16 @@ enum Tile : int { kWhole, kCut, kNarrow };
 // was so much code that fetching it took longer than the rest of a small call (1000 workers on a ring, d = 300, K = 4
 // 51 us, 23 us so; 256 workers, 4-regular, d = 3,915, K = 1 14.9 and 8.0 us).  A narrow tile is read one by one: its row's
 // last four columns lie in lines of the tile before (d = 3,906 8.4 us, 10.9 us the other way).
-// CUT = false: cut tiles are treated like narrow ones.  One register decides for all of a block's loads and stores.
-template <bool CUT>
+// CUT = false: cut tiles are treated like narrow ones.  IN_SGPR: one scalar register decides for all of a block's loads
+// and stores, which saves the kernels that live within 64 vector registers a spill in their rounds; without it the
+// compiler lays the whole tiles' code out as the straight path, which is 2 to 10 % of a phase where one block of 1024
+// threads has a compute unit to itself (1000 workers, d = 60,000, K = 1 387 and 404 us).
+template <bool CUT, bool IN_SGPR>
 __device__ __forceinline__ int tile_kind(int64_t first, int lpr_log2, int64_t d) {
   const int64_t left = d - first;
   const bool whole = left >= int64_t(4) << lpr_log2;
   if constexpr (!CUT) return whole ? kWhole : kNarrow;
+  if constexpr (IN_SGPR) return __builtin_amdgcn_readfirstlane(whole ? kWhole : left >= 4 ? kCut : kNarrow);
   return whole ? kWhole : left >= 4 ? kCut : kNarrow;
 }
 
@@ -428,10 +432,12 @@ __device__ __forceinline__ void each_row(const R &rounds, const typename R::Args
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  if (__builtin_expect(tile == kWhole, 1)) return go(std::integral_constant<int, kWhole>{});
-  if constexpr (CUT)
-    if (tile == kCut) return go(std::integral_constant<int, kCut>{});
-  go(std::integral_constant<int, kNarrow>{});
+  if (tile >= kWhole) {
+    go(std::integral_constant<int, kWhole>{});
+  } else {
+    if (CUT && tile == kCut) go(std::integral_constant<int, CUT ? kCut : kNarrow>{});
+    else go(std::integral_constant<int, kNarrow>{});
+  }
 }
 
 // Columns, rows per lane and threads of a block.  A tile takes 16 bytes per lane and row: 64 KiB at most.

@@ -24,7 +24,7 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
                                                                        float eta, float alpha, int K) {
   Place p{threadIdx.x, blockDim.x, lpr_log2};
   const int64_t first = fused::xcd_tile(blockIdx.x, gridDim.x) << (lpr_log2 + 2);
-  const int tile = tile_kind<true>(first, lpr_log2, d);
+  const int tile = tile_kind<true, R::kParked != 0>(first, lpr_log2, d);
   f4 z[R::kSlots];
   Waiting<R> v;
   R rounds;  // set up after the first loads: until then its registers are free for them

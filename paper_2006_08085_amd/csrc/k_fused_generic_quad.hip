@@ -27,7 +27,7 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadrati
   const int64_t first = fused::xcd_tile(blockIdx.x, gridDim.x) << (lpr_log2 + 2);
   // within 64 registers the third form of the loads costs the others a spill (n = 256, d = 1 M, bf16, K = 4 1167 -> 1189 us)
   constexpr bool kCutTiles = R::kParked == 0;
-  const int tile = tile_kind<kCutTiles>(first, lpr_log2, d);
+  const int tile = tile_kind<kCutTiles, R::kParked != 0>(first, lpr_log2, d);
   f4 z[R::kSlots];
   Waiting<R> v;
   R rounds;  // set up after the loads: until then its registers are free for them
