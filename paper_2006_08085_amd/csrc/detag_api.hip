@@ -182,9 +182,10 @@ detag_status choose_path(const detag_ctx *ctx, int K, Chosen *out) {
     return set_err(ctx, DETAG_EUNSUPPORTED, "no fused kernel for this topology and n");
   // More workers or neighbours than the LDS family is offered for, but lists and tile fit a compute unit: the rounds of
   // a phase run there all the same (300 workers, 4 neighbours, d = 100,000: K = 1 450 -> 160 us, K = 8 2050 -> 320 us).
-  // Not for one or two rounds of more than 512 workers on a matrix too small to fill the chip, where reading the
-  // lists is most of the work (1000 workers, d = 1,000, K = 2: 31 us with a launch per round, 47 us so).
-  const bool few = K <= 2 && ctx->shape.n > 512 && int64_t(ctx->shape.n) * ctx->shape.d <= (int64_t(1) << 21);
+  // Not for one or two rounds of more than 512 workers on so few columns that a launch per round takes them at once: there
+  // reading the lists is most of the work (1000 on a ring, d = 64, K = 2 17 us with a launch per round, 19 us so, K = 3
+  // 23 and 21 us; d = 300, K = 1 16.6 and 17.8 us; d = 1,000, K = 2 29 and 27 us).
+  const bool few = K <= 2 && ctx->shape.n > 512 && int64_t(ctx->shape.n) * ctx->shape.d <= (int64_t(1) << 19);
   return *out = ctx->has_lds && !few ? kOnChipLists : kPerRound, DETAG_OK;
 }
 

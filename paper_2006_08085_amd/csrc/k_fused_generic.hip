@@ -112,6 +112,19 @@ int launch_r(const Shape &s, const Geometry &g, size_t lds, const typename R::Ar
   return hip_rc(hipErrorInvalidValue);
 }
 
+// Whether a hub makes the kernels with one launch per round the faster ones.  In LDS a wavefront walks the longest list
+// alone while the others of its block wait; with three blocks on a compute unit that hides, and up to 32 Mi elements the
+// other kernels, whose block walks it too, are slower in any case (star of 257, d = 20,000, K = 8 1390 us against 430).
+// Beyond, per round and 1000 columns, fitted to hubs of 64 to 300 neighbours, the other workers on a path or the hub's
+// leaves (n = 257 ... 400, d = 150,000, K = 8): 0.12 + 0.0037 longest (two blocks) or 0.22 + 0.0056 longest (one)
+// against 0.0022 longest + 0.00073 entries us.  Step of a star of 256 (three blocks) 3320 -> 1990 us, of 257 2970 and
+// 3360, of 400 with a hub of 160 on a path 2940 and 2670, of 200 3180 and 3200.
+bool lopsided(const Geometry &g, size_t lds, int64_t elements, int longest, int64_t entries) {
+  const int blocks = std::min(int(kLdsMax / lds), CsrRounds<kSlotsMax>::kWaves * 4 / (g.threads / 64));
+  if (blocks >= 3 || elements <= int64_t(1) << 25) return false;
+  return entries < (blocks == 2 ? 2.1 * longest + 164 : 4.6 * longest + 304);
+}
+
 }  // namespace
 
 int launch_fused_generic(const Shape &s, const LdsTable &t, int mode, void *X, void *Y, const float *Gn, const float *Go,
@@ -127,6 +140,7 @@ int launch_fused_generic(const Shape &s, const LdsTable &t, int mode, void *X, v
 bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
   const int n = W.n;
   int maxdeg = 0;
+  int64_t entries = 0;  // off the diagonal
   bool one_weight = true, have = false;
   float weight = 0.f;
   for (int i = 0; i < n; ++i) {
@@ -138,7 +152,7 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
       else if (v != weight) one_weight = false;
       ++cnt;
     }
-    maxdeg = std::max(maxdeg, cnt);
+    maxdeg = std::max(maxdeg, cnt), entries += cnt;
   }
   out = LdsTableHost{};
   // a small matrix of more workers than two rows per lane of a 64-column tile hold (n > 128) is better off with the
@@ -208,11 +222,8 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
             out.pairs.push_back(bits);
           }
     }
-  // A wavefront walks its longest list alone while the others wait at the barrier: with more than 256 neighbours on a
-  // hub, and enough columns to fill the chip, the one-launch-per-round kernels are the faster ones (star of 300, d =
-  // 200,000, K = 8: 3570 against 3860 us; star of 100 1170 against 480 us)
-  const bool lopsided = out.max_pairs > 128 && !small_matrix(n, d);
-  if (lopsided || g.tile_bytes(0) + out.pairs.size() * 4 > kLdsMax) {
+  const size_t lds = g.tile_bytes(0) + out.pairs.size() * 4;
+  if (lds > kLdsMax || lopsided(g, lds, n * d, maxdeg, entries)) {
     out = LdsTableHost{};
     return false;
   }

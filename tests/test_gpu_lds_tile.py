@@ -239,3 +239,53 @@ def test_where_the_rows_end_in_a_tile(n, kind, big, dtype):
         before = [state[0], state[0], state[0], state[1], state[0], state[1], state[0], state[1], state[3]]
         for got, want, old in zip(run(d), whole, before):
             assert torch.equal(got[:, :d], want[:, :d]) and torch.equal(got[:, d:], old[:, d:]), more
+
+
+def _weights(kind, n):
+    if kind == "asym":
+        return D.Topology.from_dense(sum(w * np.roll(np.eye(n), s, axis=1) for w, s in ((0.5, 0), (0.25, 1), (0.15, 7), (0.1, 200))))
+    if kind == "star":
+        return D.Topology.from_edges(np.array([(0, j) for j in range(1, n)]), D.DETAG_W_METROPOLIS)
+    if kind == "complete":
+        return D.Topology.from_edges(np.array([(i, j) for i in range(n) for j in range(i + 1, n)]), D.DETAG_W_METROPOLIS)
+    return D.Topology.from_edges(_graph(kind, n), D.DETAG_W_METROPOLIS)
+
+
+@pytest.mark.parametrize("n,kind,d,op,K,on_chip", [
+    (257, "rr", 333, "gossip", 1, True), (257, "rr", 333, "step", 2, True), (257, "rr", 333, "dpsgd", 1, True),
+    (64, "complete", 333, "step", 3, True), (100, "complete", 5000, "gossip", 1, True),
+    (512, "asym", 333, "gossip", 1, True), (512, "asym", 333, "dpsgd", 1, True), (513, "asym", 333, "dpsgd", 1, False),
+    (513, "asym", 333, "gossip", 2, False), (513, "asym", 333, "step", 2, False), (513, "asym", 333, "step", 3, True),
+    (1000, "asym", 524, "gossip", 2, False), (1000, "asym", 525, "gossip", 2, True),
+    (1024, "asym", 333, "step", 3, True), (1025, "asym", 333, "step", 3, False), (1025, "asym", 5000, "gossip", 3, False),
+    (256, "star", 131_000, "step", 3, True), (257, "star", 131_000, "step", 3, False), (257, "star", 130_000, "step", 3, True)])
+def test_route_of_contexts_that_report_one_launch_per_round(n, kind, d, op, K, on_chip):
+    """On the automatic path such a context still runs on chip where that is the faster way.  Seen from outside: under
+    capture, on a context whose scratch has never been allocated, only the on-chip route is recorded."""
+    ctx = D.detag_create(_weights(kind, n), n, d, d)
+    assert ctx.kernel() == D.DETAG_KERNEL_PER_ROUND
+    X, Y, Gn, Go = (_matrix(n, d, d, k) for k in range(4))
+    call = {"gossip": lambda x, y: ctx.gossip_accel(x, K, 0.3), "step": lambda x, y: ctx.step(x, y, Gn, Go, 0.1, K, 0.3),
+            "dpsgd": lambda x, y: ctx.dpsgd_step(x, Gn, 0.1)}[op]
+    Xr, Yr, refused = X.clone(), Y.clone(), None
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            Go.add_(0.0)                                # so that the recording holds some node
+            try:
+                call(Xr, Yr)
+            except D.DetagError as e:
+                refused = e
+    assert (refused is None) == on_chip
+    if on_chip:
+        graph.replay()
+    else:
+        assert refused.status == D.DETAG_EINVAL and "detag_reserve_gossip" in refused.message
+        torch.cuda.synchronize()
+        assert torch.equal(Xr, X) and torch.equal(Yr, Y)
+        call(Xr, Yr)
+    call(X, Y)
+    torch.cuda.synchronize()
+    assert torch.equal(Xr, X) and torch.equal(Yr, Y)
+    ctx.close()
