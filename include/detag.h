@@ -29,10 +29,13 @@
  *   - Calls on one context come from one host thread at a time.  Work of two
  *     calls may run concurrently on two streams only if they use disjoint
  *     context-owned scratch: detag_gossip_round, detag_accumulate,
- *     detag_phase_end, detag_track, detag_grad_quadratic_diag and the on-chip
- *     paths of detag_gossip_accel / detag_step / detag_dpsgd_step use none;
- *     the per-round paths share one scratch area, the least-squares and
- *     softmax gradients another, the two diagnostics a third.
+ *     detag_phase_end, detag_track and detag_grad_quadratic_diag use none, nor
+ *     do detag_gossip_accel / detag_step / detag_dpsgd_step on a context that
+ *     detag_get_kernel reports as DETAG_KERNEL_REGISTER_TILE or
+ *     DETAG_KERNEL_LDS_TILE, or the first two on a DETAG_KERNEL_DENSE one.
+ *     Otherwise these three (and detag_average_consensus factor by factor)
+ *     share one scratch area, the least-squares and softmax gradients another,
+ *     the two diagnostics a third.
  *     State matrices passed to one call must not overlap unless the comment
  *     allows it.
  */
@@ -172,7 +175,7 @@ detag_status detag_set_path(detag_ctx *ctx, int32_t path /* detag_path */);
  *     weights and any kappa).  All n rows of a column in registers, K rounds
  *     on chip: 24 B per element and phase whatever K is, 0.66 of HBM peak at
  *     n = 64, d = 11.2 M.  Only this family serves detag_step_quadratic with
- *     DETAG_VARIANT_ALG2 and the one-pass detag_dpsgd_step.
+ *     DETAG_VARIANT_ALG2.
  *   DETAG_KERNEL_LDS_TILE  any other W with n <= 256 and at most 8 neighbours
  *     per worker, including rings and tori off the list above.  Same HBM
  *     bytes, and the rounds run at the rate of LDS and vector ALUs, partly
@@ -180,14 +183,21 @@ detag_status detag_set_path(detag_ctx *ctx, int32_t path /* detag_path */);
  *     takes 1.0 ms at K = 4 and 2.1 ms at K = 16, where HBM alone would take
  *     0.6 ms.  W with one off-diagonal weight (regular graphs) is the fast
  *     form; with weights of its own a round costs about 1.7 times as much.
+ *     detag_dpsgd_step is one pass in place, as on the register family.
  *   DETAG_KERNEL_PER_ROUND  everything else (n > 256, a worker with more than 8
  *     neighbours), or DETAG_PATH_PER_ROUND.  With DETAG_PATH_PER_ROUND one launch
  *     per round, 12 B per element and round (24 + 8*(3K-1) B per element and
  *     phase: 208 B at K = 8, nine times the on-chip families).  With
- *     DETAG_PATH_AUTO detag_gossip_accel and detag_step still run their K
- *     rounds in one launch where a tile of all workers and their neighbour
- *     lists fit the LDS of a compute unit (n <= 1024 and, say, 100 neighbours
- *     each at n = 100); detag_step_quadratic does not exist there.
+ *     DETAG_PATH_AUTO many of these calls run on chip in one launch all the
+ *     same: where a tile of all workers and their neighbour lists fit the LDS
+ *     of a compute unit (n <= 1024 and, say, 100 neighbours each at n = 100),
+ *     except K <= 2 with n > 512 and n*d <= 2^19, a hub with a long list on
+ *     n*d > 2^25, and detag_dpsgd_step with n > 512.  So the choice
+ *     depends on K and on the call, and a caller must not count on it: a
+ *     context that reports DETAG_KERNEL_PER_ROUND is to be treated as one whose
+ *     calls use the per-round scratch (detag_reserve_gossip before a capture,
+ *     no two of them at a time on two streams).  detag_step_quadratic does not
+ *     exist there.
  *   DETAG_KERNEL_DENSE  only after detag_set_path(DETAG_PATH_DENSE).
  */
 typedef enum {
