@@ -598,8 +598,8 @@ detag_status detag_dpsgd_step(detag_ctx *ctx, void *X_dev, const float *G_dev, d
                                            stream);
     return rc ? hip_fail(ctx, "dpsgd", rc) : DETAG_OK;
   }
-  // The same for any W whose tile fits a compute unit: 48 irregular workers, d = 1,250,000 168 -> 144 us, bf16 state 233 ->
-  // 106 us, d = 41,666 20 -> 8 us (the launch below and its copy of X).  More than 512 workers leave tiles of 16 columns,
+  // The same for any W whose tile fits a compute unit: 48 irregular workers, d = 1,250,000 171 -> 144 us, bf16 state 233 ->
+  // 105 us, d = 41,666 20 -> 7 us (the launch below and its copy of X).  More than 512 workers leave tiles of 16 columns,
   // which are slower for a single round (1000 on a ring, d = 60,000, bf16 162 against 268 us).
   if (ctx->path != DETAG_PATH_PER_ROUND && ctx->has_lds && ctx->shape.n <= 512) {
     const int rc = launch_fused_generic(ctx->shape, ctx->lds, 3, X_dev, nullptr, G_dev, nullptr, float(alpha), 1, 0.f, stream);

@@ -14,8 +14,11 @@ namespace fused {
 constexpr int kThreads = 256;
 
 // Threads of a block.  No two wavefronts of a block work together, so its size only decides how columns spread over the
-// chip: up to 32,768 columns make 128 blocks of 256 threads or fewer, which leaves half the compute units idle, and take
-// one wavefront per block (step of 64 workers on a ring, d = 30,000, K = 2 10.0 -> 8.6 us, of 32 workers 5.8 -> 5.4 us).
+// chip: up to 32,768 columns make 128 blocks of 256 threads or fewer and take one wavefront per block, which spreads them
+// over all compute units (phase and gradient-fused step of 4 to 64 workers, K = 2 and 8: 1 to 5 % faster at 8,192 to
+// 32,768 columns, the fused step of 64 workers up to 10 % at 40,000).  Beyond, both sizes are within 2 % up to 32 workers,
+// but the fused step of 64 workers holds 48 KiB of LDS per block whatever its threads, three blocks to a compute unit:
+// 30 us with 256 threads at d = 65,536, 50 with 64; its phase is 6 to 11 % slower with 64 from 49,152 columns on.
 inline int block_threads(int64_t d) { return d <= 32768 ? 64 : kThreads; }
 
 // Workgroups are handed to the eight XCDs (each with its own L2) round-robin by their index.  Mapping index b
@@ -28,9 +31,11 @@ __device__ __forceinline__ int64_t xcd_tile(uint32_t b, uint32_t tiles) {
 }
 
 // Whether a call whose matrices take `per_element` bytes per element streams past the caches.  The memory-side cache holds
-// 256 MB and a program has other matrices too: up to 80 MB a call's matrices are left to the caches, where the next call
-// finds them (gradient-fused step, ring of 16: d = 272,474 (70 MB) 22 -> 19 us, three states in turn as well; d =
-// 500,000 (128 MB) 43 -> 35 us with one state but 44 -> 46 us with three in turn).
+// 256 MB and a program has other matrices too: up to 80 MiB a call's matrices are left to the caches, where the next call
+// finds them (gradient-fused step, ring of 16: d = 272,474 (70 MB) 22 -> 19 us, three states in turn as well; a state that
+// no call has touched lately gains half of that).  Measured at 85, 95, 105, 115 and 128 MiB over all calls of ring 16 and
+// torus 8x8: with one state the caches stay 5 to 15 % ahead; with three in turn -11 to +6 % up to 105 MiB, from 115 on 5 to
+// 20 % behind.  So the line lies below where it can lose, not where one state alone would put it.
 inline bool streams(const Shape &s, int per_element) { return int64_t(s.n) * s.ld * per_element > (int64_t(80) << 20); }
 
 template <int N>

@@ -133,8 +133,8 @@ __device__ __forceinline__ void pin4(f4 &v) {
   }
 }
 
-// The tile starts at LDS offset 0: the kernels have no other LDS (tests/test_kernel_metadata.py).  Addressed as numbers, an access costs no addition of
-// a base that is zero.
+// The tile starts at LDS offset 0: the kernels have no other LDS (tests/test_kernel_metadata.py).  Addressed as numbers,
+// an access costs no addition of a base that is zero.
 typedef __attribute__((address_space(3))) f4 lds_f4;
 __device__ __forceinline__ f4 lds_read(uint32_t off) { return *reinterpret_cast<const lds_f4 *>(off); }
 __device__ __forceinline__ void lds_write(uint32_t off, f4 v) { *reinterpret_cast<lds_f4 *>(off) = v; }
@@ -483,8 +483,9 @@ inline Geometry small_geometry(int n, int cols_min) {
 // blocks on a compute unit drift apart and keep memory and LDS busy at once, where two blocks of 1024 threads tend to
 // load and to compute in turn (64 Mi elements, fp32, 4-regular, K = 8, tile of 64 / 128 / 256 columns: n = 64 331 /
 // 333 / 380 us, n = 128 385 / 458 us, n = 24 374 / 329 / 354 us).  Tiles of 32 columns for n > 128 (an instruction more
-// per address, row pieces of 64 to 128 bytes) measured slower (n = 256, bf16 state, K = 8: 457 against 417 us).  Up to 8
-// workers take 128 columns, which makes a block one wavefront (n = 7, bf16: 277 us against 333 us with two).
+// per address, row pieces of 64 to 128 bytes) measured slower (n = 256, bf16 state, K = 8: 457 against 417 us).  5 to 8
+// workers take 128 columns, which makes a block one wavefront (against 256: 1 % faster in the median of n = 5 ... 8, both
+// state types, 3 to 100 Mi elements, K = 1 and 8; 5 to 10 % at K = 8 and 100 Mi, up to 6 % slower at K = 1 and 3 Mi).
 inline Geometry byte_geometry(int n, int64_t d) {
   Geometry g;
   if (small_matrix(n, d)) {

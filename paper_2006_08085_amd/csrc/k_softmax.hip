@@ -7,8 +7,9 @@
 //
 // The features are bf16 data, weights and residuals fp32.  The batch of 32 workers x 128 samples x 3072 features is 25 MB,
 // read by both launches (the second time mostly from the memory-side cache): what bounds them is how many of those bytes
-// are in flight and how long the chain index - row - sum - softmax is, not arithmetic.  So both launches give every
-// compute unit at least one block, and a wavefront requests all the feature bytes it needs before it uses the first.
+// are in flight and how long the chain index - row - sum - softmax is, not arithmetic.  So both launches cut the features
+// into up to 16 blocks per worker, one per compute unit from 16 workers with wide features on, and a wavefront requests
+// all the feature bytes it needs before it uses the first.
 //
 //   softmax_logits_kernel  block = one worker x one chunk of up to 384 features x the whole batch, one wavefront per 16
 //     samples.  The products run on the matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulate); the chunk's
@@ -22,7 +23,7 @@
 //     multiplies on the matrix cores.  (The products in fp32 on the vector ALUs, samples shared among the wavefronts
 //     and summed in LDS at the end, took 16 to 17 us: 4.9 us of multiplications and a 3 us tail.)
 // The times at the two kernels are for 32 workers, 128 samples, 3072 features and 10 classes; with the phase after them
-// the call takes 30.3 us, 47.3 before.
+// the call takes 29.7 us, 47.3 before.
 //
 // MFMA 16x16x32 operand layout (lane l, m = l % 16, q = l / 16):
 //   A: row m, k = 8q..8q+7      B: column m, k = 8q..8q+7
@@ -115,9 +116,8 @@ __global__ __launch_bounds__(64 * kSamplesMax / 16) void softmax_logits_kernel(
     if (4 * q + r < C) out[int64_t(4 * q + r) * B] = acc[r];
 }
 
-// grid (chunks, n).  32 workers x 8 chunks: 12.2 us (15.6 us with column groups that do not match the first launch's,
-// whose features come from beyond the L2; 17 us with 256 features per block multiplied on the vector ALUs) (formerly 13.1 us with 128 features per block, the residuals split by
-// the launch before).
+// grid (chunks, n).  32 workers x 8 chunks: 12.2 us; with column groups that do not match the first launch's, whose
+// features then come from beyond the L2, 15.6 us.
 __global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
     int64_t ld, const float *__restrict__ X, const uint16_t *__restrict__ feat, const int32_t *__restrict__ labels,
     const int32_t *__restrict__ batch, int S, int F, int C, int B, int chunk, const float *__restrict__ part, int parts,
