@@ -1,0 +1,54 @@
+"""The register-resident kernels on both sides of their block size (one wavefront up to 32,768 columns, four beyond) and of
+the size from which they stream past the caches (80 MiB a call): columns are independent, so the same columns come out with
+the same bits."""
+import pytest
+import torch
+
+import paper_2006_08085_amd as D
+from tests.gpu_util import DEV, SENTINEL, _built  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(n, d, ld, seed, dtype=torch.float32):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    t = torch.full((n, ld), SENTINEL, device=DEV)
+    t[:, :d] = torch.empty(d, n, device=DEV).normal_(generator=g).T  # the same values in the columns of every width
+    return t.to(dtype)
+
+
+def _all_calls(topo, n, d, dtype):
+    ld, K, eta = D.padded_ld(d), 3, 0.35
+    sd = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32)
+    assert ctx.kernel() == D.DETAG_KERNEL_REGISTER_TILE
+    X, Y, Gn, Go, b = (_matrix(n, d, ld, k, sd if k < 2 else torch.float32) for k in range(5))
+    h = _matrix(1, d, ld, 6)[0].abs()
+    out = []
+    for variant in (D.DETAG_VARIANT_ATC, D.DETAG_VARIANT_ALG2):
+        x, y, g = X.clone(), Y.clone(), Go.clone()
+        ctx.step(x, y, Gn, Go, 0.2, K, eta, variant)
+        out += [x.clone(), y.clone()]
+        x, y = X.clone(), Y.clone()
+        ctx.step_quadratic(x, y, g, h, b, 0.2, K, sigma=0.1, seed=3, step=1, eta=eta, variant=variant)
+        out += [x, y, g]
+    z, p, r = X.clone(), X.clone(), X.clone()
+    ctx.gossip_accel(z, K, eta)
+    ctx.dpsgd_step(p, Gn, 0.2)
+    ctx.gossip_round(X, Y, r, eta)
+    ctx.close()
+    for t in out + [z, p, r]:
+        assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))
+    return [t[:, :d] for t in out + [z, p, r]]
+
+
+@pytest.mark.parametrize("topo,n", [(D.Topology.ring(), 16), (D.Topology.torus(8, 8), 64)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_same_bits_on_both_sides_of_the_block_size_and_of_the_caches(topo, n, dtype):
+    widths = (32_767, 32_768, 32_769, 5_242_880 // n, 5_242_880 // n + 70)
+    runs = [_all_calls(topo, n, d, dtype) for d in widths]
+    wide = runs[-1]
+    for d, run in zip(widths, runs):
+        for k, (got, want) in enumerate(zip(run, wide)):
+            assert torch.equal(got[:, : min(d, widths[-1])], want[:, : min(d, widths[-1])]), (d, k)
