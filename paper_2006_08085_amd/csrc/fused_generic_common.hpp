@@ -80,7 +80,12 @@ enum Tile : int { kNarrow, kCut, kWhole };
 // was so much code that fetching it took longer than the rest of a small call (1000 workers on a ring, d = 300, K = 4
 // 51 us, 23 us so; 256 workers, 4-regular, d = 3,915, K = 1 14.9 and 8.0 us).  A narrow tile is read one by one: its row's
 // last four columns lie in lines of the tile before (d = 3,906 8.4 us, 10.9 us the other way).
-// CUT = false: cut tiles are treated like narrow ones.  IN_SGPR: one scalar register decides for all of a block's loads
+struct Columns {
+  int64_t at;  // the first of them
+  int skip;    // how many of them belong to the lane before; 4 or more: none is the lane's
+};
+
+// How a block's columns lie.  CUT = false: cut tiles are treated like narrow ones.  IN_SGPR: one scalar register decides for all of a block's loads
 // and stores, which saves the kernels that live within 64 vector registers a spill in their rounds; without it the
 // compiler lays the whole tiles' code out as the straight path, which is 2 to 10 % of a phase where one block of 1024
 // threads has a compute unit to itself (1000 workers, d = 60,000, K = 1 387 and 404 us).
@@ -92,11 +97,6 @@ __device__ __forceinline__ int tile_kind(int64_t first, int lpr_log2, int64_t d)
   if constexpr (IN_SGPR) return __builtin_amdgcn_readfirstlane(whole ? kWhole : left >= 4 ? kCut : kNarrow);
   return whole ? kWhole : left >= 4 ? kCut : kNarrow;
 }
-
-struct Columns {
-  int64_t at;  // the first of them
-  int skip;    // how many of them belong to the lane before; 4 or more: none is the lane's
-};
 
 template <int TILE, class ST>
 __device__ __forceinline__ f4 load4(const ST *base, int64_t row_off, const Columns &c, int64_t d) {
