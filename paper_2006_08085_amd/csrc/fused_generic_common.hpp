@@ -85,10 +85,10 @@ struct Columns {
   int skip;    // how many of them belong to the lane before; 4 or more: none is the lane's
 };
 
-// How a block's columns lie.  CUT = false: cut tiles are treated like narrow ones.  IN_SGPR: one scalar register decides for all of a block's loads
-// and stores, which saves the kernels that live within 64 vector registers a spill in their rounds; without it the
-// compiler lays the whole tiles' code out as the straight path, which is 2 to 10 % of a phase where one block of 1024
-// threads has a compute unit to itself (1000 workers, d = 60,000, K = 1 387 and 404 us).
+// How a block's columns lie.  CUT = false: cut tiles are treated like narrow ones.  IN_SGPR: one scalar register decides
+// for all of a block's loads and stores, which saves the kernels that live within 64 vector registers a spill in their
+// rounds; without it the compiler lays the whole tiles' code out as the straight path, which is 2 to 10 % of a phase where
+// one block of 1024 threads has a compute unit to itself (1000 workers, d = 60,000, K = 1 387 and 404 us).
 template <bool CUT, bool IN_SGPR>
 __device__ __forceinline__ int tile_kind(int64_t first, int lpr_log2, int64_t d) {
   const int64_t left = d - first;
