@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 namespace detag {
 
@@ -54,12 +55,16 @@ __device__ __forceinline__ rsrc_t row_of(const E *base, int64_t tile, int64_t ld
   return make_rsrc(base + tile + int64_t(i) * ld, valid * uint32_t(sizeof(E)));
 }
 
+// How a kernel's accesses treat the caches: kStream marks loads and stores as non-temporal, kKeepReads the stores only,
+// kKeep neither.
+enum Access : int { kStream, kKeepReads, kKeep };
+template <Access A>
+using AccessTag = std::integral_constant<Access, A>;
+
 // Cache-policy bits of the buffer instructions on gfx950 (the `aux` operand): bit 0 = sc0, bit 1 = nt, bit 4 = sc1.
-// NT: state tiles are touched exactly once per kernel, so a matrix that no cache holds until the next call is streamed
-// (non-temporal).
-template <typename ST, bool NT = true>
+template <typename ST, Access A = kStream>
 __device__ __forceinline__ float buf_load(rsrc_t r, uint32_t byte_off) {
-  constexpr int aux = NT ? 2 : 0;
+  constexpr int aux = A == kStream ? 2 : 0;
   if constexpr (sizeof(ST) == 4) {
     return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, int(byte_off), 0, aux));
   } else {
@@ -68,9 +73,9 @@ __device__ __forceinline__ float buf_load(rsrc_t r, uint32_t byte_off) {
   }
 }
 
-template <typename ST, bool NT = true>
+template <typename ST, Access A = kStream>
 __device__ __forceinline__ void buf_store(rsrc_t r, uint32_t byte_off, float v) {
-  constexpr int aux = NT ? 2 : 0;
+  constexpr int aux = A != kKeep ? 2 : 0;
   if constexpr (sizeof(ST) == 4)
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, v), r, int(byte_off), 0, aux);
   else

@@ -3,6 +3,7 @@
 // registers.
 #pragma once
 
+#include <initializer_list>
 #include <type_traits>
 
 #include "detag_internal.h"
@@ -30,13 +31,28 @@ __device__ __forceinline__ int64_t xcd_tile(uint32_t b, uint32_t tiles) {
   return b < per * 8u ? int64_t(b % 8u) * per + b / 8u : int64_t(b);
 }
 
-// Whether a call whose matrices take `per_element` bytes per element streams past the caches.  The memory-side cache holds
-// 256 MB and a program has other matrices too: up to 80 MiB a call's matrices are left to the caches, where the next call
-// finds them (gradient-fused step, ring of 16: d = 272,474 (70 MB) 22 -> 19 us, three states in turn as well; a state that
-// no call has touched lately gains half of that).  Measured at 85, 95, 105, 115 and 128 MiB over all calls of ring 16 and
-// torus 8x8: with one state the caches stay 5 to 15 % ahead; with three in turn -11 to +6 % up to 105 MiB, from 115 on 5 to
-// 20 % behind.  So the line lies below where it can lose, not where one state alone would put it.
-inline bool streams(const Shape &s, int per_element) { return int64_t(s.n) * s.ld * per_element > (int64_t(80) << 20); }
+// Whether column tiles share 128-byte cache lines: rows that do not start on one (an odd pitch, a shifted base).
+inline bool shares_lines(const Shape &s, std::initializer_list<const void *> matrices) {
+  uint64_t starts = uint64_t(s.ld) * (s.bf16 ? 2 : 4);
+  for (const void *p : matrices) starts |= reinterpret_cast<uint64_t>(p);
+  return starts % 128 != 0;
+}
+// What the matrices of a call that walks column tiles take together.
+inline int64_t footprint(const Shape &s, int per_element) { return int64_t(s.n) * s.ld * per_element; }
+
+// How the register-resident kernels and those with one launch per round treat the caches.
+// Small calls leave their matrices to the caches.  The memory-side cache holds 256 MB and a program has other matrices too:
+// up to 80 MiB a call's matrices stay, where the next call finds them (gradient-fused step, ring of 16: d = 272,474 (70 MB)
+// 22 -> 19 us, three states in turn as well; a state that no call has touched lately gains half of that).  Measured at 85,
+// 95, 105, 115 and 128 MiB over all calls of ring 16 and torus 8x8: with one state the caches stay 5 to 15 % ahead; with
+// three in turn -11 to +6 % up to 105 MiB, from 115 on 5 to 20 % behind.  So the line lies below where it can lose.
+// Beyond, a call streams, but only if its tiles have their cache lines to themselves: a shared line that streams is gone
+// before the other tile wants it, or goes to memory half written.  Streamed and kept, fp32, pitch 1,000,003, K = 4: phase,
+// torus 8x8 388 and 296 us, one round 165 and 145, gradient-fused step 465 and 364; ring of 16, pitch 600,001 52 and 50, 65
+// and 60.  On lines streaming is 2 to 10 % ahead.
+inline Access tile_access(const Shape &s, int per_element, std::initializer_list<const void *> matrices) {
+  return footprint(s, per_element) > (int64_t(80) << 20) && !shares_lines(s, matrices) ? kStream : kKeep;
+}
 
 template <int N>
 struct Ring {

@@ -55,20 +55,34 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short u4_any __attribute__((ext_vector_type(4), aligned(2)));
 
-__device__ __forceinline__ f4 load4(const float *p) { return __builtin_nontemporal_load(reinterpret_cast<const f4_any *>(p)); }
+template <Access A>
+__device__ __forceinline__ f4 load4(const float *p) {
+  const f4_any *q = reinterpret_cast<const f4_any *>(p);
+  return A == kStream ? __builtin_nontemporal_load(q) : *q;
+}
+template <Access A>
 __device__ __forceinline__ f4 load4(const bf16_t *p) {
-  const u4_any t = __builtin_nontemporal_load(reinterpret_cast<const u4_any *>(p));
+  const u4_any *q = reinterpret_cast<const u4_any *>(p);
+  const u4_any t = A == kStream ? __builtin_nontemporal_load(q) : *q;
   f4 v;
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
   return v;
 }
-__device__ __forceinline__ void store4(float *p, f4 v) { __builtin_nontemporal_store(f4_any(v), reinterpret_cast<f4_any *>(p)); }
+template <Access A>
+__device__ __forceinline__ void store4(float *p, f4 v) {
+  f4_any *q = reinterpret_cast<f4_any *>(p);
+  if constexpr (A != kKeep) __builtin_nontemporal_store(f4_any(v), q);
+  else *q = v;
+}
+template <Access A>
 __device__ __forceinline__ void store4(bf16_t *p, f4 v) {
   u4_any t;
 #pragma unroll
   for (int e = 0; e < 4; ++e) t[e] = bf16_bits_rne(v[e]);
-  __builtin_nontemporal_store(t, reinterpret_cast<u4_any *>(p));
+  u4_any *q = reinterpret_cast<u4_any *>(p);
+  if constexpr (A != kKeep) __builtin_nontemporal_store(t, q);
+  else *q = t;
 }
 
 // The columns of a block: all exist; the rows end after four of them or more; after fewer than four.
@@ -98,18 +112,18 @@ __device__ __forceinline__ int tile_kind(int64_t first, int lpr_log2, int64_t d)
   return whole ? kWhole : left >= 4 ? kCut : kNarrow;
 }
 
-template <int TILE, class ST>
+template <int TILE, Access A, class ST>
 __device__ __forceinline__ f4 load4(const ST *base, int64_t row_off, const Columns &c, int64_t d) {
-  if constexpr (TILE != kNarrow) return load4(base + (row_off + c.at));
+  if constexpr (TILE != kNarrow) return load4<A>(base + (row_off + c.at));
   f4 v;  // columns past the last repeat it
 #pragma unroll
   for (int e = 0; e < 4; ++e) v[e] = to_f32(base[row_off + (c.at + e < d ? c.at + e : d - 1)]);
   return v;
 }
-template <int TILE, class ST>
+template <int TILE, Access A, class ST>
 __device__ __forceinline__ void store4(ST *base, int64_t row_off, const Columns &c, int64_t d, f4 v) {
   if (TILE == kWhole || (TILE == kCut && c.skip == 0)) {
-    store4(base + (row_off + c.at), v);
+    store4<A>(base + (row_off + c.at), v);
   } else {
 #pragma unroll
     for (int e = TILE == kCut; e < 4; ++e)
@@ -519,6 +533,32 @@ inline Geometry csr_geometry(int n, int64_t d) {
 inline int allow_lds(const void *kernel, size_t bytes) {
   if (bytes <= 65536) return 0;
   return hip_rc(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsMax)));
+}
+
+// How these kernels treat the caches: calls f(access).  Matrices with S < 4 fit the caches.
+// Where tiles have their cache lines to themselves a call streams; up to 128 MiB the calls that read a matrix late (the
+// gradients of Algorithm 2's phase and of D-PSGD, the old gradient of the fused step) leave the loads to the caches.
+// Streamed, loads kept, all kept, K = 4, three states in turn: Algorithm 2's phase 64 x 100,001 34.3, 32.2, 31.7 us, 20 x
+// 200,001 22.8, 20.2, 19.1; fused step 20 x 200,001 27.9, 25.7, 26.3, 64 x 200,001 78.9, 82.1, 85.2; but the ATC phase
+// 64 x 50,001 21.4, 22.0, 22.9, 256 x 30,001 40.2, 40.3, 46.9.
+// Where they share lines (rows that do not start on one, or tiles of 32 columns of bf16 state) nothing that streams does
+// well: phase, 64 x 1,000,001 481, 382, 337 us, fused step 637, 453, 401, bf16 540, 354, 301.  Up to 192 MiB of tiles whose
+// rows are 256 bytes or more the stores stream all the same: fused step 64 x 100,001 58, 41, 44 us, 20 x 600,001 78, 80,
+// 84.  Plain gossip of up to 32 MiB always streams: 64 x 50,001 9.7, 10.6, 10.4 us.
+enum Call : int { kPlain, kAtc, kReadsLate };
+template <class R, class F>
+int with_access(const Shape &s, const Geometry &g, Call call, int per_element, std::initializer_list<const void *> matrices,
+                F &&f) {
+  if constexpr (R::kSlots < kSlotsMax) {
+    return f(AccessTag<kKeepReads>{});
+  } else {
+    const int row_bytes = g.cols * (s.bf16 ? 2 : 4);
+    const int64_t mib = fused::footprint(s, per_element) >> 20;
+    if (call == kPlain && mib < 32) return f(AccessTag<kStream>{});
+    if (fused::shares_lines(s, matrices) || row_bytes % 128 != 0)
+      return mib < 192 && row_bytes >= 256 ? f(AccessTag<kKeepReads>{}) : f(AccessTag<kKeep>{});
+    return call == kReadsLate && mib < 128 ? f(AccessTag<kKeepReads>{}) : f(AccessTag<kStream>{});
+  }
 }
 
 template <class R>

@@ -7,26 +7,31 @@
 // partials): results are bit-reproducible.
 #include "dev_common.hpp"
 #include "detag_internal.h"
+#include "fused_common.hpp"
 
 namespace detag {
 namespace {
 
 constexpr int kThreads = 256;
 
-// X is read once per kernel: non-temporal.
-__device__ __forceinline__ float stream_f32(const float *p) { return __builtin_nontemporal_load(p); }
-__device__ __forceinline__ float stream_f32(const bf16_t *p) {
-  return __uint_as_float(uint32_t(__builtin_nontemporal_load(&p->bits)) << 16);
+// X is read once per kernel: non-temporal where the call streams (fused::tile_access; worker mean and consensus distance of
+// 64 x 1,000,003, pitch d, fp32 50 and 57 us streamed, 47 and 54 not, bf16 29 and 41, 25 and 35; on lines 43 and 51, 46 and
+// 53; 16 x 272,474, which the caches keep, distance 13 and 10).
+template <bool NT>
+__device__ __forceinline__ float load_f32(const float *p) { return NT ? __builtin_nontemporal_load(p) : *p; }
+template <bool NT>
+__device__ __forceinline__ float load_f32(const bf16_t *p) {
+  return __uint_as_float(uint32_t(NT ? __builtin_nontemporal_load(&p->bits) : p->bits) << 16);
 }
 
-template <typename ST>
+template <typename ST, bool NT>
 __global__ __launch_bounds__(kThreads) void mean_kernel(int n, int64_t d, int64_t ld, const ST *__restrict__ X,
                                                         float *__restrict__ xbar) {
   const int64_t c = int64_t(blockIdx.x) * kThreads + threadIdx.x;
   if (c >= d) return;
   double s = 0.0;
 #pragma unroll 16
-  for (int i = 0; i < n; ++i) s += double(stream_f32(X + int64_t(i) * ld + c));  // 16 rows' loads in flight
+  for (int i = 0; i < n; ++i) s += double(load_f32<NT>(X + int64_t(i) * ld + c));  // 16 rows' loads in flight
   xbar[c] = float(s / n);
 }
 
@@ -42,7 +47,7 @@ __device__ __forceinline__ double block_sum(double v) {
   return t;  // valid in thread 0
 }
 
-template <typename ST>
+template <typename ST, bool NT>
 __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(int n, int64_t d, int64_t ld,
                                                                      const ST *__restrict__ X,
                                                                      double *__restrict__ partials) {
@@ -53,11 +58,11 @@ __global__ __launch_bounds__(kThreads) void consensus_partial_kernel(int n, int6
     //   sum_i (x_i - mean)^2 = sum_i e_i^2 - (sum_i e_i)^2 / n.
     // Both terms are of the size of the result (the shift by x_0 removes the common part of the column), so the
     // subtraction does not cancel, however close the workers are to agreement.
-    const double x0 = double(stream_f32(X + c));
+    const double x0 = double(load_f32<NT>(X + c));
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll 16
     for (int i = 1; i < n; ++i) {
-      const double e = double(stream_f32(X + int64_t(i) * ld + c)) - x0;
+      const double e = double(load_f32<NT>(X + int64_t(i) * ld + c)) - x0;
       s1 += e;
       s2 = fma(e, e, s2);
     }
@@ -110,10 +115,10 @@ double *static_partials(int device) {
 int launch_mean(const Shape &s, const void *X, float *xbar, void *stream) {
   const dim3 grid(ceil_div_i64(s.d, kThreads));
   auto st = static_cast<hipStream_t>(stream);
-  if (s.bf16)
-    mean_kernel<bf16_t><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, static_cast<const bf16_t *>(X), xbar);
-  else
-    mean_kernel<float><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, static_cast<const float *>(X), xbar);
+  auto go = [&](auto *kernel, auto *x) { kernel<<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, x, xbar); };
+  const bool nt = fused::tile_access(s, s.bf16 ? 2 : 4, {X}) == kStream;
+  if (s.bf16) go(nt ? &mean_kernel<bf16_t, true> : &mean_kernel<bf16_t, false>, static_cast<const bf16_t *>(X));
+  else go(nt ? &mean_kernel<float, true> : &mean_kernel<float, false>, static_cast<const float *>(X));
   return hip_rc(hipGetLastError());
 }
 
@@ -122,12 +127,10 @@ int64_t consensus_partials_count(const Shape &s) { return (s.d + kThreads - 1) /
 int launch_consensus_error(const Shape &s, const void *X, double *partials, double *out, void *stream) {
   const int64_t blocks = consensus_partials_count(s);
   auto st = static_cast<hipStream_t>(stream);
-  if (s.bf16)
-    consensus_partial_kernel<bf16_t><<<dim3(blocks), kThreads, 0, st>>>(s.n, s.d, s.ld,
-                                                                         static_cast<const bf16_t *>(X), partials);
-  else
-    consensus_partial_kernel<float><<<dim3(blocks), kThreads, 0, st>>>(s.n, s.d, s.ld,
-                                                                        static_cast<const float *>(X), partials);
+  auto go = [&](auto *kernel, auto *x) { kernel<<<dim3(blocks), kThreads, 0, st>>>(s.n, s.d, s.ld, x, partials); };
+  const bool nt = fused::tile_access(s, s.bf16 ? 2 : 4, {X}) == kStream;
+  if (s.bf16) go(nt ? &consensus_partial_kernel<bf16_t, true> : &consensus_partial_kernel<bf16_t, false>, static_cast<const bf16_t *>(X));
+  else go(nt ? &consensus_partial_kernel<float, true> : &consensus_partial_kernel<float, false>, static_cast<const float *>(X));
   int rc = hip_rc(hipGetLastError());
   if (rc) return rc;
   sum_partials_kernel<<<1, kThreads, 0, st>>>(blocks, partials, out);

@@ -26,7 +26,7 @@ using namespace fused;
 // MODE 0: Z <- M(Z) on X.  MODE 1 (ATC): X <- M(X - alpha*Y), Y <- M(Y + Gn - Go).
 // MODE 2 (ALG2): X <- M(X) - alpha*M(Y), Y <- M(Y) + Gn - Go.
 // MODE 3 (D-PSGD baseline of the Experiments section): X <- W^T X - alpha*Gn, one plain round (c built with eta = 0).
-template <class T, typename ST, int MODE, bool NT>
+template <class T, typename ST, int MODE, Access A>
 __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_structured_kernel(
     ST *X, ST *Y, const float *__restrict__ Gn, const float *__restrict__ Go, int64_t d, int64_t ld, Coef c,
     float alpha, int K) {
@@ -39,26 +39,26 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
   float u[N], p[N];
   if constexpr (MODE == 0) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) u[i] = buf_load<ST, NT>(row_of(X, tile, ld, i, valid), so);
+    for (int i = 0; i < N; ++i) u[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
     __builtin_amdgcn_sched_barrier(0);
     ag_rounds<T>(u, p, c, K);
     __builtin_amdgcn_sched_barrier(0);
     X = launder_uniform(X);
 #pragma unroll
-    for (int i = 0; i < N; ++i) buf_store<ST, NT>(row_of(X, tile, ld, i, valid), so, u[i]);
+    for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, u[i]);
   } else if constexpr (MODE == 3) {
 #pragma unroll
-    for (int i = 0; i < N; ++i) u[i] = buf_load<ST, NT>(row_of(X, tile, ld, i, valid), so);
+    for (int i = 0; i < N; ++i) u[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
     __builtin_amdgcn_sched_barrier(0);
     X = launder_uniform(X);
     float lg[N];  // gradient rows arrive a few rows ahead of the stores that consume them
 #pragma unroll
-    for (int i = 0; i < D; ++i) lg[i] = buf_load<float, NT>(row_of(Gn, tile, ld, i, valid), go4);
+    for (int i = 0; i < D; ++i) lg[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), go4);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      if (i + D < N) lg[i + D] = buf_load<float, NT>(row_of(Gn, tile, ld, i + D, valid), go4);
-      buf_store<ST, NT>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, lg[i], fmaf(c.b, lap<T>(u, i), u[i])));
+      if (i + D < N) lg[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), go4);
+      buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, lg[i], fmaf(c.b, lap<T>(u, i), u[i])));
       __builtin_amdgcn_sched_barrier(0);
     }
   } else {
@@ -68,19 +68,19 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
       float lx[N], ly[N], lgn[N], lgo[N];
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        lx[i] = buf_load<ST, NT>(row_of(X, tile, ld, i, valid), so);
-        ly[i] = buf_load<ST, NT>(row_of(Y, tile, ld, i, valid), so);
-        lgn[i] = buf_load<float, NT>(row_of(Gn, tile, ld, i, valid), go4);
-        lgo[i] = buf_load<float, NT>(row_of(Go, tile, ld, i, valid), go4);
+        lx[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
+        ly[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+        lgn[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), go4);
+        lgo[i] = buf_load<float, A>(row_of(Go, tile, ld, i, valid), go4);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         if (i + D < N) {
-          lx[i + D] = buf_load<ST, NT>(row_of(X, tile, ld, i + D, valid), so);
-          ly[i + D] = buf_load<ST, NT>(row_of(Y, tile, ld, i + D, valid), so);
-          lgn[i + D] = buf_load<float, NT>(row_of(Gn, tile, ld, i + D, valid), go4);
-          lgo[i + D] = buf_load<float, NT>(row_of(Go, tile, ld, i + D, valid), go4);
+          lx[i + D] = buf_load<ST, A>(row_of(X, tile, ld, i + D, valid), so);
+          ly[i + D] = buf_load<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+          lgn[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), go4);
+          lgo[i + D] = buf_load<float, A>(row_of(Go, tile, ld, i + D, valid), go4);
         }
         u[i] = fmaf(-alpha, ly[i], lx[i]);
         v[i] = ly[i] + lgn[i] - lgo[i];
@@ -91,18 +91,18 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
       __builtin_amdgcn_sched_barrier(0);
       X = launder_uniform(X);
 #pragma unroll
-      for (int i = 0; i < N; ++i) buf_store<ST, NT>(row_of(X, tile, ld, i, valid), so, u[i]);
+      for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, u[i]);
       __builtin_amdgcn_sched_barrier(0);
       ag_rounds<T>(v, p, c, K);
       __builtin_amdgcn_sched_barrier(0);
       Y = launder_uniform(Y);
 #pragma unroll
-      for (int i = 0; i < N; ++i) buf_store<ST, NT>(row_of(Y, tile, ld, i, valid), so, v[i]);
+      for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, v[i]);
     } else {
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        u[i] = buf_load<ST, NT>(row_of(X, tile, ld, i, valid), so);
-        v[i] = buf_load<ST, NT>(row_of(Y, tile, ld, i, valid), so);
+        u[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
+        v[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
       }
       __builtin_amdgcn_sched_barrier(0);
       ag_rounds<T>(v, p, c, K);
@@ -114,18 +114,18 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
       float lgn[N], lgo[N];
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        lgn[i] = buf_load<float, NT>(row_of(Gn, tile, ld, i, valid), go4);
-        lgo[i] = buf_load<float, NT>(row_of(Go, tile, ld, i, valid), go4);
+        lgn[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), go4);
+        lgo[i] = buf_load<float, A>(row_of(Go, tile, ld, i, valid), go4);
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         if (i + D < N) {
-          lgn[i + D] = buf_load<float, NT>(row_of(Gn, tile, ld, i + D, valid), go4);
-          lgo[i + D] = buf_load<float, NT>(row_of(Go, tile, ld, i + D, valid), go4);
+          lgn[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), go4);
+          lgo[i + D] = buf_load<float, A>(row_of(Go, tile, ld, i + D, valid), go4);
         }
-        buf_store<ST, NT>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, v[i], u[i]));
-        buf_store<ST, NT>(row_of(Y, tile, ld, i, valid), so, v[i] + lgn[i] - lgo[i]);
+        buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, v[i], u[i]));
+        buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, v[i] + lgn[i] - lgo[i]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
 // All n rows of z_r in registers, z_{r-1} streamed a few rows ahead of the stores: 12 B per element (fp32), every row
 // read once.  Every row of z_r is in registers before the first store and a row of z_{r-1} is read before the same
 // row of out is written, so out may be z_{r-1} (the caller's usual choice) or z_r itself.
-template <class T, typename ST, bool NT>
+template <class T, typename ST, Access A>
 __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 0)) void structured_round_kernel(
     const ST *cur, const ST *prev, ST *out, int64_t d, int64_t ld, Coef c) {
   constexpr int N = T::n;
@@ -147,21 +147,21 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 0)) void structured_
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST));
   float u[N], lp[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) u[i] = buf_load<ST, NT>(row_of(cur, tile, ld, i, valid), so);
+  for (int i = 0; i < N; ++i) u[i] = buf_load<ST, A>(row_of(cur, tile, ld, i, valid), so);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < D; ++i) lp[i] = buf_load<ST, NT>(row_of(prev, tile, ld, i, valid), so);
+  for (int i = 0; i < D; ++i) lp[i] = buf_load<ST, A>(row_of(prev, tile, ld, i, valid), so);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (i + D < N) lp[i + D] = buf_load<ST, NT>(row_of(prev, tile, ld, i + D, valid), so);
+    if (i + D < N) lp[i + D] = buf_load<ST, A>(row_of(prev, tile, ld, i + D, valid), so);
     const float v = fmaf(c.eta, u[i] - lp[i], c.b * lap<T>(u, i));
-    buf_store<ST, NT>(row_of(out, tile, ld, i, valid), so, u[i] + v);
+    buf_store<ST, A>(row_of(out, tile, ld, i, valid), so, u[i] + v);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-template <class T, typename ST, bool NT>
+template <class T, typename ST, Access A>
 int launch_t(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, const Coef &c,
              float alpha, int K, void *stream) {
   const int threads = block_threads(s.d);
@@ -171,10 +171,10 @@ int launch_t(const Shape &s, int mode, void *X, void *Y, const float *Gn, const 
     kernel<<<grid, threads, 0, st>>>(static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go, s.d, s.ld, c, alpha, K);
   };
   switch (mode) {
-    case 0: go(&fused_structured_kernel<T, ST, 0, NT>); break;
-    case 1: go(&fused_structured_kernel<T, ST, 1, NT>); break;
-    case 3: go(&fused_structured_kernel<T, ST, 3, NT>); break;
-    default: go(&fused_structured_kernel<T, ST, 2, NT>); break;
+    case 0: go(&fused_structured_kernel<T, ST, 0, A>); break;
+    case 1: go(&fused_structured_kernel<T, ST, 1, A>); break;
+    case 3: go(&fused_structured_kernel<T, ST, 3, A>); break;
+    default: go(&fused_structured_kernel<T, ST, 2, A>); break;
   }
   return hip_rc(hipGetLastError());
 }
@@ -183,11 +183,11 @@ template <class T>
 int launch_s(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, const Coef &c,
              float alpha, int K, void *stream) {
   const int state = s.bf16 ? 2 : 4, per_element = mode == 0 ? state : mode == 3 ? state + 4 : 2 * state + 8;
-  auto go = [&](auto nt) {
-    return s.bf16 ? launch_t<T, bf16_t, nt>(s, mode, X, Y, Gn, Go, c, alpha, K, stream)
-                  : launch_t<T, float, nt>(s, mode, X, Y, Gn, Go, c, alpha, K, stream);
+  auto go = [&](auto access) {
+    return s.bf16 ? launch_t<T, bf16_t, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream)
+                  : launch_t<T, float, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream);
   };
-  return streams(s, per_element) ? go(std::true_type{}) : go(std::false_type{});
+  return tile_access(s, per_element, {X, Y, Gn, Go}) == kStream ? go(AccessTag<kStream>{}) : go(AccessTag<kKeep>{});
 }
 
 }  // namespace
@@ -216,10 +216,13 @@ int launch_structured_round(const Shape &s, const HostW &W, const void *cur, con
       kernel<<<grid, threads, 0, st>>>(static_cast<const ST *>(cur), static_cast<const ST *>(prev), static_cast<ST *>(out), s.d,
                                        s.ld, c);
     };
-    const bool nt = streams(s, 3 * (s.bf16 ? 2 : 4));
-    if (s.bf16) go(nt ? &structured_round_kernel<T, bf16_t, true> : &structured_round_kernel<T, bf16_t, false>, bf16_t{});
-    else go(nt ? &structured_round_kernel<T, float, true> : &structured_round_kernel<T, float, false>, float{});
-    return hip_rc(hipGetLastError());
+    auto with = [&](auto access) {
+      if (s.bf16) go(&structured_round_kernel<T, bf16_t, access>, bf16_t{});
+      else go(&structured_round_kernel<T, float, access>, float{});
+      return hip_rc(hipGetLastError());
+    };
+    const Access access = tile_access(s, 3 * (s.bf16 ? 2 : 4), {cur, prev, out});
+    return access == kStream ? with(AccessTag<kStream>{}) : with(AccessTag<kKeep>{});
   });
 }
 

@@ -17,7 +17,7 @@ using namespace lds_tile;
 // mode 0: Z <- M(Z) on X.  mode 1 (ATC): X <- M(X - alpha*Y), Y <- M(Y + Gn - Go).
 // mode 2 (ALG2): X <- M(X) - alpha*M(Y), Y <- M(Y) + Gn - Go.
 // mode 3 (D-PSGD): X <- W^T X - alpha*Gn, one plain round (called with eta = 0).
-template <typename ST, int MODE, class R>
+template <typename ST, int MODE, class R, Access A>
 __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(ST *X, ST *Y, const float *__restrict__ Gn,
                                                                        const float *__restrict__ Go, int n, int64_t d,
                                                                        int64_t ld, int lpr_log2, typename R::Args ra,
@@ -31,14 +31,14 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
   auto rows = [&](auto f) { each_row<R, true>(rounds, ra, p, tile, n, d, ld, first, f); };
   if constexpr (kFetchFirst<R::kSlots>) rounds.fetch(ra, p);
   if constexpr (MODE == 0) {
-    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F>(X, off, c, d); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F, A>(X, off, c, d); });
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F>(X, off, c, d, z[s]); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F, A>(X, off, c, d, z[s]); });
   } else if constexpr (MODE == 1) {
     // every input is read once: the second gossip's input Y + Gn - Go waits in registers under the first
     rows([&](auto F, int s, int64_t off, Columns c, bool) {
-      const f4 x = load4<F>(X, off, c, d), y = load4<F>(Y, off, c, d), gn = load4<F>(Gn, off, c, d), go = load4<F>(Go, off, c, d);
+      const f4 x = load4<F, A>(X, off, c, d), y = load4<F, A>(Y, off, c, d), gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d);
       z[s] = fma4(-alpha, y, x);
       f4 t = y + gn - go;
       pin4(t);  // the sum now, not its three operands carried through the rounds
@@ -47,15 +47,15 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
-      if (mine) store4<F>(X, off, c, d, z[s]);
+      if (mine) store4<F, A>(X, off, c, d, z[s]);
       z[s] = v.get(p, s);
     });
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F, A>(Y, off, c, d, z[s]); });
   } else if constexpr (MODE == 3) {
     f4 g[R::kSlots];
     rows([&](auto F, int s, int64_t off, Columns c, bool) {
-      z[s] = load4<F>(X, off, c, d), g[s] = load4<F>(Gn, off, c, d);
+      z[s] = load4<F, A>(X, off, c, d), g[s] = load4<F, A>(Gn, off, c, d);
       lds_write(p.own(s), z[s]);
     });
     rounds.init(ra, p, eta);
@@ -65,23 +65,23 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
       // bit for bit its result (mixed first and -alpha*g added to that: 1.4 to 1.8 times the error against 64 bits); the
       // padded list of a worker without neighbours names itself and is left out
       const f4 mix = n > 1 ? rounds.plain(s, z[s]) : f4{0.f, 0.f, 0.f, 0.f};
-      if (mine) store4<F>(X, off, c, d, z[s] + fma4(-alpha, g[s], mix));
+      if (mine) store4<F, A>(X, off, c, d, z[s] + fma4(-alpha, g[s], mix));
     });
   } else {
     // M(Y) first: both outputs need it
-    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F>(Y, off, c, d); });
+    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F, A>(Y, off, c, d); });
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, Columns c, bool) {
       v.put(p, s, z[s]);
-      z[s] = load4<F>(X, off, c, d);
+      z[s] = load4<F, A>(X, off, c, d);
     });
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
-      const f4 gn = load4<F>(Gn, off, c, d), go = load4<F>(Go, off, c, d), my = v.get(p, s);
+      const f4 gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d), my = v.get(p, s);
       if (mine) {
-        store4<F>(X, off, c, d, fma4(-alpha, my, z[s]));
-        store4<F>(Y, off, c, d, my + gn - go);
+        store4<F, A>(X, off, c, d, fma4(-alpha, my, z[s]));
+        store4<F, A>(Y, off, c, d, my + gn - go);
       }
     });
   }
@@ -103,13 +103,18 @@ int launch_r(const Shape &s, const Geometry &g, size_t lds, const typename R::Ar
     }
     return 0;
   };
-  switch (mode) {
-    case 0: return go(&fused_generic_kernel<ST, 0, R>);
-    case 1: return go(&fused_generic_kernel<ST, 1, R>);
-    case 2: return go(&fused_generic_kernel<ST, 2, R>);
-    case 3: return go(&fused_generic_kernel<ST, 3, R>);
-  }
-  return hip_rc(hipErrorInvalidValue);
+  auto with = [&](auto access) {
+    switch (mode) {
+      case 0: return go(&fused_generic_kernel<ST, 0, R, access>);
+      case 1: return go(&fused_generic_kernel<ST, 1, R, access>);
+      case 2: return go(&fused_generic_kernel<ST, 2, R, access>);
+      case 3: return go(&fused_generic_kernel<ST, 3, R, access>);
+    }
+    return hip_rc(hipErrorInvalidValue);
+  };
+  const int state = sizeof(ST), per_element = mode == 0 ? state : mode == 3 ? state + 4 : 2 * state + 8;
+  const Call call = mode == 0 ? kPlain : mode == 1 ? kAtc : kReadsLate;
+  return with_access<R>(s, g, call, per_element, {X, Y, Gn, Go}, with);
 }
 
 // Whether a hub makes the kernels with one launch per round the faster ones.  In LDS a wavefront walks the longest list

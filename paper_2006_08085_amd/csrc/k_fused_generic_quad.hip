@@ -18,7 +18,7 @@ using namespace lds_tile;
 // reads X, Y (state type), G, b (fp32) and writes X, Y, G, where the gradient kernel followed by the phase moves
 // X twice more and the gradient three times.  A lane's four columns of a row are one Philox block of the
 // counter-based noise.
-template <typename ST, bool HPW, class R>
+template <typename ST, bool HPW, class R, Access A>
 __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadratic_kernel(
     ST *X, ST *Y, float *G, const float *__restrict__ h, const float *__restrict__ b, int n, int64_t d, int64_t ld,
     int lpr_log2, typename R::Args ra, float eta, float alpha, int K, float sigma, uint32_t seed_lo, uint32_t seed_hi,
@@ -45,26 +45,26 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadrati
         noise = f4{t[0], c.skip == 1 ? t[0] : t[1], c.skip == 1 ? t[1] : t[0], c.skip == 1 ? t[2] : c.skip == 2 ? t[1] : t[0]};
     }
     __builtin_amdgcn_sched_barrier(0);
-    const f4 x = load4<F>(X, off, c, d), bb = load4<F>(b, off, c, d), hh = load4<F>(h, HPW ? off : 0, c, d);
+    const f4 x = load4<F, A>(X, off, c, d), bb = load4<F, A>(b, off, c, d), hh = load4<F, A>(h, HPW ? off : 0, c, d);
     f4 g;
 #pragma unroll
     for (int e = 0; e < 4; ++e) g[e] = fmaf(sigma, noise[e], hh[e] * (x[e] - bb[e]));
     __builtin_amdgcn_sched_barrier(0);
-    const f4 y = load4<F>(Y, off, c, d), go = load4<F>(G, off, c, d);
+    const f4 y = load4<F, A>(Y, off, c, d), go = load4<F, A>(G, off, c, d);
     z[s] = fma4(-alpha, y, x);
     f4 t = y + g - go;
     pin4(t);
     v.put(p, s, t);
-    if (mine) store4<F>(G, off, c, d, g);
+    if (mine) store4<F, A>(G, off, c, d, g);
   });
   rounds.init(ra, p, eta);
   gossip(z, rounds, p, eta, K);
   rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
-    if (mine) store4<F>(X, off, c, d, z[s]);
+    if (mine) store4<F, A>(X, off, c, d, z[s]);
     z[s] = v.get(p, s);
   });
   gossip(z, rounds, p, eta, K);
-  rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F>(Y, off, c, d, z[s]); });
+  rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F, A>(Y, off, c, d, z[s]); });
 }
 
 }  // namespace
@@ -82,14 +82,20 @@ int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, v
           uint32_t(seed >> 32), step);
       return hip_rc(hipGetLastError());
     };
-    if (s.bf16) {
-      auto *x = static_cast<bf16_t *>(X), *y = static_cast<bf16_t *>(Y);
-      return h_per_worker ? go(&fused_generic_quadratic_kernel<bf16_t, true, R>, x, y)
-                          : go(&fused_generic_quadratic_kernel<bf16_t, false, R>, x, y);
-    }
-    auto *x = static_cast<float *>(X), *y = static_cast<float *>(Y);
-    return h_per_worker ? go(&fused_generic_quadratic_kernel<float, true, R>, x, y)
-                        : go(&fused_generic_quadratic_kernel<float, false, R>, x, y);
+    auto with = [&](auto access) {
+      if (s.bf16) {
+        auto *x = static_cast<bf16_t *>(X), *y = static_cast<bf16_t *>(Y);
+        return h_per_worker ? go(&fused_generic_quadratic_kernel<bf16_t, true, R, access>, x, y)
+                            : go(&fused_generic_quadratic_kernel<bf16_t, false, R, access>, x, y);
+      }
+      auto *x = static_cast<float *>(X), *y = static_cast<float *>(Y);
+      return h_per_worker ? go(&fused_generic_quadratic_kernel<float, true, R, access>, x, y)
+                          : go(&fused_generic_quadratic_kernel<float, false, R, access>, x, y);
+    };
+    const int per_element = (s.bf16 ? 4 : 8) + 8 + (h_per_worker ? 4 : 0);
+    // blocks of 1024 threads, two to a compute unit, are better off streaming: 256 x 30,001 53.3, 62.8, 72.2 us
+    const Call call = g.threads <= 512 ? kReadsLate : kAtc;
+    return with_access<R>(s, g, call, per_element, {X, Y, G, h_per_worker ? h : nullptr, b}, with);
   });
 }
 

@@ -42,7 +42,7 @@ constexpr int quad_waves(int n, bool hpw) {
   return n >= 64 ? 3 : waves_per_simd(n, 1) - (hpw && n == 12 ? 1 : 0);
 }
 
-template <class T, typename ST, bool HPW, bool NT>
+template <class T, typename ST, bool HPW, Access A>
 __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadratic_kernel(
     ST *X, ST *Y, float *G, const float *__restrict__ h, const float *__restrict__ b, int64_t d, int64_t ld, Coef c,
     float alpha, int K, float sigma, uint32_t seed_lo, uint32_t seed_hi, uint32_t step) {
@@ -57,16 +57,16 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST)), fo = threadIdx.x * 4u;
   const unsigned j = threadIdx.x & 3u;
   const uint64_t q = uint64_t(tile + threadIdx.x) >> 2;
-  const float hc = HPW ? 0.f : buf_load<float, NT>(make_rsrc(h + tile, valid * 4u), fo);
+  const float hc = HPW ? 0.f : buf_load<float, A>(make_rsrc(h + tile, valid * 4u), fo);
   float u[N], p[N], vr[NR > 0 ? NR : 1];
   float lx[N], ly[N], lg[N], lb[N], lh[HPW ? N : 1];
 #pragma unroll
   for (int i = 0; i < D; ++i) {
-    lx[i] = buf_load<ST, NT>(row_of(X, tile, ld, i, valid), so);
-    ly[i] = buf_load<ST, NT>(row_of(Y, tile, ld, i, valid), so);
-    lg[i] = buf_load<float, NT>(row_of(G, tile, ld, i, valid), fo);
-    lb[i] = buf_load<float, NT>(row_of(b, tile, ld, i, valid), fo);
-    if constexpr (HPW) lh[i] = buf_load<float, NT>(row_of(h, tile, ld, i, valid), fo);
+    lx[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
+    ly[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+    lg[i] = buf_load<float, A>(row_of(G, tile, ld, i, valid), fo);
+    lb[i] = buf_load<float, A>(row_of(b, tile, ld, i, valid), fo);
+    if constexpr (HPW) lh[i] = buf_load<float, A>(row_of(h, tile, ld, i, valid), fo);
   }
   __builtin_amdgcn_sched_barrier(0);
   // All the noise of the tile is generated now, while the first rows' loads are in flight, and parked in p
@@ -88,11 +88,11 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     if (i + D < N) {
-      lx[i + D] = buf_load<ST, NT>(row_of(X, tile, ld, i + D, valid), so);
-      ly[i + D] = buf_load<ST, NT>(row_of(Y, tile, ld, i + D, valid), so);
-      lg[i + D] = buf_load<float, NT>(row_of(G, tile, ld, i + D, valid), fo);
-      lb[i + D] = buf_load<float, NT>(row_of(b, tile, ld, i + D, valid), fo);
-      if constexpr (HPW) lh[i + D] = buf_load<float, NT>(row_of(h, tile, ld, i + D, valid), fo);
+      lx[i + D] = buf_load<ST, A>(row_of(X, tile, ld, i + D, valid), so);
+      ly[i + D] = buf_load<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+      lg[i + D] = buf_load<float, A>(row_of(G, tile, ld, i + D, valid), fo);
+      lb[i + D] = buf_load<float, A>(row_of(b, tile, ld, i + D, valid), fo);
+      if constexpr (HPW) lh[i + D] = buf_load<float, A>(row_of(h, tile, ld, i + D, valid), fo);
     }
     const float g = fmaf(sigma, p[i], (HPW ? lh[i] : hc) * (lx[i] - lb[i]));
     u[i] = fmaf(-alpha, ly[i], lx[i]);
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
     pin_vgpr(vi);
     if (i < NR) vr[i] = vi;
     else vl[(i - NR) * kThreads + threadIdx.x] = vi;
-    buf_store<float, NT>(row_of(G, tile, ld, i, valid), fo, g);
+    buf_store<float, A>(row_of(G, tile, ld, i, valid), fo, g);
     __builtin_amdgcn_sched_barrier(0);
   }
   ag_rounds<T>(u, p, c, K);
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
   X = launder_uniform(X);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    buf_store<ST, NT>(row_of(X, tile, ld, i, valid), so, u[i]);
+    buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, u[i]);
     if (i < NR) u[i] = vr[i];
     else u[i] = vl[(i - NR) * kThreads + threadIdx.x];
   }
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
   __builtin_amdgcn_sched_barrier(0);
   Y = launder_uniform(Y);
 #pragma unroll
-  for (int i = 0; i < N; ++i) buf_store<ST, NT>(row_of(Y, tile, ld, i, valid), so, u[i]);
+  for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, u[i]);
 }
 
 // Algorithm 2 as printed: the gossip runs on X and Y themselves and the gradients enter after it,
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
 // round scratch in registers, the gradient in LDS (n KiB per block; every lane reads back only what it wrote, so
 // there is no barrier).  The old gradient is read at the end, row by row just ahead of the row's stores, and
 // overwritten in place: the same 28 B per element (32 B with per-worker curvature) as the ATC form.
-template <class T, typename ST, bool HPW, bool NT>
+template <class T, typename ST, bool HPW, Access A>
 __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadratic_alg2_kernel(
     ST *X, ST *Y, float *G, const float *__restrict__ h, const float *__restrict__ b, int64_t d, int64_t ld, Coef c,
     float alpha, int K, float sigma, uint32_t seed_lo, uint32_t seed_hi, uint32_t step) {
@@ -139,16 +139,16 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST)), fo = threadIdx.x * 4u;
   const unsigned j = threadIdx.x & 3u;
   const uint64_t q = uint64_t(tile + threadIdx.x) >> 2;
-  const float hc = HPW ? 0.f : buf_load<float, NT>(make_rsrc(h + tile, valid * 4u), fo);
+  const float hc = HPW ? 0.f : buf_load<float, A>(make_rsrc(h + tile, valid * 4u), fo);
   float u[N], v[N], p[N];
   {
     float lx[N], ly[N], lb[N], lh[HPW ? N : 1];
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      lx[i] = buf_load<ST, NT>(row_of(X, tile, ld, i, valid), so);
-      ly[i] = buf_load<ST, NT>(row_of(Y, tile, ld, i, valid), so);
-      lb[i] = buf_load<float, NT>(row_of(b, tile, ld, i, valid), fo);
-      if constexpr (HPW) lh[i] = buf_load<float, NT>(row_of(h, tile, ld, i, valid), fo);
+      lx[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
+      ly[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+      lb[i] = buf_load<float, A>(row_of(b, tile, ld, i, valid), fo);
+      if constexpr (HPW) lh[i] = buf_load<float, A>(row_of(h, tile, ld, i, valid), fo);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (sigma != 0.f) {  // the tile's noise, generated while the first rows' loads are in flight
@@ -167,10 +167,10 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       if (i + D < N) {
-        lx[i + D] = buf_load<ST, NT>(row_of(X, tile, ld, i + D, valid), so);
-        ly[i + D] = buf_load<ST, NT>(row_of(Y, tile, ld, i + D, valid), so);
-        lb[i + D] = buf_load<float, NT>(row_of(b, tile, ld, i + D, valid), fo);
-        if constexpr (HPW) lh[i + D] = buf_load<float, NT>(row_of(h, tile, ld, i + D, valid), fo);
+        lx[i + D] = buf_load<ST, A>(row_of(X, tile, ld, i + D, valid), so);
+        ly[i + D] = buf_load<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+        lb[i + D] = buf_load<float, A>(row_of(b, tile, ld, i + D, valid), fo);
+        if constexpr (HPW) lh[i + D] = buf_load<float, A>(row_of(h, tile, ld, i + D, valid), fo);
       }
       gl[i * kThreads + threadIdx.x] = fmaf(sigma, p[i], (HPW ? lh[i] : hc) * (lx[i] - lb[i]));
       u[i] = lx[i];
@@ -186,15 +186,15 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
   X = launder_uniform(X), Y = launder_uniform(Y);
   float lgo[N];
 #pragma unroll
-  for (int i = 0; i < D; ++i) lgo[i] = buf_load<float, NT>(row_of(G, tile, ld, i, valid), fo);
+  for (int i = 0; i < D; ++i) lgo[i] = buf_load<float, A>(row_of(G, tile, ld, i, valid), fo);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (i + D < N) lgo[i + D] = buf_load<float, NT>(row_of(G, tile, ld, i + D, valid), fo);
+    if (i + D < N) lgo[i + D] = buf_load<float, A>(row_of(G, tile, ld, i + D, valid), fo);
     const float g = gl[i * kThreads + threadIdx.x];
-    buf_store<ST, NT>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, v[i], u[i]));
-    buf_store<ST, NT>(row_of(Y, tile, ld, i, valid), so, v[i] + g - lgo[i]);
-    buf_store<float, NT>(row_of(G, tile, ld, i, valid), fo, g);
+    buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, v[i], u[i]));
+    buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, v[i] + g - lgo[i]);
+    buf_store<float, A>(row_of(G, tile, ld, i, valid), fo, g);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -209,17 +209,19 @@ int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float 
   auto go = [&](auto *kernel, auto *x) {
     kernel<<<grid, threads, 0, st>>>(x, static_cast<decltype(x)>(Y), G, h, b, s.d, s.ld, c, alpha, K, sigma, slo, shi, step);
   };
-  auto with = [&](auto nt, auto per_worker, auto *x) {
+  auto with = [&](auto access, auto per_worker, auto *x) {
     using ST = std::remove_pointer_t<decltype(x)>;
-    if (alg2) go(&fused_quadratic_alg2_kernel<T, ST, per_worker, nt>, x);
-    else go(&fused_quadratic_kernel<T, ST, per_worker, nt>, x);
+    if (alg2) go(&fused_quadratic_alg2_kernel<T, ST, per_worker, access>, x);
+    else go(&fused_quadratic_kernel<T, ST, per_worker, access>, x);
   };
-  auto with_h = [&](auto nt, auto *x) { hpw ? with(nt, std::true_type{}, x) : with(nt, std::false_type{}, x); };
-  auto with_nt = [&](auto *x) {
-    streams(s, 2 * int(sizeof *x) + 8 + (hpw ? 4 : 0)) ? with_h(std::true_type{}, x) : with_h(std::false_type{}, x);
+  auto with_h = [&](auto access, auto *x) { hpw ? with(access, std::true_type{}, x) : with(access, std::false_type{}, x); };
+  const int per_element = (s.bf16 ? 4 : 8) + 8 + (hpw ? 4 : 0);
+  auto with_type = [&](auto access) {
+    if (s.bf16) with_h(access, static_cast<bf16_t *>(X));
+    else with_h(access, static_cast<float *>(X));
   };
-  if (s.bf16) with_nt(static_cast<bf16_t *>(X));
-  else with_nt(static_cast<float *>(X));
+  if (tile_access(s, per_element, {X, Y, G, hpw ? h : nullptr, b}) == kStream) with_type(AccessTag<kStream>{});
+  else with_type(AccessTag<kKeep>{});
   return hip_rc(hipGetLastError());
 }
 

@@ -9,6 +9,7 @@
 // and model updates are the end-of-phase lines of Algorithm 2.
 #include "dev_common.hpp"
 #include "detag_internal.h"
+#include "fused_common.hpp"
 
 namespace detag {
 namespace {
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(kThreads) void gossip_round_kernel(int n, int64_t d
 constexpr int kTileCols = 64, kTileRowsMax = 256, kTileBatch = 4;
 constexpr int64_t kTileMinBytes = int64_t(128) << 20;
 
-template <typename ST, bool HAS_G, int kTileWaves>
+template <typename ST, bool HAS_G, int kTileWaves, Access A>
 __global__ __launch_bounds__(64 * kTileWaves) void gossip_round_tile_kernel(int n, int64_t d, int64_t ld,
                                                                          const int32_t *__restrict__ rowptr,
                                                                          const int32_t *__restrict__ colidx,
@@ -157,7 +158,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void gossip_round_tile_kernel(int 
 #pragma unroll
     for (int q = 0; q < kTileBatch; ++q) {
       const int i = i0 + q * kTileWaves;
-      z[q] = buf_load<ST>(row_of(cur, tile, ld, i < n ? i : 0, i < n ? valid : 0u), so);
+      z[q] = buf_load<ST, A>(row_of(cur, tile, ld, i < n ? i : 0, i < n ? valid : 0u), so);
     }
 #pragma unroll
     for (int q = 0; q < kTileBatch; ++q) {
@@ -171,8 +172,8 @@ __global__ __launch_bounds__(64 * kTileWaves) void gossip_round_tile_kernel(int 
 #pragma unroll
     for (int q = 0; q < kTileBatch; ++q) {
       const int i = i0 + q * kTileWaves;
-      if constexpr (HAS_G) other[q] = buf_load<float>(row_of(G, tile, ld, i < n ? i : 0, i < n ? valid : 0u), fo);
-      else other[q] = buf_load<ST>(row_of(prev, tile, ld, i < n ? i : 0, i < n ? valid : 0u), so);
+      if constexpr (HAS_G) other[q] = buf_load<float, A>(row_of(G, tile, ld, i < n ? i : 0, i < n ? valid : 0u), fo);
+      else other[q] = buf_load<ST, A>(row_of(prev, tile, ld, i < n ? i : 0, i < n ? valid : 0u), so);
     }
 #pragma unroll
     for (int q = 0; q < kTileBatch; ++q) {
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void gossip_round_tile_kernel(int 
       float o;
       if constexpr (HAS_G) o = own + fmaf(-alpha, other[q], c_mix * acc);
       else o = own + fmaf(c_mix, acc, eta * (own - other[q]));
-      buf_store<ST>(row_of(out, tile, ld, i, valid), so, o);
+      buf_store<ST, A>(row_of(out, tile, ld, i, valid), so, o);
     }
   }
 }
@@ -336,15 +337,19 @@ int launch_round_t(const Shape &s, const DevCsr &w, const void *cur, const void 
   if (round_stages_tile(s)) {
     const dim3 tgrid(ceil_div_i64(s.d, kTileCols));
     const size_t lds_bytes = size_t(s.n) * kTileCols * sizeof(float);
-#define DETAG_TILE_GO(RW)                                                                                      \
-  gossip_round_tile_kernel<ST, HAS_G, RW><<<tgrid, 64 * RW, lds_bytes, st>>>(                                  \
-      s.n, s.d, s.ld, w.rowptr, w.colidx, w.vals, static_cast<const ST *>(cur), static_cast<const ST *>(prev), \
-      static_cast<ST *>(out), G, c_mix, eta, alpha)
-    if (s.n <= 64) DETAG_TILE_GO(4);
-    else if (s.n <= 128) DETAG_TILE_GO(8);
-    else DETAG_TILE_GO(16);
-#undef DETAG_TILE_GO
-    return hip_rc(hipGetLastError());
+    const Access access = fused::tile_access(s, int(sizeof(ST)) * (HAS_G ? 1 : 3) + (HAS_G ? 4 : 0), {cur, prev, out, G});
+    auto with = [&](auto waves) {
+      auto go = [&](auto a) {
+        gossip_round_tile_kernel<ST, HAS_G, waves, a><<<tgrid, 64 * waves, lds_bytes, st>>>(
+            s.n, s.d, s.ld, w.rowptr, w.colidx, w.vals, static_cast<const ST *>(cur), static_cast<const ST *>(prev),
+            static_cast<ST *>(out), G, c_mix, eta, alpha);
+        return hip_rc(hipGetLastError());
+      };
+      return access == kStream ? go(AccessTag<kStream>{}) : go(AccessTag<kKeep>{});
+    };
+    if (s.n <= 64) return with(std::integral_constant<int, 4>{});
+    if (s.n <= 128) return with(std::integral_constant<int, 8>{});
+    return with(std::integral_constant<int, 16>{});
   }
   const int per_block = kThreads * VEC;
   const int col_blocks = ceil_div_i64(s.d, per_block);

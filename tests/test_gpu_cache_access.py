@@ -1,0 +1,73 @@
+"""Which accesses stream past the caches depends on the size of a call and on whether its column tiles share cache lines
+(the pitch, the base address): the bits of the result do not.  Sizes on both sides of the lines the kernels draw (32, 80,
+128 and 192 MiB a call)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2006_08085_amd as D
+from tests.gpu_util import DEV, SENTINEL, _built  # noqa: F401
+from workloads import generate as gen
+
+pytestmark = pytest.mark.gpu
+
+
+def _topology(kind, n):
+    if kind == "torus":
+        return D.Topology.torus(8, 8)
+    if kind == "path":  # rows of different weights
+        return D.Topology.from_edges(np.array([(i, i + 1) for i in range(n - 1)], np.int32), D.DETAG_W_METROPOLIS)
+    return D.Topology.from_edges(gen.edges_random_regular(n, 4, seed=1), D.DETAG_W_METROPOLIS)
+
+
+def _place(values, ld, shift, dtype):
+    n, d = values.shape
+    flat = torch.full((n * ld + shift,), SENTINEL, device=DEV, dtype=dtype)
+    t = flat[shift:].view(n, ld)
+    t[:, :d] = values
+    return t
+
+
+def _all_calls(topo, n, d, ld, shift, dtype, values):
+    K, eta = 3, 0.35
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if dtype == torch.bfloat16 else D.DETAG_F32)
+    new = lambda k: _place(values[k], ld, shift, dtype if k < 2 else torch.float32)  # noqa: E731
+    h = values[4][0].abs().contiguous()
+    out = []
+    for variant in (D.DETAG_VARIANT_ATC, D.DETAG_VARIANT_ALG2):
+        x, y, gn, go = new(0), new(1), new(2), new(3)
+        ctx.step(x, y, gn, go, 0.2, K, eta, variant)
+        out += [x, y]
+        if ctx.kernel() == D.DETAG_KERNEL_REGISTER_TILE or (ctx.has_fused() and variant == D.DETAG_VARIANT_ATC):
+            x, y = new(0), new(1)
+            ctx.step_quadratic(x, y, go, h, gn, 0.2, K, sigma=0.1, seed=3, step=1, eta=eta, variant=variant)
+            out += [x, y, go]
+    z, p, r = new(0), new(0), new(0)
+    ctx.gossip_accel(z, K, eta)
+    ctx.dpsgd_step(p, new(2), 0.2)
+    ctx.gossip_round(new(0), new(1), r, eta)
+    out += [z, p, r]
+    ctx.set_path(D.DETAG_PATH_PER_ROUND)
+    p = new(0)
+    ctx.dpsgd_step(p, new(2), 0.2)
+    out += [p, ctx.mean(new(0))[None], ctx.consensus_error(new(0))[None]]
+    torch.cuda.synchronize()
+    ctx.close()
+    for t in out[:-2]:
+        assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))
+    return [t[:, :d] for t in out]
+
+
+@pytest.mark.parametrize("kind,n", [("torus", 64), ("rr", 64), ("rr", 20), ("rr", 200), ("path", 100)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_the_layout_does_not_change_the_bits(kind, n, dtype):
+    topo = _topology(kind, n)
+    for elements in (2_200_000, 4_000_000, 6_500_000, 9_500_000):
+        d = elements // n + 3
+        g = torch.Generator(device=DEV)
+        g.manual_seed(d)
+        values = [torch.empty(n, d, device=DEV).normal_(generator=g) for _ in range(5)]
+        on_lines = _all_calls(topo, n, d, D.padded_ld(d), 0, dtype, values)
+        for ld, shift in ((d + 1 - d % 2, 0), (D.padded_ld(d), 1)):
+            for k, (got, want) in enumerate(zip(_all_calls(topo, n, d, ld, shift, dtype, values), on_lines)):
+                assert torch.equal(got, want), (d, ld, shift, k)
