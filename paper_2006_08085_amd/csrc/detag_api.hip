@@ -50,8 +50,9 @@ struct detag_factors {
   int32_t *d_rowptr = nullptr, *d_colidx = nullptr;
   float *d_vals = nullptr;
   std::vector<int64_t> offs;
-  std::vector<uint32_t> table;  // program of the on-chip kernel; empty if build_factor_table declined
-  uint32_t *d_table = nullptr;
+  std::vector<uint32_t> table;  // program of the sequence; empty if build_factor_table declined
+  uint32_t *d_table = nullptr;  // the same as the on-chip kernel reads it
+  int table_words = 0;
 };
 
 namespace {
@@ -679,9 +680,12 @@ detag_status factors_create_impl(detag_ctx *ctx, int32_t root, detag_factors *f)
   if (e == hipSuccess) e = hipMemcpy(f->d_colidx, ci.data(), ci.size() * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(f->d_vals, va.data(), va.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess && !f->table.empty()) {
-    const size_t bytes = f->table.size() * sizeof(uint32_t);
+    std::vector<uint32_t> entries;
+    build_factor_entries(ctx->W.n, f->table, entries);
+    f->table_words = int(entries.size());
+    const size_t bytes = entries.size() * sizeof(uint32_t);
     e = hipMalloc(reinterpret_cast<void **>(&f->d_table), bytes);
-    if (e == hipSuccess) e = hipMemcpy(f->d_table, f->table.data(), bytes, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemcpy(f->d_table, entries.data(), bytes, hipMemcpyHostToDevice);
   }
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -770,7 +774,7 @@ detag_status detag_average_consensus(detag_ctx *ctx, const detag_factors *f, voi
   const int R = int(f->host.size());
   if (R == 0) return DETAG_OK;
   if (f->d_table && ctx->path != DETAG_PATH_PER_ROUND) {
-    const int rc = launch_factor_sequence(ctx->shape, f->d_table, int(f->table.size()), Z_dev, stream);
+    const int rc = launch_factor_sequence(ctx->shape, f->d_table, f->table_words, Z_dev, stream);
     if (rc == 0) return DETAG_OK;
     if (rc > 0) return hip_fail(ctx, "factor sequence", rc);
     // rc < 0: does not fit the LDS of a block here; fall through to one launch per factor

@@ -39,10 +39,9 @@ struct HostFactor {
 // Spanning-tree (gather, then propagate) factors on the undirected support of W, rooted at `root`.
 bool build_consensus_factors(const HostW &W, int root, std::vector<HostFactor> &out, std::string &err);
 
-// Device table of a factor sequence for the on-chip kernel: batches of four 4-word operations (header, two packed
-// 16-bit LDS byte offsets, two fp32 weights) covering the non-identity rows of every factor in an order the kernel
-// may execute batch by batch.  false if n > 256, a factor row has more than 8 terms, or the rows a step changes
-// read each other in a cycle.
+// Program of a factor sequence that runs on chip: batches of four 8-word operations covering the non-identity rows of every
+// factor in an order in which they may be done batch by batch (detag_factors_get_program).
+// false if n > 256, a factor row has more than 8 terms, or the rows a step changes read each other in a cycle.
 bool build_factor_table(int n, const std::vector<HostFactor> &factors, std::vector<uint32_t> &table);
 
 // Eigenvalues (ascending) of a dense symmetric matrix, cyclic Jacobi. a is n*n row-major, destroyed.
@@ -88,7 +87,9 @@ struct Shape {
   bool bf16;  // storage of X/Y
 };
 
-// Z <- A_{R-1} ... A_0 Z on chip, in place (table from build_factor_table).  -1 if n rows of 64 columns do not
+// The table the on-chip kernel reads, from a program of build_factor_table (n <= 256).
+void build_factor_entries(int n, const std::vector<uint32_t> &program, std::vector<uint32_t> &table);
+// Z <- A_{R-1} ... A_0 Z on chip, in place (table from build_factor_entries).  -1 if n rows of 32 columns do not
 // fit a block's LDS on this device.
 int launch_factor_sequence(const Shape &s, const uint32_t *table, int table_words, void *Z, void *stream);
 // The matrix polynomial of K rounds of Algorithm 3, P = p_K(W^T), as bf16 terms in the operand order of

@@ -2,35 +2,47 @@
 // paper; spanning-tree gather and propagate steps) applied on chip, for up to
 // 256 workers: Z <- A_{R-1} ... A_0 Z with the state read and written once.
 //
-// One wavefront owns 64 columns and all n rows of them; the rows sit in LDS
-// (n x 64 fp32) and stay there.  A gather or propagate step changes only the
-// rows of one level of the tree and their parents; every other row of the factor
-// is an identity row and costs nothing, and a changed row that no later step
-// reads before it is overwritten again (the emptied rows of the gather steps) is
-// dropped on the host.  What remains becomes one list of small operations, four
-// to a batch:
-//   acc_j = (acc_{j-1} & keep) + w0 * (row[o0] & m0) + w1 * (row[o1] & m1),   row[dst] = acc_j,
-// the masks being all ones or zero, so that an absent term is exactly absent
-// whatever the row it points at holds.  A row of up to 8 terms is a chain of up
-// to 4 operations of one batch, each writing its partial sum to the row, the
-// last one last.  The code of a batch has no branch: 32 words fetched with
-// scalar loads (the next batch's while this one computes), every operand read
-// before any row is written.  Within a step the host orders the rows so that a
-// row is overwritten only in or after the batch of its last reader, which is
-// what a step of the sequence means (every row is computed from the state
-// before the step); a step whose rows cannot be ordered that way (a cycle of
-// rows reading each other) is left to the one-launch-per-factor path.
-// No wavefront waits for another: there is no barrier.
+// A wavefront owns 32 columns (more with few workers) and all n rows of them; the rows sit in LDS (128
+// bytes each) and stay there.  A gather or propagate step changes only the rows
+// of one level of the tree and their parents; every other row of the factor is
+// an identity row and costs nothing, and a changed row that no later step reads
+// before it is overwritten again (the emptied rows of the gather steps) is
+// dropped on the host.  What remains is a list of row operations
+//   row[dst] = sum_k w_k * row[o_k],   at most 8 terms,
+// to be done in order; the host packs them, eight at a time, into groups that
+// may be done side by side: no row of a group is read by a later row of it, so
+// that the order within a group does not matter once every operand is read
+// before any row is written.  Rows of different steps share a group where
+// nothing forbids it, which makes the number of groups little more than the
+// depth of the tree: 64 workers, 4-regular: 15 groups, 22 slots of two terms
+// (batches of four operations within a step: 42).
+//
+// Eight lanes side by side take a row, four columns each, and the eight rows of
+// a group are done at once: a slot of two terms is two 16-byte LDS reads, eight
+// multiply-adds and, after the last slot of a group, one 16-byte write, with the
+// operands of a lane's row in one 16-byte word fetched four slots ahead.  An
+// absent term reads a row of zeros with weight 0, an idle lane writes to it.  No
+// wavefront waits for another: there is no barrier.
+//
+// With one column per lane, the four operations of a batch one after the other
+// and 16 KiB of LDS per wavefront (10 of them on a compute unit, 19 now), 64
+// workers, 4-regular, d = 272,474 took 49 us, 31 now; d = 1,000,000 139 and 109;
+// 256 workers, d = 400,000 566 and 257; 64 workers, d = 20,000 14.5 and 6.8.
+#include <algorithm>
+
 #include "detag_internal.h"
 #include "dev_common.hpp"
 #include "fused_common.hpp"
+#include "fused_generic_common.hpp"
 
 namespace detag {
 namespace {
 
-constexpr int kCols = 64, kRowsMax = 256, kTerms = 8;
-constexpr int kBatch = 4;                      // operations per batch
-constexpr int kRowChunk = 64, kRowTail = 16;  // rows loaded or stored together
+using namespace lds_tile;
+
+constexpr int kRowsMax = 256, kTerms = 8;
+constexpr int kProgramRow = 256;  // bytes per row index in the program that detag_factors_get_program shows
+constexpr int kBatch = 4;         // its operations per batch
 
 struct Op {
   uint32_t o0, o1, dst;  // byte offsets of the two source rows and of the written row in the tile (< 65536)
@@ -38,98 +50,89 @@ struct Op {
   uint32_t w0, w1;       // fp32 weights
   uint32_t m0, m1;       // all ones: the term is there; 0: it is not
 };
-struct BatchWords {
-  Op op[kBatch];
+constexpr int kOpWords = sizeof(Op) / 4;
+
+// Lanes side by side that take a row.  Few workers make few rows that can be done side by side and a tile that is soon
+// loaded: wider rows keep the wavefronts busy (8, 16 and 32 lanes: n = 8, d = 3,000,000 79, 54, 40 us; n = 16, d = 272,474
+// 13.6, 11.0, 10.9; n = 24, d = 400,000 18.5, 16.5, 20; n = 40, d = 200,000 15, 16, 17; n = 64, d = 272,474 30, 33, 48).
+constexpr int lanes_per_row(int n) { return n <= 12 ? 32 : n <= 24 ? 16 : 8; }
+template <int LPR>
+struct Layout {
+  static constexpr int kCols = 4 * LPR, kGroup = 64 / LPR;  // columns of a wavefront, rows done side by side
+  static constexpr uint32_t kRowBytes = kCols * 4;
 };
-constexpr int kBatchWords = sizeof(BatchWords) / 4;
+constexpr int kAhead = 4;   // slots fetched ahead; their number is a multiple of it
+constexpr int kChunk = 8;   // rows a lane loads or stores together
 
-__device__ __forceinline__ float masked(float v, uint32_t m) { return __uint_as_float(__float_as_uint(v) & m); }
+// What a row of a group does in a slot: the LDS offsets of two source rows (the second in the upper half of the word), the
+// offset of the written row with kLast in the group's last slot, two fp32 weights.
+struct alignas(16) Entry {
+  uint32_t from, to;
+  float w0, w1;
+};
+constexpr uint32_t kLast = 1u << 16;
 
-// One batch on the wavefront's tile; `mine` is the lane's column of row 0.
-__device__ __forceinline__ void run_batch(const BatchWords &t, char *mine) {
-  float x0[kBatch], x1[kBatch], acc[kBatch];
-#pragma unroll
-  for (int j = 0; j < kBatch; ++j) {
-    x0[j] = *reinterpret_cast<const float *>(mine + t.op[j].o0);
-    x1[j] = *reinterpret_cast<const float *>(mine + t.op[j].o1);
-  }
-#pragma unroll
-  for (int j = 0; j < kBatch; ++j) {
-    float a = j ? masked(acc[j - 1], t.op[j].keep) : 0.f;
-    a = fmaf(__uint_as_float(t.op[j].w0), masked(x0[j], t.op[j].m0), a);
-    acc[j] = fmaf(__uint_as_float(t.op[j].w1), masked(x1[j], t.op[j].m1), a);
-  }
-#pragma unroll
-  for (int j = 0; j < kBatch; ++j) *reinterpret_cast<float *>(mine + t.op[j].dst) = acc[j];
-}
-
-// The whole table: two batches per trip (the host makes their number even), each fetched while the other one runs.
-__device__ __forceinline__ void run_table(const BatchWords *__restrict__ table, int batches, char *mine) {
-  BatchWords even = table[0];
-  for (int b = 0; b < batches; b += 2) {
-    const BatchWords odd = table[b + 1];
-    __builtin_amdgcn_sched_barrier(0);
-    run_batch(even, mine);
-    even = table[b + 2 < batches ? b + 2 : b];
-    __builtin_amdgcn_sched_barrier(0);
-    run_batch(odd, mine);
-  }
-}
-
-// CHUNK rows from r0 on, HBM -> LDS, every load issued before the first value is needed.  Rows past the last one
-// repeat it (the same value goes to the same place twice), so CHUNK need not divide n.
-template <typename ST, int CHUNK>
-__device__ __forceinline__ void rows_in_chunk(const ST *Z, int64_t tile, int64_t ld, int n, int r0, uint32_t valid,
-                                              uint32_t so, float *col) {
-  float v[CHUNK];
-#pragma unroll
-  for (int k = 0; k < CHUNK; ++k) v[k] = buf_load<ST>(row_of(Z, tile, ld, r0 + k < n ? r0 + k : n - 1, valid), so);
-#pragma unroll
-  for (int k = 0; k < CHUNK; ++k) col[(r0 + k < n ? r0 + k : n - 1) * kCols] = v[k];
-}
-
-template <typename ST, int CHUNK>
-__device__ __forceinline__ void rows_out_chunk(ST *Z, int64_t tile, int64_t ld, int n, int r0, uint32_t valid,
-                                               uint32_t so, const float *col) {
-  float v[CHUNK];
-#pragma unroll
-  for (int k = 0; k < CHUNK; ++k) v[k] = col[(r0 + k < n ? r0 + k : n - 1) * kCols];
-#pragma unroll
-  for (int k = 0; k < CHUNK; ++k) buf_store<ST>(row_of(Z, tile, ld, r0 + k < n ? r0 + k : n - 1, valid), so, v[k]);
-}
-
-// All n rows of the wavefront's 64 columns: 64 at a time while that many are left, then 16 at a time.
-template <typename ST>
-__device__ __forceinline__ void rows_in(const ST *Z, int64_t tile, int64_t ld, int n, uint32_t valid, uint32_t so,
-                                        float *col) {
-  int r0 = 0;
-  for (; r0 + kRowChunk <= n; r0 += kRowChunk) rows_in_chunk<ST, kRowChunk>(Z, tile, ld, n, r0, valid, so, col);
-  for (; r0 < n; r0 += kRowTail) rows_in_chunk<ST, kRowTail>(Z, tile, ld, n, r0, valid, so, col);
-}
-
-template <typename ST>
-__device__ __forceinline__ void rows_out(ST *Z, int64_t tile, int64_t ld, int n, uint32_t valid, uint32_t so,
-                                         const float *col) {
-  int r0 = 0;
-  for (; r0 + kRowChunk <= n; r0 += kRowChunk) rows_out_chunk<ST, kRowChunk>(Z, tile, ld, n, r0, valid, so, col);
-  for (; r0 < n; r0 += kRowTail) rows_out_chunk<ST, kRowTail>(Z, tile, ld, n, r0, valid, so, col);
-}
-
-template <typename ST>
-__global__ __launch_bounds__(256) void factor_sequence_kernel(ST *Z, int n, int64_t d, int64_t ld,
-                                                              const BatchWords *__restrict__ table, int batches) {
-  extern __shared__ float smem[];  // one n x 64 tile per wavefront
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+template <typename ST, int LPR, Access A>
+__global__ __launch_bounds__(256, 7) void factor_sequence_kernel(ST *Z, int n, int64_t d, int64_t ld,
+                                                              const Entry *__restrict__ table, int slots) {
+  constexpr int kCols = Layout<LPR>::kCols, kGroup = Layout<LPR>::kGroup;
+  constexpr uint32_t kRowBytes = Layout<LPR>::kRowBytes;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  uint32_t group = lane / LPR;
   // neighbouring tiles on one XCD (64 x 3,000,000 542 -> 493 us, odd pitch 64 x 300,007 68 -> 59 us)
-  const int64_t tile = (fused::xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + w) * kCols;
-  if (tile >= d) return;  // no barrier anywhere below
-  float *tile_f = smem + size_t(w) * n * kCols;
-  char *mine = reinterpret_cast<char *>(tile_f + lane);
-  const uint32_t valid = uint32_t(d - tile < kCols ? d - tile : kCols);
-  const uint32_t so = lane * uint32_t(sizeof(ST));
-  rows_in<ST>(Z, tile, ld, n, valid, so, tile_f + lane);
-  run_table(table, batches, mine);
-  rows_out<ST>(Z, tile, ld, n, valid, so, tile_f + lane);
+  const int64_t first = (fused::xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + w) * kCols;
+  if (first >= d) return;  // no barrier anywhere below
+  const uint32_t tile = w * uint32_t(n + 1) * kRowBytes + (lane % LPR) * 16u;  // the lane's columns of row 0
+  Entry ahead[kAhead];
+  const Entry *mine = table + group;
+#pragma unroll
+  for (int q = 0; q < kAhead; ++q) ahead[q] = mine[q * kGroup];
+  Columns c{first + (lane % LPR) * 4, 0};
+  const int kind = d - first >= kCols ? kWhole : d - first >= 4 ? kCut : kNarrow;
+  if (kind == kCut && c.at > d - 4) c = Columns{d - 4, int(c.at - (d - 4))};
+  // f(kind, k, row) for the lane's rows of a chunk; past the last row it is repeated, which does no harm
+  auto each_row = [&](int r0, auto of, auto f) {
+    asm volatile("" : "+v"(group));  // addresses are made anew, not kept
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k)
+      if (r0 + k * kGroup < n) f(of, k, min(r0 + k * kGroup + int(group), n - 1));
+  };
+  auto with_kind = [&](auto f) {
+    if (kind == kWhole) f(std::integral_constant<int, kWhole>{});
+    else if (kind == kCut) f(std::integral_constant<int, kCut>{});
+    else f(std::integral_constant<int, kNarrow>{});
+  };
+  if (group == 0) lds_write(tile + uint32_t(n) * kRowBytes, f4{0.f, 0.f, 0.f, 0.f});
+  with_kind([&](auto kind_of) {
+    for (int r0 = 0; r0 < n; r0 += kChunk * kGroup) {
+      f4 v[kChunk];
+      each_row(r0, kind_of, [&](auto of, int k, int row) { v[k] = load4<of, A>(Z, int64_t(row) * ld, c, d); });
+      __builtin_amdgcn_sched_barrier(0);
+      each_row(r0, kind_of, [&](auto, int k, int row) { lds_write(tile + uint32_t(row) * kRowBytes, v[k]); });
+    }
+  });
+  f4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < slots; s += kAhead) {
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const Entry e = ahead[q];
+      ahead[q] = mine[(s + kAhead < slots ? s + kAhead + q : q) * kGroup];
+      acc = fma4(e.w0, lds_read(tile + (e.from & 0xffffu)), acc);
+      acc = fma4(e.w1, lds_read(tile + (e.from >> 16)), acc);
+      if (__builtin_amdgcn_readfirstlane(e.to) & kLast) {  // the same in all groups
+        lds_write(tile + (e.to & 0xffffu), acc);
+        acc = f4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+  }
+  with_kind([&](auto kind_of) {
+    for (int r0 = 0; r0 < n; r0 += kChunk * kGroup) {
+      f4 v[kChunk];
+      each_row(r0, kind_of, [&](auto, int k, int row) { v[k] = lds_read(tile + uint32_t(row) * kRowBytes); });
+      __builtin_amdgcn_sched_barrier(0);
+      each_row(r0, kind_of, [&](auto of, int k, int row) { store4<of, A>(Z, int64_t(row) * ld, c, d, v[k]); });
+    }
+  });
 }
 
 uint32_t f32_bits(float f) {
@@ -150,6 +153,16 @@ int max_lds_per_block() {
     return v;
   }();
   return bytes;
+}
+
+// How the sequence treats the caches: as the other tile kernels where tiles share cache lines (64 x 1,000,001 streamed,
+// loads kept, all kept 249, 155, 131 us).  On lines, sequences that fit the memory-side cache beside other matrices leave
+// the loads to it (64 x 272,474 31.5, 30.4, 29.9; 8 x 3,000,000 of bf16 30.7, 25.3, 25.2), small ones with fp32 state do not
+// (16 x 272,474 9.9, 11.0, 11.1), large ones stream (64 x 1,000,000 109, 117, 118).
+Access sequence_access(const Shape &s, const void *Z) {
+  if (fused::shares_lines(s, {Z})) return kKeep;
+  const int64_t mib = fused::footprint(s, s.bf16 ? 2 : 4) >> 20;
+  return mib >= 96 || (mib < 32 && !s.bf16) ? kStream : kKeepReads;
 }
 
 struct Row {  // a row of a factor that is not an identity row
@@ -224,7 +237,7 @@ bool build_factor_table(int n, const std::vector<HostFactor> &factors, std::vect
     steps.push_back(std::move(rows));
   }
   drop_unused_rows(n, steps);
-  const auto row_off = [](int i) { return uint32_t(i) * kCols * 4u; };  // byte offset of row i in the tile
+  const auto row_off = [](int i) { return uint32_t(i) * kProgramRow; };
   const uint32_t ones = ~0u, one_f = f32_bits(1.f);
   std::vector<Op> ops;
   for (std::vector<Row> &rows : steps) {
@@ -259,37 +272,103 @@ bool build_factor_table(int n, const std::vector<HostFactor> &factors, std::vect
   return true;
 }
 
+// The table of factor_sequence_kernel from the program above: the program's row operations in order, each put into the
+// first group that comes after the writers of the rows it reads and of the row it writes, and not before the readers of
+// that row's old value.
+void build_factor_entries(int n, const std::vector<uint32_t> &program, std::vector<uint32_t> &table) {
+  struct Terms {
+    int dst, cnt;
+    uint32_t from[kTerms];
+    float w[kTerms];
+  };
+  const int kGroup = 64 / lanes_per_row(n);
+  const uint32_t kRowBytes = 16u * uint32_t(lanes_per_row(n));
+  std::vector<Op> ops(program.size() / kOpWords);
+  if (!ops.empty()) __builtin_memcpy(ops.data(), program.data(), program.size() * 4);
+  std::vector<std::vector<Terms>> groups;
+  std::vector<int> written(n, -1), read(n, -1);  // last group that writes or reads a row
+  for (size_t k = 0; k < ops.size(); ++k) {
+    Terms t{int(ops[k].dst / kProgramRow), 0, {}, {}};
+    for (;; ++k) {  // the operations of a row: partial sums to the same row, one after the other
+      const Op &op = ops[k];
+      float w;
+      if (op.m0) __builtin_memcpy(&w, &op.w0, 4), t.from[t.cnt] = op.o0 / kProgramRow, t.w[t.cnt++] = w;
+      if (op.m1) __builtin_memcpy(&w, &op.w1, 4), t.from[t.cnt] = op.o1 / kProgramRow, t.w[t.cnt++] = w;
+      if ((k + 1) % kBatch == 0 || !ops[k + 1].keep || ops[k + 1].dst != op.dst) break;
+    }
+    if (t.cnt == 1 && int(t.from[0]) == t.dst && t.w[0] == 1.f) continue;  // a copy of a row to itself fills a batch
+    size_t g = size_t(std::max(written[t.dst] + 1, std::max(read[t.dst], 0)));
+    for (int i = 0; i < t.cnt; ++i) g = std::max(g, size_t(written[t.from[i]] + 1));
+    while (g < groups.size() && int(groups[g].size()) == kGroup) ++g;
+    if (g >= groups.size()) groups.resize(g + 1);
+    groups[g].push_back(t);
+    written[t.dst] = int(g);
+    for (int i = 0; i < t.cnt; ++i) read[t.from[i]] = std::max(read[t.from[i]], int(g));
+  }
+  const uint32_t zero = uint32_t(n) * kRowBytes;
+  std::vector<Entry> entries;
+  for (const std::vector<Terms> &rows : groups) {
+    int slots = 1;
+    for (const Terms &t : rows) slots = std::max(slots, (t.cnt + 1) / 2);
+    for (int s = 0; s < slots; ++s)
+      for (int q = 0; q < kGroup; ++q) {
+        Entry e{zero | zero << 16, (q < int(rows.size()) ? uint32_t(rows[q].dst) * kRowBytes : zero) | (s + 1 == slots ? kLast : 0u),
+                0.f, 0.f};
+        if (q < int(rows.size())) {
+          const Terms &t = rows[q];
+          if (2 * s < t.cnt) e.from = (e.from & ~0xffffu) | t.from[2 * s] * kRowBytes, e.w0 = t.w[2 * s];
+          if (2 * s + 1 < t.cnt) e.from = (e.from & 0xffffu) | t.from[2 * s + 1] * kRowBytes << 16, e.w1 = t.w[2 * s + 1];
+        }
+        entries.push_back(e);
+      }
+  }
+  while (entries.size() % (kAhead * kGroup)) entries.push_back(Entry{zero | zero << 16, zero | kLast, 0.f, 0.f});
+  table.resize(entries.size() * (sizeof(Entry) / 4));
+  if (!entries.empty()) __builtin_memcpy(table.data(), entries.data(), entries.size() * sizeof(Entry));
+}
+
 // -1: a tile of n rows does not fit the LDS of a block on this device (the caller applies the factors one by one).
 int launch_factor_sequence(const Shape &s, const uint32_t *table, int table_words, void *Z, void *stream) {
-  const int batches = table_words / kBatchWords;
-  if (batches == 0) return 0;  // every row of every factor is an identity row
-  const size_t tile_bytes = size_t(s.n) * kCols * sizeof(float), lds_max = size_t(max_lds_per_block());
+  const int lpr = lanes_per_row(s.n), cols = 4 * lpr, slots = table_words / int(sizeof(Entry) / 4) / (64 / lpr);
+  if (slots == 0) return 0;  // every row of every factor is an identity row
+  const size_t tile_bytes = size_t(s.n + 1) * 16 * lpr, lds_max = size_t(max_lds_per_block());
   // wavefronts per block: whatever keeps most wavefronts on a compute unit, larger blocks on a tie while they
   // stay within the 64 KiB a launch may ask for without raising the kernel's limit
   int waves = 0, resident = 0;
   for (int wv = 1; wv <= 4; wv *= 2) {
     const size_t lds = tile_bytes * wv;
     if (lds > lds_max) break;
-    const int res = int(lds_max / lds) * wv;
+    const int res = std::min(int(lds_max / lds) * wv, 32);
     if (res > resident || (res == resident && lds <= 65536)) waves = wv, resident = res;
   }
   if (waves == 0) return -1;
   const size_t lds_bytes = tile_bytes * waves;
-  const int64_t tiles = ceil_div_i64(s.d, kCols);
+  const int64_t piece = kThreadsPerLaunch / 64 * cols;  // columns of one launch
   auto st = static_cast<hipStream_t>(stream);
-  const auto *tb = reinterpret_cast<const BatchWords *>(table);
-  auto launch = [&](auto *kernel, auto *z, int64_t blocks) -> int {
-    if (lds_bytes > 65536) {  // above the default limit of a launch: raise it for this kernel
-      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
-      if (e != hipSuccess) return hip_rc(e);
+  auto launch = [&](auto *kernel, auto *z) -> int {
+    if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds_bytes)) return rc;
+    for (int64_t first = 0; first < s.d; first += piece) {
+      const int64_t d = std::min(s.d - first, piece);
+      kernel<<<dim3(ceil_div_i64(d, int64_t(cols) * waves)), 64 * waves, lds_bytes, st>>>(
+          z + first, s.n, d, s.ld, reinterpret_cast<const Entry *>(table), slots);
+      if (int rc = hip_rc(hipGetLastError())) return rc;
     }
-    kernel<<<dim3(uint32_t(blocks)), 64 * waves, lds_bytes, st>>>(z, s.n, s.d, s.ld, tb, batches);
-    return hip_rc(hipGetLastError());
+    return 0;
   };
-  const int64_t blocks = (tiles + waves - 1) / waves;
-  return s.bf16 ? launch(&factor_sequence_kernel<bf16_t>, static_cast<bf16_t *>(Z), blocks)
-                : launch(&factor_sequence_kernel<float>, static_cast<float *>(Z), blocks);
+  auto with = [&](auto lanes, auto access) {
+    return s.bf16 ? launch(&factor_sequence_kernel<bf16_t, lanes, access>, static_cast<bf16_t *>(Z))
+                  : launch(&factor_sequence_kernel<float, lanes, access>, static_cast<float *>(Z));
+  };
+  auto with_lanes = [&](auto access) {
+    return lpr == 32   ? with(std::integral_constant<int, 32>{}, access)
+           : lpr == 16 ? with(std::integral_constant<int, 16>{}, access)
+                       : with(std::integral_constant<int, 8>{}, access);
+  };
+  switch (sequence_access(s, Z)) {
+    case kStream: return with_lanes(AccessTag<kStream>{});
+    case kKeepReads: return with_lanes(AccessTag<kKeepReads>{});
+    default: return with_lanes(AccessTag<kKeep>{});
+  }
 }
 
 }  // namespace detag

@@ -46,3 +46,9 @@ def test_the_tile_of_the_lds_resident_kernels_starts_at_offset_zero():
     assert len(tile) >= 100
     assert {k[".group_segment_fixed_size"] for k in tile} == {0}
     assert any(k[".group_segment_fixed_size"] > 0 for name, k in kernels.items() if "softmax" in name)  # the note is read
+
+
+def test_so_does_the_tile_of_the_consensus_sequence():
+    kernels = [k for name, k in _kernels().items() if "factor_sequence" in name]
+    assert len(kernels) >= 6
+    assert {k[".group_segment_fixed_size"] for k in kernels} == {0}
