@@ -40,6 +40,12 @@ inline bool shares_lines(const Shape &s, std::initializer_list<const void *> mat
 // What the matrices of a call that walks column tiles take together.
 inline int64_t footprint(const Shape &s, int per_element) { return int64_t(s.n) * s.ld * per_element; }
 
+// Whether the loads of a kernel that walks rows as they lie stream past the caches (its stores do in any case).  Up to
+// 128 MiB they find their matrices in the memory-side cache, three states in turn as well: phase end of 64 x 100,001
+// (122 MiB, fp32) 38.9 -> 34.2 us, gradient of 16 x 272,474 12.3 -> 11.2, accumulation 11.4 -> 10.4; from 146 MiB on the
+// update of model and tracker is 3 to 8 % slower so, at 200 MiB all of them but the gradient with one curvature per worker.
+inline bool loads_stream(const Shape &s, int per_element) { return footprint(s, per_element) > (int64_t(128) << 20); }
+
 // How the register-resident kernels and those with one launch per round treat the caches.
 // Small calls leave their matrices to the caches.  The memory-side cache holds 256 MB and a program has other matrices too:
 // up to 80 MiB a call's matrices stay, where the next call finds them (gradient-fused step, ring of 16: d = 272,474 (70 MB)

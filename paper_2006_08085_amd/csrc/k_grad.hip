@@ -10,6 +10,7 @@
 
 #include "detag_internal.h"
 #include "dev_common.hpp"
+#include "fused_common.hpp"
 #include "noise_dev.hpp"
 
 namespace detag {
@@ -20,12 +21,17 @@ constexpr int kThreads = 256;
 typedef float vf4_t __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned short vu4_t __attribute__((ext_vector_type(4), aligned(2)));
 
+template <bool NT>
+__device__ __forceinline__ vf4_t load_wide(const vf4_t *p) { return NT ? __builtin_nontemporal_load(p) : *p; }
+template <bool NT>
+__device__ __forceinline__ vu4_t load_wide(const vu4_t *p) { return NT ? __builtin_nontemporal_load(p) : *p; }
+
 // A block works on kGradRows consecutive worker rows of its 1024 columns, so that a shared curvature vector is
 // read once per kGradRows rows instead of once per row (read per row it is a fourth stream: measured 1.33 x the
 // bytes of X, b and G on 64 x 11.2 M).
 constexpr int kGradRows = 4;
 
-template <typename ST>
+template <typename ST, bool NT>
 __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t d, int64_t ld, const ST *__restrict__ X,
                                                                   const float *__restrict__ h, int64_t h_row_stride,
                                                                   const float *__restrict__ b,
@@ -55,23 +61,26 @@ __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t
     const int64_t off = int64_t(i) * ld + c0;
     float x[4], hv[4], bv[4], z[4] = {0.f, 0.f, 0.f, 0.f};
     if (wide) {
-      // X, b, the noise array, per-worker curvature and G are touched once: non-temporal
+      // b, the noise array, per-worker curvature and G are touched once: large calls stream them.  X never: the step that
+      // follows reads it again, and finds what the memory-side cache kept of it (this call and a step with K = 4, 64
+      // workers, 4-regular, fp32, three states in turn: d = 300,000 140 -> 132 us, 1,000,000 428 -> 389, 2,000,000 852 ->
+      // 812; D-PSGD 87 -> 82, 272 -> 241, 550 -> 509; the round of Algorithm 1 that does not, 157 -> 166, 475, 935).
       if constexpr (sizeof(ST) == 4) {
-        const vf4_t t = __builtin_nontemporal_load(reinterpret_cast<const vf4_t *>(X + off));
+        const vf4_t t = load_wide<false>(reinterpret_cast<const vf4_t *>(X + off));
         x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
       } else {
-        const vu4_t t = __builtin_nontemporal_load(reinterpret_cast<const vu4_t *>(X + off));
+        const vu4_t t = load_wide<false>(reinterpret_cast<const vu4_t *>(X + off));
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = __uint_as_float(uint32_t(t[e]) << 16);
       }
-      const vf4_t tb = __builtin_nontemporal_load(reinterpret_cast<const vf4_t *>(b + off));
+      const vf4_t tb = load_wide<NT>(reinterpret_cast<const vf4_t *>(b + off));
       bv[0] = tb.x, bv[1] = tb.y, bv[2] = tb.z, bv[3] = tb.w;
       if (h_row_stride) {
-        const vf4_t th = __builtin_nontemporal_load(reinterpret_cast<const vf4_t *>(h + int64_t(i) * h_row_stride + c0));
+        const vf4_t th = load_wide<NT>(reinterpret_cast<const vf4_t *>(h + int64_t(i) * h_row_stride + c0));
         hv[0] = th.x, hv[1] = th.y, hv[2] = th.z, hv[3] = th.w;
       }
       if (noise) {
-        const vf4_t tz = __builtin_nontemporal_load(reinterpret_cast<const vf4_t *>(noise + off));
+        const vf4_t tz = load_wide<NT>(reinterpret_cast<const vf4_t *>(noise + off));
         z[0] = tz.x, z[1] = tz.y, z[2] = tz.z, z[3] = tz.w;
       }
     } else {
@@ -197,12 +206,12 @@ int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_p
   auto st = static_cast<hipStream_t>(stream);
   const int64_t hstride = h_per_worker ? s.ld : 0;
   const uint32_t slo = uint32_t(seed & 0xffffffffu), shi = uint32_t(seed >> 32);
-#define DETAG_LAUNCH(ST)                                                                                        \
-  grad_quadratic_kernel<ST><<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, static_cast<const ST *>(X), h, hstride, b, noise, \
-                                                       sigma, slo, shi, step, G)
-  if (s.bf16) DETAG_LAUNCH(bf16_t);
-  else DETAG_LAUNCH(float);
-#undef DETAG_LAUNCH
+  auto go = [&](auto *kernel, auto *x) {
+    kernel<<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, x, h, hstride, b, noise, sigma, slo, shi, step, G);
+  };
+  const bool nt = fused::loads_stream(s, (s.bf16 ? 2 : 4) + 8 + (h_per_worker ? 4 : 0) + (noise ? 4 : 0));
+  if (s.bf16) go(nt ? &grad_quadratic_kernel<bf16_t, true> : &grad_quadratic_kernel<bf16_t, false>, static_cast<const bf16_t *>(X));
+  else go(nt ? &grad_quadratic_kernel<float, true> : &grad_quadratic_kernel<float, false>, static_cast<const float *>(X));
   return hip_rc(hipGetLastError());
 }
 

@@ -81,7 +81,7 @@ __device__ __forceinline__ void store_vec(ST *p, int valid, const float (&v)[VEC
 // the worker mean does not drift over many rounds; and the increment is formed at its own (small) magnitude,
 // so the only rounding at the magnitude of the state is the last add.
 // With HAS_G: out[i,:] = cur[i,:] + sum_k ... - alpha * G[i,:] (D-PSGD) and prev is not read.
-template <typename ST, bool HAS_G>
+template <typename ST, bool HAS_G, bool NT>
 __global__ __launch_bounds__(kThreads) void gossip_round_kernel(int n, int64_t d, int64_t ld,
                                                                 const int32_t *__restrict__ rowptr,
                                                                 const int32_t *__restrict__ colidx,
@@ -112,12 +112,12 @@ __global__ __launch_bounds__(kThreads) void gossip_round_kernel(int n, int64_t d
     float o[VEC];
     if constexpr (HAS_G) {
       float g[VEC];
-      load_vec<float>(G + int64_t(i) * ld + c0, valid, g);
+      load_vec<float, NT>(G + int64_t(i) * ld + c0, valid, g);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) o[e] = own[e] + fmaf(-alpha, g[e], c_mix * acc[e]);
     } else {
       float p[VEC];
-      load_vec<ST>(prev + int64_t(i) * ld + c0, valid, p);
+      load_vec<ST, NT>(prev + int64_t(i) * ld + c0, valid, p);
 #pragma unroll
       for (int e = 0; e < VEC; ++e) o[e] = own[e] + fmaf(c_mix, acc[e], eta * (own[e] - p[e]));
     }
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void gossip_round_tile_kernel(int 
 }
 
 // mode 0: Y += Gn - Go.   mode 1: X -= alpha*Y (Y before the update); Y += Gn - Go.
-template <typename ST, int MODE>
+template <typename ST, int MODE, bool NT>
 __global__ __launch_bounds__(kThreads) void elementwise_kernel(int64_t d, int64_t ld, ST *X, ST *Y,
                                                                const float *__restrict__ Gn,
                                                                const float *__restrict__ Go, float alpha) {
@@ -204,12 +204,12 @@ __global__ __launch_bounds__(kThreads) void elementwise_kernel(int64_t d, int64_
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float y[VEC], gn[VEC], go[VEC];
-  load_vec<ST>(Y + off, valid, y);
-  load_vec<float>(Gn + off, valid, gn);
-  load_vec<float>(Go + off, valid, go);
+  load_vec<ST, NT>(Y + off, valid, y);
+  load_vec<float, NT>(Gn + off, valid, gn);
+  load_vec<float, NT>(Go + off, valid, go);
   if constexpr (MODE == 1) {
     float x[VEC];
-    load_vec<ST>(X + off, valid, x);
+    load_vec<ST, NT>(X + off, valid, x);
 #pragma unroll
     for (int e = 0; e < VEC; ++e) x[e] = fmaf(-alpha, y[e], x[e]);
     store_vec<ST>(X + off, valid, x);
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(kThreads) void spmm_kernel(int n, int64_t d, int64_
 }
 
 // End of a round of Algorithm 1: X = Xt - scale*G; Xt = X; G = 0.
-template <typename ST>
+template <typename ST, bool NT>
 __global__ __launch_bounds__(kThreads) void defacto_update_kernel(int64_t d, int64_t ld, ST *X, ST *Xt, float *G,
                                                                   float scale) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -256,8 +256,8 @@ __global__ __launch_bounds__(kThreads) void defacto_update_kernel(int64_t d, int
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float x[VEC], g[VEC];
-  load_vec<ST>(Xt + off, valid, x);
-  load_vec<float>(G + off, valid, g);
+  load_vec<ST, NT>(Xt + off, valid, x);
+  load_vec<float, NT>(G + off, valid, g);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
     x[e] = fmaf(-scale, g[e], x[e]);
@@ -269,6 +269,7 @@ __global__ __launch_bounds__(kThreads) void defacto_update_kernel(int64_t d, int
 }
 
 // Gacc += scale * g
+template <bool NT>
 __global__ __launch_bounds__(kThreads) void accumulate_kernel(int64_t d, int64_t ld, float *Gacc,
                                                               const float *__restrict__ g, float scale) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -276,15 +277,15 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(int64_t d, int64_t
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float a[VEC], x[VEC];
-  load_vec<float>(Gacc + off, valid, a);
-  load_vec<float>(g + off, valid, x);
+  load_vec<float, NT>(Gacc + off, valid, a);
+  load_vec<float, NT>(g + off, valid, x);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) a[e] = fmaf(scale, x[e], a[e]);
   store_vec<float>(Gacc + off, valid, a);
 }
 
 // End of a phase of Algorithm 2: X = Xt - alpha*Y; Y += Gk - Gkm1; Xt = X; Gkm1 = 0.
-template <typename ST>
+template <typename ST, bool NT>
 __global__ __launch_bounds__(kThreads) void phase_end_kernel(int64_t d, int64_t ld, ST *X, ST *Xt, ST *Y,
                                                              const float *__restrict__ Gk, float *Gkm1, float alpha) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -292,10 +293,10 @@ __global__ __launch_bounds__(kThreads) void phase_end_kernel(int64_t d, int64_t 
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float x[VEC], y[VEC], gk[VEC], gm[VEC];
-  load_vec<ST>(Xt + off, valid, x);
-  load_vec<ST>(Y + off, valid, y);
-  load_vec<float>(Gk + off, valid, gk);
-  load_vec<float>(Gkm1 + off, valid, gm);
+  load_vec<ST, NT>(Xt + off, valid, x);
+  load_vec<ST, NT>(Y + off, valid, y);
+  load_vec<float, NT>(Gk + off, valid, gk);
+  load_vec<float, NT>(Gkm1 + off, valid, gm);
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
     x[e] = fmaf(-alpha, y[e], x[e]);
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(kThreads) void phase_end_kernel(int64_t d, int64_t 
 }
 
 // dst = src with a change of storage type (bf16 -> fp32 exact, fp32 -> bf16 round to nearest even)
-template <typename TS, typename TD>
+template <typename TS, typename TD, bool NT>
 __global__ __launch_bounds__(kThreads) void convert_kernel(int64_t d, int64_t ld, const TS *__restrict__ src,
                                                            TD *__restrict__ dst) {
   const int64_t c0 = (int64_t(blockIdx.x) * kThreads + threadIdx.x) * VEC;
@@ -317,8 +318,16 @@ __global__ __launch_bounds__(kThreads) void convert_kernel(int64_t d, int64_t ld
   const int valid = int(d - c0 < VEC ? d - c0 : VEC);
   const int64_t off = int64_t(blockIdx.y) * ld + c0;
   float x[VEC];
-  load_vec<TS>(src + off, valid, x);
+  load_vec<TS, NT>(src + off, valid, x);
   store_vec<TD>(dst + off, valid, x);
+}
+
+// Launches with launch(nt): whether the call's loads stream.
+template <class F>
+int with_loads(const Shape &s, int per_element, F &&launch) {
+  if (fused::loads_stream(s, per_element)) launch(std::true_type{});
+  else launch(std::false_type{});
+  return hip_rc(hipGetLastError());
 }
 
 int rows_per_group_for(const Shape &s, int col_blocks) {
@@ -355,10 +364,11 @@ int launch_round_t(const Shape &s, const DevCsr &w, const void *cur, const void 
   const int col_blocks = ceil_div_i64(s.d, per_block);
   const int rpg = rows_per_group_for(s, col_blocks);
   dim3 grid(col_blocks, (s.n + rpg - 1) / rpg);
-  gossip_round_kernel<ST, HAS_G><<<grid, kThreads, 0, st>>>(
+  return with_loads(s, int(sizeof(ST)) * (HAS_G ? 2 : 3) + (HAS_G ? 4 : 0), [&](auto nt) {
+    gossip_round_kernel<ST, HAS_G, nt><<<grid, kThreads, 0, st>>>(
         s.n, s.d, s.ld, w.rowptr, w.colidx, w.vals, static_cast<const ST *>(cur), static_cast<const ST *>(prev),
         static_cast<ST *>(out), G, c_mix, eta, alpha, rpg);
-  return hip_rc(hipGetLastError());
+  });
 }
 
 template <typename ST, int MODE>
@@ -367,18 +377,18 @@ int launch_elementwise_t(const Shape &s, void *X, void *Y, const float *Gn, cons
   const int per_block = kThreads * VEC;
   dim3 grid(ceil_div_i64(s.d, per_block), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  elementwise_kernel<ST, MODE><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X),
-                                                                static_cast<ST *>(Y), Gn, Go, alpha);
-  return hip_rc(hipGetLastError());
+  return with_loads(s, int(sizeof(ST)) * (MODE + 1) + 8, [&](auto nt) {
+    elementwise_kernel<ST, MODE, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go, alpha);
+  });
 }
 
 template <typename TS, typename TD>
 int launch_convert_t(const Shape &s, const void *src, void *dst, void *stream) {
   dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  convert_kernel<TS, TD><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<const TS *>(src),
-                                                         static_cast<TD *>(dst));
-  return hip_rc(hipGetLastError());
+  return with_loads(s, int(sizeof(TS) + sizeof(TD)), [&](auto nt) {
+    convert_kernel<TS, TD, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<const TS *>(src), static_cast<TD *>(dst));
+  });
 }
 
 }  // namespace
@@ -402,9 +412,9 @@ template <typename ST>
 int launch_defacto_update_t(const Shape &s, void *X, void *Xt, float *G, float scale, void *stream) {
   dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  defacto_update_kernel<ST><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt), G,
-                                                            scale);
-  return hip_rc(hipGetLastError());
+  return with_loads(s, 2 * int(sizeof(ST)) + 4, [&](auto nt) {
+    defacto_update_kernel<ST, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt), G, scale);
+  });
 }
 
 int launch_defacto_update(const Shape &s, void *X, void *Xt, float *G, float scale, void *stream) {
@@ -415,8 +425,7 @@ int launch_defacto_update(const Shape &s, void *X, void *Xt, float *G, float sca
 int launch_accumulate(const Shape &s, float *Gacc, const float *g, float scale, void *stream) {
   dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  accumulate_kernel<<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale);
-  return hip_rc(hipGetLastError());
+  return with_loads(s, 8, [&](auto nt) { accumulate_kernel<nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale); });
 }
 
 template <typename ST>
@@ -424,9 +433,10 @@ int launch_phase_end_t(const Shape &s, void *X, void *Xt, void *Y, const float *
                        void *stream) {
   dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  phase_end_kernel<ST><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt),
-                                                       static_cast<ST *>(Y), Gk, Gkm1, alpha);
-  return hip_rc(hipGetLastError());
+  return with_loads(s, 3 * int(sizeof(ST)) + 8, [&](auto nt) {
+    phase_end_kernel<ST, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Xt),
+                                                        static_cast<ST *>(Y), Gk, Gkm1, alpha);
+  });
 }
 
 int launch_phase_end(const Shape &s, void *X, void *Xt, void *Y, const float *Gk, float *Gkm1, float alpha,

@@ -71,3 +71,41 @@ def test_the_layout_does_not_change_the_bits(kind, n, dtype):
         for ld, shift in ((d + 1 - d % 2, 0), (D.padded_ld(d), 1)):
             for k, (got, want) in enumerate(zip(_all_calls(topo, n, d, ld, shift, dtype, values), on_lines)):
                 assert torch.equal(got, want), (d, ld, shift, k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_row_walking_kernels_on_both_sides_of_128_mib(dtype):
+    """Their loads stream from 128 MiB a call on: the same columns, alone and as part of a call beyond that."""
+    n, few, many = 16, 1003, 1_200_003
+    g = torch.Generator(device=DEV)
+    g.manual_seed(2)
+    values = [torch.empty(n, many, device=DEV).normal_(generator=g) for _ in range(5)]
+
+    def calls(d):
+        ld = d + 1
+        ctx = D.detag_create(D.Topology.ring(), n, d, ld, D.DETAG_BF16 if dtype == torch.bfloat16 else D.DETAG_F32)
+        new = lambda k: _place(values[k][:, :d], ld, 0, dtype if k < 2 else torch.float32)  # noqa: E731
+        out = [new(4)]
+        ctx.grad_quadratic_diag(new(0), values[3][0].abs().contiguous(), new(2), out[0], sigma=0.1, seed=3, step=1)
+        x, y = new(0), new(1)
+        ctx.step(x, y, new(2), new(3), 0.2, 0)
+        out += [x, y]
+        y = new(1)
+        ctx.track(y, new(2), new(3))
+        a = new(2)
+        ctx.accumulate(a, new(3), 0.3)
+        out += [y, a]
+        x, xt, y, old = new(0), new(0), new(1), new(3)
+        ctx.phase_end(x, xt, y, new(2), old, 0.2)
+        out += [x, xt, y, old]
+        x, xt, a = new(0), new(1), new(2)
+        ctx.defacto_update(x, xt, a, 0.2)
+        out += [x, xt, a]
+        torch.cuda.synchronize()
+        ctx.close()
+        for t in out:
+            assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))
+        return [t[:, :few] for t in out]
+
+    for k, (got, want) in enumerate(zip(calls(many), calls(few))):
+        assert torch.equal(got, want), k
