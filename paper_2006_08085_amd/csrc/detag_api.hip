@@ -154,12 +154,15 @@ bool lds_family_serves(const HostW &W) {
 
 hipError_t upload_lds_table(detag_ctx *ctx, const LdsTableHost &t) {
   // 16-byte pairs first, then whatever needs 4-byte alignment
-  const size_t words[4] = {t.pairs.size(), t.byte_table.size(), t.rows.size(), t.groups.size()};
-  const void *src[4] = {t.pairs.data(), t.byte_table.data(), t.rows.data(), t.groups.data()};
-  const uint32_t *at[4];
-  hipError_t e = hipMalloc(&ctx->d_lds, (words[0] + words[1] + words[2] + words[3]) * 4);
+  constexpr int kArrays = 5;
+  const size_t words[kArrays] = {t.pairs.size(), t.byte_table.size(), t.rows.size(), t.groups.size(), t.offsets.size()};
+  const void *src[kArrays] = {t.pairs.data(), t.byte_table.data(), t.rows.data(), t.groups.data(), t.offsets.data()};
+  const uint32_t *at[kArrays];
+  size_t total = 0;
+  for (size_t w : words) total += w;
+  hipError_t e = hipMalloc(&ctx->d_lds, total * 4);
   uint32_t *next = static_cast<uint32_t *>(ctx->d_lds);
-  for (int k = 0; k < 4 && e == hipSuccess; ++k) {
+  for (int k = 0; k < kArrays && e == hipSuccess; ++k) {
     at[k] = words[k] ? next : nullptr;
     if (words[k]) e = hipMemcpy(next, src[k], words[k] * 4, hipMemcpyHostToDevice);
     next += words[k];
@@ -168,6 +171,7 @@ hipError_t upload_lds_table(detag_ctx *ctx, const LdsTableHost &t) {
   ctx->lds.bytes_deg = t.bytes_deg, ctx->lds.weight = t.weight, ctx->lds.byte_table = at[1];
   ctx->lds.pairs = at[0], ctx->lds.rows = reinterpret_cast<const int32_t *>(at[2]), ctx->lds.groups = at[3];
   ctx->lds.pair_count = int(t.pairs.size() / 4), ctx->lds.max_pairs = t.max_pairs;
+  ctx->lds.half_deg = t.half_deg, ctx->lds.offsets = at[4];
   return hipSuccess;
 }
 

@@ -57,7 +57,7 @@ struct DevCsr {
   const float *vals = nullptr;      // nnz, fp32 copies of W_ji
 };
 
-// Neighbour table of the LDS-resident kernels for arbitrary W, in one of two forms (fused_generic_common.hpp).
+// Neighbour table of the LDS-resident kernels for arbitrary W, in one of three forms (fused_generic_common.hpp).
 struct LdsTableHost {
   // one byte per neighbour, 256 rows of bytes_deg (2, 4 or 8) entries padded with the row itself; 0: the lists below
   int bytes_deg = 0;
@@ -67,6 +67,9 @@ struct LdsTableHost {
   std::vector<int32_t> rows;
   std::vector<uint32_t> groups, pairs;
   int max_pairs = 0;  // longest list, in pairs
+  // or, in place of groups and pairs, half_deg (2, 4 or 8) 16-bit LDS row offsets per position and `weight`
+  int half_deg = 0;
+  std::vector<uint32_t> offsets;
 };
 // The device copy.
 struct LdsTable {
@@ -77,6 +80,8 @@ struct LdsTable {
   const uint32_t *groups = nullptr, *pairs = nullptr;
   int pair_count = 0;  // 16-byte words in `pairs`
   int max_pairs = 0;
+  int half_deg = 0;
+  const uint32_t *offsets = nullptr;
 };
 // false if a tile of n rows and the lists do not fit the LDS of a compute unit.
 bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out);

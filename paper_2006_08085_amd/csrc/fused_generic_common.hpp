@@ -22,6 +22,7 @@
 //   ByteRounds<DEG, S>  n <= 256, at most 8 neighbours, one weight for the whole matrix (any regular graph with uniform
 //                    or Metropolis weights): a neighbour is one byte, the high byte of its row's LDS offset, so the table
 //                    of a row is DEG/4 registers and an address is one byte permute.
+//   HalfRounds<DEG>  the same with more than 256 workers and S = 4: two bytes per neighbour.
 //   ListRounds<S>    any weights, at most 8 neighbours, S < 4: the row's (offset, weight) pairs in registers.
 //   CsrRounds<S>     any weights and degrees, n <= 1024: the rows' lists sit in LDS next to the tile as pairs of (offset,
 //                    weight), two per 16-byte read, which all lanes of a row read together.  The host orders the
@@ -238,6 +239,65 @@ struct ByteRounds {
 #pragma unroll
         for (int q = 0; q < kWords; ++q) asm volatile("" : "+v"(w[s][q]));
     }
+  }
+};
+
+// One weight, at most 8 neighbours, more than 256 workers: as ByteRounds with two bytes to a neighbour, the LDS offset of
+// its row, 16 bits of which name any row of a tile.  An address costs the same one instruction, the table DEG/2 registers a
+// row; against the lists in LDS a round saves a read in three and half of the instructions (300 workers, 4-regular, d =
+// 100,000, K = 8: phase 314 -> 257 us; 600 workers, d = 50,000, K = 4 304 -> 240; ring of 1000, d = 60,000, bf16 state,
+// K = 4, Algorithm 2's phase 541 -> 297).
+struct HalfArgs {
+  const int32_t *rows;      // row number of each position (-1: none)
+  const uint32_t *offsets;  // DEG / 2 words per position
+  float weight;
+};
+template <int DEG>
+struct HalfRounds {
+  static constexpr int kSlots = kSlotsMax, kParked = 1, kWaves = DEG <= 4 ? 6 : 5, kWords = DEG / 2;
+  using Args = HalfArgs;
+  uint32_t w[kSlots][kWords];
+  float b;
+
+  __device__ __forceinline__ void fetch(const Args &, const Place &) {}
+  __device__ __forceinline__ void init(const Args &a, const Place &p, float eta) {
+    const uint32_t col_bytes = p.col() * 4u;
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s)
+#pragma unroll
+      for (int q = 0; q < kWords; ++q) w[s][q] = a.offsets[p.pos(s) * kWords + q] + col_bytes * 0x00010001u;
+    b = (1.f + eta) * a.weight;
+  }
+  __device__ __forceinline__ int row(const Args &a, const Place &p, int s) const { return a.rows[p.pos(s)]; }
+
+  __device__ __forceinline__ f4 neighbour(int s, int k) const { return lds_read(k & 1 ? w[s][k / 2] >> 16 : w[s][k / 2] & 0xffffu); }
+  // Difference by difference, pairwise.  The sum of the neighbours, rounded at DEG times the magnitude of z, would take
+  // three instructions less of nine and leave a quarter more error against 64 bits than the lists in LDS (300 workers,
+  // 4-regular, K = 8: 5.8e-8 against 4.6e-8; so 4.6e-8).
+  template <uint32_t IN>
+  __device__ __forceinline__ f4 diff_sum(int s, f4 z) const {
+    static_assert(IN == 0, "one tile");
+    f4 d[DEG];
+#pragma unroll
+    for (int k = 0; k < DEG; ++k) d[k] = neighbour(s, k) - z;
+#pragma unroll
+    for (int o = DEG / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < o; ++k) d[k] += d[k + o];
+    return d[0];
+  }
+  __device__ __forceinline__ float scale() const { return b; }
+  __device__ __forceinline__ f4 plain(int s, f4 z) const {  // as in ByteRounds
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < DEG; ++k) acc = fma4(b, neighbour(s, k) - z, acc);
+    return acc;
+  }
+  __device__ __forceinline__ void keep_packed() {
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s)
+#pragma unroll
+      for (int q = 0; q < kWords; ++q) asm volatile("" : "+v"(w[s][q]));
   }
 };
 
@@ -587,8 +647,19 @@ int with_rounds(const Shape &s, const LdsTable &t, F &&f) {
            : g.slots == 2 ? with_degree(std::integral_constant<int, 2>{})
                           : with_degree(std::integral_constant<int, 4>{});
   }
-  if (!t.pairs) return -1;
+  if (!t.pairs && !t.half_deg) return -1;
   const Geometry g = csr_geometry(s.n, s.d);
+  if (t.half_deg) {
+    auto go = [&](auto r) {
+      using R = typename decltype(r)::type;
+      return f(r, g, g.tile_bytes(R::kParked), HalfArgs{t.rows, t.offsets, t.weight});
+    };
+    switch (t.half_deg) {
+      case 2: return go(RoundsTag<HalfRounds<2>>{});
+      case 4: return go(RoundsTag<HalfRounds<4>>{});
+      default: return go(RoundsTag<HalfRounds<8>>{});
+    }
+  }
   auto go = [&](auto r) {
     using R = typename decltype(r)::type;
     const size_t tile = g.tile_bytes(R::kParked), lists = t.max_pairs <= kListPairs && R::kSlots < kSlotsMax ? 0 : t.pair_count;

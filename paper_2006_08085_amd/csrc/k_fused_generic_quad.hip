@@ -75,6 +75,9 @@ int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, v
   if (K < 1) return -1;
   return with_rounds(s, t, [&](auto r, const Geometry &g, size_t lds, const auto &ra) {
     using R = typename decltype(r)::type;
+    if constexpr (std::is_same_v<typename R::Args, HalfArgs>) {
+      return -1;  // more than 256 workers: no fused step
+    } else {
     auto go = [&](auto *kernel, auto *x, auto *y) -> int {
       if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
       kernel<<<dim3(ceil_div_i64(s.d, g.cols)), g.threads, lds, static_cast<hipStream_t>(stream)>>>(
@@ -96,6 +99,7 @@ int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, v
     // blocks of 1024 threads, two to a compute unit, are better off streaming: 256 x 30,001 53.3, 62.8, 72.2 us
     const Call call = g.threads <= 512 ? kReadsLate : kAtc;
     return with_access<R>(s, g, call, per_element, {X, Y, G, h_per_worker ? h : nullptr, b}, with);
+    }
   });
 }
 

@@ -289,3 +289,39 @@ def test_route_of_contexts_that_report_one_launch_per_round(n, kind, d, op, K, o
     torch.cuda.synchronize()
     assert torch.equal(Xr, X) and torch.equal(Yr, Y)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,degree", [(257, 2), (257, 4), (300, 8), (512, 5), (513, 3), (1024, 4)])
+@pytest.mark.parametrize("dtype,K", [("f32", 3), ("bf16", 2)])
+def test_one_weight_beyond_256_workers(n, degree, dtype, K):
+    """Lists of 16-bit offsets in registers, full and padded: every call against the oracle, and the same bits as one launch
+    per round from the D-PSGD step (not from 513 workers on, which has no on-chip form)."""
+    d = (1 << 19) // n * 4 + 5
+    ld = d + 3
+    bf = dtype == "bf16"
+    sd, tol = (torch.bfloat16, TOL_BF16) if bf else (torch.float32, TOL_F32)
+    w = 0.7 / degree
+    W = 0.3 * np.eye(n) + sum(w * np.roll(np.eye(n), s, axis=1) for s in (1, n - 1, 7, 200, 97, 31, n - 60, 128)[:degree])
+    ctx = D.detag_create(D.Topology.from_dense(W), n, d, ld, D.DETAG_BF16 if bf else D.DETAG_F32)
+    eta, alpha = 0.35, 0.2
+    cols = np.unique(np.concatenate([np.arange(40), np.arange(d - 70, d)]))
+    X, Y, Gn, Go = (_matrix(n, d, ld, k, sd if k < 2 else torch.float32) for k in range(4))
+    x, y, gn, go = (_cols(t, cols) for t in (X, Y, Gn, Go))
+    S = amax(x, y, gn, go)
+    Z, Xp = X.clone(), X.clone()
+    ctx.gossip_accel(Z, K, eta)
+    assert rel_err(_cols(Z, cols), OG.accelerated_gossip(x, W, K, eta), S) < tol
+    ctx.dpsgd_step(Xp, Gn, alpha)
+    assert rel_err(_cols(Xp, cols), OG.dpsgd_step(x, gn, W, alpha), S) < tol
+    for variant, code in (("atc", D.DETAG_VARIANT_ATC), ("alg2", D.DETAG_VARIANT_ALG2)):
+        Xs, Ys = X.clone(), Y.clone()
+        ctx.step(Xs, Ys, Gn, Go, alpha, K, eta, code)
+        xr, yr = OG.detag_step(x, y, gn, go, W, alpha, K, eta, variant)
+        assert rel_err(_cols(Xs, cols), xr, S) < tol and rel_err(_cols(Ys, cols), yr, S) < tol, variant
+        for t in (Z, Xp, Xs, Ys):
+            assert torch.equal(t[:, d:], torch.full_like(t[:, d:], SENTINEL))
+    ctx.set_path(D.DETAG_PATH_PER_ROUND)
+    Xr = X.clone()
+    ctx.dpsgd_step(Xr, Gn, alpha)
+    assert torch.equal(Xp, Xr)
+    ctx.close()
