@@ -40,6 +40,7 @@ constexpr int kCols = 64, kThreads = 256, kWaves = 4;
 constexpr int kRowsMax = 256, kMTiles = kRowsMax / 32, kKSteps = kRowsMax / 16;
 constexpr int kUnitSteps = 8;    // k-steps (of 16 rows) staged in LDS at a time
 constexpr int kOutPitch = 72;    // floats per row of a wavefront's 16 x 64 output scratch: rows 4 apart are 32 banks apart
+constexpr int64_t kKeepBytes = int64_t(128) << 20;
 constexpr int kOutBytes = kWaves * 16 * kOutPitch * 4;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -107,7 +108,7 @@ struct Geo {
 // One unit (rows 16 KU u ...) of the block's 64 columns -> the elementwise part -> TU bf16 terms in LDS, laid out
 // [term][column][row].  Lane = column; wavefront w takes the groups of 8 rows w, w+4, ...; rows >= n are staged as
 // zeros (their resource has no valid bytes).
-template <typename ST, int TU, int PRE, int KS>
+template <typename ST, int TU, int PRE, int KS, Access A>
 __device__ __forceinline__ void stage_unit(uint16_t *stage, int u, int w, int lane, const ST *X, const ST *Y,
                                            const float *Gn, const float *Go, int n, int64_t tile, int64_t ld,
                                            uint32_t valid, float alpha) {
@@ -128,16 +129,16 @@ __device__ __forceinline__ void stage_unit(uint16_t *stage, int u, int w, int la
         const uint32_t ok = row0 + e < n ? valid : 0u;
         const int rr = row0 + e < n ? row0 + e : 0;
         if constexpr (PRE == kPreX) {
-          v[c][e] = buf_load<ST>(row_of(X, tile, ld, rr, ok), so);
+          v[c][e] = buf_load<ST, A>(row_of(X, tile, ld, rr, ok), so);
         } else if constexpr (PRE == kPreY) {
-          v[c][e] = buf_load<ST>(row_of(Y, tile, ld, rr, ok), so);
+          v[c][e] = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
         } else if constexpr (PRE == kPreXminusAlphaY) {
-          const float x = buf_load<ST>(row_of(X, tile, ld, rr, ok), so), y = buf_load<ST>(row_of(Y, tile, ld, rr, ok), so);
+          const float x = buf_load<ST, A>(row_of(X, tile, ld, rr, ok), so), y = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
           v[c][e] = fmaf(-alpha, y, x);
         } else {
-          const float y = buf_load<ST>(row_of(Y, tile, ld, rr, ok), so);
-          const float gn = buf_load<float>(row_of(Gn, tile, ld, rr, ok), fo);
-          const float go = buf_load<float>(row_of(Go, tile, ld, rr, ok), fo);
+          const float y = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
+          const float gn = buf_load<float, A>(row_of(Gn, tile, ld, rr, ok), fo);
+          const float go = buf_load<float, A>(row_of(Go, tile, ld, rr, ok), fo);
           v[c][e] = y + gn - go;
         }
       }
@@ -222,7 +223,7 @@ __device__ __forceinline__ void clear(f32x16 (&acc)[2][2]) {
 
 // acc = P * (the pass's input), unit by unit.  `fresh` = nothing has used LDS yet.  Ends with a barrier: every
 // wavefront is done with the staged input.
-template <typename ST, int TP, int TU, int PRE, int KS>
+template <typename ST, int TP, int TU, int PRE, int KS, Access A>
 __device__ __forceinline__ void pass(f32x16 (&acc)[2][2], uint16_t *stage, bool fresh, bool rows_mine, int w, int lane,
                                      const ST *X, const ST *Y, const float *Gn, const float *Go, int n, int64_t tile,
                                      int64_t ld, uint32_t valid, float alpha, const u16x8 *__restrict__ frag) {
@@ -231,7 +232,7 @@ __device__ __forceinline__ void pass(f32x16 (&acc)[2][2], uint16_t *stage, bool 
 #pragma unroll
   for (int u = 0; u < G::kUnits; ++u) {
     if (u > 0 || !fresh) __syncthreads();  // every wavefront is done with what LDS held
-    stage_unit<ST, TU, PRE, KS>(stage, u, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha);
+    stage_unit<ST, TU, PRE, KS, A>(stage, u, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha);
     __builtin_amdgcn_sched_barrier(0);  // the rows of P are requested after the staging loads, not among them
     AFrag<TP> ring[kDepth];
     if (rows_mine) {
@@ -272,14 +273,14 @@ __device__ __forceinline__ void write_out(const f32x16 (&acc)[2][2], float *scra
 // mode 0: X <- P X.  mode 1 (ATC): X <- P (X - alpha*Y), Y <- P (Y + Gn - Go).
 // mode 2 (ALG2): X <- P X - alpha * P Y = P (X - alpha*Y) (P is linear), Y <- P Y + Gn - Go.  n <= 16 KS.
 // A pass writes its result once every wavefront has staged all the pass reads of the array it overwrites.
-template <typename ST, int TP, int TU, int MODE, int KS, bool BY_XCD>
+template <typename ST, int TP, int TU, int MODE, int KS, Access A>
 __global__ __launch_bounds__(kThreads, TP >= 3 ? 2 : 3) void dense_phase_kernel(ST *X, ST *Y, const float *__restrict__ Gn,
                                                                   const float *__restrict__ Go, int n, int64_t d,
                                                                   int64_t ld, const u16x8 *__restrict__ frag,
                                                                   float alpha) {
   extern __shared__ uint16_t stage[];  // TU terms of one unit of the 64-column tile; afterwards the output scratch
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int64_t tile = (BY_XCD ? fused::xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x)) * kCols;
+  const int64_t tile = (A == kKeep ? fused::xcd_tile(blockIdx.x, gridDim.x) : int64_t(blockIdx.x)) * kCols;
   const uint32_t valid = uint32_t(d - tile < kCols ? d - tile : kCols);
   const bool rows_mine = 64 * w < n;  // wavefront-uniform: this wavefront has output rows
   const uint32_t so = lane * uint32_t(sizeof(ST)), fo = lane * 4u;
@@ -287,25 +288,25 @@ __global__ __launch_bounds__(kThreads, TP >= 3 ? 2 : 3) void dense_phase_kernel(
   f32x16 acc[2][2];
   auto store_rows = [&](ST *out) {
     if (rows_mine)
-      write_out(acc, scratch, w, lane, n, [&](int row, float v) { buf_store<ST>(row_of(out, tile, ld, row, valid), so, v); });
+      write_out(acc, scratch, w, lane, n, [&](int row, float v) { buf_store<ST, A>(row_of(out, tile, ld, row, valid), so, v); });
   };
   if constexpr (MODE == 0) {
-    pass<ST, TP, TU, kPreX, KS>(acc, stage, true, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
+    pass<ST, TP, TU, kPreX, KS, A>(acc, stage, true, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
     store_rows(X);
   } else {
-    pass<ST, TP, TU, kPreXminusAlphaY, KS>(acc, stage, true, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha,
+    pass<ST, TP, TU, kPreXminusAlphaY, KS, A>(acc, stage, true, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha,
                                            frag);
     store_rows(X);
     if constexpr (MODE == 1) {
-      pass<ST, TP, TU, kPreTrack, KS>(acc, stage, false, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
+      pass<ST, TP, TU, kPreTrack, KS, A>(acc, stage, false, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
       store_rows(Y);
     } else {
-      pass<ST, TP, TU, kPreY, KS>(acc, stage, false, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
+      pass<ST, TP, TU, kPreY, KS, A>(acc, stage, false, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
       if (rows_mine)
         write_out(acc, scratch, w, lane, n, [&](int row, float v) {
-          const float gn = buf_load<float>(row_of(Gn, tile, ld, row, valid), fo);
-          const float go = buf_load<float>(row_of(Go, tile, ld, row, valid), fo);
-          buf_store<ST>(row_of(Y, tile, ld, row, valid), so, v + gn - go);
+          const float gn = buf_load<float, A>(row_of(Gn, tile, ld, row, valid), fo);
+          const float go = buf_load<float, A>(row_of(Go, tile, ld, row, valid), fo);
+          buf_store<ST, A>(row_of(Y, tile, ld, row, valid), so, v + gn - go);
         });
     }
   }
@@ -336,18 +337,23 @@ int launch_ks(const Shape &s, int mode, void *X, void *Y, const float *Gn, const
                                         reinterpret_cast<const u16x8 *>(frag), alpha);
     return hip_rc(hipGetLastError());
   };
-  auto with_mode = [&](auto by_xcd) -> int {
+  auto with_mode = [&](auto access) -> int {
     switch (mode) {
-      case 0: return go(&dense_phase_kernel<ST, TP, TU, 0, KS, by_xcd>);
-      case 1: return go(&dense_phase_kernel<ST, TP, TU, 1, KS, by_xcd>);
-      default: return go(&dense_phase_kernel<ST, TP, TU, 2, KS, by_xcd>);
+      case 0: return go(&dense_phase_kernel<ST, TP, TU, 0, KS, access>);
+      case 1: return go(&dense_phase_kernel<ST, TP, TU, 1, KS, access>);
+      default: return go(&dense_phase_kernel<ST, TP, TU, 2, KS, access>);
     }
   };
-  // Where rows do not start on a cache line, neighbouring tiles share lines and go to one XCD (64 x 1,000,003 fp32: 616 ->
-  // 470 us).  Where they do, tiles keep their order, in which 256 workers with bf16 state measured 1 % faster.  A kernel
-  // for each: the choice made at run time cost the aligned one 0.6 to 5 %.
-  const bool shares_lines = ((uint64_t(s.ld) * sizeof(ST)) | reinterpret_cast<uint64_t>(X)) % 128 != 0;
-  return shares_lines ? with_mode(std::true_type{}) : with_mode(std::false_type{});
+  // Where rows do not start on a cache line, neighbouring tiles share lines: they go to one XCD (64 x 1,000,003 fp32: 616 ->
+  // 470 us) and leave their accesses to the caches (pitch 1,000,001, K = 4 505 -> 414 us; 256 x 200,001 of bf16 397 -> 355).
+  // Where they do, tiles keep their order, in which 256 workers with bf16 state measured 1 % faster, and stream, but not calls
+  // that the memory-side cache holds: they read a matrix twice (Algorithm 2's phase of 64 x 50,001 52.5 -> 39.8 us, 64 x
+  // 100,001 of bf16 63.5 -> 50.9; the ATC phase of 256 x 10,001 50.6 -> 45.4, of bf16 40.7 -> 45.7, which streams).  A
+  // kernel for each: the choice made at run time cost the aligned one 0.6 to 5 %.
+  const int state = sizeof(ST), per_element = mode == 0 ? state : 2 * state + 8;
+  const bool small = fused::footprint(s, per_element) <= kKeepBytes && (!s.bf16 || mode == 2);
+  const bool keep = fused::shares_lines(s, {X, Y, Gn, Go}) || small;
+  return keep ? with_mode(AccessTag<kKeep>{}) : with_mode(AccessTag<kStream>{});
 }
 
 // The kernel is compiled for 2, 4, 8 and 16 k-steps of 16 workers: the smallest that covers n.

@@ -47,6 +47,11 @@ def _all_calls(topo, n, d, ld, shift, dtype, values):
     ctx.dpsgd_step(p, new(2), 0.2)
     ctx.gossip_round(new(0), new(1), r, eta)
     out += [z, p, r]
+    ctx.set_path(D.DETAG_PATH_DENSE)
+    for variant in (D.DETAG_VARIANT_ATC, D.DETAG_VARIANT_ALG2):
+        x, y = new(0), new(1)
+        ctx.step(x, y, new(2), new(3), 0.2, K, eta, variant)
+        out += [x, y]
     ctx.set_path(D.DETAG_PATH_PER_ROUND)
     p = new(0)
     ctx.dpsgd_step(p, new(2), 0.2)
