@@ -97,20 +97,22 @@ class ByPhase:
     def iteration(self, R: int, eta: float = -1.0):
         """One iteration of a phase of length R (the same R for all iterations of one phase)."""
         import torch
+        self._iteration(R, eta, torch.cuda.current_stream(self.X.device))
+
+    def _iteration(self, R: int, eta: float, main):
         ctx, r = self.ctx, self.r
-        main = torch.cuda.current_stream(self.X.device)
         comm = self.comm if self.comm is not None else main
         if r == 0 and comm is not main:
             comm.wait_stream(main)                     # the last phase end produced Xt and Y
-        with torch.cuda.stream(comm):
-            if self.granularity == "phase":
-                if r == 0:
-                    ctx.gossip_accel(self.xt[0], R, eta)
-                    ctx.gossip_accel(self.y[0], R, eta)
-            else:
-                for z in (self.xt, self.y):
-                    ctx.gossip_round(z[0], z[0] if r == 0 else z[1], z[1], eta)
-                    z[0], z[1] = z[1], z[0]
+        on = comm.cuda_stream  # handed to the calls: entering and leaving it takes the host longer than they do
+        if self.granularity == "phase":
+            if r == 0:
+                ctx.gossip_accel(self.xt[0], R, eta, stream=on)
+                ctx.gossip_accel(self.y[0], R, eta, stream=on)
+        else:
+            for z in (self.xt, self.y):
+                ctx.gossip_round(z[0], z[0] if r == 0 else z[1], z[1], eta, stream=on)
+                z[0], z[1] = z[1], z[0]
         for q in range(self.B):
             self.grad(self.t, q, self.X, self.g)
             ctx.accumulate(self.G_k, self.g, self.scale)
@@ -127,8 +129,10 @@ class ByPhase:
     def phase(self, R: int, eta: float = -1.0):
         if self.r != 0:
             raise RuntimeError("a phase is in progress")
+        import torch
+        main = torch.cuda.current_stream(self.X.device)
         for _ in range(R):
-            self.iteration(R, eta)
+            self._iteration(R, eta, main)
 
     def capture_two_phases(self, R: int, eta: float = -1.0):
         """Record two consecutive phases of length R into a HIP graph (two, because the gradient buffers and,

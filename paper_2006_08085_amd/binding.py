@@ -383,8 +383,10 @@ class Context:
         self._check(lib().detag_reserve_gradient(self._h, m, F, C_classes, B))
 
     # -- hot path ------------------------------------------------------------
-    def gossip_accel(self, Z, K: int, eta: float = -1.0):
-        self._check(lib().detag_gossip_accel(self._h, self._state(Z, "Z"), K, eta, self._stream()))
+    # stream: a raw HIP stream to enqueue on in place of the current one
+    def gossip_accel(self, Z, K: int, eta: float = -1.0, stream: Optional[int] = None):
+        self._check(lib().detag_gossip_accel(self._h, self._state(Z, "Z"), K, eta,
+                                             self._stream() if stream is None else stream))
 
     def track(self, Y, G_new, G_old):
         self._check(lib().detag_track(self._h, self._state(Y, "Y"), self._f32(G_new, "G_new"),
@@ -400,9 +402,10 @@ class Context:
                                            self._stream()))
 
     # -- Algorithm 2 iteration by iteration ---------------------------------------
-    def gossip_round(self, Z_cur, Z_prev, Z_out, eta: float = -1.0):
+    def gossip_round(self, Z_cur, Z_prev, Z_out, eta: float = -1.0, stream: Optional[int] = None):
         self._check(lib().detag_gossip_round(self._h, self._state(Z_cur, "Z_cur"), self._state(Z_prev, "Z_prev"),
-                                             self._state(Z_out, "Z_out"), eta, self._stream()))
+                                             self._state(Z_out, "Z_out"), eta,
+                                             self._stream() if stream is None else stream))
 
     def accumulate(self, G_acc, g, scale: float = 1.0):
         self._check(lib().detag_accumulate(self._h, self._f32(G_acc, "G_acc"),
