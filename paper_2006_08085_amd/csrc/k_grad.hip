@@ -156,15 +156,9 @@ __global__ __launch_bounds__(64) void lstsq_resid_kernel(int64_t first_row, int 
 // of a row.
 constexpr int kSumThreads = 1024;
 template <int LANES>
-__global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_col, int m, int64_t d, int64_t ld,
-                                                                 const float *__restrict__ A, const float *__restrict__ resid,
-                                                                 float *__restrict__ G) {
-  constexpr int kRows = kSumThreads / LANES, kCols = 4 * LANES, kWaves = kSumThreads / 64;
-  __shared__ float part[kWaves][kCols];
-  const int i = blockIdx.y, lane = threadIdx.x % LANES, r0 = threadIdx.x / LANES;
-  const int64_t c0 = first_col + int64_t(blockIdx.x) * kCols, c = c0 + 4 * lane;
-  const float *a = A + int64_t(i) * m * d;
-  const float *res = resid + int64_t(i) * m;
+__device__ __forceinline__ void lstsq_columns(const float *a, const float *res, int m, int64_t d, int64_t c, int r0, int lane,
+                                              float (*part)[4 * LANES]) {
+  constexpr int kRows = kSumThreads / LANES;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
   if (c + 4 <= d) {
 #pragma unroll 4
@@ -188,14 +182,90 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_c
     for (int e = 0; e < 4; ++e) part[threadIdx.x >> 6][4 * lane + e] = acc[e];
   }
   __syncthreads();
-  if (threadIdx.x < kCols) {
-    const int64_t col = c0 + threadIdx.x;
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += part[w][threadIdx.x];
-    if (col < d) G[int64_t(i) * ld + col] = sum;
-  }
 }
+template <int COLS>
+__device__ __forceinline__ float lstsq_total(const float (*part)[COLS], int col) {
+  float sum = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSumThreads / 64; ++w) sum += part[w][col];
+  return sum;
+}
+
+template <int LANES>
+__global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_col, int m, int64_t d, int64_t ld,
+                                                                 const float *__restrict__ A, const float *__restrict__ resid,
+                                                                 float *__restrict__ G) {
+  constexpr int kCols = 4 * LANES, kWaves = kSumThreads / 64;
+  __shared__ float part[kWaves][kCols];
+  const int i = blockIdx.y, lane = threadIdx.x % LANES, r0 = threadIdx.x / LANES;
+  const int64_t c0 = first_col + int64_t(blockIdx.x) * kCols;
+  lstsq_columns<LANES>(A + int64_t(i) * m * d, resid + int64_t(i) * m, m, d, c0 + 4 * lane, r0, lane, part);
+  if (threadIdx.x < kCols && c0 + threadIdx.x < d) G[int64_t(i) * ld + c0 + threadIdx.x] = lstsq_total(part, threadIdx.x);
+}
+
+// Both products in one launch, for problems so small that a block of 64 columns computes all residuals of its worker itself,
+// in one go: a wavefront per row as in lstsq_resid_kernel, whose sums they are bit for bit, kSumRows rows side by side.  What
+// such a call costs is the host behind its launches (8 workers, 64 x 1024: two launches 8.9 us a call, 5.6 of them on the
+// GPU; one 6.3, where the GPU takes 6.8; 32 workers, 64 x 500 8.4 and 5.9).  Blocks of a worker go to one XCD where n is a
+// multiple of eight, so that its L2 serves all of them but the first.
+constexpr int kSumRows = 4;
+constexpr int kSmallRows = kSumRows * (kSumThreads / 64), kSmallCols = 1024;
+template <typename ST>
+__global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t d, int64_t ld, const ST *__restrict__ X,
+                                                                  const float *__restrict__ A, const float *__restrict__ b,
+                                                                  float *__restrict__ G) {
+  constexpr int kPieces = 4, kLanes = 16, kCols = 4 * kLanes, kWaves = kSumThreads / 64;
+  __shared__ float res[kSmallRows];
+  __shared__ float part[kWaves][kCols];
+  const int i = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const float *a = A + int64_t(i) * m * d;
+  const ST *x = X + int64_t(i) * ld;
+  {
+    const int r0 = wave < m ? wave : 0;  // rows past the last repeat another one
+    float acc[kSumRows][kPieces] = {};
+    const float *row[kSumRows];
+#pragma unroll
+    for (int q = 0; q < kSumRows; ++q) row[q] = a + int64_t(wave + q * kWaves < m ? wave + q * kWaves : r0) * d;
+    int64_t c = lane * 4;
+    for (; c - lane * 4 + kPieces * 256 <= d; c += kPieces * 256) {
+      vf4_t av[kSumRows][kPieces], xv[kPieces];
+#pragma unroll
+      for (int k = 0; k < kPieces; ++k) {
+        xv[k] = load4(x + c + 256 * k);
+#pragma unroll
+        for (int q = 0; q < kSumRows; ++q) av[q][k] = load4(row[q] + c + 256 * k);
+      }
+#pragma unroll
+      for (int q = 0; q < kSumRows; ++q)
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[q][k] = fmaf(av[q][k][e], xv[k][e], acc[q][k]);
+    }
+    for (int64_t t = c - lane * 3; t < d; t += 64) {  // the last d % 1024 columns
+      const float xt = to_f32(x[t]);
+#pragma unroll
+      for (int q = 0; q < kSumRows; ++q) acc[q][0] = fmaf(row[q][t], xt, acc[q][0]);
+    }
+#pragma unroll
+    for (int q = 0; q < kSumRows; ++q) {
+      float sum = (acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
+      const int r = wave + q * kWaves;
+      if (lane == 0 && r < m) res[r] = sum - b[int64_t(i) * m + r];
+    }
+  }
+  __syncthreads();
+  const int l = threadIdx.x % kLanes, r0 = threadIdx.x / kLanes;
+  const int64_t c0 = int64_t(blockIdx.y) * kCols;
+  lstsq_columns<kLanes>(a, res, m, d, c0 + 4 * l, r0, l, part);
+  if (threadIdx.x < kCols && c0 + threadIdx.x < d) G[int64_t(i) * ld + c0 + threadIdx.x] = lstsq_total(part, threadIdx.x);
+}
+
+// One launch while a block takes its rows in one go and the blocks take a compute unit each.  With twice the rows or columns
+// it is slower on the GPU by more than the launch it saves (8 workers, 128 x 1024 8.7 and 8.4 us, 256 x 512 8.8 and 13.1).
+bool lstsq_is_small(const Shape &s, int m) { return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256; }
 
 }  // namespace
 
@@ -219,6 +289,12 @@ int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float
                       void *stream) {
   auto st = static_cast<hipStream_t>(stream);
   const int64_t rows = int64_t(s.n) * m;
+  if (lstsq_is_small(s, m)) {
+    const dim3 grid(s.n, ceil_div_i64(s.d, 64));
+    if (s.bf16) lstsq_small_kernel<bf16_t><<<grid, kSumThreads, 0, st>>>(m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, G);
+    else lstsq_small_kernel<float><<<grid, kSumThreads, 0, st>>>(m, s.d, s.ld, static_cast<const float *>(X), A, b, G);
+    return hip_rc(hipGetLastError());
+  }
   for (int64_t first = 0; first < rows; first += kThreadsPerLaunch / 64) {
     const dim3 grid(uint32_t(std::min(rows - first, kThreadsPerLaunch / 64)));
     if (s.bf16)

@@ -55,3 +55,27 @@ def test_more_columns_than_a_launch_has_threads_for():
     X, G = torch.zeros(1, d, device=DEV), torch.full((1, d), SENTINEL, device=DEV)
     _alone(d).grad_lstsq(X, A, b, G)
     assert torch.equal(G, 2.0 * A[0])                   # A^T (A x - b), exact in fp32
+
+
+@pytest.mark.parametrize("n,d,m", [(1, 1, 1), (8, 1024, 64), (16, 1024, 64), (3, 1023, 63), (5, 64, 17), (64, 256, 5), (85, 129, 64), (7, 1021, 16)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_one_launch_gives_the_bits_of_two(n, d, m, dtype):
+    """Problems of up to 64 samples and 1024 columns take one launch; the same rows among more samples, weighted by zero
+    residuals, take two."""
+    ld = d + 1
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X = to_dev(gen.state(n, d, seed=1), ld, tdt)
+    A, b = (torch.from_numpy(t).to(DEV) for t in gen.lstsq_problem(n, m, d, seed=2, shift=0.5))
+    topo = D.Topology.ring() if n > 1 else D.Topology.from_dense(np.ones((1, 1)))
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32)
+    G, G2 = to_dev(np.zeros((n, d)), ld), to_dev(np.zeros((n, d)), ld)
+    ctx.grad_lstsq(X, A, b, G)
+    # samples of zeros from the 65th on: exact zero residuals, which add exact zeros to every column
+    A2, b2 = torch.zeros(n, 64 + 1, d, device=DEV), torch.zeros(n, 64 + 1, device=DEV)
+    A2[:, :m], b2[:, :m] = A, b
+    ctx.grad_lstsq(X, A2, b2, G2)
+    assert torch.equal(G[:, :d], G2[:, :d])
+    assert padding_ok(G, d) and padding_ok(G2, d)
+    ref = OO.grad_lstsq(to_host(X, d), A.cpu().numpy(), b.cpu().numpy())
+    S = max(amax(ref), amax(A.cpu().numpy()) * np.sqrt(d) * amax(A.cpu().numpy()) * amax(to_host(X, d)))
+    assert rel_err(to_host(G, d), ref, S) < TOL_F32
