@@ -31,11 +31,11 @@ __device__ __forceinline__ int64_t xcd_tile(uint32_t b, uint32_t tiles) {
   return b < per * 8u ? int64_t(b % 8u) * per + b / 8u : int64_t(b);
 }
 
-// Whether column tiles share 128-byte cache lines: rows that do not start on one (an odd pitch, a shifted base).
-inline bool shares_lines(const Shape &s, std::initializer_list<const void *> matrices) {
+// Whether column tiles share cache lines of 128 bytes: rows that do not start on one (an odd pitch, a shifted base).
+inline bool shares_lines(const Shape &s, std::initializer_list<const void *> matrices, uint64_t line = 128) {
   uint64_t starts = uint64_t(s.ld) * (s.bf16 ? 2 : 4);
   for (const void *p : matrices) starts |= reinterpret_cast<uint64_t>(p);
-  return starts % 128 != 0;
+  return starts % line != 0;
 }
 // What the matrices of a call that walks column tiles take together.
 inline int64_t footprint(const Shape &s, int per_element) { return int64_t(s.n) * s.ld * per_element; }
@@ -56,8 +56,10 @@ inline bool loads_stream(const Shape &s, int per_element) { return footprint(s, 
 // before the other tile wants it, or goes to memory half written.  Streamed and kept, fp32, pitch 1,000,003, K = 4: phase,
 // torus 8x8 388 and 296 us, one round 165 and 145, gradient-fused step 465 and 364; ring of 16, pitch 600,001 52 and 50, 65
 // and 60.  On lines streaming is 2 to 10 % ahead.
-inline Access tile_access(const Shape &s, int per_element, std::initializer_list<const void *> matrices) {
-  return footprint(s, per_element) > (int64_t(80) << 20) && !shares_lines(s, matrices) ? kStream : kKeep;
+// The phase and the fused step of the ATC form with bf16 state stream on half lines too (torus 8x8, pitch 1,000,032: 338 and
+// 355 us, 336 and 341; pitch 1,000,003 368 and 352, 420 and 338): `line` = 64.
+inline Access tile_access(const Shape &s, int per_element, std::initializer_list<const void *> matrices, uint64_t line = 128) {
+  return footprint(s, per_element) > (int64_t(80) << 20) && !shares_lines(s, matrices, line) ? kStream : kKeep;
 }
 
 template <int N>

@@ -187,7 +187,8 @@ int launch_s(const Shape &s, int mode, void *X, void *Y, const float *Gn, const 
     return s.bf16 ? launch_t<T, bf16_t, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream)
                   : launch_t<T, float, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream);
   };
-  return tile_access(s, per_element, {X, Y, Gn, Go}) == kStream ? go(AccessTag<kStream>{}) : go(AccessTag<kKeep>{});
+  const uint64_t line = s.bf16 && mode == 1 ? 64 : 128;
+  return tile_access(s, per_element, {X, Y, Gn, Go}, line) == kStream ? go(AccessTag<kStream>{}) : go(AccessTag<kKeep>{});
 }
 
 }  // namespace

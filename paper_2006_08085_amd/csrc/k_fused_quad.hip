@@ -220,7 +220,8 @@ int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float 
     if (s.bf16) with_h(access, static_cast<bf16_t *>(X));
     else with_h(access, static_cast<float *>(X));
   };
-  if (tile_access(s, per_element, {X, Y, G, hpw ? h : nullptr, b}) == kStream) with_type(AccessTag<kStream>{});
+  const uint64_t line = s.bf16 && !alg2 ? 64 : 128;
+  if (tile_access(s, per_element, {X, Y, G, hpw ? h : nullptr, b}, line) == kStream) with_type(AccessTag<kStream>{});
   else with_type(AccessTag<kKeep>{});
   return hip_rc(hipGetLastError());
 }

@@ -18,7 +18,8 @@ constexpr int kThreads = 256;
 
 // Streamed data (touched once per kernel) goes through non-temporal accesses: on the 64 x 11.2 M fp32 matrices the
 // update-and-track pass takes 2.78 ms with them against 3.14 ms without (0.77 against 0.68 of HBM peak), the
-// tracker update 1.75 against 2.06 ms.  Rows that neighbours read again within a kernel (NT = false) stay cached.
+// tracker update 1.75 against 2.06 ms.  Rows that neighbours read again within a kernel (NT = false) stay cached, and the
+// loads of small calls (fused::loads_stream).
 // Four columns are one access wherever the row starts: memory needs element alignment only, so an odd pitch or a shifted
 // base takes the same path (quadratic gradient of 100 workers, d = 300,007, pitch d, per-worker curvature: 148 us one
 // column at a time, 90 us so).
