@@ -347,8 +347,9 @@ detag_status detag_factor_apply(detag_ctx *ctx, const detag_factors *f, int32_t 
  */
 detag_status detag_average_consensus(detag_ctx *ctx, const detag_factors *f, void *Z_dev, void *stream);
 /*
- * Host view of what the on-chip form of detag_average_consensus executes (for inspection and tests; lives until
- * detag_factors_destroy): `*batches` batches of 4 operations of 8 words each,
+ * Host view of the row operations of the on-chip form of detag_average_consensus, in order (for inspection and tests;
+ * lives until detag_factors_destroy; the kernel does those that do not depend on each other side by side):
+ * `*batches` batches of 4 operations of 8 words each,
  *   { o0, o1, dst, keep, w0, w1, m0, m1 }:   acc = (previous acc & keep) + w0*(row[o0] & m0) + w1*(row[o1] & m1),
  *                                            row[dst] = acc,
  * o0, o1, dst = 256 * row index, w0, w1 fp32 bit patterns, keep/m0/m1 all ones or 0, the first operation of a batch
