@@ -442,7 +442,8 @@ detag_status detag_step_quadratic(detag_ctx *ctx, void *X_dev, void *Y_dev, floa
 /*
  * Gradient of f_i(x) = 1/2 ||A_i x - b_i||^2:  G[i,:] = A_i^T (A_i X[i,:] - b_i).
  * A_dev: fp32 n x m x d (row pitch d), b_dev: fp32 n x m, G_dev: fp32 n x ld.
- * Uses a context-owned scratch of n*m floats (allocated on first use).
+ * Uses a context-owned scratch of n*m floats (allocated on first use).  G may lie
+ * over X or b (they are read before it is written), not over A.
  */
 detag_status detag_grad_lstsq(detag_ctx *ctx, const void *X_dev, const float *A_dev,
                               const float *b_dev, int32_t m, float *G_dev, void *stream);

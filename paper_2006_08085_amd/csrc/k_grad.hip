@@ -267,6 +267,17 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t
 // it is slower on the GPU by more than the launch it saves (8 workers, 128 x 1024 8.7 and 8.4 us, 256 x 512 8.8 and 13.1).
 bool lstsq_is_small(const Shape &s, int m) { return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256; }
 
+bool overlap(const void *p, size_t p_bytes, const void *q, size_t q_bytes) {
+  const auto a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+  return a < b + q_bytes && b < a + p_bytes;
+}
+// Whether G lies over X or b.  Two launches have read both before the second writes G; in the one launch a block writes its
+// columns while others still read.
+bool lstsq_in_place(const Shape &s, const void *X, const float *b, int m, const float *G) {
+  const size_t elements = size_t(s.n - 1) * s.ld + s.d;
+  return overlap(G, elements * 4, X, elements * (s.bf16 ? 2 : 4)) || overlap(G, elements * 4, b, size_t(s.n) * m * 4);
+}
+
 }  // namespace
 
 int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_per_worker, const float *b,
@@ -289,7 +300,7 @@ int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float
                       void *stream) {
   auto st = static_cast<hipStream_t>(stream);
   const int64_t rows = int64_t(s.n) * m;
-  if (lstsq_is_small(s, m)) {
+  if (lstsq_is_small(s, m) && !lstsq_in_place(s, X, b, m, G)) {
     const dim3 grid(s.n, ceil_div_i64(s.d, 64));
     if (s.bf16) lstsq_small_kernel<bf16_t><<<grid, kSumThreads, 0, st>>>(m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, G);
     else lstsq_small_kernel<float><<<grid, kSumThreads, 0, st>>>(m, s.d, s.ld, static_cast<const float *>(X), A, b, G);

@@ -79,3 +79,31 @@ def test_one_launch_gives_the_bits_of_two(n, d, m, dtype):
     ref = OO.grad_lstsq(to_host(X, d), A.cpu().numpy(), b.cpu().numpy())
     S = max(amax(ref), amax(A.cpu().numpy()) * np.sqrt(d) * amax(A.cpu().numpy()) * amax(to_host(X, d)))
     assert rel_err(to_host(G, d), ref, S) < TOL_F32
+
+
+@pytest.mark.parametrize("n,d,m", [(8, 1024, 64), (16, 500, 16), (3, 1023, 63), (5, 64, 17), (4, 65, 64), (8, 1025, 64)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_the_gradient_may_lie_over_the_state_or_the_targets(n, d, m, dtype):
+    """Both are read before G is written: the bits of a call whose G lies apart."""
+    ld = d + 1
+    bf16 = dtype == "bf16"
+    X = to_dev(gen.state(n, d, seed=1), ld, torch.bfloat16 if bf16 else torch.float32)
+    A, b = (torch.from_numpy(t).to(DEV) for t in gen.lstsq_problem(n, m, d, seed=2, shift=0.5))
+    ctx = D.detag_create(D.Topology.ring(), n, d, ld, D.DETAG_BF16 if bf16 else D.DETAG_F32)
+    G = torch.zeros(n, ld, device=DEV)
+    ctx.grad_lstsq(X, A, b, G)
+
+    over_x = torch.empty(n, ld, device=DEV)
+    x = over_x.view(torch.bfloat16).view(-1)[:n * ld].view(n, ld) if bf16 else over_x
+    shifted = torch.empty(n * ld + 70, device=DEV)          # G starts 64 floats into X
+    y = (shifted.view(torch.bfloat16) if bf16 else shifted)[:n * ld].view(n, ld)
+    over_b = torch.empty(n, ld, device=DEV)
+    for state, grad in ((x, over_x), (y, shifted[64:64 + n * ld].view(n, ld))):
+        state.copy_(X)
+        ctx.grad_lstsq(state, A, b, grad)
+        assert torch.equal(grad[:, :d], G[:, :d])
+    if m <= ld:
+        targets = over_b.view(-1)[-n * m:].view(n, m)
+        targets.copy_(b)
+        ctx.grad_lstsq(X, A, targets, over_b)
+        assert torch.equal(over_b[:, :d], G[:, :d])
