@@ -97,14 +97,11 @@ class ByPhase:
     def iteration(self, R: int, eta: float = -1.0):
         """One iteration of a phase of length R (the same R for all iterations of one phase)."""
         import torch
-        self._iteration(R, eta, torch.cuda.current_stream(self.X.device))
-
-    def _iteration(self, R: int, eta: float, main):
-        ctx, r = self.ctx, self.r
-        comm = self.comm if self.comm is not None else main
-        if r == 0 and comm is not main:
-            comm.wait_stream(main)                     # the last phase end produced Xt and Y
-        on = comm.cuda_stream  # handed to the calls: entering and leaving it takes the host longer than they do
+        ctx, r, comm = self.ctx, self.r, self.comm
+        if r == 0 and comm is not None:
+            comm.wait_stream(torch.cuda.current_stream(self.X.device))   # the last phase end produced Xt and Y
+        # handed to the calls: entering and leaving a stream takes the host longer than they do
+        on = comm.cuda_stream if comm is not None else None
         if self.granularity == "phase":
             if r == 0:
                 ctx.gossip_accel(self.xt[0], R, eta, stream=on)
@@ -119,8 +116,8 @@ class ByPhase:
         self.t += 1
         self.r += 1
         if self.r == R:
-            if comm is not main:
-                main.wait_stream(comm)
+            if comm is not None:                       # the stream that is current now: grad may have changed it
+                torch.cuda.current_stream(self.X.device).wait_stream(comm)
             ctx.phase_end(self.X, self.xt[0], self.y[0], self.G_k, self.G_km1, self.alpha)
             self.G_k, self.G_km1 = self.G_km1, self.G_k
             self.r = 0
@@ -129,10 +126,8 @@ class ByPhase:
     def phase(self, R: int, eta: float = -1.0):
         if self.r != 0:
             raise RuntimeError("a phase is in progress")
-        import torch
-        main = torch.cuda.current_stream(self.X.device)
         for _ in range(R):
-            self._iteration(R, eta, main)
+            self.iteration(R, eta)
 
     def capture_two_phases(self, R: int, eta: float = -1.0):
         """Record two consecutive phases of length R into a HIP graph (two, because the gradient buffers and,
