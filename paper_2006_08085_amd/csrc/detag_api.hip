@@ -55,6 +55,21 @@ struct detag_factors {
   int table_words = 0;
 };
 
+namespace detag {
+
+// A stream that is being recorded into a HIP graph must see kernel launches only: an allocation, a blocking
+// copy or a device synchronisation would fail or invalidate the recording half-way.
+bool is_capturing(void *stream) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return st != hipStreamCaptureStatusNone;
+}
+
+}  // namespace detag
+
 namespace {
 
 thread_local std::string g_create_err;
@@ -76,17 +91,6 @@ detag_status need_device(const detag_ctx *ctx) {
   if (!ctx) return DETAG_EINVAL;
   if (!ctx->has_device) return set_err(ctx, DETAG_EHIP, "no GPU was present when this context was created");
   return DETAG_OK;
-}
-
-// A stream that is being recorded into a HIP graph must see kernel launches only: an allocation, a blocking
-// copy or a device synchronisation would fail or invalidate the recording half-way.
-bool is_capturing(void *stream) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(static_cast<hipStream_t>(stream), &st) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return st != hipStreamCaptureStatusNone;
 }
 
 detag_status refuse_while_capturing(const detag_ctx *ctx, const char *what, const char *reserve) {

@@ -166,6 +166,8 @@ double *static_partials(int device);
 int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_per_worker, const float *b,
                           const float *noise, float sigma, uint64_t seed, uint32_t step, float *G,
                           void *stream);
+// Whether the stream is being recorded into a graph.
+bool is_capturing(void *stream);
 int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float *b, int m, float *resid,
                       float *G, void *stream);
 int64_t softmax_scratch_floats(int n, int C, int B, int F);

@@ -205,9 +205,11 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_c
 
 // Both products in one launch, for problems so small that a block of 64 columns computes all residuals of its worker itself,
 // in one go: a wavefront per row as in lstsq_resid_kernel, whose sums they are bit for bit, kSumRows rows side by side.  What
-// such a call costs is the host behind its launches (8 workers, 64 x 1024: two launches 8.9 us a call, 5.6 of them on the
-// GPU; one 6.3, where the GPU takes 6.8; 32 workers, 64 x 500 8.4 and 5.9).  Blocks of a worker go to one XCD where n is a
-// multiple of eight, so that its L2 serves all of them but the first.
+// such a call costs is the host behind its launches, not the GPU: called back to back, two launches and one, 8 workers, 64 x
+// 1024 8.3 and 6.0 us a call, 32 workers, 64 x 500 8.7 and 6.2, while on the GPU (a recorded graph of 20 calls, a replay of
+// it by the call) they take 5.4 and 6.7, 6.7 and 6.7.  Blocks of a worker go to one XCD where n is a multiple of eight, so
+// that its L2 serves all of them but the first.  Blocks of 128 and 256 columns repeat less of the first product and are
+// slower both ways (8 workers, 64 x 1024 6.8 and 8.7 us a call).
 constexpr int kSumRows = 4;
 constexpr int kSmallRows = kSumRows * (kSumThreads / 64), kSmallCols = 1024;
 template <typename ST>
@@ -265,7 +267,13 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t
 
 // One launch while a block takes its rows in one go and the blocks take a compute unit each.  With twice the rows or columns
 // it is slower on the GPU by more than the launch it saves (8 workers, 128 x 1024 8.7 and 8.4 us, 256 x 512 8.8 and 13.1).
-bool lstsq_is_small(const Shape &s, int m) { return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256; }
+// A recorded call costs the host nothing at its replay and takes what is faster on the GPU, which is one launch up to 256
+// columns (two and one: 8 workers, 32 x 200 5.2 and 5.1 us, 64 workers, 64 x 256 6.6 and 5.7, 85, 40 x 129 6.3 and 5.3; but 32
+// workers, 8 x 512 5.8 and 6.0, 8 workers, 64 x 1000 6.9 and 7.9).
+constexpr int kRecordedCols = 256;
+bool lstsq_is_small(const Shape &s, int m, void *stream) {
+  return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256 && (s.d <= kRecordedCols || !is_capturing(stream));
+}
 
 bool overlap(const void *p, size_t p_bytes, const void *q, size_t q_bytes) {
   const auto a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
@@ -300,7 +308,7 @@ int launch_grad_lstsq(const Shape &s, const void *X, const float *A, const float
                       void *stream) {
   auto st = static_cast<hipStream_t>(stream);
   const int64_t rows = int64_t(s.n) * m;
-  if (lstsq_is_small(s, m) && !lstsq_in_place(s, X, b, m, G)) {
+  if (lstsq_is_small(s, m, stream) && !lstsq_in_place(s, X, b, m, G)) {
     const dim3 grid(s.n, ceil_div_i64(s.d, 64));
     if (s.bf16) lstsq_small_kernel<bf16_t><<<grid, kSumThreads, 0, st>>>(m, s.d, s.ld, static_cast<const bf16_t *>(X), A, b, G);
     else lstsq_small_kernel<float><<<grid, kSumThreads, 0, st>>>(m, s.d, s.ld, static_cast<const float *>(X), A, b, G);

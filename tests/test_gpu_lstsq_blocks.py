@@ -107,3 +107,22 @@ def test_the_gradient_may_lie_over_the_state_or_the_targets(n, d, m, dtype):
         targets.copy_(b)
         ctx.grad_lstsq(X, A, targets, over_b)
         assert torch.equal(over_b[:, :d], G[:, :d])
+
+
+@pytest.mark.parametrize("n,d,m", [(8, 1024, 64), (8, 257, 16), (8, 256, 16), (85, 129, 64), (4, 1025, 64)])
+def test_a_recorded_call_gives_the_bits_of_the_others(n, d, m):
+    """A recorded call goes to one launch up to 256 columns, others up to 1024."""
+    ctx = D.detag_create(D.Topology.ring(), n, d, d)
+    X, G = to_dev(gen.state(n, d, seed=1), d), torch.zeros(n, d, device=DEV)
+    A, b = (torch.from_numpy(t).to(DEV) for t in gen.lstsq_problem(n, m, d, seed=2, shift=0.5))
+    ctx.grad_lstsq(X, A, b, G)
+    graph, recorded = torch.cuda.CUDAGraph(), torch.zeros(n, d, device=DEV)
+    with torch.cuda.graph(graph):
+        ctx.grad_lstsq(X, A, b, recorded)
+    for k in range(3):
+        recorded.zero_()
+        X.mul_(1.0 if k == 0 else -0.5)
+        graph.replay()
+        ctx.grad_lstsq(X, A, b, G)
+        torch.cuda.synchronize()
+        assert torch.equal(recorded, G), k
