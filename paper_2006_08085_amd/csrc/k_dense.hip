@@ -40,7 +40,7 @@ constexpr int kCols = 64, kThreads = 256, kWaves = 4;
 constexpr int kRowsMax = 256, kMTiles = kRowsMax / 32, kKSteps = kRowsMax / 16;
 constexpr int kUnitSteps = 8;    // k-steps (of 16 rows) staged in LDS at a time
 constexpr int kOutPitch = 72;    // floats per row of a wavefront's 16 x 64 output scratch: rows 4 apart are 32 banks apart
-constexpr int64_t kKeepBytes = int64_t(128) << 20;
+constexpr int64_t kMiB = int64_t(1) << 20;
 constexpr int kOutBytes = kWaves * 16 * kOutPitch * 4;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -347,12 +347,16 @@ int launch_ks(const Shape &s, int mode, void *X, void *Y, const float *Gn, const
   // Where rows do not start on a cache line, neighbouring tiles share lines: they go to one XCD (64 x 1,000,003 fp32: 616 ->
   // 470 us) and leave their accesses to the caches (pitch 1,000,001, K = 4 505 -> 414 us; 256 x 200,001 of bf16 397 -> 355).
   // Where they do, tiles keep their order, in which 256 workers with bf16 state measured 1 % faster, and stream, but not calls
-  // that the memory-side cache holds: they read a matrix twice (Algorithm 2's phase of 64 x 50,001 52.5 -> 39.8 us, 64 x
-  // 100,001 of bf16 63.5 -> 50.9; the ATC phase of 256 x 10,001 50.6 -> 45.4, of bf16 40.7 -> 45.7, which streams).  A
-  // kernel for each: the choice made at run time cost the aligned one 0.6 to 5 %.
-  const int state = sizeof(ST), per_element = mode == 0 ? state : 2 * state + 8;
-  const bool small = fused::footprint(s, per_element) <= kKeepBytes && (!s.bf16 || mode == 2);
-  const bool keep = fused::shares_lines(s, {X, Y, Gn, Go}) || small;
+  // of up to 80 MiB that read a matrix twice (streamed and kept, K = 4, three states in turn: Algorithm 2's phase of 64 workers
+  // 64 MiB 56.8 and 41.8 us, 96 MiB 86.7 and 82.4, 126 MiB 96.4 and 98.5; the ATC phase of 128 workers 80 MiB 79.7 and 75.0,
+  // 96 MiB 81.2 and 90.6, 126 MiB 88.2 and 104.5; with bf16 state 256 workers 40 MiB 40.3 and 45.4, which streams), nor plain
+  // gossip of fp32 state from 32 to 80 MiB (128 workers 14 MiB 14.3 and 15.2, 40 MiB 33.3 and 33.1, 80 MiB 58.3 and 55.1, 96 MiB
+  // 69.9 and 75.3; 256 workers 64 MiB 58.5 and 52.4).  A kernel for each: the choice made at run time cost the aligned one 0.6
+  // to 5 %.
+  const int state = sizeof(ST);
+  const int64_t bytes = fused::footprint(s, mode == 0 ? state : 2 * state + 8);
+  const bool gains = mode == 2 || (!s.bf16 && (mode == 1 || bytes >= 32 * kMiB));
+  const bool keep = fused::shares_lines(s, {X, Y, Gn, Go}) || (bytes <= 80 * kMiB && gains);
   return keep ? with_mode(AccessTag<kKeep>{}) : with_mode(AccessTag<kStream>{});
 }
 
