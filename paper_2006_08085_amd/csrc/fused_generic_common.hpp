@@ -595,29 +595,64 @@ inline int allow_lds(const void *kernel, size_t bytes) {
   return hip_rc(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, int(kLdsMax)));
 }
 
+enum Call : int { kPlain, kAtc, kFusedStep, kAlg2, kDpsgd };  // the last three read a matrix late
+
+// How a call of tiles that share cache lines (rows that do not start on one, or tiles of 32 columns of bf16 state) treats
+// them: up to `reads` MiB only its stores stream, from there to `streams` MiB all does, beyond nothing.  A shared line that
+// streams is gone before the other tile wants it, or goes to memory half written; the wider the tile, the fewer are shared.
+// Streamed, loads kept, all kept, K = 4, three states in turn:
+// Up to 64 columns every other line is shared and nothing that streams does well: phase, 64 x 1,000,001 481, 382, 337 us,
+// fused step 637, 453, 401, bf16 540, 354, 301; up to 192 MiB of rows of 256 bytes and more the stores may: fused step 64 x
+// 100,001 58, 41, 44.
+// 128 columns (5 to 8 and 21 to 40 workers): fused step, n = 28, 200 MiB 99, 88, 89, 330 MiB 174, 143, 138; ATC phase, n =
+// 40, 200 MiB 82, 81, 86, 420 MiB 172, 159, 156; D-PSGD 330 MiB 126, 116, 113.
+// 256 columns (up to 20 workers): ATC phase, n = 20, 128 MiB 48.9, 48.2, 53.8, 200 MiB 75, 80, 83, 330 MiB 114, 120, 122, 560
+// MiB 201, 199, 199; fused step, n = 12, 260 MiB 111, 105, 109, 560 MiB 242, 223, 220; D-PSGD 128 MiB 38.8, 36.1, 41.1, 200
+// MiB 61, 65, 67, 420 MiB 139, 138, 137.  With up to 4 rows a tile the loads are best kept: ATC phase, n = 3, 210 MiB 75, 72,
+// 78.
+// Plain gossip of lists: n = 16, 260 MiB 130, 144, 144, n = 24 (128 columns) 180 MiB 101, 104, 101; of bf16 state: n = 20, 160
+// MiB 115, 122, 122, n = 28 128 MiB 91, 95, 94, 200 MiB 147, 148, 146.
+struct SharedLines {
+  int reads, streams;
+};
+inline SharedLines shared_lines(const Shape &s, const Geometry &g, Call call, bool lists) {
+  constexpr int kEver = 1 << 30;
+  if (g.cols < 128) return g.cols * (s.bf16 ? 2 : 4) >= 256 ? SharedLines{192, 192} : SharedLines{0, 0};
+  const bool wide = g.cols > 128;
+  if (call == kPlain) {
+    if (wide && (lists || s.bf16)) return {96, kEver};
+    if (lists) return {96, 96};
+    if (s.bf16) return {100, 176};
+  }
+  if (wide && s.n <= 4) return {400, 400};
+  switch (call) {
+    case kAtc: return wide ? SharedLines{144, 480} : SharedLines{260, 260};
+    case kFusedStep: return wide ? SharedLines{288, 288} : SharedLines{260, 260};
+    case kDpsgd: return wide ? SharedLines{144, 300} : SharedLines{192, 192};
+    default: return {192, 192};
+  }
+}
+
 // How these kernels treat the caches: calls f(access).  Matrices with S < 4 fit the caches.
 // Where tiles have their cache lines to themselves a call streams; up to 128 MiB the calls that read a matrix late (the
 // gradients of Algorithm 2's phase and of D-PSGD, the old gradient of the fused step) leave the loads to the caches.
 // Streamed, loads kept, all kept, K = 4, three states in turn: Algorithm 2's phase 64 x 100,001 34.3, 32.2, 31.7 us, 20 x
 // 200,001 22.8, 20.2, 19.1; fused step 20 x 200,001 27.9, 25.7, 26.3, 64 x 200,001 78.9, 82.1, 85.2; but the ATC phase
-// 64 x 50,001 21.4, 22.0, 22.9, 256 x 30,001 40.2, 40.3, 46.9.
-// Where they share lines (rows that do not start on one, or tiles of 32 columns of bf16 state) nothing that streams does
-// well: phase, 64 x 1,000,001 481, 382, 337 us, fused step 637, 453, 401, bf16 540, 354, 301.  Up to 192 MiB of tiles whose
-// rows are 256 bytes or more the stores stream all the same: fused step 64 x 100,001 58, 41, 44 us, 20 x 600,001 78, 80,
-// 84.  Plain gossip of up to 32 MiB always streams: 64 x 50,001 9.7, 10.6, 10.4 us.
-enum Call : int { kPlain, kAtc, kReadsLate };
+// 64 x 50,001 21.4, 22.0, 22.9, 256 x 30,001 40.2, 40.3, 46.9.  Plain gossip of up to 32 MiB streams wherever its rows start:
+// 64 x 50,001 9.7, 10.6, 10.4 us.
 template <class R, class F>
 int with_access(const Shape &s, const Geometry &g, Call call, int per_element, std::initializer_list<const void *> matrices,
                 F &&f) {
   if constexpr (R::kSlots < kSlotsMax) {
     return f(AccessTag<kKeepReads>{});
   } else {
-    const int row_bytes = g.cols * (s.bf16 ? 2 : 4);
     const int64_t mib = fused::footprint(s, per_element) >> 20;
     if (call == kPlain && mib < 32) return f(AccessTag<kStream>{});
-    if (fused::shares_lines(s, matrices) || row_bytes % 128 != 0)
-      return mib < 192 && row_bytes >= 256 ? f(AccessTag<kKeepReads>{}) : f(AccessTag<kKeep>{});
-    return call == kReadsLate && mib < 128 ? f(AccessTag<kKeepReads>{}) : f(AccessTag<kStream>{});
+    SharedLines lines{call > kAtc ? 128 : 0, 1 << 30};
+    if (fused::shares_lines(s, matrices) || g.cols * (s.bf16 ? 2 : 4) % 128 != 0)
+      lines = shared_lines(s, g, call, std::is_same_v<typename R::Args, ListArgs>);
+    if (mib < lines.reads) return f(AccessTag<kKeepReads>{});
+    return mib < lines.streams ? f(AccessTag<kStream>{}) : f(AccessTag<kKeep>{});
   }
 }
 

@@ -113,7 +113,7 @@ int launch_r(const Shape &s, const Geometry &g, size_t lds, const typename R::Ar
     return hip_rc(hipErrorInvalidValue);
   };
   const int state = sizeof(ST), per_element = mode == 0 ? state : mode == 3 ? state + 4 : 2 * state + 8;
-  const Call call = mode == 0 ? kPlain : mode == 1 ? kAtc : kReadsLate;
+  const Call call = mode == 0 ? kPlain : mode == 1 ? kAtc : mode == 2 ? kAlg2 : kDpsgd;
   return with_access<R>(s, g, call, per_element, {X, Y, Gn, Go}, with);
 }
 

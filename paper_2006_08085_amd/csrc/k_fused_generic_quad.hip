@@ -97,7 +97,7 @@ int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, v
     };
     const int per_element = (s.bf16 ? 4 : 8) + 8 + (h_per_worker ? 4 : 0);
     // blocks of 1024 threads, two to a compute unit, are better off streaming: 256 x 30,001 53.3, 62.8, 72.2 us
-    const Call call = g.threads <= 512 ? kReadsLate : kAtc;
+    const Call call = g.threads <= 512 ? kFusedStep : kAtc;
     return with_access<R>(s, g, call, per_element, {X, Y, G, h_per_worker ? h : nullptr, b}, with);
     }
   });

@@ -78,6 +78,21 @@ def test_the_layout_does_not_change_the_bits(kind, n, dtype):
                 assert torch.equal(got, want), (d, ld, shift, k)
 
 
+@pytest.mark.parametrize("kind,n", [("path", 3), ("path", 14), ("rr", 20), ("path", 24), ("rr", 28)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tiles_of_128_and_256_columns_beyond_the_caches(kind, n, dtype):
+    """Few workers: whether a call at an odd pitch streams depends on the width of its tiles up to 480 MiB."""
+    topo = _topology(kind, n)
+    for elements in (18_000_000, 33_000_000):
+        d = elements // n | 1
+        g = torch.Generator(device=DEV)
+        g.manual_seed(d)
+        values = [torch.empty(n, d, device=DEV).normal_(generator=g) for _ in range(5)]
+        on_lines = _all_calls(topo, n, d, D.padded_ld(d), 0, dtype, values)
+        for k, (got, want) in enumerate(zip(_all_calls(topo, n, d, d, 0, dtype, values), on_lines)):
+            assert torch.equal(got, want), (d, k)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_row_walking_kernels_on_both_sides_of_128_mib(dtype):
     """Their loads stream from 128 MiB a call on: the same columns, alone and as part of a call beyond that."""
