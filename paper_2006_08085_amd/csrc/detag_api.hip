@@ -689,7 +689,7 @@ detag_status factors_create_impl(detag_ctx *ctx, int32_t root, detag_factors *f)
   if (e == hipSuccess) e = hipMemcpy(f->d_vals, va.data(), va.size() * sizeof(float), hipMemcpyHostToDevice);
   if (e == hipSuccess && !f->table.empty()) {
     std::vector<uint32_t> entries;
-    build_factor_entries(ctx->W.n, f->table, entries);
+    build_factor_entries(ctx->shape, f->table, entries);
     f->table_words = int(entries.size());
     const size_t bytes = entries.size() * sizeof(uint32_t);
     e = hipMalloc(reinterpret_cast<void **>(&f->d_table), bytes);

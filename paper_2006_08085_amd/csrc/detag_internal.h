@@ -93,7 +93,7 @@ struct Shape {
 };
 
 // The table the on-chip kernel reads, from a program of build_factor_table (n <= 256).
-void build_factor_entries(int n, const std::vector<uint32_t> &program, std::vector<uint32_t> &table);
+void build_factor_entries(const Shape &s, const std::vector<uint32_t> &program, std::vector<uint32_t> &table);
 // Z <- A_{R-1} ... A_0 Z on chip, in place (table from build_factor_entries).  -1 if n rows of 32 columns do not
 // fit a block's LDS on this device.
 int launch_factor_sequence(const Shape &s, const uint32_t *table, int table_words, void *Z, void *stream);

@@ -20,7 +20,7 @@
 // Eight lanes side by side take a row, four columns each, and the eight rows of
 // a group are done at once: a slot of two terms is two 16-byte LDS reads, eight
 // multiply-adds and, after the last slot of a group, one 16-byte write, with the
-// operands of a lane's row in one 16-byte word fetched four slots ahead.  An
+// operands of a lane's row in one 16-byte word fetched some slots ahead.  An
 // absent term reads a row of zeros with weight 0, an idle lane writes to it.  No
 // wavefront waits for another: there is no barrier.
 //
@@ -28,6 +28,11 @@
 // and 16 KiB of LDS per wavefront (10 of them on a compute unit, 19 now), 64
 // workers, 4-regular, d = 272,474 took 49 us, 31 now; d = 1,000,000 139 and 109;
 // 256 workers, d = 400,000 566 and 257; 64 workers, d = 20,000 14.5 and 6.8.
+//
+// The words of the slots come through vector memory, where they queue behind the
+// rows of other wavefronts: 16 workers, bf16 state, 300 MiB 207 us, where one
+// column per lane and words in scalar registers had taken 184.  A tile of few
+// workers leaves room in LDS for a copy of them per wavefront: 164 us.
 #include <algorithm>
 
 #include "detag_internal.h"
@@ -53,16 +58,36 @@ struct Op {
 constexpr int kOpWords = sizeof(Op) / 4;
 
 // Lanes side by side that take a row.  Few workers make few rows that can be done side by side and a tile that is soon
-// loaded: wider rows keep the wavefronts busy (8, 16 and 32 lanes: n = 8, d = 3,000,000 79, 54, 40 us; n = 16, d = 272,474
-// 13.6, 11.0, 10.9; n = 24, d = 400,000 18.5, 16.5, 20; n = 40, d = 200,000 15, 16, 17; n = 64, d = 272,474 30, 33, 48).
-constexpr int lanes_per_row(int n) { return n <= 12 ? 32 : n <= 24 ? 16 : 8; }
+// loaded: wider rows keep the wavefronts busy, and their pieces of a row fill the cache lines, until the tiles leave too few
+// wavefronts on a compute unit (8, 16 and 32 lanes; fp32 unless said otherwise, 4-regular: n = 8, 300 MiB of bf16 -, 171,
+// 142 us; n = 12, 64 MiB of bf16 -, 38, 34, 300 MiB -, 158, 180; n = 16, 4 MiB -, 5.8, 6.6, 300 MiB -, 125, 125, of a ring -,
+// 132, 126; n = 24, 300 MiB 129, 126, -; n = 28, 24 MiB 12.3, 11.1, -, 160 MiB 75, 68, -, of bf16 64 MiB 41, 37, -, 160 MiB
+// 126, 108, -; n = 32, 64 MiB of bf16 36, 40, -, 300 MiB 216, 216, -; n = 40, 160 MiB 77, 70, -; ring of 48, 300 MiB 171, 142,
+// 163; n = 64, 64 MiB 29, 32, 38).
+int lanes_per_row(const Shape &s) {
+  const int64_t mib = fused::footprint(s, s.bf16 ? 2 : 4) >> 20;
+  if (s.bf16) return s.n <= 8 || (s.n <= 12 && mib < 88) ? 32 : s.n <= 24 || (s.n <= 32 && mib >= 88) ? 16 : 8;
+  const int narrow = mib >= 256 ? 48 : mib >= 128 ? 40 : mib >= 16 ? 32 : 24;  // up to here, 16 lanes
+  return s.n <= (mib >= 16 ? 16 : 12) ? 32 : s.n <= narrow ? 16 : 8;
+}
+// Whether each wavefront has a copy of its table behind the tiles.  It pays while wavefronts enough remain (table in memory
+// and in LDS, 300 MiB: fp32 n = 16 131 and 125 us, 32 135 and 133, 40 133 and 127; bf16 n = 8 184 and 142, 16 207 and 164, 20
+// 179 and 157, but n = 12 in rows of 32 lanes 64 MiB 34 and 36, ring of 24 221 and 243); a long one only where the rows crowd
+// vector memory (bf16, ring of 16 64 MiB 41 and 42, 88 MiB 68 and 62), and small calls do without (fp32 n = 24, 4 MiB 5.0 and
+// 5.4; bf16 n = 16, 20 MiB 16.2 and 17.0).
+bool table_in_lds(const Shape &s, size_t tile_bytes, size_t table_bytes) {
+  const int lanes = lanes_per_row(s);
+  const int64_t mib = fused::footprint(s, s.bf16 ? 2 : 4) >> 20;
+  if (lanes == 8 || mib < (s.bf16 && lanes == 16 ? 32 : 16) || (s.bf16 && s.n > (lanes == 32 ? 8 : 20))) return false;
+  return table_bytes * 4 <= tile_bytes || mib >= (s.bf16 ? 88 : 80);
+}
 template <int LPR>
 struct Layout {
   static constexpr int kCols = 4 * LPR, kGroup = 64 / LPR;  // columns of a wavefront, rows done side by side
   static constexpr uint32_t kRowBytes = kCols * 4;
 };
-constexpr int kAhead = 4;   // slots fetched ahead; their number is a multiple of it
-constexpr int kChunk = 8;   // rows a lane loads or stores together
+constexpr int kSlotsPadded = 4;  // the number of slots is a multiple of it
+constexpr int kChunk = 8;        // rows a lane loads or stores together
 
 // What a row of a group does in a slot: the LDS offsets of two source rows (the second in the upper half of the word), the
 // offset of the written row with kLast in the group's last slot, two fp32 weights.
@@ -72,9 +97,10 @@ struct alignas(16) Entry {
 };
 constexpr uint32_t kLast = 1u << 16;
 
-template <typename ST, int LPR, Access A>
-__global__ __launch_bounds__(256, 7) void factor_sequence_kernel(ST *Z, int n, int64_t d, int64_t ld,
-                                                              const Entry *__restrict__ table, int slots) {
+template <typename ST, int LPR, bool TABLE_IN_LDS, Access A>
+__global__ __launch_bounds__(256, TABLE_IN_LDS ? 8 : 7) void factor_sequence_kernel(ST *Z, int n, int64_t d, int64_t ld,
+                                                                                 const Entry *__restrict__ table, int slots) {
+  constexpr int kAhead = TABLE_IN_LDS ? 2 : kSlotsPadded;
   constexpr int kCols = Layout<LPR>::kCols, kGroup = Layout<LPR>::kGroup;
   constexpr uint32_t kRowBytes = Layout<LPR>::kRowBytes;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
@@ -83,10 +109,21 @@ __global__ __launch_bounds__(256, 7) void factor_sequence_kernel(ST *Z, int n, i
   const int64_t first = (fused::xcd_tile(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + w) * kCols;
   if (first >= d) return;  // no barrier anywhere below
   const uint32_t tile = w * uint32_t(n + 1) * kRowBytes + (lane % LPR) * 16u;  // the lane's columns of row 0
+  const uint32_t copy = (blockDim.x >> 6) * uint32_t(n + 1) * kRowBytes + w * uint32_t(slots) * (kGroup * 16u);
+  auto entry = [&](int slot) {
+    if constexpr (TABLE_IN_LDS) return __builtin_bit_cast(Entry, lds_read(copy + (slot * kGroup + lane / LPR) * 16u));
+    else return table[slot * kGroup + lane / LPR];
+  };
   Entry ahead[kAhead];
-  const Entry *mine = table + group;
+  auto fetch_first = [&] {
 #pragma unroll
-  for (int q = 0; q < kAhead; ++q) ahead[q] = mine[q * kGroup];
+    for (int q = 0; q < kAhead; ++q) ahead[q] = entry(q);
+  };
+  if constexpr (TABLE_IN_LDS) {
+    for (int q = int(lane); q < slots * kGroup; q += 64) lds_write(copy + q * 16u, *reinterpret_cast<const f4 *>(table + q));
+  } else {
+    fetch_first();
+  }
   Columns c{first + (lane % LPR) * 4, 0};
   const int kind = d - first >= kCols ? kWhole : d - first >= 4 ? kCut : kNarrow;
   if (kind == kCut && c.at > d - 4) c = Columns{d - 4, int(c.at - (d - 4))};
@@ -111,12 +148,14 @@ __global__ __launch_bounds__(256, 7) void factor_sequence_kernel(ST *Z, int n, i
       each_row(r0, kind_of, [&](auto, int k, int row) { lds_write(tile + uint32_t(row) * kRowBytes, v[k]); });
     }
   });
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // lanes read what others wrote
+  if constexpr (TABLE_IN_LDS) fetch_first();
   f4 acc = {0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < slots; s += kAhead) {
 #pragma unroll
     for (int q = 0; q < kAhead; ++q) {
       const Entry e = ahead[q];
-      ahead[q] = mine[(s + kAhead < slots ? s + kAhead + q : q) * kGroup];
+      ahead[q] = entry(s + kAhead < slots ? s + kAhead + q : q);
       acc = fma4(e.w0, lds_read(tile + (e.from & 0xffffu)), acc);
       acc = fma4(e.w1, lds_read(tile + (e.from >> 16)), acc);
       if (__builtin_amdgcn_readfirstlane(e.to) & kLast) {  // the same in all groups
@@ -158,11 +197,17 @@ int max_lds_per_block() {
 // How the sequence treats the caches: as the other tile kernels where tiles share cache lines (64 x 1,000,001 streamed,
 // loads kept, all kept 249, 155, 131 us).  On lines, sequences that fit the memory-side cache beside other matrices leave
 // the loads to it (64 x 272,474 31.5, 30.4, 29.9; 8 x 3,000,000 of bf16 30.7, 25.3, 25.2), small ones with fp32 state do not
-// (16 x 272,474 9.9, 11.0, 11.1), large ones stream (64 x 1,000,000 109, 117, 118).
+// (16 x 272,474 9.9, 11.0, 11.1; with a copy of the table in LDS they do from 26 MiB on, 9 x 850,000 15.3, 13.5, -), large
+// ones stream (64 x 1,000,000 109, 117, 118; 16 workers, bf16, 88 MiB 53, 54, 55, 160 MiB 88, 94, 94).  Pieces of half a line
+// (8 lanes to a row of bf16) are left to the caches up to 64 workers: 64 workers 24 MiB 24.4, 22.4, 22.3, 88 MiB 73, 74, 72,
+// 300 MiB 261, 251, 241, 40 workers 300 MiB 231, 218, 213; but 128 workers 104 MiB 115, 121, 122 and 256 workers 300 MiB 555,
+// 590, 599.
 Access sequence_access(const Shape &s, const void *Z) {
   if (fused::shares_lines(s, {Z})) return kKeep;
   const int64_t mib = fused::footprint(s, s.bf16 ? 2 : 4) >> 20;
-  return mib >= 96 || (mib < 32 && !s.bf16) ? kStream : kKeepReads;
+  const bool narrow = lanes_per_row(s) == 8;
+  if (s.bf16) return narrow && s.n <= 64 ? kKeep : mib >= (narrow ? 96 : 88) ? kStream : kKeepReads;
+  return mib >= 96 || mib < (narrow ? 32 : 26) ? kStream : kKeepReads;
 }
 
 struct Row {  // a row of a factor that is not an identity row
@@ -275,14 +320,14 @@ bool build_factor_table(int n, const std::vector<HostFactor> &factors, std::vect
 // The table of factor_sequence_kernel from the program above: the program's row operations in order, each put into the
 // first group that comes after the writers of the rows it reads and of the row it writes, and not before the readers of
 // that row's old value.
-void build_factor_entries(int n, const std::vector<uint32_t> &program, std::vector<uint32_t> &table) {
+void build_factor_entries(const Shape &s, const std::vector<uint32_t> &program, std::vector<uint32_t> &table) {
   struct Terms {
     int dst, cnt;
     uint32_t from[kTerms];
     float w[kTerms];
   };
-  const int kGroup = 64 / lanes_per_row(n);
-  const uint32_t kRowBytes = 16u * uint32_t(lanes_per_row(n));
+  const int n = s.n, kGroup = 64 / lanes_per_row(s);
+  const uint32_t kRowBytes = 16u * uint32_t(lanes_per_row(s));
   std::vector<Op> ops(program.size() / kOpWords);
   if (!ops.empty()) __builtin_memcpy(ops.data(), program.data(), program.size() * 4);
   std::vector<std::vector<Terms>> groups;
@@ -322,16 +367,18 @@ void build_factor_entries(int n, const std::vector<uint32_t> &program, std::vect
         entries.push_back(e);
       }
   }
-  while (entries.size() % (kAhead * kGroup)) entries.push_back(Entry{zero | zero << 16, zero | kLast, 0.f, 0.f});
+  while (entries.size() % (kSlotsPadded * kGroup)) entries.push_back(Entry{zero | zero << 16, zero | kLast, 0.f, 0.f});
   table.resize(entries.size() * (sizeof(Entry) / 4));
   if (!entries.empty()) __builtin_memcpy(table.data(), entries.data(), entries.size() * sizeof(Entry));
 }
 
 // -1: a tile of n rows does not fit the LDS of a block on this device (the caller applies the factors one by one).
 int launch_factor_sequence(const Shape &s, const uint32_t *table, int table_words, void *Z, void *stream) {
-  const int lpr = lanes_per_row(s.n), cols = 4 * lpr, slots = table_words / int(sizeof(Entry) / 4) / (64 / lpr);
+  const int lpr = lanes_per_row(s), cols = 4 * lpr, slots = table_words / int(sizeof(Entry) / 4) / (64 / lpr);
   if (slots == 0) return 0;  // every row of every factor is an identity row
-  const size_t tile_bytes = size_t(s.n + 1) * 16 * lpr, lds_max = size_t(max_lds_per_block());
+  const size_t rows_bytes = size_t(s.n + 1) * 16 * lpr, table_bytes = size_t(table_words) * 4;
+  const bool in_lds = table_in_lds(s, rows_bytes, table_bytes);
+  const size_t tile_bytes = rows_bytes + (in_lds ? table_bytes : 0), lds_max = size_t(max_lds_per_block());
   // wavefronts per block: whatever keeps most wavefronts on a compute unit, larger blocks on a tie while they
   // stay within the 64 KiB a launch may ask for without raising the kernel's limit
   int waves = 0, resident = 0;
@@ -356,8 +403,13 @@ int launch_factor_sequence(const Shape &s, const uint32_t *table, int table_word
     return 0;
   };
   auto with = [&](auto lanes, auto access) {
-    return s.bf16 ? launch(&factor_sequence_kernel<bf16_t, lanes, access>, static_cast<bf16_t *>(Z))
-                  : launch(&factor_sequence_kernel<float, lanes, access>, static_cast<float *>(Z));
+    auto go = [&](auto in_lds) {
+      return s.bf16 ? launch(&factor_sequence_kernel<bf16_t, lanes, in_lds, access>, static_cast<bf16_t *>(Z))
+                    : launch(&factor_sequence_kernel<float, lanes, in_lds, access>, static_cast<float *>(Z));
+    };
+    if constexpr (lanes >= 16)
+      if (in_lds) return go(std::true_type{});
+    return go(std::false_type{});
   };
   auto with_lanes = [&](auto access) {
     return lpr == 32   ? with(std::integral_constant<int, 32>{}, access)

@@ -65,3 +65,34 @@ def test_the_layout_of_the_rows_does_not_change_the_bits(dtype):
             f.close()
             ctx.close()
         assert torch.equal(runs[0], runs[1]) and torch.equal(runs[0], runs[2]), d
+
+
+@pytest.mark.parametrize("n", [3, 8, 9, 12, 13, 16, 20, 21, 24, 25, 28, 32, 33, 40])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_large_calls_of_few_workers_give_the_bits_of_small_ones(n, dtype):
+    """The lanes to a row, and whether a wavefront copies its table to LDS, depend on the size of a call (16, 80 and 88 MiB) for
+    up to 40 workers."""
+    few, edges = 1003, np.array([(max(0, i - 2), i) for i in range(1, n)], np.int32)   # a deep tree: a long table
+    for topo in (D.Topology.from_edges(_graph(n, np.random.default_rng(n))), D.Topology.from_edges(edges)):
+        size = 2 if dtype == torch.bfloat16 else 4
+        for mib in (17, 89):
+            many = (mib << 20) // (n * size) + 3
+            g = torch.Generator(device="cuda")
+            g.manual_seed(n)
+            values, runs = torch.empty(n, many, device="cuda").normal_(generator=g) + 1.0, []
+            for d, ld in ((few, few), (many, D.padded_ld(many)), (many, many | 1)):
+                Z = torch.full((n, ld), SENTINEL, device="cuda", dtype=dtype)
+                Z[:, :d] = values[:, :d]
+                want, largest = Z[:, :d].double().mean(0), Z[:, :d].double().abs().amax(0)
+                ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if dtype == torch.bfloat16 else D.DETAG_F32)
+                f = D.Factors(ctx, 0)
+                assert f.program().shape[0] > 0
+                f.average(Z)
+                torch.cuda.synchronize()
+                bound = 8 * f.R * 2.0 ** -24 * largest.max() + (2.0 ** -8 * want.abs() if dtype == torch.bfloat16 else 0.0)
+                assert ((Z[:, :d].double() - want).abs() <= bound).all(), (d, ld)
+                assert torch.equal(Z[:, d:], torch.full_like(Z[:, d:], SENTINEL))
+                runs.append(Z[:, :d])
+                f.close()
+                ctx.close()
+            assert torch.equal(runs[1], runs[2]) and torch.equal(runs[0], runs[1][:, :few]), mib
