@@ -56,10 +56,36 @@ inline bool loads_stream(const Shape &s, int per_element) { return footprint(s, 
 // before the other tile wants it, or goes to memory half written.  Streamed and kept, fp32, pitch 1,000,003, K = 4: phase,
 // torus 8x8 388 and 296 us, one round 165 and 145, gradient-fused step 465 and 364; ring of 16, pitch 600,001 52 and 50, 65
 // and 60.  On lines streaming is 2 to 10 % ahead.
-// The phase and the fused step of the ATC form with bf16 state stream on half lines too (torus 8x8, pitch 1,000,032: 338 and
-// 355 us, 336 and 341; pitch 1,000,003 368 and 352, 420 and 338): `line` = 64.
+// A kernel may set another mark than the line: rows that start on a multiple of `line` bytes stream.
 inline Access tile_access(const Shape &s, int per_element, std::initializer_list<const void *> matrices, uint64_t line = 128) {
   return footprint(s, per_element) > (int64_t(80) << 20) && !shares_lines(s, matrices, line) ? kStream : kKeep;
+}
+
+// The mark of the register-resident kernels.  Few rows share few lines, and a row of bf16 state that starts on half a line
+// shares with one neighbour.  Streamed and kept, bf16 rows on half lines: the ATC phase and the step fused with it (torus
+// 8x8, pitch 1,000,032: 338 and 355 us, 336 and 341; pitch 1,000,003 368 and 352, 420 and 338); Algorithm 2's phase, ring of
+// 4, 220 MiB a call 63 and 67, 800 MiB 209 and 213, ring of 16 100 MiB 29 and 27, 220 MiB 61 and 64, 300 MiB 91 and 86; the
+// D-PSGD step, ring of 16, 220 MiB 60 and 63, 800 MiB 220 and 218; plain gossip, ring of 8, 100 MiB 44 and 44, 400 MiB 169 and
+// 175, ring of 16 181 and 174; one round, ring of 8, 100 MiB 21 and 24, torus 8x8, 140 MiB 31 and 33, 300 MiB 69 and 67.
+// Wherever the rows start, ring of 4: one round, fp32, 100 MiB 19 and 21, 400 MiB 76 and 78; plain gossip, fp32, 100 MiB 39
+// and 38, 300 MiB 116 and 121, bf16 100 MiB 52 and 55; the D-PSGD step, fp32, 140 MiB 41 and 43, 800 MiB 250 and 238, bf16 204
+// and 211; ring of 8, one round, bf16, 300 MiB 80 and 65.
+enum Form : int { kGossipForm, kAtcForm, kAlg2Form, kDpsgdForm, kRoundForm };
+inline uint64_t register_line(const Shape &s, int per_element, Form form) {
+  const int64_t mib = footprint(s, per_element) >> 20;
+  const bool few = s.n <= 8;
+  if (s.n <= 4) {
+    if (form == kRoundForm && mib >= 96) return 1;
+    if (form == kGossipForm && mib >= (s.bf16 ? 96 : 128)) return 1;
+    if (form == kDpsgdForm && mib >= 128 && (s.bf16 || mib < 200)) return 1;
+  }
+  if (!s.bf16) return 128;
+  switch (form) {
+    case kAtcForm: return 64;
+    case kRoundForm: return mib >= 96 && (few || mib < 200) ? 64 : 128;
+    case kGossipForm: return mib >= 128 && few ? 64 : 128;
+    default: return mib >= 128 && (few || mib < 280) ? 64 : 128;
+  }
 }
 
 template <int N>

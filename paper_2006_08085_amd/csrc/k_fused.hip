@@ -187,7 +187,8 @@ int launch_s(const Shape &s, int mode, void *X, void *Y, const float *Gn, const 
     return s.bf16 ? launch_t<T, bf16_t, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream)
                   : launch_t<T, float, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream);
   };
-  const uint64_t line = s.bf16 && mode == 1 ? 64 : 128;
+  static_assert(kGossipForm == 0 && kAtcForm == 1 && kAlg2Form == 2 && kDpsgdForm == 3, "the modes in order");
+  const uint64_t line = register_line(s, per_element, Form(mode));
   return tile_access(s, per_element, {X, Y, Gn, Go}, line) == kStream ? go(AccessTag<kStream>{}) : go(AccessTag<kKeep>{});
 }
 
@@ -222,7 +223,8 @@ int launch_structured_round(const Shape &s, const HostW &W, const void *cur, con
       else go(&structured_round_kernel<T, float, access>, float{});
       return hip_rc(hipGetLastError());
     };
-    const Access access = tile_access(s, 3 * (s.bf16 ? 2 : 4), {cur, prev, out});
+    const int per_element = 3 * (s.bf16 ? 2 : 4);
+    const Access access = tile_access(s, per_element, {cur, prev, out}, register_line(s, per_element, kRoundForm));
     return access == kStream ? with(AccessTag<kStream>{}) : with(AccessTag<kKeep>{});
   });
 }

@@ -220,7 +220,7 @@ int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float 
     if (s.bf16) with_h(access, static_cast<bf16_t *>(X));
     else with_h(access, static_cast<float *>(X));
   };
-  const uint64_t line = s.bf16 && !alg2 ? 64 : 128;
+  const uint64_t line = register_line(s, per_element, alg2 ? kAlg2Form : kAtcForm);
   if (tile_access(s, per_element, {X, Y, G, hpw ? h : nullptr, b}, line) == kStream) with_type(AccessTag<kStream>{});
   else with_type(AccessTag<kKeep>{});
   return hip_rc(hipGetLastError());

@@ -93,6 +93,21 @@ def test_tiles_of_128_and_256_columns_beyond_the_caches(kind, n, dtype):
             assert torch.equal(got, want), (d, k)
 
 
+@pytest.mark.parametrize("kind,n", [("ring", 4), ("ring", 8), ("ring", 16)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rings_at_odd_and_half_pitches(kind, n, dtype):
+    """Register-resident calls: where rows may start for a call to stream depends on its form, up to 280 MiB."""
+    for elements in (9_000_000, 18_000_000, 34_000_000):
+        d = elements // n // 64 * 64 + 31
+        g = torch.Generator(device=DEV)
+        g.manual_seed(d)
+        values = [torch.empty(n, d, device=DEV).normal_(generator=g) for _ in range(5)]
+        on_lines = _all_calls(D.Topology.ring(), n, d, D.padded_ld(d), 0, dtype, values)
+        for ld in (d, d + 1):
+            for k, (got, want) in enumerate(zip(_all_calls(D.Topology.ring(), n, d, ld, 0, dtype, values), on_lines)):
+                assert torch.equal(got, want), (d, ld, k)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_row_walking_kernels_on_both_sides_of_128_mib(dtype):
     """Their loads stream from 128 MiB a call on: the same columns, alone and as part of a call beyond that."""
