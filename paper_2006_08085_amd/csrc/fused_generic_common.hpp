@@ -270,7 +270,9 @@ struct HalfRounds {
   }
   __device__ __forceinline__ int row(const Args &a, const Place &p, int s) const { return a.rows[p.pos(s)]; }
 
-  __device__ __forceinline__ f4 neighbour(int s, int k) const { return lds_read(k & 1 ? w[s][k / 2] >> 16 : w[s][k / 2] & 0xffffu); }
+  __device__ __forceinline__ f4 neighbour(int s, int k) const {
+    return lds_read(k & 1 ? w[s][k / 2] >> 16 : w[s][k / 2] & 0xffffu);
+  }
   // Difference by difference, pairwise.  The sum of the neighbours, rounded at DEG times the magnitude of z, would take
   // three instructions less of nine and leave a quarter more error against 64 bits than the lists in LDS (300 workers,
   // 4-regular, K = 8: 5.8e-8 against 4.6e-8; so 4.6e-8).

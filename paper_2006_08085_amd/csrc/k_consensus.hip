@@ -357,8 +357,8 @@ void build_factor_entries(const Shape &s, const std::vector<uint32_t> &program, 
     for (const Terms &t : rows) slots = std::max(slots, (t.cnt + 1) / 2);
     for (int s = 0; s < slots; ++s)
       for (int q = 0; q < kGroup; ++q) {
-        Entry e{zero | zero << 16, (q < int(rows.size()) ? uint32_t(rows[q].dst) * kRowBytes : zero) | (s + 1 == slots ? kLast : 0u),
-                0.f, 0.f};
+        const uint32_t to = q < int(rows.size()) ? uint32_t(rows[q].dst) * kRowBytes : zero;
+        Entry e{zero | zero << 16, to | (s + 1 == slots ? kLast : 0u), 0.f, 0.f};
         if (q < int(rows.size())) {
           const Terms &t = rows[q];
           if (2 * s < t.cnt) e.from = (e.from & ~0xffffu) | t.from[2 * s] * kRowBytes, e.w0 = t.w[2 * s];

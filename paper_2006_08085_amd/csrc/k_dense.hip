@@ -133,7 +133,8 @@ __device__ __forceinline__ void stage_unit(uint16_t *stage, int u, int w, int la
         } else if constexpr (PRE == kPreY) {
           v[c][e] = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
         } else if constexpr (PRE == kPreXminusAlphaY) {
-          const float x = buf_load<ST, A>(row_of(X, tile, ld, rr, ok), so), y = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
+          const float x = buf_load<ST, A>(row_of(X, tile, ld, rr, ok), so);
+          const float y = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
           v[c][e] = fmaf(-alpha, y, x);
         } else {
           const float y = buf_load<ST, A>(row_of(Y, tile, ld, rr, ok), so);
@@ -288,7 +289,8 @@ __global__ __launch_bounds__(kThreads, TP >= 3 ? 2 : 3) void dense_phase_kernel(
   f32x16 acc[2][2];
   auto store_rows = [&](ST *out) {
     if (rows_mine)
-      write_out(acc, scratch, w, lane, n, [&](int row, float v) { buf_store<ST, A>(row_of(out, tile, ld, row, valid), so, v); });
+      write_out(acc, scratch, w, lane, n,
+                [&](int row, float v) { buf_store<ST, A>(row_of(out, tile, ld, row, valid), so, v); });
   };
   if constexpr (MODE == 0) {
     pass<ST, TP, TU, kPreX, KS, A>(acc, stage, true, rows_mine, w, lane, X, Y, Gn, Go, n, tile, ld, valid, alpha, frag);
@@ -350,9 +352,9 @@ int launch_ks(const Shape &s, int mode, void *X, void *Y, const float *Gn, const
   // of up to 80 MiB that read a matrix twice (streamed and kept, K = 4, three states in turn: Algorithm 2's phase of 64 workers
   // 64 MiB 56.8 and 41.8 us, 96 MiB 86.7 and 82.4, 126 MiB 96.4 and 98.5; the ATC phase of 128 workers 80 MiB 79.7 and 75.0,
   // 96 MiB 81.2 and 90.6, 126 MiB 88.2 and 104.5; with bf16 state 256 workers 40 MiB 40.3 and 45.4, which streams), nor plain
-  // gossip of fp32 state from 32 to 80 MiB (128 workers 14 MiB 14.3 and 15.2, 40 MiB 33.3 and 33.1, 80 MiB 58.3 and 55.1, 96 MiB
-  // 69.9 and 75.3; 256 workers 64 MiB 58.5 and 52.4).  A kernel for each: the choice made at run time cost the aligned one 0.6
-  // to 5 %.
+  // gossip of fp32 state from 32 to 80 MiB (128 workers 14 MiB 14.3 and 15.2, 40 MiB 33.3 and 33.1, 80 MiB 58.3 and 55.1, 96
+  // MiB 69.9 and 75.3; 256 workers 64 MiB 58.5 and 52.4).  A kernel for each: the choice made at run time cost the aligned one
+  // 0.6 to 5 %.
   const int state = sizeof(ST);
   const int64_t bytes = fused::footprint(s, mode == 0 ? state : 2 * state + 8);
   const bool gains = mode == 2 || (!s.bf16 && (mode == 1 || bytes >= 32 * kMiB));

@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kThreads) void mean_kernel(int n, int64_t d, int64_
   double s = 0.0;
 #pragma unroll 16
   for (int i = 0; i < n; ++i) s += double(load_f32<NT>(X + int64_t(i) * ld + c));  // 16 rows' loads in flight
-  __builtin_nontemporal_store(float(s / n), xbar + c);  // 64 x 11.2 M: 465 us with a plain store, 453 so
+  __builtin_nontemporal_store(float(s / n), xbar + c);  // 64 x 11.2 M: 465 us with a plain store, 453 so; up to 64 x 1,000,000 the same
 }
 
 template <int THREADS = kThreads>
@@ -140,8 +140,12 @@ int launch_consensus_error(const Shape &s, const void *X, double *partials, doub
   auto st = static_cast<hipStream_t>(stream);
   auto go = [&](auto *kernel, auto *x) { kernel<<<dim3(blocks), kThreads, 0, st>>>(s.n, s.d, s.ld, x, partials); };
   const bool nt = fused::tile_access(s, s.bf16 ? 2 : 4, {X}) == kStream;
-  if (s.bf16) go(nt ? &consensus_partial_kernel<bf16_t, true> : &consensus_partial_kernel<bf16_t, false>, static_cast<const bf16_t *>(X));
-  else go(nt ? &consensus_partial_kernel<float, true> : &consensus_partial_kernel<float, false>, static_cast<const float *>(X));
+  auto with = [&](auto *x) {
+    using ST = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
+    go(nt ? &consensus_partial_kernel<ST, true> : &consensus_partial_kernel<ST, false>, x);
+  };
+  if (s.bf16) with(static_cast<const bf16_t *>(X));
+  else with(static_cast<const float *>(X));
   int rc = hip_rc(hipGetLastError());
   if (rc) return rc;
   sum_partials_kernel<<<1, kSumThreads, 0, st>>>(blocks, partials, out);

@@ -38,7 +38,8 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
   } else if constexpr (MODE == 1) {
     // every input is read once: the second gossip's input Y + Gn - Go waits in registers under the first
     rows([&](auto F, int s, int64_t off, Columns c, bool) {
-      const f4 x = load4<F, A>(X, off, c, d), y = load4<F, A>(Y, off, c, d), gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d);
+      const f4 x = load4<F, A>(X, off, c, d), y = load4<F, A>(Y, off, c, d);
+      const f4 gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d);
       z[s] = fma4(-alpha, y, x);
       f4 t = y + gn - go;
       pin4(t);  // the sum now, not its three operands carried through the rounds
@@ -202,6 +203,24 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
       }
     }
   auto offset = [&](int p) { return uint32_t(p) * g.cols * 4u; };
+  // with weights of their own the lists stay in LDS: offsets in registers (16 of them, and one wavefront less per SIMD) and
+  // only the weights there measured -16 to +13 % (D-PSGD step and Algorithm 2's phase of 48 and 200 irregular workers 112 ->
+  // 125 us and 153 -> 166)
+  if (g.slots == kSlotsMax && maxdeg <= 8 && one_weight) {
+    out.half_deg = maxdeg <= 2 ? 2 : maxdeg <= 4 ? 4 : 8;
+    out.weight = weight;
+    out.offsets.assign(size_t(positions) * out.half_deg / 2, 0u);
+    for (int p = 0; p < positions; ++p) {
+      const int i = out.rows[p];
+      size_t k = size_t(p) * out.half_deg;
+      auto put = [&](uint32_t off) { out.offsets[k / 2] |= off << (16 * (k % 2)), ++k; };
+      if (i >= 0)
+        for (int t = W.rowptr[i]; t < W.rowptr[i + 1]; ++t)
+          if (W.colidx[t] != i) put(offset(position[W.colidx[t]]));
+      while (k < size_t(p + 1) * out.half_deg) put(offset(p));  // a missing neighbour is the row itself: difference zero
+    }
+    return true;
+  }
   for (int w = 0; w < waves; ++w)
     for (int s = 0; s < g.slots; ++s) {
       const int p0 = s * per_slot + w * rows_per_wave;
@@ -227,25 +246,6 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
             out.pairs.push_back(bits);
           }
     }
-  // with weights of their own the lists stay in LDS: offsets in registers (16 of them, and one wavefront less per SIMD) and
-  // only the weights there measured -16 to +13 % (D-PSGD step and Algorithm 2's phase of 48 and 200 irregular workers 112 ->
-  // 125 us and 153 -> 166)
-  if (g.slots == kSlotsMax && maxdeg <= 8 && one_weight) {
-    out.half_deg = maxdeg <= 2 ? 2 : maxdeg <= 4 ? 4 : 8;
-    out.weight = weight;
-    out.offsets.assign(size_t(positions) * out.half_deg / 2, 0u);
-    for (int p = 0; p < positions; ++p) {
-      const int i = out.rows[p];
-      size_t k = size_t(p) * out.half_deg;
-      auto put = [&](uint32_t off) { out.offsets[k / 2] |= off << (16 * (k % 2)), ++k; };
-      if (i >= 0)
-        for (int t = W.rowptr[i]; t < W.rowptr[i + 1]; ++t)
-          if (W.colidx[t] != i) put(offset(position[W.colidx[t]]));
-      while (k < size_t(p + 1) * out.half_deg) put(offset(p));  // a missing neighbour is the row itself: difference zero
-    }
-    out.groups.clear(), out.pairs.clear();
-    return true;
-  }
   const size_t lds = g.tile_bytes(0) + out.pairs.size() * 4;
   if (lds > kLdsMax || lopsided(g, lds, n * d, maxdeg, entries)) {
     out = LdsTableHost{};

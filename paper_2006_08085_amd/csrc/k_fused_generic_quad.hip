@@ -78,27 +78,27 @@ int launch_fused_generic_quadratic(const Shape &s, const LdsTable &t, void *X, v
     if constexpr (std::is_same_v<typename R::Args, HalfArgs>) {
       return -1;  // more than 256 workers: no fused step
     } else {
-    auto go = [&](auto *kernel, auto *x, auto *y) -> int {
-      if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
-      kernel<<<dim3(ceil_div_i64(s.d, g.cols)), g.threads, lds, static_cast<hipStream_t>(stream)>>>(
-          x, y, G, h, b, s.n, s.d, s.ld, g.lpr_log2(), ra, eta, alpha, K, sigma, uint32_t(seed & 0xffffffffu),
-          uint32_t(seed >> 32), step);
-      return hip_rc(hipGetLastError());
-    };
-    auto with = [&](auto access) {
-      if (s.bf16) {
-        auto *x = static_cast<bf16_t *>(X), *y = static_cast<bf16_t *>(Y);
-        return h_per_worker ? go(&fused_generic_quadratic_kernel<bf16_t, true, R, access>, x, y)
-                            : go(&fused_generic_quadratic_kernel<bf16_t, false, R, access>, x, y);
-      }
-      auto *x = static_cast<float *>(X), *y = static_cast<float *>(Y);
-      return h_per_worker ? go(&fused_generic_quadratic_kernel<float, true, R, access>, x, y)
-                          : go(&fused_generic_quadratic_kernel<float, false, R, access>, x, y);
-    };
-    const int per_element = (s.bf16 ? 4 : 8) + 8 + (h_per_worker ? 4 : 0);
-    // blocks of 1024 threads, two to a compute unit, are better off streaming: 256 x 30,001 53.3, 62.8, 72.2 us
-    const Call call = g.threads <= 512 ? kFusedStep : kAtc;
-    return with_access<R>(s, g, call, per_element, {X, Y, G, h_per_worker ? h : nullptr, b}, with);
+      auto go = [&](auto *kernel, auto *x, auto *y) -> int {
+        if (int rc = allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
+        kernel<<<dim3(ceil_div_i64(s.d, g.cols)), g.threads, lds, static_cast<hipStream_t>(stream)>>>(
+            x, y, G, h, b, s.n, s.d, s.ld, g.lpr_log2(), ra, eta, alpha, K, sigma, uint32_t(seed & 0xffffffffu),
+            uint32_t(seed >> 32), step);
+        return hip_rc(hipGetLastError());
+      };
+      auto with = [&](auto access) {
+        if (s.bf16) {
+          auto *x = static_cast<bf16_t *>(X), *y = static_cast<bf16_t *>(Y);
+          return h_per_worker ? go(&fused_generic_quadratic_kernel<bf16_t, true, R, access>, x, y)
+                              : go(&fused_generic_quadratic_kernel<bf16_t, false, R, access>, x, y);
+        }
+        auto *x = static_cast<float *>(X), *y = static_cast<float *>(Y);
+        return h_per_worker ? go(&fused_generic_quadratic_kernel<float, true, R, access>, x, y)
+                            : go(&fused_generic_quadratic_kernel<float, false, R, access>, x, y);
+      };
+      const int per_element = (s.bf16 ? 4 : 8) + 8 + (h_per_worker ? 4 : 0);
+      // blocks of 1024 threads, two to a compute unit, are better off streaming: 256 x 30,001 53.3, 62.8, 72.2 us
+      const Call call = g.threads <= 512 ? kFusedStep : kAtc;
+      return with_access<R>(s, g, call, per_element, {X, Y, G, h_per_worker ? h : nullptr, b}, with);
     }
   });
 }

@@ -272,7 +272,8 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t
 // workers, 8 x 512 5.8 and 6.0, 8 workers, 64 x 1000 6.9 and 7.9).
 constexpr int kRecordedCols = 256;
 bool lstsq_is_small(const Shape &s, int m, void *stream) {
-  return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256 && (s.d <= kRecordedCols || !is_capturing(stream));
+  return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256 &&
+         (s.d <= kRecordedCols || !is_capturing(stream));
 }
 
 bool overlap(const void *p, size_t p_bytes, const void *q, size_t q_bytes) {
@@ -299,8 +300,12 @@ int launch_grad_quadratic(const Shape &s, const void *X, const float *h, int h_p
     kernel<<<grid, kThreads, 0, st>>>(s.n, s.d, s.ld, x, h, hstride, b, noise, sigma, slo, shi, step, G);
   };
   const bool nt = fused::loads_stream(s, (s.bf16 ? 2 : 4) + 8 + (h_per_worker ? 4 : 0) + (noise ? 4 : 0));
-  if (s.bf16) go(nt ? &grad_quadratic_kernel<bf16_t, true> : &grad_quadratic_kernel<bf16_t, false>, static_cast<const bf16_t *>(X));
-  else go(nt ? &grad_quadratic_kernel<float, true> : &grad_quadratic_kernel<float, false>, static_cast<const float *>(X));
+  auto with = [&](auto *x) {
+    using ST = std::remove_const_t<std::remove_pointer_t<decltype(x)>>;
+    go(nt ? &grad_quadratic_kernel<ST, true> : &grad_quadratic_kernel<ST, false>, x);
+  };
+  if (s.bf16) with(static_cast<const bf16_t *>(X));
+  else with(static_cast<const float *>(X));
   return hip_rc(hipGetLastError());
 }
 

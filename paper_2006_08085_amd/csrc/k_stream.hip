@@ -379,7 +379,8 @@ int launch_elementwise_t(const Shape &s, void *X, void *Y, const float *Gn, cons
   dim3 grid(ceil_div_i64(s.d, per_block), s.n);
   auto st = static_cast<hipStream_t>(stream);
   return with_loads(s, int(sizeof(ST)) * (MODE + 1) + 8, [&](auto nt) {
-    elementwise_kernel<ST, MODE, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go, alpha);
+    elementwise_kernel<ST, MODE, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go,
+                                                                alpha);
   });
 }
 
