@@ -94,12 +94,15 @@ class ByPhase:
         """The tracker (valid between phases)."""
         return self.y[0]
 
+    def _current_stream(self):
+        import torch
+        return torch.cuda.current_stream(self.X.device)
+
     def iteration(self, R: int, eta: float = -1.0):
         """One iteration of a phase of length R (the same R for all iterations of one phase)."""
-        import torch
         ctx, r, comm = self.ctx, self.r, self.comm
         if r == 0 and comm is not None:
-            comm.wait_stream(torch.cuda.current_stream(self.X.device))   # the last phase end produced Xt and Y
+            comm.wait_stream(self._current_stream())   # the last phase end produced Xt and Y
         # handed to the calls: entering and leaving a stream takes the host longer than they do
         on = comm.cuda_stream if comm is not None else None
         if self.granularity == "phase":
@@ -117,7 +120,7 @@ class ByPhase:
         self.r += 1
         if self.r == R:
             if comm is not None:                       # the stream that is current now: grad may have changed it
-                torch.cuda.current_stream(self.X.device).wait_stream(comm)
+                self._current_stream().wait_stream(comm)
             ctx.phase_end(self.X, self.xt[0], self.y[0], self.G_k, self.G_km1, self.alpha)
             self.G_k, self.G_km1 = self.G_km1, self.G_k
             self.r = 0
