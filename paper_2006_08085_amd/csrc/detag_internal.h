@@ -94,8 +94,8 @@ struct Shape {
 
 // The table the on-chip kernel reads, from a program of build_factor_table (n <= 256).
 void build_factor_entries(const Shape &s, const std::vector<uint32_t> &program, std::vector<uint32_t> &table);
-// Z <- A_{R-1} ... A_0 Z on chip, in place (table from build_factor_entries).  -1 if n rows of 32 columns do not
-// fit a block's LDS on this device.
+// Z <- A_{R-1} ... A_0 Z on chip, in place (table from build_factor_entries).  -1 if a wavefront's rows
+// (and its copy of the table) do not fit a block's LDS on this device.
 int launch_factor_sequence(const Shape &s, const uint32_t *table, int table_words, void *Z, void *stream);
 // The matrix polynomial of K rounds of Algorithm 3, P = p_K(W^T), as bf16 terms in the operand order of
 // dense_phase_kernel (`terms` = dense_poly_terms(state type), dense_poly_words(terms) 16-bit words).  false if n > 256.

@@ -64,7 +64,8 @@ __global__ __launch_bounds__(kThreads) void grad_quadratic_kernel(int n, int64_t
       // b, the noise array, per-worker curvature and G are touched once: large calls stream them.  X never: the step that
       // follows reads it again, and finds what the memory-side cache kept of it (this call and a step with K = 4, 64
       // workers, 4-regular, fp32, three states in turn: d = 300,000 140 -> 132 us, 1,000,000 428 -> 389, 2,000,000 852 ->
-      // 812; D-PSGD 87 -> 82, 272 -> 241, 550 -> 509; the round of Algorithm 1 that does not, 157 -> 166, 475, 935).
+      // 812; D-PSGD 87 -> 82, 272 -> 241, 550 -> 509).  The round of Algorithm 1 does not read X again: streamed and not, 139.5
+      // and 140.6, 442.6 and 444.7, 885.3 and 884.2; 300 workers, d = 200,000, factor by factor, 1395 and 1399.
       if constexpr (sizeof(ST) == 4) {
         const vf4_t t = load_wide<false>(reinterpret_cast<const vf4_t *>(X + off));
         x[0] = t.x, x[1] = t.y, x[2] = t.z, x[3] = t.w;
