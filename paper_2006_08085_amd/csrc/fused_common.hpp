@@ -42,9 +42,15 @@ inline int64_t footprint(const Shape &s, int per_element) { return int64_t(s.n) 
 
 // Whether the loads of a kernel that walks rows as they lie stream past the caches (its stores do in any case).  Up to
 // 128 MiB they find their matrices in the memory-side cache, three states in turn as well: phase end of 64 x 100,001
-// (122 MiB, fp32) 38.9 -> 34.2 us, gradient of 16 x 272,474 12.3 -> 11.2, accumulation 11.4 -> 10.4; from 146 MiB on the
-// update of model and tracker is 3 to 8 % slower so, at 200 MiB all of them but the gradient with one curvature per worker.
-inline bool loads_stream(const Shape &s, int per_element) { return footprint(s, per_element) > (int64_t(128) << 20); }
+// (122 MiB, fp32) 38.9 -> 34.2 us, gradient of 16 x 272,474 12.3 -> 11.2, accumulation 11.4 -> 10.4; at 200 MiB all of them
+// but the gradient with one curvature per worker are slower so.  The updates of tracker and model and the accumulation, which
+// read what they write and little else, up to 104 MiB (16 workers, streamed and kept: tracker 104 MiB 24.3 and 24.2, 126 MiB
+// 29.3 and 31.1; with the model 28.4 and 27.8, 33.5 and 35.6; accumulation 27.4 and 27.2, 32.7 and 34.5; phase end 31.1 and
+// 27.4, 38.0 and 34.5).
+constexpr int kRowLoadsMiB = 128, kUpdateLoadsMiB = 104;
+inline bool loads_stream(const Shape &s, int per_element, int up_to_mib = kRowLoadsMiB) {
+  return footprint(s, per_element) > (int64_t(up_to_mib) << 20);
+}
 
 // How the register-resident kernels and those with one launch per round treat the caches.
 // Small calls leave their matrices to the caches.  The memory-side cache holds 256 MB and a program has other matrices too:

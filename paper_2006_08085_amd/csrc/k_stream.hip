@@ -325,8 +325,8 @@ __global__ __launch_bounds__(kThreads) void convert_kernel(int64_t d, int64_t ld
 
 // Launches with launch(nt): whether the call's loads stream.
 template <class F>
-int with_loads(const Shape &s, int per_element, F &&launch) {
-  if (fused::loads_stream(s, per_element)) launch(std::true_type{});
+int with_loads(const Shape &s, int per_element, F &&launch, int up_to_mib = fused::kRowLoadsMiB) {
+  if (fused::loads_stream(s, per_element, up_to_mib)) launch(std::true_type{});
   else launch(std::false_type{});
   return hip_rc(hipGetLastError());
 }
@@ -378,10 +378,11 @@ int launch_elementwise_t(const Shape &s, void *X, void *Y, const float *Gn, cons
   const int per_block = kThreads * VEC;
   dim3 grid(ceil_div_i64(s.d, per_block), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  return with_loads(s, int(sizeof(ST)) * (MODE + 1) + 8, [&](auto nt) {
+  auto go = [&](auto nt) {
     elementwise_kernel<ST, MODE, nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go,
                                                                 alpha);
-  });
+  };
+  return with_loads(s, int(sizeof(ST)) * (MODE + 1) + 8, go, fused::kUpdateLoadsMiB);
 }
 
 template <typename TS, typename TD>
@@ -427,7 +428,8 @@ int launch_defacto_update(const Shape &s, void *X, void *Xt, float *G, float sca
 int launch_accumulate(const Shape &s, float *Gacc, const float *g, float scale, void *stream) {
   dim3 grid(ceil_div_i64(s.d, kThreads * VEC), s.n);
   auto st = static_cast<hipStream_t>(stream);
-  return with_loads(s, 8, [&](auto nt) { accumulate_kernel<nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale); });
+  auto go = [&](auto nt) { accumulate_kernel<nt><<<grid, kThreads, 0, st>>>(s.d, s.ld, Gacc, g, scale); };
+  return with_loads(s, 8, go, fused::kUpdateLoadsMiB);
 }
 
 template <typename ST>

@@ -110,7 +110,7 @@ def test_rings_at_odd_and_half_pitches(kind, n, dtype):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_row_walking_kernels_on_both_sides_of_128_mib(dtype):
-    """Their loads stream from 128 MiB a call on: the same columns, alone and as part of a call beyond that."""
+    """Their loads stream from 104 or 128 MiB a call on: the same columns, alone and as part of a call beyond that."""
     n, few, many = 16, 1003, 1_200_003
     g = torch.Generator(device=DEV)
     g.manual_seed(2)
