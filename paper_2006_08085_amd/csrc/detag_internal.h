@@ -107,6 +107,10 @@ bool build_dense_poly(const HostW &W, int K, double eta, int terms, std::vector<
 // mode 2: X <- P X - alpha * P Y (evaluated as P (X - alpha*Y)), Y <- P Y + Gn - Go.  n <= 256.
 int launch_dense_phase(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
                        const uint16_t *frag, void *stream);
+// The same for bf16 state with P in registers, where that serves (k_dense_bf16.hip).
+bool dense_resident_serves(const Shape &s, int mode);
+int launch_dense_resident(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
+                          const uint16_t *frag, void *stream);
 // out = A cur for a CSR matrix A whose rows need not sum to one (row i lists (j, A_ij)); out != cur.
 int launch_spmm(const Shape &s, const DevCsr &a, const void *cur, void *out, void *stream);
 // X = Xt - scale*G; Xt = X; G = 0   (X may be Xt)

@@ -17,6 +17,7 @@
 // term).  An infinite input leaves NaN in its column (Inf - Inf in the split),
 // where the round-by-round kernels leave Inf or NaN.
 //
+// This is the general kernel; with bf16 state all but the smallest calls take the one in k_dense_bf16.hip.
 // One block = 64 columns, 4 wavefronts, three blocks to a compute unit (two with fp32 state, whose three-term
 // operands need the registers).  The input of a pass is staged in units of
 // 128 workers.  Staging: lane = column, a wavefront loads groups of 8 consecutive rows (coalesced row segments),
@@ -427,6 +428,7 @@ bool build_dense_poly(const HostW &W, int K, double eta, int terms, std::vector<
 int launch_dense_phase(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
                        const uint16_t *frag, void *stream) {
   auto st = static_cast<hipStream_t>(stream);
+  if (dense_resident_serves(s, mode)) return launch_dense_resident(s, mode, X, Y, Gn, Go, alpha, frag, stream);
   return s.bf16 ? launch_mode<bf16_t, 2, 2>(s, mode, X, Y, Gn, Go, alpha, frag, st)
                 : launch_mode<float, 3, 3>(s, mode, X, Y, Gn, Go, alpha, frag, st);
 }

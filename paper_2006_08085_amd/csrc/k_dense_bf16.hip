@@ -1,0 +1,432 @@
+// The dense phase of k_dense.hip for bf16 state, with the rows of P resident in registers.
+//
+// The general kernel fetches the rows of P with every tile, through the same in-order load counter as the state, so neither
+// is hidden.  Here a block of eight wavefronts stays on its compute unit: each wavefront holds its 32 rows of P (two bf16
+// terms, 8 KS registers a lane) for the whole call and walks tiles of 1024 / KS columns, so that a block always has 16 units
+// of (16 workers x 64 columns) to stage, two to a wavefront.  The loads of the next units are in flight under the products of
+// the present ones.
+//
+// Lane (m, g) of a unit loads columns 2m, 2m+1 of rows 8g..8g+7, which is what it holds of the B operand of two column tiles
+// (even columns, odd columns).  So the terms go to LDS in fragment order, 16 bytes a lane, read and written without bank
+// conflicts, and an accumulator pair is one 32-bit word of two columns at the store: no transposition, one instruction moves
+// 128 bytes of each of two rows.  Same operands, products and order as the general kernel: the same values bit for bit.
+//
+// Measured (K = 16, three states in turn, general kernel and this one): 256 workers, d = 1,000,000, pitch 1,000,064, ATC 1310
+// and 911 us (4.5 TB/s; without its products 777), plain gossip 472 and 273; pitch 1,048,576, whose rows all start on the same
+// memory channel, 1400 and 1063, 505 and 305; 128 workers, d = 2,000,000 1510 and 787 (5.2 TB/s: memory), 486 and 209; 64
+// workers, d = 1,000,000 380 and 194, 102 and 50; 256 workers, d = 1,000 37 and 16, 15 and 7.5.  At 256 workers the matrix
+// cores are busy 40 % of the time and staging takes another 20 % of the issue slots, between two barriers a tile; a deeper
+// prefetch (one more quarter of the gradient rows) spills and loses, wavefront priorities change nothing.
+#include "detag_internal.h"
+#include "dev_common.hpp"
+#include "fused_common.hpp"
+#include "fused_generic_common.hpp"
+
+namespace detag {
+namespace {
+
+constexpr int kThreads = 512, kWaves = 8, kUnits = 16;
+constexpr int kMTiles = 8, kKSteps = 16;  // of the fragment order of P
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32_any __attribute__((aligned(2)));                        // two bf16 columns wherever they start
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));     // two fp32 columns
+
+template <Access A>
+__device__ __forceinline__ uint32_t load_pair(const char *base, uint32_t off) {
+  const auto *p = reinterpret_cast<const u32_any *>(base + off);
+  return A == kStream ? __builtin_nontemporal_load(p) : *p;
+}
+template <Access A>
+__device__ __forceinline__ f32x2 load_two(const char *base, uint32_t off) {
+  const auto *p = reinterpret_cast<const f32x2_any *>(base + off);
+  return A == kStream ? __builtin_nontemporal_load(p) : *p;
+}
+template <Access A>
+__device__ __forceinline__ void store_pair(char *base, uint32_t off, uint32_t v) {
+  auto *p = reinterpret_cast<u32_any *>(base + off);
+  if constexpr (A == kStream) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+__device__ __forceinline__ float low(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float high(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
+__device__ __forceinline__ uint32_t pack(float a, float b) {  // both rounded to nearest even, a in the lower half
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// The columns of a unit or of a wavefront's output, 64 from `col` on, `valid` of them (<= 0: none) inside the matrix.  A lane
+// works on two adjacent columns from `at` on (relative to col); all of them are inside the matrix, so the last lanes of a
+// ragged tile take columns twice and store nothing, or the second of theirs only.
+struct Cols {
+  int64_t col;
+  int valid;
+  uint32_t at;
+  __device__ __forceinline__ Cols(int64_t c, int64_t d, int m) {
+    const int v = int(d - c < 64 ? d - c : 64);
+    const int c0 = 2 * m;
+    valid = v;
+    col = v == 1 ? c - 1 : c;  // a lone column: with the one before it, which is another tile's (d >= 64)
+    at = v == 1 ? 0 : c0 + 1 < v ? c0 : c0 < v ? c0 - 1 : 0;
+  }
+  __device__ __forceinline__ bool both(int m) const { return 2 * m + 1 < valid; }
+  __device__ __forceinline__ bool last(int m) const { return 2 * m + 1 == valid; }
+};
+
+// Rows of two columns a lane, `lane_rows` and up from wavefront-uniform row0 on, of `span` that the wavefront walks.  Rows past
+// the last one repeat it: P is zero there, and what zero does not cancel (an infinity, a NaN) spoils its whole column anyway.
+struct Rows {
+  int64_t first;   // wavefront-uniform row the offsets count from
+  bool full;       // wavefront-uniform: all `span` rows exist
+  uint32_t start, step, lim;
+  __device__ __forceinline__ Rows(int row0, int lane_rows, int span, int n, uint32_t pitch, uint32_t at, uint32_t size) {
+    first = row0 < n ? row0 : n - 1;
+    step = pitch * size;
+    const int left = n - 1 - int(first);
+    full = left >= span - 1 && row0 < n;
+    lim = uint32_t(left < span - 1 ? left : span - 1) * step + at * size;
+    start = uint32_t(lane_rows) * step + at * size;
+  }
+  // f(e, base of the row or of the first one, offset from there)
+  template <int E0, int E1, class F>
+  __device__ __forceinline__ void each(F &&f) const {
+    if (full) {
+#pragma unroll
+      for (int e = 0; e < E1 - E0; ++e) f(e, uint64_t(E0 + e) * step, start);
+    } else {
+#pragma unroll
+      for (int e = 0; e < E1 - E0; ++e) f(e, uint64_t(0), at(E0 + e));
+    }
+  }
+  __device__ __forceinline__ uint32_t at(int e) const {
+    const uint32_t o = start + uint32_t(e) * step;
+    return o < lim ? o : lim;
+  }
+};
+
+// The pitch, hidden from the optimiser: what follows from it is computed where it is used, with scalar instructions, instead of
+// being kept for all rows across the walk over tiles.
+__device__ __forceinline__ int64_t fresh(int64_t ld) {
+  asm volatile("" : "+s"(ld));
+  return ld;
+}
+
+// Two bf16 terms (both rounded to nearest) of 4 rows of a column: 8 bytes each.
+__device__ __forceinline__ void split4(f32x4 v, uint2 &t0, uint2 &t1) {
+  t0.x = pack(v[0], v[1]), t0.y = pack(v[2], v[3]);
+  t1.x = pack(v[0] - low(t0.x), v[1] - high(t0.x)), t1.y = pack(v[2] - low(t0.y), v[3] - high(t0.y));
+}
+
+// mode 0: X <- P X.  mode 1 (ATC): X <- P (X - alpha*Y), Y <- P (Y + Gn - Go).
+// mode 2 (ALG2): X <- P (X - alpha*Y), Y <- P Y + Gn - Go.  n <= 16 KS, d >= 64.
+template <int MODE, int KS, Access A>
+__global__ __launch_bounds__(kThreads, 2) void dense_resident_kernel(bf16_t *X, bf16_t *Y, const float *__restrict__ Gn,
+                                                                  const float *__restrict__ Go, int n, int64_t d, int64_t ld,
+                                                                  const u16x8 *__restrict__ frag, float alpha, int tiles) {
+  constexpr int CT = kUnits / KS;            // sub-tiles of 64 columns in a tile
+  constexpr int MT = KS / 2;                 // 32-row tiles of P
+  constexpr bool kTwo = MODE != 0;           // X - alpha*Y
+  extern __shared__ uint4 staged[];          // [pass or turn][unit][column tile][term][lane]
+  uint4 *const lds_u = staged, *const lds_v = staged + kUnits * 256;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int m = lane & 31, g = lane >> 5;
+  const int mt = w % MT, osub = w / MT;      // this wavefront's output: 32 rows, one sub-tile
+
+  u16x8 P[2][KS];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int s = 0; s < KS; ++s) P[t][s] = frag[((t * kMTiles + mt) * kKSteps + s) * 64 + lane];
+
+  // the tiles of this block
+  int tile, last, hop;
+  if (A == kKeep && gridDim.x % 8 == 0) {    // tiles that share cache lines: a contiguous eighth to every XCD
+    const int per = (tiles + 7) / 8, x = blockIdx.x % 8;
+    tile = x * per + blockIdx.x / 8, hop = gridDim.x / 8;
+    last = (x + 1) * per < tiles ? (x + 1) * per : tiles;
+  } else {
+    tile = blockIdx.x, hop = gridDim.x, last = tiles;
+  }
+  if (tile >= last) return;
+
+  u32x8 lx[2], ly[2];                        // units w and w + 8
+  using std::integral_constant;
+  constexpr integral_constant<int, 0> k0{};
+  constexpr integral_constant<int, 1> k1{};
+  auto unit_cols = [&](int t, int k) { return Cols(int64_t(t) * (64 * CT) + 64 * ((w + 8 * k) % CT), d, m); };
+  auto unit_rows = [&](int k, uint32_t pitch, uint32_t at, uint32_t size) {
+    return Rows(16 * ((w + 8 * k) / CT), 8 * g, 16, n, pitch, at, size);
+  };
+  auto request_unit = [&](int t, auto k) {
+    const Cols c = unit_cols(t, k);
+    asm volatile("" : "=v"(lx[k]), "=v"(ly[k]));  // whatever: the old values must not stay alive for the case without a unit
+    if (t >= last || c.valid <= 0) return;   // wavefront-uniform
+    const int64_t l = fresh(ld);
+    const Rows r = unit_rows(k, uint32_t(l), c.at, 2);
+    const char *x = reinterpret_cast<const char *>(X + r.first * l + c.col);
+    const char *y = reinterpret_cast<const char *>(Y + r.first * l + c.col);
+    r.template each<0, 8>([&](int e, uint64_t row, uint32_t off) {
+      lx[k][e] = load_pair<A>(x + row, off);
+      if constexpr (kTwo) ly[k][e] = load_pair<A>(y + row, off);
+    });
+  };
+  auto request_state = [&](int t) { request_unit(t, k0), request_unit(t, k1); };
+  // A quarter of a wavefront's gradient rows (half a unit), and the tracker's terms of it -> LDS.
+  f32x8 g0[2], g1[2];
+  auto request_track = [&](int t, auto part, f32x8 (&to)[2]) {
+    constexpr int k = part / 2, h = part % 2;
+    const Cols c = unit_cols(t, k);
+    asm volatile("" : "=v"(to[0]), "=v"(to[1]));
+    if (t >= last || c.valid <= 0) return;
+    const int64_t l = fresh(ld);
+    const Rows r = unit_rows(k, uint32_t(l), c.at, 4);
+    const char *a = reinterpret_cast<const char *>(Gn + r.first * l + c.col);
+    const char *b = reinterpret_cast<const char *>(Go + r.first * l + c.col);
+    r.template each<4 * h, 4 * h + 4>([&](int e, uint64_t row, uint32_t off) {
+      const f32x2 p = load_two<A>(a + row, off), q = load_two<A>(b + row, off);
+      to[0][2 * e] = p[0], to[0][2 * e + 1] = p[1], to[1][2 * e] = q[0], to[1][2 * e + 1] = q[1];
+    });
+  };
+  auto stage_track = [&](auto part, const f32x8 (&from)[2]) {
+    constexpr int k = part / 2, h = part % 2;
+    f32x4 even, odd;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      even[e] = low(ly[k][4 * h + e]) + from[0][2 * e] - from[1][2 * e];
+      odd[e] = high(ly[k][4 * h + e]) + from[0][2 * e + 1] - from[1][2 * e + 1];
+    }
+    uint2 *at = reinterpret_cast<uint2 *>(lds_v + (w + 8 * k) * 256 + lane) + h;
+    uint2 t0, t1;
+    split4(even, t0, t1);
+    at[0] = t0, at[128] = t1;
+    split4(odd, t0, t1);
+    at[256] = t0, at[384] = t1;
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Waits for the state requested above.  Loads and stores are counted together and in order: without this, the first use
+  // after the stores of a tile, whose number the compiler does not know, would wait for those as well.
+  auto arrived = [&] {
+    asm volatile("" : "+v"(lx[0]), "+v"(lx[1]));
+    if constexpr (kTwo) asm volatile("" : "+v"(ly[0]), "+v"(ly[1]));
+    if constexpr (MODE == 1) asm volatile("" : "+v"(g1[0]), "+v"(g1[1]));
+  };
+  // The state as it is stored is its own only term: half the room and two products of three.
+  auto put_plain = [&](uint4 *lds, u32x8 v, int k) {
+    uint4 *at = lds + (w + 8 * k) * 128 + lane;
+    auto halves = [&](int e, uint32_t pick) { return __builtin_amdgcn_perm(v[2 * e + 1], v[2 * e], pick); };
+    auto column = [&](uint32_t pick) { return make_uint4(halves(0, pick), halves(1, pick), halves(2, pick), halves(3, pick)); };
+    at[0] = column(0x05040100u), at[64] = column(0x07060302u);
+  };
+  f32x16 acc[2];
+  auto clear = [&] {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+  };
+  // products with k-steps s0..s1-1, the smallest first; two: the staged input has two terms
+  auto multiply = [&](const uint4 *lds, auto two, auto s0, auto s1) {
+    constexpr int T = two ? 2 : 1;
+#pragma unroll
+    for (int s = s0; s < s1; ++s) {
+      const uint4 *at = lds + (s * CT + osub) * (128 * T) + lane;
+      u16x8 b[2][T];
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int t = 0; t < T; ++t) b[nt][t] = __builtin_bit_cast(u16x8, at[(nt * T + t) * 64]);
+      constexpr int order[3][2] = {{0, 1}, {1, 0}, {0, 0}};
+#pragma unroll
+      for (int q = two ? 0 : 1; q < 3; ++q)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+          acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, P[order[q][0]][s]),
+                                                            __builtin_bit_cast(bf16x8, b[nt][order[q][1]]), acc[nt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // the wavefront's 32 rows of two columns a lane -> memory; fn(r) may change the pair of register r
+  auto store_out = [&](bf16_t *out, int t, auto &&fn) {
+    const Cols c(int64_t(t) * (64 * CT) + 64 * osub, d, m);
+    if (c.valid <= 0 || 32 * mt >= n) return;
+    const int64_t l = fresh(ld);
+    const uint32_t step = uint32_t(l) * 2;
+    char *base = reinterpret_cast<char *>(out + int64_t(32 * mt) * l + c.col);
+    const uint32_t lane_off = 4 * g * step + 2 * c.at;
+    if (c.valid == 64 && 32 * mt + 32 <= n) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        float a = acc[0][r], b = acc[1][r];
+        fn(r, a, b);
+        store_pair<A>(base + int64_t(8 * (r / 4) + r % 4) * step, lane_off, pack(a, b));
+      }
+      return;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float a = acc[0][r], b = acc[1][r];
+      fn(r, a, b);
+      char *row = base + int64_t(8 * (r / 4) + r % 4) * step;
+      if (32 * mt + 8 * (r / 4) + 4 * g + r % 4 < n) {
+        const uint32_t v = pack(a, b);
+        if (c.both(m)) store_pair<A>(row, lane_off, v);
+        else if (c.last(m)) *reinterpret_cast<uint16_t *>(row + lane_off + 2) = uint16_t(v >> 16);
+      }
+    }
+  };
+  constexpr integral_constant<int, KS> kAll{};
+  constexpr integral_constant<bool, true> kBoth{};
+  [[maybe_unused]] int turn = 0;
+  auto plain = [](int, float &, float &) {};
+
+  request_state(tile);
+  if constexpr (MODE == 1) request_track(tile, k0, g1);
+  for (; tile < last; tile += hop) {
+    const int next = tile + hop;
+    if constexpr (MODE == 0) {
+      // two buffers in turn: who is here has passed the barrier behind the last products with this one
+      uint4 *const lds = staged + turn * kUnits * 128;
+      turn ^= 1;
+      put_plain(lds, lx[0], k0), put_plain(lds, lx[1], k1);
+      request_state(next);
+      __syncthreads();
+      clear();
+      multiply(lds, integral_constant<bool, false>{}, k0, kAll);
+      arrived();
+      store_out(X, tile, plain);
+    } else {
+      auto stage_model = [&](auto k) {
+        f32x8 even, odd;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          even[e] = fmaf(-alpha, low(ly[k][e]), low(lx[k][e]));
+          odd[e] = fmaf(-alpha, high(ly[k][e]), high(lx[k][e]));
+        }
+        uint4 *at = lds_u + (w + 8 * k) * 256 + lane;
+        auto column = [&](int o, f32x8 v) {
+          uint2 a0, a1, b0, b1;
+          split4(v.lo, a0, a1), split4(v.hi, b0, b1);
+          at[o] = make_uint4(a0.x, a0.y, b0.x, b0.y), at[o + 64] = make_uint4(a1.x, a1.y, b1.x, b1.y);
+        };
+        column(0, even), column(128, odd);
+      };
+      stage_model(k0), stage_model(k1);
+      if constexpr (MODE == 1) {
+        __syncthreads();                     // the terms of X - alpha*Y are in place, those of the last tracker are done with
+        stage_track(k0, g1);
+        request_track(tile, k1, g0);
+        request_track(tile, integral_constant<int, 2>{}, g1);
+        __builtin_amdgcn_sched_barrier(0);
+        clear();
+        multiply(lds_u, kBoth, k0, integral_constant<int, KS / 2>{});
+        stage_track(k1, g0);
+        request_track(tile, integral_constant<int, 3>{}, g0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(lds_u, kBoth, integral_constant<int, KS / 2>{}, integral_constant<int, KS * 3 / 4>{});
+        stage_track(integral_constant<int, 2>{}, g1);
+        multiply(lds_u, kBoth, integral_constant<int, KS * 3 / 4>{}, kAll);
+        stage_track(integral_constant<int, 3>{}, g0);
+      } else {
+        __syncthreads();
+        put_plain(lds_v, ly[0], k0), put_plain(lds_v, ly[1], k1);
+        clear();
+        multiply(lds_u, kBoth, k0, kAll);
+      }
+      request_state(next);
+      if constexpr (MODE == 1) request_track(next, k0, g1);
+      __builtin_amdgcn_sched_barrier(0);
+      store_out(X, tile, plain);
+      __syncthreads();                       // the terms of the tracker are in place, those of the model are done with
+      clear();
+      multiply(lds_v, integral_constant<bool, MODE == 1>{}, k0, kAll);
+      arrived();
+      if constexpr (MODE == 1) {
+        store_out(Y, tile, plain);
+      } else {
+        const Cols c(int64_t(tile) * (64 * CT) + 64 * osub, d, m);
+        if (c.valid > 0 && 32 * mt < n) {
+          // register r: row 32 mt + 8 (r / 4) + 4 g + r % 4; four rows ahead of the stores
+          const int64_t l = fresh(ld);
+          const Rows q(32 * mt, 4 * g, 32, n, uint32_t(l), c.at, 4);
+          const char *a = reinterpret_cast<const char *>(Gn + q.first * l + c.col);
+          const char *b = reinterpret_cast<const char *>(Go + q.first * l + c.col);
+          f32x2 wn[16], wo[16];
+          auto ahead = [&](int r) {
+            const int e = 8 * (r / 4) + r % 4;
+            wn[r] = load_two<A>(a, q.at(e)), wo[r] = load_two<A>(b, q.at(e));
+          };
+#pragma unroll
+          for (int r = 0; r < 4; ++r) ahead(r);
+          store_out(Y, tile, [&](int r, float &even, float &odd) {
+            if (r + 4 < 16) ahead(r + 4);
+            even = even + wn[r][0] - wo[r][0], odd = odd + wn[r][1] - wo[r][1];
+            __builtin_amdgcn_sched_barrier(0);
+          });
+        }
+      }
+    }
+  }
+}
+
+template <int KS, Access A>
+int launch_ks(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha, const uint16_t *frag,
+              hipStream_t st) {
+  constexpr int cols = 64 * (kUnits / KS);
+  const int tiles = ceil_div_i64(s.d, cols);
+  const int grid = tiles < 256 ? tiles : 256;  // one block to a compute unit
+  const size_t lds = size_t(mode == 0 ? 256 : mode == 1 ? 512 : 384) * kUnits * sizeof(uint4);
+  auto go = [&](auto *kernel) -> int {
+    if (int rc = lds_tile::allow_lds(reinterpret_cast<const void *>(kernel), lds)) return rc;
+    kernel<<<grid, kThreads, lds, st>>>(static_cast<bf16_t *>(X), static_cast<bf16_t *>(Y), Gn, Go, s.n, s.d, s.ld,
+                                        reinterpret_cast<const u16x8 *>(frag), alpha, tiles);
+    return hip_rc(hipGetLastError());
+  };
+  switch (mode) {
+    case 0: return go(&dense_resident_kernel<0, KS, A>);
+    case 1: return go(&dense_resident_kernel<1, KS, A>);
+    default: return go(&dense_resident_kernel<2, KS, A>);
+  }
+}
+
+template <Access A>
+int launch_access(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
+                  const uint16_t *frag, hipStream_t st) {
+  if (s.n <= 32) return launch_ks<2, A>(s, mode, X, Y, Gn, Go, alpha, frag, st);
+  if (s.n <= 64) return launch_ks<4, A>(s, mode, X, Y, Gn, Go, alpha, frag, st);
+  if (s.n <= 128) return launch_ks<8, A>(s, mode, X, Y, Gn, Go, alpha, frag, st);
+  return launch_ks<16, A>(s, mode, X, Y, Gn, Go, alpha, frag, st);
+}
+
+}  // namespace
+
+// What this kernel takes: lanes count their offsets within 32 rows of fp32 in 32 bits, a lone last column is loaded with the one
+// before it, and the P of a call is read by every block before its first tile, which the smallest calls of few workers notice
+// (general kernel and this one: 12 workers, ATC, d = 1,000 6.8 and 7.6 us, 16,000 6.9 and 7.6, 50,000 10.3 and 7.8; plain gossip
+// of 32 workers, d = 1,000 4.9 and 5.2, 16,000 5.0 and 5.3, 50,000 6.4 and 5.2; Algorithm 2's phase of 12 7.2 and 6.5).
+bool dense_resident_serves(const Shape &s, int mode) {
+  if (!s.bf16 || s.d < 64 || s.ld > (int64_t(1) << 25)) return false;
+  const int few = mode == 0 ? 32 : mode == 1 ? 16 : 0;
+  return s.n > few || s.d >= 32768;
+}
+
+int launch_dense_resident(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
+                          const uint16_t *frag, void *stream) {
+  auto st = static_cast<hipStream_t>(stream);
+  // Tiles that share cache lines go to one XCD and leave their accesses to the caches (streamed and kept, ATC: 256 x 200,001
+  // 316 and 213 us, 64 x 546,113 164 and 128, 20 x 1,747,585 166 and 143), and so do calls that the memory-side cache serves
+  // (256 workers, 60 MiB 31.0 and 27.7, 100 MiB 44.2 and 43.3, 130 MiB 47.0 and 47.0, 200 MiB 75.1 and 79.4; 64 workers 80 MiB
+  // 24.3 and 22.3, 200 MiB 57.3 and 66.2; Algorithm 2's phase the same; plain gossip of 256 workers, 33 MiB 25.5 and 24.3, 95
+  // MiB of 64 and 100 workers 49.6 and 53.1, 95.5 and 97.5).
+  const int64_t bytes = fused::footprint(s, mode == 0 ? 2 : 12);
+  const bool keep = fused::shares_lines(s, {X, Y, Gn, Go}) || bytes <= (int64_t(mode == 0 ? 64 : 104) << 20);
+  return keep ? launch_access<kKeep>(s, mode, X, Y, Gn, Go, alpha, frag, st)
+              : launch_access<kStream>(s, mode, X, Y, Gn, Go, alpha, frag, st);
+}
+
+}  // namespace detag

@@ -161,3 +161,35 @@ def test_config5_shape_bf16_short_run_dense():
     S = amax(X, Y, Gold)
     assert rel_err(to_host(Xd, d), X, S, floor=1.0) < TOL_BF16
     assert rel_err(to_host(Yd, d), Y, S, floor=1.0) < TOL_BF16
+
+
+@pytest.mark.parametrize("n", [12, 17, 33, 64, 65, 100, 128, 129, 200, 256])
+@pytest.mark.parametrize("d,ld", [(64, 64), (65, 65), (129, 160), (701, 704), (1025, 1025), (40001, 40001), (33000, 33024)])
+def test_resident_kernel_gives_the_bits_of_the_general_one(n, d, ld):
+    """bf16 state: the kernel that holds P in registers against the general kernel, which serves contexts of fewer than 64
+    columns: the same columns in slices of 63, around the edges of tiles of every width (64 to 512) and of a block's walk."""
+    topo, W, eta = _graph(n, "rr")
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    normal = lambda: torch.randn(n, ld, device=DEV, generator=g)  # noqa: E731
+    X, Y, Gn, Go = normal().bfloat16(), normal().bfloat16(), normal(), normal()
+    for t in (X, Y, Gn, Go):
+        t[:, d:] = SENTINEL
+    edges = sorted({0, d - 63} | {min(max(0, e - 31), d - 63) for e in (64, 128, 256, 512, 1024, 16384, 32768) if e < d + 31})
+
+    def call(ctx, mode, x, y, gn, go):
+        if mode == 0:
+            ctx.gossip_accel(x, 3, eta)
+        else:
+            ctx.step(x, y, gn, go, 0.05, 3, eta, D.DETAG_VARIANT_ATC if mode == 1 else D.DETAG_VARIANT_ALG2)
+
+    whole, narrow = D.detag_create(topo, n, d, ld, D.DETAG_BF16), D.detag_create(topo, n, 63, ld, D.DETAG_BF16)
+    for ctx in (whole, narrow):
+        ctx.set_path(D.DETAG_PATH_DENSE)
+    for mode in (0, 1, 2):
+        x, y = X.clone(), Y.clone()
+        call(whole, mode, x, y, Gn, Go)
+        assert padding_ok(x, d) and padding_ok(y, d)
+        for c in edges:
+            xs, ys = X.clone(), Y.clone()
+            call(narrow, mode, xs[:, c:], ys[:, c:], Gn[:, c:], Go[:, c:])
+            assert torch.equal(xs[:, c:c + 63], x[:, c:c + 63]) and torch.equal(ys[:, c:c + 63], y[:, c:c + 63]), (mode, c)
