@@ -28,7 +28,7 @@
  *     detag_last_error() gives the text of the last failure.
  *   - Calls on one context come from one host thread at a time.  Work of two
  *     calls may run concurrently on two streams only if they use disjoint
- *     context-owned scratch: detag_gossip_round, detag_accumulate,
+ *     context-owned scratch: detag_gossip_round(s), detag_accumulate,
  *     detag_phase_end, detag_track and detag_grad_quadratic_diag use none, nor
  *     do detag_gossip_accel / detag_step / detag_dpsgd_step on a context that
  *     detag_get_kernel reports as DETAG_KERNEL_REGISTER_TILE or
@@ -297,6 +297,17 @@ detag_status detag_dpsgd_step(detag_ctx *ctx, void *X_dev, const float *G_dev, d
  */
 detag_status detag_gossip_round(detag_ctx *ctx, const void *Zcur_dev, const void *Zprev_dev, void *Zout_dev,
                                 double eta, void *stream);
+
+/*
+ * The R rounds of a phase's communication in one launch: what R calls of
+ * detag_gossip_round compute from z_{-1} = z_0, bit for bit, in place on Z and,
+ * unless it is NULL, on Z2 (n x ld, state type, not overlapping), at 8 B per
+ * element and matrix (fp32) whatever R.  For callers whose grain is the phase;
+ * the rounding is the iteration's, not that of detag_gossip_accel.  R >= 0.
+ * Uses no scratch.  DETAG_EUNSUPPORTED unless detag_get_kernel reports
+ * DETAG_KERNEL_REGISTER_TILE.
+ */
+detag_status detag_gossip_rounds(detag_ctx *ctx, void *Z_dev, void *Z2_dev, int32_t R, double eta, void *stream);
 
 /* Gradient buffer of Algorithm 2: Gacc += scale * g  (both fp32 n x ld; Gacc != g). */
 detag_status detag_accumulate(detag_ctx *ctx, float *Gacc_dev, const float *g_dev, double scale, void *stream);

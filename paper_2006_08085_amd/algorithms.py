@@ -12,7 +12,7 @@ from __future__ import annotations
 
 from typing import Callable, Dict, List, Optional
 
-from .binding import Context, Factors, DETAG_VARIANT_ATC
+from .binding import Context, Factors, DETAG_KERNEL_REGISTER_TILE, DETAG_VARIANT_ATC
 from .memory import new_matrix
 
 ALGORITHMS = ("detag", "dsgt", "dpsgd")
@@ -62,7 +62,9 @@ class ByPhase:
     end), which is what lets the two run side by side - the paper's overlap of communication with
     computation, on one GPU.
 
-    granularity = "iteration": one detag_gossip_round per matrix per iteration (2R launches a phase).
+    granularity = "iteration": one detag_gossip_round per matrix per iteration (2R launches a phase); phase(),
+    which knows that R and eta hold for all of it, issues the rounds at its first iteration as one launch with the
+    same bits where the register-resident kernels serve the graph.
     granularity = "phase": the R steps of a phase as one on-chip K-round call per matrix, issued at the
     phase's first iteration (same arithmetic up to rounding order; needs has_fused()).
     overlap = False puts everything on the current stream.
@@ -88,6 +90,8 @@ class ByPhase:
         self.t = 0           # iterations done
         self.k = 0           # phases done
         self.r = 0           # step within the current phase
+        self._whole = False  # within phase(): R and eta hold for every iteration of this phase
+        self._ahead = 0      # gossip steps of the current phase that are issued already
 
     @property
     def Y(self):
@@ -109,7 +113,10 @@ class ByPhase:
             if r == 0:
                 ctx.gossip_accel(self.xt[0], R, eta, stream=on)
                 ctx.gossip_accel(self.y[0], R, eta, stream=on)
-        else:
+        elif r == 0 and self._whole and ctx.kernel() == DETAG_KERNEL_REGISTER_TILE:
+            ctx.gossip_rounds(self.xt[0], self.y[0], int(R), eta, stream=on)
+            self._ahead = R
+        elif r >= self._ahead:
             for z in (self.xt, self.y):
                 ctx.gossip_round(z[0], z[0] if r == 0 else z[1], z[1], eta, stream=on)
                 z[0], z[1] = z[1], z[0]
@@ -123,14 +130,18 @@ class ByPhase:
                 self._current_stream().wait_stream(comm)
             ctx.phase_end(self.X, self.xt[0], self.y[0], self.G_k, self.G_km1, self.alpha)
             self.G_k, self.G_km1 = self.G_km1, self.G_k
-            self.r = 0
+            self.r = self._ahead = 0
             self.k += 1
 
     def phase(self, R: int, eta: float = -1.0):
         if self.r != 0:
             raise RuntimeError("a phase is in progress")
-        for _ in range(R):
-            self.iteration(R, eta)
+        self._whole = True
+        try:
+            for _ in range(R):
+                self.iteration(R, eta)
+        finally:
+            self._whole = False
 
     def capture_two_phases(self, R: int, eta: float = -1.0):
         """Record two consecutive phases of length R into a HIP graph (two, because the gradient buffers and,
@@ -169,8 +180,11 @@ def run_by_phase(ctx: Context, grad: Callable, X, alpha: float, T: int, R, eta=-
     phase_eta = eta if callable(eta) else (lambda k: eta)
     while bp.t < T:
         Rk, ek = int(phase_len(bp.k)), float(phase_eta(bp.k))
-        for _ in range(min(Rk, T - bp.t)):
-            bp.iteration(Rk, ek)
+        if Rk <= T - bp.t:
+            bp.phase(Rk, ek)
+        else:
+            for _ in range(T - bp.t):
+                bp.iteration(Rk, ek)
     return bp
 
 

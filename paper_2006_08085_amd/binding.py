@@ -31,7 +31,7 @@ _STATUS_NAMES = ["DETAG_OK", "DETAG_EINVAL", "DETAG_ENOT_DOUBLY_STOCHASTIC", "DE
                  "DETAG_EUNSUPPORTED", "DETAG_ENOMEM", "DETAG_EHIP"]
 
 EXPORTS = ["detag_create", "detag_destroy", "detag_get_spectrum", "detag_get_csr", "detag_set_path",
-           "detag_get_phase_length", "detag_get_gossip_polynomial", "detag_has_fused", "detag_get_kernel", "detag_reserve_gossip", "detag_reserve_gradient", "detag_gossip_accel", "detag_track", "detag_step", "detag_dpsgd_step", "detag_gossip_round", "detag_accumulate", "detag_phase_end",
+           "detag_get_phase_length", "detag_get_gossip_polynomial", "detag_has_fused", "detag_get_kernel", "detag_reserve_gossip", "detag_reserve_gradient", "detag_gossip_accel", "detag_track", "detag_step", "detag_dpsgd_step", "detag_gossip_round", "detag_gossip_rounds", "detag_accumulate", "detag_phase_end",
            "detag_factors_create", "detag_factors_destroy", "detag_factors_count", "detag_factors_get_csr",
            "detag_factors_get_program",
            "detag_factor_apply", "detag_average_consensus", "detag_defacto_update",
@@ -112,6 +112,8 @@ def lib() -> C.CDLL:
     L.detag_dpsgd_step.restype = C.c_int
     L.detag_gossip_round.argtypes = [vp, vp, vp, vp, f64, vp]
     L.detag_gossip_round.restype = C.c_int
+    L.detag_gossip_rounds.argtypes = [vp, vp, vp, i32, f64, vp]
+    L.detag_gossip_rounds.restype = C.c_int
     L.detag_accumulate.argtypes = [vp, vp, vp, f64, vp]
     L.detag_accumulate.restype = C.c_int
     L.detag_phase_end.argtypes = [vp, vp, vp, vp, vp, vp, f64, vp]
@@ -407,6 +409,11 @@ class Context:
                                              self._state(Z_out, "Z_out"), eta,
                                              self._stream() if stream is None else stream))
 
+    def gossip_rounds(self, Z, Z2, R: int, eta: float = -1.0, stream: Optional[int] = None):
+        """R gossip_round calls from z_{-1} = z_0 in one launch, in place on Z and on Z2 (or None)."""
+        self._check(lib().detag_gossip_rounds(self._h, self._state(Z, "Z"), None if Z2 is None else self._state(Z2, "Z2"),
+                                              R, eta, self._stream() if stream is None else stream))
+
     def accumulate(self, G_acc, g, scale: float = 1.0):
         self._check(lib().detag_accumulate(self._h, self._f32(G_acc, "G_acc"),
                                            self._f32(g, "g"), scale, self._stream()))
@@ -533,6 +540,7 @@ def detag_step(ctx: Context, X, Y, G_new, G_old, alpha, K, eta=-1.0, variant=DET
     ctx.step(X, Y, G_new, G_old, alpha, K, eta, variant)
 def detag_dpsgd_step(ctx: Context, X, G, alpha): ctx.dpsgd_step(X, G, alpha)
 def detag_gossip_round(ctx: Context, Z_cur, Z_prev, Z_out, eta=-1.0): ctx.gossip_round(Z_cur, Z_prev, Z_out, eta)
+def detag_gossip_rounds(ctx: Context, Z, Z2, R, eta=-1.0): ctx.gossip_rounds(Z, Z2, R, eta)
 def detag_accumulate(ctx: Context, G_acc, g, scale=1.0): ctx.accumulate(G_acc, g, scale)
 def detag_phase_end(ctx: Context, X, X_tilde, Y, G_k, G_km1, alpha): ctx.phase_end(X, X_tilde, Y, G_k, G_km1, alpha)
 def detag_factors_create(ctx: Context, root=0): return Factors(ctx, root)

@@ -637,6 +637,24 @@ detag_status detag_gossip_round(detag_ctx *ctx, const void *Zcur_dev, const void
   return rc ? hip_fail(ctx, "gossip round", rc) : DETAG_OK;
 }
 
+detag_status detag_gossip_rounds(detag_ctx *ctx, void *Z_dev, void *Z2_dev, int32_t R, double eta, void *stream) {
+  if (detag_status st = need_device(ctx)) return st;
+  if (detag_status st = check_state_ptr(ctx, Z_dev, "Z_dev")) return st;
+  if (Z2_dev)
+    if (detag_status st = check_state_ptr(ctx, Z2_dev, "Z2_dev")) return st;
+  if (Z2_dev == Z_dev) return set_err(ctx, DETAG_EINVAL, "Z and Z2 must not overlap");
+  if (R < 0) return set_err(ctx, DETAG_EINVAL, "R must be >= 0");
+  float e;
+  if (detag_status st = resolve_eta(ctx, eta, &e)) return st;
+  Chosen path;
+  if (detag_status st = choose_path(ctx, R, &path)) return st;
+  if (path != kFusedStructured)
+    return set_err(ctx, DETAG_EUNSUPPORTED, "detag_gossip_rounds needs a context of the register-resident kernels");
+  if (R == 0) return DETAG_OK;
+  const int rc = launch_structured_rounds(ctx->shape, ctx->W, Z_dev, Z2_dev, R, e, stream);
+  return rc ? hip_fail(ctx, "gossip rounds", rc) : DETAG_OK;
+}
+
 detag_status detag_accumulate(detag_ctx *ctx, float *Gacc_dev, const float *g_dev, double scale, void *stream) {
   if (detag_status st = need_device(ctx)) return st;
   if (detag_status st = check_f32_ptr(ctx, Gacc_dev, "Gacc_dev")) return st;

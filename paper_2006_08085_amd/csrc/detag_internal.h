@@ -125,6 +125,8 @@ int launch_update_track(const Shape &s, void *X, void *Y, const float *Gn, const
                         void *stream);
 // X = c_mix * (W^T Xin) - alpha*G  (D-PSGD); Xin != X
 bool round_stages_tile(const Shape &s);
+// K rounds of that kernel from z_{-1} = z_0 on Z0 and, unless it is null, Z1: in place, in one launch, the same bits.
+int launch_structured_rounds(const Shape &s, const HostW &W, void *Z0, void *Z1, int K, float eta, void *stream);
 int launch_structured_round(const Shape &s, const HostW &W, const void *cur, const void *prev, void *out, float eta,
                             void *stream);
 int launch_dpsgd(const Shape &s, const DevCsr &w, const void *Xin, void *X, const float *G, float alpha,

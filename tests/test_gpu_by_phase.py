@@ -72,6 +72,60 @@ def test_accumulate_and_phase_end(dtype, separate_replica):
         ctx.phase_end(Xd, Xtd, Yd, Gkd, Gkd, alpha)
 
 
+@pytest.mark.parametrize("kind,n", [("ring", 4), ("ring", 8), ("ring", 16), ("ring", 24), ("ring", 64), ("torus44", 16),
+                                    ("torus88", 64)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d,ld", [(65, 65), (1029, 1032), (40001, 40064)])
+def test_rounds_in_one_launch_have_the_bits_of_single_rounds(kind, n, dtype, d, ld):
+    bf = dtype == "bf16"
+    topo = D.Topology.ring() if kind == "ring" else D.Topology.torus(4, 4) if kind == "torus44" else D.Topology.torus(8, 8)
+    ctx = D.detag_create(topo, n, d, ld, D.DETAG_BF16 if bf else D.DETAG_F32)
+    tdt = torch.bfloat16 if bf else torch.float32
+    A, B = (to_dev(gen.state(n, d, s), ld, tdt) for s in (1, 2))
+    A[0, 3] = float("inf")                                     # spreads one neighbour a round, as NaN from the second on
+    for R in (0, 1, 2, 5, 8):
+        want = []
+        for Z in (A, B):
+            z = [Z.clone(), to_dev(np.zeros((n, d)), ld, tdt)]
+            for r in range(R):
+                ctx.gossip_round(z[0], z[0] if r == 0 else z[1], z[1], 0.4)
+                z.reverse()
+            want.append(z[0])
+        one, both, two = A.clone(), A.clone(), B.clone()
+        ctx.gossip_rounds(one, None, R, 0.4)
+        ctx.gossip_rounds(both, two, R, 0.4)
+        for got, ref in ((one, want[0]), (both, want[0]), (two, want[1])):
+            assert np.array_equal(to_host(got, d), to_host(ref, d), equal_nan=True), R
+            assert padding_ok(got, d)
+    with pytest.raises(D.DetagError):
+        ctx.gossip_rounds(A, A, 2, 0.4)
+    ctx.set_path(D.DETAG_PATH_PER_ROUND)
+    with pytest.raises(D.DetagError) as e:
+        ctx.gossip_rounds(A, None, 2, 0.4)
+    assert e.value.status == D.DETAG_EUNSUPPORTED
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+def test_a_phase_has_the_bits_of_its_iterations(overlap):
+    n, d, ld, R = 16, 3001, 3008, 5
+    ctx, _ = make_ctx("ring", n, d, ld)
+    h, b = torch.rand(d, device=DEV), to_dev(gen.state(n, d, 7), ld)
+    grad = lambda t, q, X, g: ctx.grad_quadratic_diag(X, h, b, g, sigma=0.1, seed=3, step=t)
+    runs = []
+    for whole in (True, False):
+        X = to_dev(gen.state(n, d, 1), ld)
+        bp = ALG.ByPhase(ctx, X, 0.1, grad, scale=1.0 / R, overlap=overlap)
+        for _ in range(3):
+            if whole:
+                bp.phase(R)
+            else:
+                for _ in range(R):
+                    bp.iteration(R)
+        torch.cuda.synchronize()
+        runs.append((to_host(X, d), to_host(bp.Y, d), to_host(bp.G_km1, d), bp.t, bp.k, bp.r))
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
+
+
 def _lstsq_setup():
     cfg = CONFIGS[1]
     n, d, m = cfg.n, cfg.d, cfg.extra["m"]
