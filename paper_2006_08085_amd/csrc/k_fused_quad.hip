@@ -50,7 +50,8 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
   static_assert(N % 4 == 0, "rows are processed in groups of four");
   constexpr int NL = N >= 64 ? kParkedRows : 0;
   constexpr int NR = N - NL;
-  constexpr int D = kRowsAhead < N ? kRowsAhead : N;
+  constexpr int kAhead = kRowsAhead - (HPW && N >= 64 ? 2 : 0);  // two rows less of five arrays, or some of them spill
+  constexpr int D = kAhead < N ? kAhead : N;
   __shared__ float vl[NL > 0 ? NL * kThreads : 1];
   const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
   const uint32_t valid = uint32_t(d - tile < blockDim.x ? d - tile : blockDim.x);
