@@ -16,13 +16,8 @@ struct bf16_t {
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(bf16_t v) { return __uint_as_float(uint32_t(v.bits) << 16); }
 
-// Round to nearest, ties to even; NaN stays NaN.
-__device__ __forceinline__ uint16_t bf16_bits_rne(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return uint16_t((u >> 16) | 0x0040u);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return uint16_t(u >> 16);
-}
+// Round to nearest, ties to even; NaN stays NaN.  One instruction of gfx950 (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ uint16_t bf16_bits_rne(float f) { return __builtin_bit_cast(uint16_t, static_cast<__bf16>(f)); }
 
 template <typename ST>
 __device__ __forceinline__ ST from_f32(float f);
@@ -71,6 +66,23 @@ __device__ __forceinline__ float buf_load(rsrc_t r, uint32_t byte_off) {
     const uint16_t h = uint16_t(__builtin_amdgcn_raw_buffer_load_b16(r, int(byte_off), 0, aux));
     return __uint_as_float(uint32_t(h) << 16);
   }
+}
+
+// A value on its way: what a load brings, turned into a float where it is used and not where it was requested.  A kernel that
+// keeps the loads of some rows in flight, in an order pinned by scheduling barriers, must not convert next to the load: the
+// conversion waits for it (bf16 state, torus 8x8, K = 8, converted at the load and at the use: ATC phase, d = 2,000,000 715 and
+// 414 us, 200,000 95 and 54; fused step 705 and 540, with Algorithm 2 as printed 860 and 594; ring of 32, d = 30,000 13.8 and
+// 8.0).
+template <typename ST>
+struct Loaded {
+  uint32_t bits;
+  __device__ __forceinline__ operator float() const { return __uint_as_float(sizeof(ST) == 4 ? bits : bits << 16); }
+};
+template <typename ST, Access A = kStream>
+__device__ __forceinline__ Loaded<ST> buf_request(rsrc_t r, uint32_t byte_off) {
+  constexpr int aux = A == kStream ? 2 : 0;
+  if constexpr (sizeof(ST) == 4) return {uint32_t(__builtin_amdgcn_raw_buffer_load_b32(r, int(byte_off), 0, aux))};
+  else return {uint32_t(uint16_t(__builtin_amdgcn_raw_buffer_load_b16(r, int(byte_off), 0, aux)))};
 }
 
 template <typename ST, Access A = kStream>

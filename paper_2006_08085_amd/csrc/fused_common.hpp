@@ -69,7 +69,9 @@ inline Access tile_access(const Shape &s, int per_element, std::initializer_list
 
 // The mark of the register-resident kernels.  Few rows share few lines, and a row of bf16 state that starts on half a line
 // shares with one neighbour.  Streamed and kept, bf16 rows on half lines: the ATC phase and the step fused with it (torus
-// 8x8, pitch 1,000,032: 338 and 355 us, 336 and 341; pitch 1,000,003 368 and 352, 420 and 338); Algorithm 2's phase, ring of
+// 8x8, 183 MiB 54.0 and 59.7 us, fused step 68 and 73, 732 MiB 212 and 213, 275 and 281; ring of 4, 183 MiB 45.8 and 49.9, 732
+// MiB 196 and 197; rings of 16 and 32, 183 MiB 50.1 and 52.6, 50.5 and 53.8, but 732 MiB 206 and 200, 208 and 203, fused step
+// 273 and 257, 271 and 261); Algorithm 2's phase, ring of
 // 4, 220 MiB a call 63 and 67, 800 MiB 209 and 213, ring of 16 100 MiB 29 and 27, 220 MiB 61 and 64, 300 MiB 91 and 86; the
 // D-PSGD step, ring of 16, 220 MiB 60 and 63, 800 MiB 220 and 218; plain gossip, ring of 8, 100 MiB 44 and 44, 400 MiB 169 and
 // 175, ring of 16 181 and 174; one round, ring of 8, 100 MiB 21 and 24, torus 8x8, 140 MiB 31 and 33, 300 MiB 69 and 67.
@@ -87,7 +89,7 @@ inline uint64_t register_line(const Shape &s, int per_element, Form form) {
   }
   if (!s.bf16) return 128;
   switch (form) {
-    case kAtcForm: return 64;
+    case kAtcForm: return few || s.n >= 48 || mib < 400 ? 64 : 128;
     case kRoundForm: return mib >= 96 && (few || mib < 200) ? 64 : 128;
     case kGossipForm: return mib >= 128 && few ? 64 : 128;
     default: return mib >= 128 && (few || mib < 280) ? 64 : 128;

@@ -38,23 +38,29 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
   const uint32_t go4 = threadIdx.x * 4u;                   // ... in an fp32 row
   float u[N], p[N];
   if constexpr (MODE == 0) {
+    Loaded<ST> lx[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) u[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
+    for (int i = 0; i < N; ++i) lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) u[i] = lx[i];
     ag_rounds<T>(u, p, c, K);
     __builtin_amdgcn_sched_barrier(0);
     X = launder_uniform(X);
 #pragma unroll
     for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, u[i]);
   } else if constexpr (MODE == 3) {
+    Loaded<ST> lx[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) u[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
+    for (int i = 0; i < N; ++i) lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
     __builtin_amdgcn_sched_barrier(0);
     X = launder_uniform(X);
     float lg[N];  // gradient rows arrive a few rows ahead of the stores that consume them
 #pragma unroll
     for (int i = 0; i < D; ++i) lg[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), go4);
     __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) u[i] = lx[i];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       if (i + D < N) lg[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), go4);
@@ -65,11 +71,12 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
     static_assert(MODE == 1 || MODE == 2, "unknown mode");
     float v[N];
     if constexpr (MODE == 1) {
-      float lx[N], ly[N], lgn[N], lgo[N];
+      Loaded<ST> lx[N], ly[N];
+      float lgn[N], lgo[N];
 #pragma unroll
       for (int i = 0; i < D; ++i) {
-        lx[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
-        ly[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+        lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
+        ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
         lgn[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), go4);
         lgo[i] = buf_load<float, A>(row_of(Go, tile, ld, i, valid), go4);
       }
@@ -77,8 +84,8 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         if (i + D < N) {
-          lx[i + D] = buf_load<ST, A>(row_of(X, tile, ld, i + D, valid), so);
-          ly[i + D] = buf_load<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+          lx[i + D] = buf_request<ST, A>(row_of(X, tile, ld, i + D, valid), so);
+          ly[i + D] = buf_request<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
           lgn[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), go4);
           lgo[i + D] = buf_load<float, A>(row_of(Go, tile, ld, i + D, valid), go4);
         }
@@ -99,12 +106,18 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
 #pragma unroll
       for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, v[i]);
     } else {
+      Loaded<ST> lx[N], ly[N];
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        u[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
-        v[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+        lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
+        ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
       }
       __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        u[i] = lx[i], v[i] = ly[i];
+        pin_vgpr(u[i]);  // or its load moves behind the tracker's rounds
+      }
       ag_rounds<T>(v, p, c, K);
       __builtin_amdgcn_sched_barrier(0);
       ag_rounds<T>(u, p, c, K);
@@ -151,16 +164,19 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 0)) void structured_
   const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * blockDim.x;
   const uint32_t valid = uint32_t(d - tile < blockDim.x ? d - tile : blockDim.x);
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST));
-  float u[N], lp[N];
+  float u[N];
+  Loaded<ST> lc[N], lp[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) u[i] = buf_load<ST, A>(row_of(cur, tile, ld, i, valid), so);
+  for (int i = 0; i < N; ++i) lc[i] = buf_request<ST, A>(row_of(cur, tile, ld, i, valid), so);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < D; ++i) lp[i] = buf_load<ST, A>(row_of(prev, tile, ld, i, valid), so);
+  for (int i = 0; i < D; ++i) lp[i] = buf_request<ST, A>(row_of(prev, tile, ld, i, valid), so);
   __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < N; ++i) u[i] = lc[i];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    if (i + D < N) lp[i + D] = buf_load<ST, A>(row_of(prev, tile, ld, i + D, valid), so);
+    if (i + D < N) lp[i + D] = buf_request<ST, A>(row_of(prev, tile, ld, i + D, valid), so);
     buf_store<ST, A>(row_of(out, tile, ld, i, valid), so, next_iterate<T>(u, i, lp[i], c));
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -184,11 +200,12 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 0)) void structured_
   const uint32_t so = threadIdx.x * uint32_t(sizeof(ST));
   ST *Z = blockIdx.y ? Z1 : Z0;
   float z[N], p[N];
+  Loaded<ST> lz[N];
 #pragma unroll
-  for (int i = 0; i < N; ++i) z[i] = buf_load<ST, A>(row_of(Z, tile, ld, i, valid), so);
+  for (int i = 0; i < N; ++i) lz[i] = buf_request<ST, A>(row_of(Z, tile, ld, i, valid), so);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int i = 0; i < N; ++i) p[i] = z[i];
+  for (int i = 0; i < N; ++i) p[i] = z[i] = lz[i];
   for (int r = 0; r + 1 < K; r += 2) {
 #pragma unroll
     for (int i = 0; i < N; ++i) p[i] = as_stored<ST>(next_iterate<T>(z, i, p[i], c));

@@ -60,11 +60,12 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
   const uint64_t q = uint64_t(tile + threadIdx.x) >> 2;
   const float hc = HPW ? 0.f : buf_load<float, A>(make_rsrc(h + tile, valid * 4u), fo);
   float u[N], p[N], vr[NR > 0 ? NR : 1];
-  float lx[N], ly[N], lg[N], lb[N], lh[HPW ? N : 1];
+  Loaded<ST> lx[N], ly[N];
+  float lg[N], lb[N], lh[HPW ? N : 1];
 #pragma unroll
   for (int i = 0; i < D; ++i) {
-    lx[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
-    ly[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+    lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
+    ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
     lg[i] = buf_load<float, A>(row_of(G, tile, ld, i, valid), fo);
     lb[i] = buf_load<float, A>(row_of(b, tile, ld, i, valid), fo);
     if constexpr (HPW) lh[i] = buf_load<float, A>(row_of(h, tile, ld, i, valid), fo);
@@ -89,8 +90,8 @@ __global__ __launch_bounds__(kThreads, quad_waves(T::n, HPW)) void fused_quadrat
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     if (i + D < N) {
-      lx[i + D] = buf_load<ST, A>(row_of(X, tile, ld, i + D, valid), so);
-      ly[i + D] = buf_load<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+      lx[i + D] = buf_request<ST, A>(row_of(X, tile, ld, i + D, valid), so);
+      ly[i + D] = buf_request<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
       lg[i + D] = buf_load<float, A>(row_of(G, tile, ld, i + D, valid), fo);
       lb[i + D] = buf_load<float, A>(row_of(b, tile, ld, i + D, valid), fo);
       if constexpr (HPW) lh[i + D] = buf_load<float, A>(row_of(h, tile, ld, i + D, valid), fo);
@@ -143,11 +144,12 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
   const float hc = HPW ? 0.f : buf_load<float, A>(make_rsrc(h + tile, valid * 4u), fo);
   float u[N], v[N], p[N];
   {
-    float lx[N], ly[N], lb[N], lh[HPW ? N : 1];
+    Loaded<ST> lx[N], ly[N];
+    float lb[N], lh[HPW ? N : 1];
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      lx[i] = buf_load<ST, A>(row_of(X, tile, ld, i, valid), so);
-      ly[i] = buf_load<ST, A>(row_of(Y, tile, ld, i, valid), so);
+      lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
+      ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
       lb[i] = buf_load<float, A>(row_of(b, tile, ld, i, valid), fo);
       if constexpr (HPW) lh[i] = buf_load<float, A>(row_of(h, tile, ld, i, valid), fo);
     }
@@ -168,8 +170,8 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       if (i + D < N) {
-        lx[i + D] = buf_load<ST, A>(row_of(X, tile, ld, i + D, valid), so);
-        ly[i + D] = buf_load<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+        lx[i + D] = buf_request<ST, A>(row_of(X, tile, ld, i + D, valid), so);
+        ly[i + D] = buf_request<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
         lb[i + D] = buf_load<float, A>(row_of(b, tile, ld, i + D, valid), fo);
         if constexpr (HPW) lh[i + D] = buf_load<float, A>(row_of(h, tile, ld, i + D, valid), fo);
       }

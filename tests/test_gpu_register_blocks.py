@@ -52,3 +52,23 @@ def test_same_bits_on_both_sides_of_the_block_size_and_of_the_caches(topo, n, dt
     for d, run in zip(widths, runs):
         for k, (got, want) in enumerate(zip(run, wide)):
             assert torch.equal(got[:, : min(d, widths[-1])], want[:, : min(d, widths[-1])]), (d, k)
+
+
+def test_bf16_state_is_rounded_to_nearest_even():
+    """Every exponent, ties, denormals, infinities and NaN through a store of bf16 state: y = 0 + g - 0."""
+    exp = torch.arange(256, dtype=torch.int64)[:, None] << 23
+    man = torch.tensor([0, 1, 0x7fff, 0x8000, 0x8001, 0xffff, 0x10000, 0x17fff, 0x18000, 0x18001, 0x7f7fff, 0x7f8000, 0x7fffff])
+    bits = (exp + man).reshape(-1)
+    bits = torch.cat([bits, bits + (1 << 31)])
+    vals = torch.where(bits >= 1 << 31, bits - (1 << 32), bits).to(torch.int32).view(torch.float32)
+    d = vals.numel()
+    ctx = D.detag_create(D.Topology.ring(), 4, d, d, D.DETAG_BF16)
+    g = vals.expand(4, d).contiguous().cuda()
+    y, zero = torch.zeros(4, d, dtype=torch.bfloat16, device="cuda"), torch.zeros(4, d, device="cuda")
+    ctx.track(y, g, zero)
+    x, y2 = torch.zeros_like(y), torch.zeros_like(y)
+    ctx.step(x, y2, g, zero, 0.0, 1, 0.0, D.DETAG_VARIANT_ALG2)     # the same through the register kernels
+    want = vals.to(torch.bfloat16).float()
+    for got in (y[0], y[3], y2[1]):
+        got = got.float().cpu()
+        assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.nan_to_num(7.0), want.nan_to_num(7.0))
