@@ -16,11 +16,21 @@ constexpr int kThreads = 256;
 
 // Threads of a block.  No two wavefronts of a block work together, so its size only decides how columns spread over the
 // chip: up to 32,768 columns make 128 blocks of 256 threads or fewer and take one wavefront per block, which spreads them
-// over all compute units (phase and gradient-fused step of 4 to 64 workers, K = 2 and 8: 1 to 5 % faster at 8,192 to
-// 32,768 columns, the fused step of 64 workers up to 10 % at 40,000).  Beyond, both sizes are within 2 % up to 32 workers,
-// but the fused step of 64 workers holds 48 KiB of LDS per block whatever its threads, three blocks to a compute unit:
-// 30 us with 256 threads at d = 65,536, 50 with 64; its phase is 6 to 11 % slower with 64 from 49,152 columns on.
+// over all compute units (rounds of 4 to 64 workers 1 to 5 % faster at 8,192 to 32,768 columns).  Beyond, both sizes are
+// within 2 %.
 inline int block_threads(int64_t d) { return d <= 32768 ? 64 : kThreads; }
+
+// Small calls run the model side and the tracker side of a phase in two wavefronts of a block (fused_pair_kernel,
+// fused_quadratic_pair_kernel), which halves the chain of rounds where there are too few columns to fill the chip; with more,
+// the second read of a matrix costs more than that saves.  One wavefront for both sides and two, K = 8, fp32 (bf16 within 5 %
+// of it), replayed from a recorded graph: phase, torus 8x8 d = 1,000 15.4 and 9.2 us, 32,000 19.6 and 15.3, 65,000 26.1 and
+// 22.5, 130,000 41.2 and 50.6; ring of 32 6.7 and 4.5, 8.8 and 7.5, 12.8 and 11.7, 18.3 and 17.7; fused step, torus 8x8 19.6
+// and 13.7, 22.7 and 16.9, at 45,000 25.1 and 18.8, at 65,000 28.8 and 24.8; ring of 16 at 60,000 7.5 and 7.8; Algorithm 2 as
+// printed gains more.  K = 1: phase, ring of 32, d = 5,001 3.9 and 3.1, 32,000 5.5 and 5.5, 45,000 7.3 and 7.5.
+constexpr int kPairThreads = 128;
+inline bool pair_serves(int64_t d, int K, bool with_query) {
+  return d <= (K == 1 ? 32768 : K >= 4 && !with_query ? 65536 : 49152);
+}
 
 // Workgroups are handed to the eight XCDs (each with its own L2) round-robin by their index.  Mapping index b
 // to column tile (b % 8) * (tiles / 8) + b / 8 gives every XCD one contiguous eighth of the columns instead of

@@ -145,6 +145,100 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
   }
 }
 
+// The phase for small calls: a block is two wavefronts on the same 64 columns, the first with the model side (X), the second
+// with the tracker side (Y), so that their rounds run beside each other and not one after the other.  Both read Y (the second
+// time from the caches); nothing is stored before the barrier behind both sides' loads.  MODE 2 hands the gossiped tracker to
+// the model side through LDS.  Same arithmetic as the kernel above, same bits.
+template <class T, typename ST, int MODE>
+__global__ __launch_bounds__(kPairThreads, 2) void fused_pair_kernel(
+    ST *X, ST *Y, const float *__restrict__ Gn, const float *__restrict__ Go, int64_t d, int64_t ld, Coef c, float alpha, int K) {
+  constexpr int N = T::n;
+  constexpr int D = kRowsAhead < N ? kRowsAhead : N;
+  constexpr Access A = kKeep;
+  __shared__ float handed[MODE == 2 ? N * 64 : 1];
+  const int side = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * 64;
+  const uint32_t valid = uint32_t(d - tile < 64 ? d - tile : 64);
+  const uint32_t so = lane * uint32_t(sizeof(ST)), fo = lane * 4u;
+  float z[N], p[N];
+  if (MODE == 2 || side == 0) {
+    const ST *Z = MODE == 2 && side ? Y : X;
+    Loaded<ST> lz[N], ly[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) lz[i] = buf_request<ST, A>(row_of(Z, tile, ld, i, valid), so);
+    if constexpr (MODE == 2) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) z[i] = lz[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < D; ++i) ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if (i + D < N) ly[i + D] = buf_request<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+        z[i] = fmaf(-alpha, ly[i], lz[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else {
+    Loaded<ST> ly[N];
+    float lgn[N], lgo[N];
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
+      lgn[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), fo);
+      lgo[i] = buf_load<float, A>(row_of(Go, tile, ld, i, valid), fo);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (i + D < N) {
+        ly[i + D] = buf_request<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+        lgn[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), fo);
+        lgo[i + D] = buf_load<float, A>(row_of(Go, tile, ld, i + D, valid), fo);
+      }
+      z[i] = ly[i] + lgn[i] - lgo[i];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  ag_rounds<T>(z, p, c, K);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (MODE == 1) {
+    __syncthreads();
+    ST *Z = side ? Y : X;
+#pragma unroll
+    for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(Z, tile, ld, i, valid), so, z[i]);
+  } else {
+    float lgn[N], lgo[N];
+    if (side) {
+#pragma unroll
+      for (int i = 0; i < D; ++i) {
+        lgn[i] = buf_load<float, A>(row_of(Gn, tile, ld, i, valid), fo);
+        lgo[i] = buf_load<float, A>(row_of(Go, tile, ld, i, valid), fo);
+      }
+#pragma unroll
+      for (int i = 0; i < N; ++i) handed[i * 64 + lane] = z[i];
+    }
+    __syncthreads();
+    if (side == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, handed[i * 64 + lane], z[i]));
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if (i + D < N) {
+          lgn[i + D] = buf_load<float, A>(row_of(Gn, tile, ld, i + D, valid), fo);
+          lgo[i + D] = buf_load<float, A>(row_of(Go, tile, ld, i + D, valid), fo);
+        }
+        buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, z[i] + lgn[i] - lgo[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+}
+
 // z_{r+1} of worker i from the rows of z_r and its own z_{r-1}: what a round given z_{r-1} computes, alone or among others.
 template <class T>
 __device__ __forceinline__ float next_iterate(const float (&z)[T::n], int i, float prev, const Coef &c) {
@@ -245,6 +339,17 @@ int launch_t(const Shape &s, int mode, void *X, void *Y, const float *Gn, const 
 template <class T>
 int launch_s(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, const Coef &c,
              float alpha, int K, void *stream) {
+  if ((mode == 1 || mode == 2) && pair_serves(s.d, K, false)) {
+    const dim3 grid(ceil_div_i64(s.d, 64));
+    auto pair = [&](auto *kernel, auto of) {
+      using ST = decltype(of);
+      kernel<<<grid, kPairThreads, 0, static_cast<hipStream_t>(stream)>>>(static_cast<ST *>(X), static_cast<ST *>(Y), Gn, Go, s.d,
+                                                                          s.ld, c, alpha, K);
+      return hip_rc(hipGetLastError());
+    };
+    if (s.bf16) return mode == 1 ? pair(&fused_pair_kernel<T, bf16_t, 1>, bf16_t{}) : pair(&fused_pair_kernel<T, bf16_t, 2>, bf16_t{});
+    return mode == 1 ? pair(&fused_pair_kernel<T, float, 1>, 0.f) : pair(&fused_pair_kernel<T, float, 2>, 0.f);
+  }
   const int state = s.bf16 ? 2 : 4, per_element = mode == 0 ? state : mode == 3 ? state + 4 : 2 * state + 8;
   auto go = [&](auto access) {
     return s.bf16 ? launch_t<T, bf16_t, access>(s, mode, X, Y, Gn, Go, c, alpha, K, stream)

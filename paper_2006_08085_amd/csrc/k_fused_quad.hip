@@ -202,11 +202,130 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, 1)) void fused_quadr
   }
 }
 
+// Both forms for small calls: two wavefronts to a block on the same 64 columns, the first with the model side, the second with
+// the tracker side, whose rounds so run beside each other.  ATC: both read X and Y, the tracker side takes the gradient query.
+// Algorithm 2 as printed: the model side, which reads X, takes it and hands the gradient over in LDS, as the tracker side does
+// with the gossiped tracker.  Nothing that both read is stored before the barrier.  Same arithmetic as the kernels above, same
+// bits.
+template <class T, typename ST, bool HPW, bool ALG2>
+__global__ __launch_bounds__(kPairThreads, 2) void fused_quadratic_pair_kernel(
+    ST *X, ST *Y, float *G, const float *__restrict__ h, const float *__restrict__ b, int64_t d, int64_t ld, Coef c,
+    float alpha, int K, float sigma, uint32_t seed_lo, uint32_t seed_hi, uint32_t step) {
+  constexpr int N = T::n;
+  constexpr int D = kRowsAhead < N ? kRowsAhead : N;
+  constexpr Access A = kKeep;
+  constexpr int kQuerySide = ALG2 ? 0 : 1;
+  __shared__ float tracker[ALG2 ? N * 64 : 1], gradient[ALG2 ? N * 64 : 1];
+  const int side = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t tile = xcd_tile(blockIdx.x, gridDim.x) * 64;
+  const uint32_t valid = uint32_t(d - tile < 64 ? d - tile : 64);
+  const uint32_t so = lane * uint32_t(sizeof(ST)), fo = lane * 4u;
+  float z[N], p[N];
+  if (side == kQuerySide) {
+    const unsigned j = lane & 3u;
+    const uint64_t q = uint64_t(tile + lane) >> 2;
+    const float hc = HPW ? 0.f : buf_load<float, A>(make_rsrc(h + tile, valid * 4u), fo);
+    Loaded<ST> lx[N], ly[N];
+    float lg[N], lb[N], lh[HPW ? N : 1];
+    auto request = [&](int i) {
+      lx[i] = buf_request<ST, A>(row_of(X, tile, ld, i, valid), so);
+      lb[i] = buf_load<float, A>(row_of(b, tile, ld, i, valid), fo);
+      if constexpr (HPW) lh[i] = buf_load<float, A>(row_of(h, tile, ld, i, valid), fo);
+      if constexpr (!ALG2) {
+        ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
+        lg[i] = buf_load<float, A>(row_of(G, tile, ld, i, valid), fo);
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < D; ++i) request(i);
+    __builtin_amdgcn_sched_barrier(0);
+    if (sigma != 0.f) {  // under the first rows' loads
+#pragma unroll
+      for (int i = 0; i < N; i += 4) {
+        float r[4];
+        normal4(q, uint32_t(i) + j, step, seed_lo, seed_hi, r);
+        quad_transpose(r, j);
+        p[i] = r[0], p[i + 1] = r[1], p[i + 2] = r[2], p[i + 3] = r[3];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) p[i] = 0.f;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (i + D < N) request(i + D);
+      const float g = fmaf(sigma, p[i], (HPW ? lh[i] : hc) * (lx[i] - lb[i]));
+      if constexpr (ALG2) {
+        gradient[i * 64 + lane] = g;
+        z[i] = lx[i];
+      } else {
+        z[i] = ly[i] + g - lg[i];
+        pin_vgpr(z[i]);
+        buf_store<float, A>(row_of(G, tile, ld, i, valid), fo, g);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    Loaded<ST> lz[N], ly[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) lz[i] = buf_request<ST, A>(row_of(ALG2 ? Y : X, tile, ld, i, valid), so);
+    if constexpr (ALG2) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) z[i] = lz[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < D; ++i) ly[i] = buf_request<ST, A>(row_of(Y, tile, ld, i, valid), so);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if (i + D < N) ly[i + D] = buf_request<ST, A>(row_of(Y, tile, ld, i + D, valid), so);
+        z[i] = fmaf(-alpha, ly[i], lz[i]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  ag_rounds<T>(z, p, c, K);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!ALG2) {
+    __syncthreads();
+    ST *Z = side ? Y : X;
+#pragma unroll
+    for (int i = 0; i < N; ++i) buf_store<ST, A>(row_of(Z, tile, ld, i, valid), so, z[i]);
+  } else {
+    float lg[N];
+    if (side) {
+#pragma unroll
+      for (int i = 0; i < D; ++i) lg[i] = buf_load<float, A>(row_of(G, tile, ld, i, valid), fo);
+#pragma unroll
+      for (int i = 0; i < N; ++i) tracker[i * 64 + lane] = z[i];
+    }
+    __syncthreads();
+    if (side == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+        buf_store<ST, A>(row_of(X, tile, ld, i, valid), so, fmaf(-alpha, tracker[i * 64 + lane], z[i]));
+    } else {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        if (i + D < N) lg[i + D] = buf_load<float, A>(row_of(G, tile, ld, i + D, valid), fo);
+        const float g = gradient[i * 64 + lane];
+        buf_store<ST, A>(row_of(Y, tile, ld, i, valid), so, z[i] + g - lg[i]);
+        buf_store<float, A>(row_of(G, tile, ld, i, valid), fo, g);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+}
+
 template <class T>
 int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float *h, bool hpw, const float *b,
              const Coef &c, float alpha, int K, float sigma, uint64_t seed, uint32_t step, void *stream) {
-  const int threads = block_threads(s.d);
-  const dim3 grid(ceil_div_i64(s.d, threads));
+  const bool pair = pair_serves(s.d, K, true);
+  const int threads = pair ? kPairThreads : block_threads(s.d);
+  const dim3 grid(ceil_div_i64(s.d, pair ? 64 : threads));
   auto st = static_cast<hipStream_t>(stream);
   const uint32_t slo = uint32_t(seed & 0xffffffffu), shi = uint32_t(seed >> 32);
   auto go = [&](auto *kernel, auto *x) {
@@ -218,6 +337,18 @@ int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float 
     else go(&fused_quadratic_kernel<T, ST, per_worker, access>, x);
   };
   auto with_h = [&](auto access, auto *x) { hpw ? with(access, std::true_type{}, x) : with(access, std::false_type{}, x); };
+  if (pair) {
+    auto with_pair = [&](auto *x) {
+      using ST = std::remove_pointer_t<decltype(x)>;
+      auto form = [&](auto per_worker) {
+        alg2 ? go(&fused_quadratic_pair_kernel<T, ST, per_worker, true>, x) : go(&fused_quadratic_pair_kernel<T, ST, per_worker, false>, x);
+      };
+      hpw ? form(std::true_type{}) : form(std::false_type{});
+    };
+    if (s.bf16) with_pair(static_cast<bf16_t *>(X));
+    else with_pair(static_cast<float *>(X));
+    return hip_rc(hipGetLastError());
+  }
   const int per_element = (s.bf16 ? 4 : 8) + 8 + (hpw ? 4 : 0);
   auto with_type = [&](auto access) {
     if (s.bf16) with_h(access, static_cast<bf16_t *>(X));

@@ -54,6 +54,39 @@ def test_same_bits_on_both_sides_of_the_block_size_and_of_the_caches(topo, n, dt
             assert torch.equal(got[:, : min(d, widths[-1])], want[:, : min(d, widths[-1])]), (d, k)
 
 
+@pytest.mark.parametrize("kind,n", [("ring", 4), ("ring", 12), ("ring", 16), ("torus44", 16), ("torus48", 32), ("ring", 48),
+                                    ("ring", 64), ("torus88", 64)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [1, 63, 64, 65, 1000, 4097])
+def test_two_wavefronts_to_a_phase_give_the_bits_of_one(kind, n, dtype, d):
+    """Narrow contexts run the two sides of a phase in two wavefronts, wide ones in one: the first columns of both."""
+    wide, ld, bf = 70001, 70016, dtype == "bf16"
+    topo = D.Topology.ring() if kind == "ring" else D.Topology.torus(*{16: (4, 4), 32: (4, 8), 64: (8, 8)}[n])
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    normal = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+    sdt = torch.bfloat16 if bf else torch.float32
+    X, Y, G, B = normal(n, ld).to(sdt), normal(n, ld).to(sdt), normal(n, ld), normal(n, ld)
+    X[1, 0] = float("inf")
+    h = torch.rand(n, ld, device="cuda", generator=g)
+    dts = D.DETAG_BF16 if bf else D.DETAG_F32
+    one, two = D.detag_create(topo, n, wide, ld, dts), D.detag_create(topo, n, d, ld, dts)
+    for variant in (D.DETAG_VARIANT_ATC, D.DETAG_VARIANT_ALG2):
+        for K in (1, 4):
+            for curvature in (None, h[0].contiguous(), h):
+                out = []
+                for ctx in (one, two):
+                    x, y, gr = X.clone(), Y.clone(), G.clone()
+                    if curvature is None:
+                        ctx.step(x, y, gr, B, 0.1, K, 0.3, variant)
+                    else:
+                        ctx.step_quadratic(x, y, gr, curvature, B, 0.1, K, sigma=0.2, seed=7, step=3, eta=0.3, variant=variant)
+                    out.append((x, y, gr))
+                for a, b, before in zip(*out, (X, Y, G)):
+                    assert torch.equal(a[:, :d].nan_to_num(), b[:, :d].nan_to_num())
+                    assert torch.equal(a[:, :d].isnan(), b[:, :d].isnan())
+                    assert torch.equal(b[:, d:].nan_to_num(), before[:, d:].nan_to_num())
+
+
 def test_bf16_state_is_rounded_to_nearest_even():
     """Every exponent, ties, denormals, infinities and NaN through a store of bf16 state: y = 0 + g - 0."""
     exp = torch.arange(256, dtype=torch.int64)[:, None] << 23
