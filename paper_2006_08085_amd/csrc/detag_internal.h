@@ -107,7 +107,7 @@ bool build_dense_poly(const HostW &W, int K, double eta, int terms, std::vector<
 // mode 2: X <- P X - alpha * P Y (evaluated as P (X - alpha*Y)), Y <- P Y + Gn - Go.  n <= 256.
 int launch_dense_phase(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
                        const uint16_t *frag, void *stream);
-// The same for bf16 state with P in registers, where that serves (k_dense_bf16.hip).
+// The same with P in registers, where that serves (k_dense_resident.hip).
 bool dense_resident_serves(const Shape &s, int mode);
 int launch_dense_resident(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
                           const uint16_t *frag, void *stream);

@@ -17,7 +17,8 @@
 // term).  An infinite input leaves NaN in its column (Inf - Inf in the split),
 // where the round-by-round kernels leave Inf or NaN.
 //
-// This is the general kernel; with bf16 state all but the smallest calls take the one in k_dense_bf16.hip.
+// This is the general kernel; all but the smallest calls with bf16 state, or
+// with fp32 state and up to 128 workers, take the one in k_dense_resident.hip.
 // One block = 64 columns, 4 wavefronts, three blocks to a compute unit (two with fp32 state, whose three-term
 // operands need the registers).  The input of a pass is staged in units of
 // 128 workers.  Staging: lane = column, a wavefront loads groups of 8 consecutive rows (coalesced row segments),

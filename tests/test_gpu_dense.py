@@ -165,13 +165,16 @@ def test_config5_shape_bf16_short_run_dense():
 
 @pytest.mark.parametrize("n", [12, 17, 33, 64, 65, 100, 128, 129, 200, 256])
 @pytest.mark.parametrize("d,ld", [(64, 64), (65, 65), (129, 160), (701, 704), (1025, 1025), (40001, 40001), (33000, 33024)])
-def test_resident_kernel_gives_the_bits_of_the_general_one(n, d, ld):
-    """bf16 state: the kernel that holds P in registers against the general kernel, which serves contexts of fewer than 64
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_resident_kernel_gives_the_bits_of_the_general_one(n, d, ld, dtype):
+    """The kernel that holds P in registers against the general kernel, which serves contexts of fewer than 64
     columns: the same columns in slices of 63, around the edges of tiles of every width (64 to 512) and of a block's walk."""
     topo, W, eta = _graph(n, "rr")
+    bf = dtype == "bf16"
+    state = (lambda t: t.bfloat16()) if bf else (lambda t: t)
     g = torch.Generator(device=DEV).manual_seed(n + d)
     normal = lambda: torch.randn(n, ld, device=DEV, generator=g)  # noqa: E731
-    X, Y, Gn, Go = normal().bfloat16(), normal().bfloat16(), normal(), normal()
+    X, Y, Gn, Go = state(normal()), state(normal()), normal(), normal()
     for t in (X, Y, Gn, Go):
         t[:, d:] = SENTINEL
     edges = sorted({0, d - 63} | {min(max(0, e - 31), d - 63) for e in (64, 128, 256, 512, 1024, 16384, 32768) if e < d + 31})
@@ -182,7 +185,8 @@ def test_resident_kernel_gives_the_bits_of_the_general_one(n, d, ld):
         else:
             ctx.step(x, y, gn, go, 0.05, 3, eta, D.DETAG_VARIANT_ATC if mode == 1 else D.DETAG_VARIANT_ALG2)
 
-    whole, narrow = D.detag_create(topo, n, d, ld, D.DETAG_BF16), D.detag_create(topo, n, 63, ld, D.DETAG_BF16)
+    code = D.DETAG_BF16 if bf else D.DETAG_F32
+    whole, narrow = D.detag_create(topo, n, d, ld, code), D.detag_create(topo, n, 63, ld, code)
     for ctx in (whole, narrow):
         ctx.set_path(D.DETAG_PATH_DENSE)
     for mode in (0, 1, 2):
