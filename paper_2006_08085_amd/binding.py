@@ -1,4 +1,4 @@
-"""ctypes binding of libdetag.so: argument marshalling only.
+"""Binding of libdetag.so: argument marshalling only, by ctypes, the calls of the hot path in native code (_calls.so).
 
 Every function mirrors one entry point of include/detag.h (same name, same
 argument order) and takes torch tensors where the C call takes device
@@ -68,6 +68,7 @@ class _Topology(C.Structure):
 
 
 _lib = None
+_calls = None
 
 
 def lib() -> C.CDLL:
@@ -155,6 +156,27 @@ def lib() -> C.CDLL:
     L.detag_version.restype = C.c_char_p
     _lib = L
     return L
+
+
+def calls():
+    """The native form of the hot path's calls (once, with the first of them: it needs torch).  Raises if it has not been
+    built."""
+    global _calls
+    if _calls is None:
+        import importlib.machinery
+        import importlib.util
+        import torch
+        path = os.path.join(_HERE, "_calls.so")
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2006_08085_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_calls", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_calls", path, loader=loader))
+        loader.exec_module(module)
+        L = lib()
+        module.bind({name: C.cast(getattr(L, name), C.c_void_p).value for name in EXPORTS}, torch._C._cuda_getDevice,
+                    torch._C._cuda_getCurrentRawStream)
+        _calls = module
+    return _calls
 
 
 @dataclass
@@ -277,7 +299,10 @@ class Factors:
     def average(self, Z):
         """Z <- A_{R-1} ... A_0 Z in place: every row becomes the column mean."""
         c = self.ctx
-        c._check(lib().detag_average_consensus(c._h, self._h, c._state(Z, "Z"), c._stream()))
+        st = (c._fast or c._native()).average_consensus(self._h.value or 0, Z)
+        if st is None:
+            st = lib().detag_average_consensus(c._h, self._h, c._state(Z, "Z"), c._stream())
+        c._check(st)
 
 
 class Context:
@@ -287,8 +312,11 @@ class Context:
         self._h = C.c_void_p(handle)
         self.n, self.d, self.ld, self.dtype = n, d, ld, dtype
         self._strides = (ld, 1)
+        self._fast = None
 
     def close(self):
+        if self._fast is not None:
+            self._fast.close()
         if self._h:
             lib().detag_destroy(self._h)
             self._h = C.c_void_p(None)
@@ -300,6 +328,12 @@ class Context:
             pass
 
     # -- helpers -------------------------------------------------------------
+    def _native(self):
+        """The native calls on this context: each returns a status, or None for arguments that it leaves to ctypes."""
+        if self._fast is None:
+            self._fast = calls().Calls(self._h.value or 0, self.n, self.d, self.ld, self.dtype == DETAG_BF16)
+        return self._fast
+
     def _check(self, status: int):
         if status != DETAG_OK:
             raise DetagError(status, lib().detag_last_error(self._h).decode())
@@ -387,60 +421,92 @@ class Context:
     # -- hot path ------------------------------------------------------------
     # stream: a raw HIP stream to enqueue on in place of the current one
     def gossip_accel(self, Z, K: int, eta: float = -1.0, stream: Optional[int] = None):
-        self._check(lib().detag_gossip_accel(self._h, self._state(Z, "Z"), K, eta,
-                                             self._stream() if stream is None else stream))
+        st = (self._fast or self._native()).gossip_accel(Z, K, eta, stream)
+        if st is None:
+            st = lib().detag_gossip_accel(self._h, self._state(Z, "Z"), K, eta,
+                                          self._stream() if stream is None else stream)
+        self._check(st)
 
     def track(self, Y, G_new, G_old):
-        self._check(lib().detag_track(self._h, self._state(Y, "Y"), self._f32(G_new, "G_new"),
-                                      self._f32(G_old, "G_old"), self._stream()))
+        st = (self._fast or self._native()).track(Y, G_new, G_old)
+        if st is None:
+            st = lib().detag_track(self._h, self._state(Y, "Y"), self._f32(G_new, "G_new"),
+                                   self._f32(G_old, "G_old"), self._stream())
+        self._check(st)
 
     def step(self, X, Y, G_new, G_old, alpha: float, K: int, eta: float = -1.0, variant: int = DETAG_VARIANT_ATC):
-        self._check(lib().detag_step(self._h, self._state(X, "X"), self._state(Y, "Y"),
-                                     self._f32(G_new, "G_new"), self._f32(G_old, "G_old"),
-                                     alpha, K, eta, variant, self._stream()))
+        st = (self._fast or self._native()).step(X, Y, G_new, G_old, alpha, K, eta, variant)
+        if st is None:
+            st = lib().detag_step(self._h, self._state(X, "X"), self._state(Y, "Y"),
+                                  self._f32(G_new, "G_new"), self._f32(G_old, "G_old"),
+                                  alpha, K, eta, variant, self._stream())
+        self._check(st)
 
     def dpsgd_step(self, X, G, alpha: float):
-        self._check(lib().detag_dpsgd_step(self._h, self._state(X, "X"), self._f32(G, "G"), alpha,
-                                           self._stream()))
+        st = (self._fast or self._native()).dpsgd_step(X, G, alpha)
+        if st is None:
+            st = lib().detag_dpsgd_step(self._h, self._state(X, "X"), self._f32(G, "G"), alpha,
+                                        self._stream())
+        self._check(st)
 
     # -- Algorithm 2 iteration by iteration ---------------------------------------
     def gossip_round(self, Z_cur, Z_prev, Z_out, eta: float = -1.0, stream: Optional[int] = None):
-        self._check(lib().detag_gossip_round(self._h, self._state(Z_cur, "Z_cur"), self._state(Z_prev, "Z_prev"),
-                                             self._state(Z_out, "Z_out"), eta,
-                                             self._stream() if stream is None else stream))
+        st = (self._fast or self._native()).gossip_round(Z_cur, Z_prev, Z_out, eta, stream)
+        if st is None:
+            st = lib().detag_gossip_round(self._h, self._state(Z_cur, "Z_cur"), self._state(Z_prev, "Z_prev"),
+                                          self._state(Z_out, "Z_out"), eta,
+                                          self._stream() if stream is None else stream)
+        self._check(st)
 
     def gossip_rounds(self, Z, Z2, R: int, eta: float = -1.0, stream: Optional[int] = None):
         """R gossip_round calls from z_{-1} = z_0 in one launch, in place on Z and on Z2 (or None)."""
-        self._check(lib().detag_gossip_rounds(self._h, self._state(Z, "Z"), None if Z2 is None else self._state(Z2, "Z2"),
-                                              R, eta, self._stream() if stream is None else stream))
+        st = (self._fast or self._native()).gossip_rounds(Z, Z2, R, eta, stream)
+        if st is None:
+            st = lib().detag_gossip_rounds(self._h, self._state(Z, "Z"), None if Z2 is None else self._state(Z2, "Z2"),
+                                           R, eta, self._stream() if stream is None else stream)
+        self._check(st)
 
     def accumulate(self, G_acc, g, scale: float = 1.0):
-        self._check(lib().detag_accumulate(self._h, self._f32(G_acc, "G_acc"),
-                                           self._f32(g, "g"), scale, self._stream()))
+        st = (self._fast or self._native()).accumulate(G_acc, g, scale)
+        if st is None:
+            st = lib().detag_accumulate(self._h, self._f32(G_acc, "G_acc"),
+                                        self._f32(g, "g"), scale, self._stream())
+        self._check(st)
 
     def phase_end(self, X, X_tilde, Y, G_k, G_km1, alpha: float):
-        self._check(lib().detag_phase_end(self._h, self._state(X, "X"), self._state(X_tilde, "X_tilde"),
-                                          self._state(Y, "Y"), self._f32(G_k, "G_k"),
-                                          self._f32(G_km1, "G_km1"), alpha, self._stream()))
+        st = (self._fast or self._native()).phase_end(X, X_tilde, Y, G_k, G_km1, alpha)
+        if st is None:
+            st = lib().detag_phase_end(self._h, self._state(X, "X"), self._state(X_tilde, "X_tilde"),
+                                       self._state(Y, "Y"), self._f32(G_k, "G_k"),
+                                       self._f32(G_km1, "G_km1"), alpha, self._stream())
+        self._check(st)
 
     def defacto_update(self, X, X_tilde, G, scale: float):
-        self._check(lib().detag_defacto_update(self._h, self._state(X, "X"), self._state(X_tilde, "X_tilde"),
-                                               self._f32(G, "G"), scale, self._stream()))
+        st = (self._fast or self._native()).defacto_update(X, X_tilde, G, scale)
+        if st is None:
+            st = lib().detag_defacto_update(self._h, self._state(X, "X"), self._state(X_tilde, "X_tilde"),
+                                            self._f32(G, "G"), scale, self._stream())
+        self._check(st)
 
     # -- diagnostics -----------------------------------------------------------
     def mean(self, X, out=None):
         if out is None:
             out = _torch.empty(self.d, dtype=_torch.float32, device=X.device)
-        if out.dtype != _torch.float32 or out.numel() < self.d or not out.is_contiguous():
-            raise ValueError("out must be a contiguous float32 vector of length >= d")
-        self._check(lib().detag_mean(self._h, self._state(X, "X"), out.data_ptr(), self._stream()))
+        st = (self._fast or self._native()).mean(X, out)
+        if st is None:
+            if out.dtype != _torch.float32 or out.numel() < self.d or not out.is_contiguous():
+                raise ValueError("out must be a contiguous float32 vector of length >= d")
+            st = lib().detag_mean(self._h, self._state(X, "X"), out.data_ptr(), self._stream())
+        self._check(st)
         return out
 
     def consensus_error(self, X, out=None):
         if out is None:
             out = _torch.empty(1, dtype=_torch.float64, device=X.device)
-        self._check(lib().detag_consensus_error(self._h, self._state(X, "X"), out.data_ptr(),
-                                                self._stream()))
+        st = (self._fast or self._native()).consensus_error(X, out)
+        if st is None:
+            st = lib().detag_consensus_error(self._h, self._state(X, "X"), out.data_ptr(), self._stream())
+        self._check(st)
         return out
 
     def consensus_error_static(self, X, out):
@@ -454,66 +520,76 @@ class Context:
 
     # -- gradients ---------------------------------------------------------------
     def grad_quadratic_diag(self, X, h, b, G, noise=None, sigma: float = 0.0, seed: int = 0, step: int = 0):
-        per_worker = 1 if h.dim() == 2 else 0
-        if per_worker:
-            hp = self._f32(h, "h")
-        else:
-            if h.dtype != _torch.float32 or not h.is_cuda or h.numel() < self.d or not h.is_contiguous():
-                raise ValueError("h must be a contiguous float32 GPU vector of length >= d")
-            hp = h.data_ptr()
-        npz = None if noise is None else self._f32(noise, "noise")
-        self._check(lib().detag_grad_quadratic_diag(self._h, self._state(X, "X"), hp, per_worker,
-                                                    self._f32(b, "b"), npz, sigma, seed, step,
-                                                    self._f32(G, "G"), self._stream()))
+        st = (self._fast or self._native()).grad_quadratic_diag(X, h, b, G, sigma, seed, step) if noise is None else None
+        if st is None:
+            per_worker = 1 if h.dim() == 2 else 0
+            if per_worker:
+                hp = self._f32(h, "h")
+            else:
+                if h.dtype != _torch.float32 or not h.is_cuda or h.numel() < self.d or not h.is_contiguous():
+                    raise ValueError("h must be a contiguous float32 GPU vector of length >= d")
+                hp = h.data_ptr()
+            npz = None if noise is None else self._f32(noise, "noise")
+            st = lib().detag_grad_quadratic_diag(self._h, self._state(X, "X"), hp, per_worker,
+                                                 self._f32(b, "b"), npz, sigma, seed, step,
+                                                 self._f32(G, "G"), self._stream())
+        self._check(st)
 
     def step_quadratic(self, X, Y, G, h, b, alpha: float, K: int, sigma: float = 0.0, seed: int = 0, step: int = 0,
                        eta: float = -1.0, variant: int = DETAG_VARIANT_ATC):
         """h: a float32 vector of length >= d shared by the workers, or an n x ld matrix with one row per worker."""
-        per_worker = 1 if h.dim() == 2 else 0
-        if per_worker:
-            hp = self._f32(h, "h")
-        else:
-            if h.dtype != _torch.float32 or not h.is_cuda or h.dim() != 1 or h.numel() < self.d or not h.is_contiguous():
-                raise ValueError("h must be a contiguous float32 GPU vector of length >= d")
-            hp = h.data_ptr()
-        self._check(lib().detag_step_quadratic(self._h, self._state(X, "X"), self._state(Y, "Y"),
-                                               self._f32(G, "G"), hp, per_worker,
-                                               self._f32(b, "b"), sigma, seed, step, alpha, K, eta,
-                                               variant, self._stream()))
+        st = (self._fast or self._native()).step_quadratic(X, Y, G, h, b, alpha, K, sigma, seed, step, eta, variant)
+        if st is None:
+            per_worker = 1 if h.dim() == 2 else 0
+            if per_worker:
+                hp = self._f32(h, "h")
+            else:
+                if h.dtype != _torch.float32 or not h.is_cuda or h.dim() != 1 or h.numel() < self.d or not h.is_contiguous():
+                    raise ValueError("h must be a contiguous float32 GPU vector of length >= d")
+                hp = h.data_ptr()
+            st = lib().detag_step_quadratic(self._h, self._state(X, "X"), self._state(Y, "Y"),
+                                            self._f32(G, "G"), hp, per_worker,
+                                            self._f32(b, "b"), sigma, seed, step, alpha, K, eta,
+                                            variant, self._stream())
+        self._check(st)
 
     def grad_lstsq(self, X, A, b, G):
-        if A.dtype != _torch.float32 or not A.is_cuda or not A.is_contiguous() or A.dim() != 3 \
-                or A.shape[0] != self.n or A.shape[2] != self.d:
-            raise ValueError("A must be a contiguous float32 GPU tensor of shape (n, m, d)")
-        m = A.shape[1]
-        if b.dtype != _torch.float32 or not b.is_cuda or not b.is_contiguous() or tuple(b.shape) != (self.n, m):
-            raise ValueError("b must be a contiguous float32 GPU tensor of shape (n, m)")
-        self._check(lib().detag_grad_lstsq(self._h, self._state(X, "X"), A.data_ptr(),
-                                           b.data_ptr(), m, self._f32(G, "G"),
-                                           self._stream()))
+        st = (self._fast or self._native()).grad_lstsq(X, A, b, G)
+        if st is None:
+            if A.dtype != _torch.float32 or not A.is_cuda or not A.is_contiguous() or A.dim() != 3 \
+                    or A.shape[0] != self.n or A.shape[2] != self.d:
+                raise ValueError("A must be a contiguous float32 GPU tensor of shape (n, m, d)")
+            m = A.shape[1]
+            if b.dtype != _torch.float32 or not b.is_cuda or not b.is_contiguous() or tuple(b.shape) != (self.n, m):
+                raise ValueError("b must be a contiguous float32 GPU tensor of shape (n, m)")
+            st = lib().detag_grad_lstsq(self._h, self._state(X, "X"), A.data_ptr(),
+                                        b.data_ptr(), m, self._f32(G, "G"),
+                                        self._stream())
+        self._check(st)
 
     def grad_softmax_bf16(self, X, feats, labels, batch, C_classes: int, G, loss=None):
-        if feats.dtype != _torch.bfloat16 or not feats.is_cuda or not feats.is_contiguous() or feats.dim() != 3 \
-                or feats.shape[0] != self.n:
-            raise ValueError("feats must be a contiguous bfloat16 GPU tensor of shape (n, S, F)")
-        S, F = feats.shape[1], feats.shape[2]
-        if labels.dtype != _torch.int32 or not labels.is_cuda or not labels.is_contiguous() or tuple(labels.shape) != (self.n, S):
-            raise ValueError("labels must be a contiguous int32 GPU tensor of shape (n, S)")
-        if batch.dtype != _torch.int32 or not batch.is_cuda or not batch.is_contiguous() or batch.dim() != 2 \
-                or batch.shape[0] != self.n:
-            raise ValueError("batch must be a contiguous int32 GPU tensor of shape (n, B)")
-        B = batch.shape[1]
-        lp = None
-        if loss is not None:
-            if loss.dtype != _torch.float32 or not loss.is_cuda or loss.numel() < self.n or not loss.is_contiguous():
-                raise ValueError("loss must be a contiguous float32 GPU vector of length >= n")
-            lp = loss.data_ptr()
-        self._check(lib().detag_grad_softmax_bf16(self._h, self._state(X, "X"), feats.data_ptr(),
-                                                  labels.data_ptr(), batch.data_ptr(),
-                                                  S, F, C_classes, B, self._f32(G, "G"), lp,
-                                                  self._stream()))
-
-
+        st = (self._fast or self._native()).grad_softmax_bf16(X, feats, labels, batch, C_classes, G, loss)
+        if st is None:
+            if feats.dtype != _torch.bfloat16 or not feats.is_cuda or not feats.is_contiguous() or feats.dim() != 3 \
+                    or feats.shape[0] != self.n:
+                raise ValueError("feats must be a contiguous bfloat16 GPU tensor of shape (n, S, F)")
+            S, F = feats.shape[1], feats.shape[2]
+            if labels.dtype != _torch.int32 or not labels.is_cuda or not labels.is_contiguous() or tuple(labels.shape) != (self.n, S):
+                raise ValueError("labels must be a contiguous int32 GPU tensor of shape (n, S)")
+            if batch.dtype != _torch.int32 or not batch.is_cuda or not batch.is_contiguous() or batch.dim() != 2 \
+                    or batch.shape[0] != self.n:
+                raise ValueError("batch must be a contiguous int32 GPU tensor of shape (n, B)")
+            B = batch.shape[1]
+            lp = None
+            if loss is not None:
+                if loss.dtype != _torch.float32 or not loss.is_cuda or loss.numel() < self.n or not loss.is_contiguous():
+                    raise ValueError("loss must be a contiguous float32 GPU vector of length >= n")
+                lp = loss.data_ptr()
+            st = lib().detag_grad_softmax_bf16(self._h, self._state(X, "X"), feats.data_ptr(),
+                                               labels.data_ptr(), batch.data_ptr(),
+                                               S, F, C_classes, B, self._f32(G, "G"), lp,
+                                               self._stream())
+        self._check(st)
 def detag_create(topology: Topology, n: int, d: int, ld: Optional[int] = None, dtype: int = DETAG_F32) -> Context:
     ld = d if ld is None else ld
     h = C.c_void_p()

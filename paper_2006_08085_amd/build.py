@@ -1,4 +1,4 @@
-"""Build libdetag.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libdetag.so (HIP, gfx950 only) in-tree with hipcc, and _calls.so (host code) with g++.
 
     python -m paper_2006_08085_amd.build [--sanitize-host]
 
@@ -17,6 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdetag.so")
+CALLS = os.path.join(HERE, "_calls.so")
 
 SOURCES = ["topology.cpp", "consensus.cpp", "detag_api.hip", "k_stream.hip", "k_fused.hip", "k_fused_quad.hip", "k_fused_generic.hip", "k_fused_generic_quad.hip",
            "k_diag.hip", "k_grad.hip", "k_softmax.hip", "k_consensus.hip", "k_dense.hip", "k_dense_resident.hip"]
@@ -55,6 +56,26 @@ def sanitizer_runtime() -> str:
     return hits[-1]
 
 
+def build_calls() -> str:
+    """Builds _calls.so next to this file: the Python calls of the hot path, host code against torch's headers."""
+    import sysconfig
+    from importlib.util import find_spec
+    torch_dir = os.path.dirname(find_spec("torch").origin)
+    torch_include = os.path.join(torch_dir, "include")
+    tmp = CALLS + ".tmp"
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"], "-isystem", torch_include,
+           "-isystem", os.path.join(torch_include, "torch", "csrc", "api", "include"),
+           os.path.join(CSRC, "py_calls.cpp"), "-o", tmp,
+           # loaded already, with torch, when this library is
+           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on py_calls.cpp:\n" + r.stdout + r.stderr)
+    os.replace(tmp, CALLS)
+    return CALLS
+
+
 def build(verbose: bool = True, jobs: int = 8, sanitize_host: bool = False) -> str:
     """Builds libdetag.so next to this file; with sanitize_host the instrumented SAN_LIB under _build/san instead
     (load it with DETAG_LIB=<path> and LD_PRELOAD=sanitizer_runtime())."""
@@ -78,7 +99,10 @@ def build(verbose: bool = True, jobs: int = 8, sanitize_host: bool = False) -> s
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        native_calls = None if sanitize_host else ex.submit(build_calls)
         objs = list(ex.map(compile_one, srcs))
+        if native_calls:
+            native_calls.result()
     lib_out = SAN_LIB if sanitize_host else LIB
     tmp = lib_out + ".tmp"
     r = subprocess.run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-fno-gpu-rdc", *link_extra, "-o", tmp, *objs],
