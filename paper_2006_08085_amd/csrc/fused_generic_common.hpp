@@ -52,9 +52,10 @@ constexpr int kSlotsMax = 4;         // rows per lane (S above)
 constexpr int kThreadsMax = 1024;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 // the same for rows that start anywhere (an odd pitch): one access all the same, memory needs no 16-byte alignment
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef unsigned short u4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u2_any __attribute__((ext_vector_type(2), aligned(2)));  // four bf16 values
 
 template <Access A>
 __device__ __forceinline__ f4 load4(const float *p) {
@@ -62,14 +63,20 @@ __device__ __forceinline__ f4 load4(const float *p) {
   return A == kStream ? __builtin_nontemporal_load(q) : *q;
 }
 template <Access A>
-__device__ __forceinline__ f4 load4(const bf16_t *p) {
-  const u4_any *q = reinterpret_cast<const u4_any *>(p);
-  const u4_any t = A == kStream ? __builtin_nontemporal_load(q) : *q;
+__device__ __forceinline__ u2 load4(const bf16_t *p) {
+  const u2_any *q = reinterpret_cast<const u2_any *>(p);
+  return A == kStream ? __builtin_nontemporal_load(q) : *q;
+}
+// What a load brought, as floats: next to the use, since whatever touches it waits for it.
+__device__ __forceinline__ f4 floats(f4 v) { return v; }
+__device__ __forceinline__ f4 floats(u2 t) {
   f4 v;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(uint32_t(t[e]) << 16);
+  for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(e & 1 ? t[e / 2] & 0xffff0000u : t[e / 2] << 16);
   return v;
 }
+template <class ST>
+using Raw = std::conditional_t<std::is_same_v<ST, float>, f4, u2>;
 template <Access A>
 __device__ __forceinline__ void store4(float *p, f4 v) {
   f4_any *q = reinterpret_cast<f4_any *>(p);
@@ -78,11 +85,9 @@ __device__ __forceinline__ void store4(float *p, f4 v) {
 }
 template <Access A>
 __device__ __forceinline__ void store4(bf16_t *p, f4 v) {
-  u4_any t;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) t[e] = bf16_bits_rne(v[e]);
-  u4_any *q = reinterpret_cast<u4_any *>(p);
-  if constexpr (A != kKeep) __builtin_nontemporal_store(t, q);
+  const u2 t = {bf16_bits_rne(v[0]) | uint32_t(bf16_bits_rne(v[1])) << 16, bf16_bits_rne(v[2]) | uint32_t(bf16_bits_rne(v[3])) << 16};
+  u2_any *q = reinterpret_cast<u2_any *>(p);
+  if constexpr (A != kKeep) __builtin_nontemporal_store(u2_any(t), q);
   else *q = t;
 }
 
@@ -114,12 +119,11 @@ __device__ __forceinline__ int tile_kind(int64_t first, int lpr_log2, int64_t d)
 }
 
 template <int TILE, Access A, class ST>
-__device__ __forceinline__ f4 load4(const ST *base, int64_t row_off, const Columns &c, int64_t d) {
+__device__ __forceinline__ Raw<ST> load4(const ST *base, int64_t row_off, const Columns &c, int64_t d) {
   if constexpr (TILE != kNarrow) return load4<A>(base + (row_off + c.at));
-  f4 v;  // columns past the last repeat it
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = to_f32(base[row_off + (c.at + e < d ? c.at + e : d - 1)]);
-  return v;
+  auto one = [&](int e) { return base[row_off + (c.at + e < d ? c.at + e : d - 1)]; };  // columns past the last repeat it
+  if constexpr (std::is_same_v<ST, float>) return f4{one(0), one(1), one(2), one(3)};
+  else return u2{one(0).bits | uint32_t(one(1).bits) << 16, one(2).bits | uint32_t(one(3).bits) << 16};
 }
 template <int TILE, Access A, class ST>
 __device__ __forceinline__ void store4(ST *base, int64_t row_off, const Columns &c, int64_t d, f4 v) {
@@ -173,12 +177,23 @@ constexpr uint32_t second_tile(int S) { return uint32_t(S) * kThreadsMax * 16u; 
 // comes after them.
 template <int S>
 constexpr bool kFetchFirst = S < kSlotsMax;
+// Rows requested ahead of the one in use, where a row is four or five arrays (PLENTY of two arrays or four; with the noise
+// one less).  A lane's rows one after the other, each waiting for its own loads, were the memory phases of these kernels:
+// half of the blocks of a compute unit are in their rounds, and the others did not keep the memory busy.  Within 64 registers
+// one row fits ahead, none beside the noise, whose Philox state then spills (bf16 values unpacked next to their loads took
+// two registers to one and spilled 22).  One by one and ahead: phase, 300 workers, 4-regular, d = 100,000, K = 8 fp32 253 ->
+// 240 us, K = 2, bf16 140 -> 115; 200 irregular workers, d = 300,000, K = 8, bf16 505 -> 455; fused step, 100 irregular
+// workers, d = 500,000, K = 8 460 -> 425, 30, d = 1,000,000, K = 3, bf16 158 -> 135, 64 workers, 4-regular, d = 1,000,000,
+// K = 8 375 -> 368, 24 irregular workers, d = 3,000, K = 4 with its gradient 12.7 -> 10.9.
+template <class R, int PLENTY>
+constexpr int kAhead = R::kSlots < kSlotsMax ? R::kSlots - 1 : PLENTY - (R::kWaves == 8);
 
 template <int DEG, int S>
 struct ByteRounds {
   static constexpr int kSlots = S, kWords = DEG <= 4 ? 1 : DEG / 4;
   static constexpr int kWaves = S == 4 ? 8 : 4;  // wavefronts per SIMD asked of the register allocator
   static constexpr int kParked = S == 4 ? 1 : 0;
+  static constexpr bool kRowsInMemory = false;
   struct Args {
     const uint32_t *table;  // kWords words per row, 256 rows: one byte per neighbour, its row number
     float weight;
@@ -248,13 +263,13 @@ struct ByteRounds {
 // 100,000, K = 8: phase 314 -> 257 us; 600 workers, d = 50,000, K = 4 304 -> 240; ring of 1000, d = 60,000, bf16 state,
 // K = 4, Algorithm 2's phase 541 -> 297).
 struct HalfArgs {
-  const int32_t *rows;      // row number of each position (-1: none)
   const uint32_t *offsets;  // DEG / 2 words per position
   float weight;
 };
 template <int DEG>
 struct HalfRounds {
   static constexpr int kSlots = kSlotsMax, kParked = 1, kWaves = DEG <= 4 ? 6 : 5, kWords = DEG / 2;
+  static constexpr bool kRowsInMemory = false;
   using Args = HalfArgs;
   uint32_t w[kSlots][kWords];
   float b;
@@ -268,7 +283,7 @@ struct HalfRounds {
       for (int q = 0; q < kWords; ++q) w[s][q] = a.offsets[p.pos(s) * kWords + q] + col_bytes * 0x00010001u;
     b = (1.f + eta) * a.weight;
   }
-  __device__ __forceinline__ int row(const Args &a, const Place &p, int s) const { return a.rows[p.pos(s)]; }
+  __device__ __forceinline__ int row(const Args &, const Place &p, int s) const { return int(p.pos(s)); }
 
   __device__ __forceinline__ f4 neighbour(int s, int k) const {
     return lds_read(k & 1 ? w[s][k / 2] >> 16 : w[s][k / 2] & 0xffffu);
@@ -318,6 +333,7 @@ struct ListArgs {
 template <int S>
 struct CsrRounds {
   static constexpr int kSlots = S, kWaves = S == 4 ? 6 : 4, kParked = 0;
+  static constexpr bool kRowsInMemory = true;
   using Args = ListArgs;
   uint32_t first[S], count[S];  // uniform in a wavefront
   uint32_t list;                // LDS offset of the lane's row in a group's first pair
@@ -360,6 +376,7 @@ constexpr int kListPairs = 4;
 template <int S>
 struct ListRounds {
   static constexpr int kSlots = S, kWaves = 4, kParked = 0;
+  static constexpr bool kRowsInMemory = false;
   using Args = ListArgs;
   f4 list[S][kListPairs];
   uint32_t at[S][2 * kListPairs];
@@ -490,22 +507,37 @@ __device__ __forceinline__ void gossip(f4 (&z)[R::kSlots], R &rounds, Place &p, 
   p.forget();
 }
 
-// Calls f(tile, s, row offset, columns, mine) for the lane's rows in turn, with the scheduler fenced in between: left
-// alone, the compiler issues every row's loads at once and spills.  `tile` is a compile-time value of Tile.  A position
-// past the last row reads row 0 and must not store (mine = false); no list names it.  CUT as above.
-template <class R, bool CUT, class F>
+// Calls request(tile, s, row offset, columns, row) for the lane's rows in turn and, AHEAD rows behind, use(tile, s, row offset,
+// columns, mine, what request returned), with the scheduler fenced in between: left alone, the compiler issues every row's
+// loads at once and spills.  `tile` is a compile-time value of Tile.  A position past the last row reads row 0 and must not
+// store (mine = false); no list names it.  CUT as above.
+template <int AHEAD, class R, bool CUT, class Request, class Use>
 __device__ __forceinline__ void each_row(const R &rounds, const typename R::Args &ra, Place &p, int tile, int n, int64_t d,
-                                         int64_t ld, int64_t first, F &&f) {
-  auto go = [&](auto of) {
+                                         int64_t ld, int64_t first, Request &&request, Use &&use) {
+  constexpr int S = R::kSlots;
+  int rows[S];
+  if constexpr (R::kRowsInMemory) {  // together, and not each ahead of its own accesses
+    p.forget();
 #pragma unroll
-    for (int s = 0; s < R::kSlots; ++s) {
+    for (int s = 0; s < S; ++s) rows[s] = rounds.row(ra, p, s);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  auto go = [&](auto of) {
+    auto at = [&](int s, auto &&f) {
       p.forget();
       Columns c{first + p.col(), 0};
       if (of == kCut && c.at > d - 4) c = Columns{d - 4, int(c.at - (d - 4))};
-      const int row = rounds.row(ra, p, s);
+      const int row = R::kRowsInMemory ? rows[s] : rounds.row(ra, p, s);
       const bool mine = row >= 0 && row < n;
-      f(of, s, int64_t(mine ? row : 0) * ld, c, mine);
+      f(int64_t(mine ? row : 0) * ld, c, row, mine);
       __builtin_amdgcn_sched_barrier(0);
+    };
+    decltype(request(of, 0, int64_t{}, Columns{}, 0)) on_the_way[S];
+#pragma unroll
+    for (int s = 0; s < S + AHEAD; ++s) {
+      if (s < S) at(s, [&](int64_t off, Columns c, int row, bool) { on_the_way[s] = request(of, s, off, c, row); });
+      if (s >= AHEAD)
+        at(s - AHEAD, [&](int64_t off, Columns c, int, bool mine) { use(of, s - AHEAD, off, c, mine, on_the_way[s - AHEAD]); });
     }
   };
   if (tile >= kWhole) {
@@ -514,6 +546,14 @@ __device__ __forceinline__ void each_row(const R &rounds, const typename R::Args
     if (CUT && tile == kCut) go(std::integral_constant<int, CUT ? kCut : kNarrow>{});
     else go(std::integral_constant<int, kNarrow>{});
   }
+}
+// use(tile, s, row offset, columns, mine) alone.
+struct Nothing {};
+template <class R, bool CUT, class Use>
+__device__ __forceinline__ void each_row(const R &rounds, const typename R::Args &ra, Place &p, int tile, int n, int64_t d,
+                                         int64_t ld, int64_t first, Use &&use) {
+  each_row<0, R, CUT>(rounds, ra, p, tile, n, d, ld, first, [&](auto, int, int64_t, Columns, int) { return Nothing{}; },
+                      [&](auto F, int s, int64_t off, Columns c, bool mine, Nothing) { use(F, s, off, c, mine); });
 }
 
 // Columns, rows per lane and threads of a block.  A tile takes 16 bytes per lane and row: 64 KiB at most.
@@ -689,7 +729,7 @@ int with_rounds(const Shape &s, const LdsTable &t, F &&f) {
   if (t.half_deg) {
     auto go = [&](auto r) {
       using R = typename decltype(r)::type;
-      return f(r, g, g.tile_bytes(R::kParked), HalfArgs{t.rows, t.offsets, t.weight});
+      return f(r, g, g.tile_bytes(R::kParked), HalfArgs{t.offsets, t.weight});
     };
     switch (t.half_deg) {
       case 2: return go(RoundsTag<HalfRounds<2>>{});

@@ -142,10 +142,10 @@ __global__ __launch_bounds__(256, TABLE_IN_LDS ? 8 : 7) void factor_sequence_ker
   if (group == 0) lds_write(tile + uint32_t(n) * kRowBytes, f4{0.f, 0.f, 0.f, 0.f});
   with_kind([&](auto kind_of) {
     for (int r0 = 0; r0 < n; r0 += kChunk * kGroup) {
-      f4 v[kChunk];
+      Raw<ST> v[kChunk];
       each_row(r0, kind_of, [&](auto of, int k, int row) { v[k] = load4<of, A>(Z, int64_t(row) * ld, c, d); });
       __builtin_amdgcn_sched_barrier(0);
-      each_row(r0, kind_of, [&](auto, int k, int row) { lds_write(tile + uint32_t(row) * kRowBytes, v[k]); });
+      each_row(r0, kind_of, [&](auto, int k, int row) { lds_write(tile + uint32_t(row) * kRowBytes, floats(v[k])); });
     }
   });
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // lanes read what others wrote

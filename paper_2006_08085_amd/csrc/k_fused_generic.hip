@@ -28,21 +28,34 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
   f4 z[R::kSlots];
   Waiting<R> v;
   R rounds;  // set up after the first loads: until then its registers are free for them
-  auto rows = [&](auto f) { each_row<R, true>(rounds, ra, p, tile, n, d, ld, first, f); };
+  auto rows = [&](auto use) { each_row<R, true>(rounds, ra, p, tile, n, d, ld, first, use); };
+  auto rows_ahead = [&](auto ahead, auto request, auto use) {
+    each_row<ahead, R, true>(rounds, ra, p, tile, n, d, ld, first, request, use);
+  };
+  constexpr std::integral_constant<int, R::kSlots - 1> kAllAhead;
+  auto load_all = [&](const ST *from) {
+    rows_ahead(kAllAhead, [&](auto F, int, int64_t off, Columns c, int) { return load4<F, A>(from, off, c, d); },
+               [&](auto, int s, int64_t, Columns, bool, Raw<ST> r) { z[s] = floats(r); });
+  };
   if constexpr (kFetchFirst<R::kSlots>) rounds.fetch(ra, p);
   if constexpr (MODE == 0) {
-    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F, A>(X, off, c, d); });
+    load_all(X);
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F, A>(X, off, c, d, z[s]); });
   } else if constexpr (MODE == 1) {
     // every input is read once: the second gossip's input Y + Gn - Go waits in registers under the first
-    rows([&](auto F, int s, int64_t off, Columns c, bool) {
-      const f4 x = load4<F, A>(X, off, c, d), y = load4<F, A>(Y, off, c, d);
-      const f4 gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d);
-      z[s] = fma4(-alpha, y, x);
-      f4 t = y + gn - go;
-      pin4(t);  // the sum now, not its three operands carried through the rounds
+    struct Row {
+      Raw<ST> x, y;
+      f4 gn, go;
+    };
+    rows_ahead(std::integral_constant<int, kAhead<R, 2>>{}, [&](auto F, int, int64_t off, Columns c, int) {
+      return Row{load4<F, A>(X, off, c, d), load4<F, A>(Y, off, c, d), load4<F, A>(Gn, off, c, d), load4<F, A>(Go, off, c, d)};
+    }, [&](auto, int s, int64_t, Columns, bool, const Row &r) {
+      const f4 y = floats(r.y);
+      z[s] = fma4(-alpha, y, floats(r.x));
+      f4 t = y + r.gn - r.go;
+      pin4(z[s]), pin4(t);  // the sums now, not their operands carried through the rounds
       v.put(p, s, t);
     });
     rounds.init(ra, p, eta);
@@ -55,8 +68,14 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F, A>(Y, off, c, d, z[s]); });
   } else if constexpr (MODE == 3) {
     f4 g[R::kSlots];
-    rows([&](auto F, int s, int64_t off, Columns c, bool) {
-      z[s] = load4<F, A>(X, off, c, d), g[s] = load4<F, A>(Gn, off, c, d);
+    struct Row {
+      Raw<ST> x;
+      f4 g;
+    };
+    rows_ahead(kAllAhead, [&](auto F, int, int64_t off, Columns c, int) {
+      return Row{load4<F, A>(X, off, c, d), load4<F, A>(Gn, off, c, d)};
+    }, [&](auto, int s, int64_t, Columns, bool, const Row &r) {
+      z[s] = floats(r.x), g[s] = r.g;
       lds_write(p.own(s), z[s]);
     });
     rounds.init(ra, p, eta);
@@ -70,19 +89,23 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     });
   } else {
     // M(Y) first: both outputs need it
-    rows([&](auto F, int s, int64_t off, Columns c, bool) { z[s] = load4<F, A>(Y, off, c, d); });
+    load_all(Y);
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, Columns c, bool) {
-      v.put(p, s, z[s]);
-      z[s] = load4<F, A>(X, off, c, d);
-    });
+#pragma unroll
+    for (int s = 0; s < R::kSlots; ++s) v.put(p, s, z[s]);
+    load_all(X);
     gossip(z, rounds, p, eta, K);
-    rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
-      const f4 gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d), my = v.get(p, s);
+    struct Row {
+      f4 gn, go;
+    };
+    rows_ahead(std::integral_constant<int, kAhead<R, 2>>{}, [&](auto F, int, int64_t off, Columns c, int) {
+      return Row{load4<F, A>(Gn, off, c, d), load4<F, A>(Go, off, c, d)};
+    }, [&](auto F, int s, int64_t off, Columns c, bool mine, const Row &r) {
+      const f4 my = v.get(p, s);
       if (mine) {
         store4<F, A>(X, off, c, d, fma4(-alpha, my, z[s]));
-        store4<F, A>(Y, off, c, d, my + gn - go);
+        store4<F, A>(Y, off, c, d, my + r.gn - r.go);
       }
     });
   }
@@ -185,6 +208,24 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
   if (g.cols == 0) return false;
   const int positions = g.positions(), lpr = g.cols / 4, rows_per_wave = 64 / lpr, waves = g.threads / 64;
   const int per_slot = g.threads / lpr;
+  auto offset = [&](int p) { return uint32_t(p) * g.cols * 4u; };
+  // with weights of their own the lists stay in LDS: offsets in registers (16 of them, and one wavefront less per SIMD) and
+  // only the weights there measured -16 to +13 % (D-PSGD step and Algorithm 2's phase of 48 and 200 irregular workers 112 ->
+  // 125 us and 153 -> 166)
+  if (g.slots == kSlotsMax && maxdeg <= 8 && one_weight) {
+    out.half_deg = maxdeg <= 2 ? 2 : maxdeg <= 4 ? 4 : 8;
+    out.weight = weight;
+    out.offsets.assign(size_t(positions) * out.half_deg / 2, 0u);
+    for (int i = 0; i < positions; ++i) {  // a row sits at its own number
+      size_t k = size_t(i) * out.half_deg;
+      auto put = [&](uint32_t off) { out.offsets[k / 2] |= off << (16 * (k % 2)), ++k; };
+      if (i < n)
+        for (int t = W.rowptr[i]; t < W.rowptr[i + 1]; ++t)
+          if (W.colidx[t] != i) put(offset(W.colidx[t]));
+      while (k < size_t(i + 1) * out.half_deg) put(offset(i));  // a missing neighbour is the row itself: difference zero
+    }
+    return true;
+  }
   // rows by falling degree; slot by slot, every other slot from the last wavefront to the first, so that no wavefront
   // gets the longest lists of every slot
   std::vector<int> order(n);
@@ -202,25 +243,6 @@ bool build_lds_table(const HostW &W, int64_t d, LdsTableHost &out) {
         out.rows[p] = order[next], position[order[next]] = p, ++next;
       }
     }
-  auto offset = [&](int p) { return uint32_t(p) * g.cols * 4u; };
-  // with weights of their own the lists stay in LDS: offsets in registers (16 of them, and one wavefront less per SIMD) and
-  // only the weights there measured -16 to +13 % (D-PSGD step and Algorithm 2's phase of 48 and 200 irregular workers 112 ->
-  // 125 us and 153 -> 166)
-  if (g.slots == kSlotsMax && maxdeg <= 8 && one_weight) {
-    out.half_deg = maxdeg <= 2 ? 2 : maxdeg <= 4 ? 4 : 8;
-    out.weight = weight;
-    out.offsets.assign(size_t(positions) * out.half_deg / 2, 0u);
-    for (int p = 0; p < positions; ++p) {
-      const int i = out.rows[p];
-      size_t k = size_t(p) * out.half_deg;
-      auto put = [&](uint32_t off) { out.offsets[k / 2] |= off << (16 * (k % 2)), ++k; };
-      if (i >= 0)
-        for (int t = W.rowptr[i]; t < W.rowptr[i + 1]; ++t)
-          if (W.colidx[t] != i) put(offset(position[W.colidx[t]]));
-      while (k < size_t(p + 1) * out.half_deg) put(offset(p));  // a missing neighbour is the row itself: difference zero
-    }
-    return true;
-  }
   for (int w = 0; w < waves; ++w)
     for (int s = 0; s < g.slots; ++s) {
       const int p0 = s * per_slot + w * rows_per_wave;

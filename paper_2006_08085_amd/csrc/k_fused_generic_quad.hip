@@ -31,29 +31,36 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_quadrati
   f4 z[R::kSlots];
   Waiting<R> v;
   R rounds;  // set up after the loads: until then its registers are free for them
-  auto rows = [&](auto f) { each_row<R, kCutTiles>(rounds, ra, p, tile, n, d, ld, first, f); };
+  auto rows = [&](auto use) { each_row<R, kCutTiles>(rounds, ra, p, tile, n, d, ld, first, use); };
   if constexpr (kFetchFirst<R::kSlots>) rounds.fetch(ra, p);
-  rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
+  struct Row {
+    f4 noise, b, h, go;
+    Raw<ST> x, y;
+  };
+  each_row<kAhead<R, 1>, R, kCutTiles>(rounds, ra, p, tile, n, d, ld, first, [&](auto F, int, int64_t off, Columns c, int row) {
     // the row's noise first, its loads after: generated under the loads, the Philox state and the values in flight
     // are live together and the kernel does not fit its registers
-    f4 noise = {0.f, 0.f, 0.f, 0.f};
+    Row r;
+    r.noise = f4{0.f, 0.f, 0.f, 0.f};
     if (sigma != 0.f) {
       float t[4];
-      normal4(uint64_t(c.at + c.skip) >> 2, uint32_t(rounds.row(ra, p, s)), step, seed_lo, seed_hi, t);
-      noise = f4{t[0], t[1], t[2], t[3]};
+      normal4(uint64_t(c.at + c.skip) >> 2, uint32_t(row), step, seed_lo, seed_hi, t);
+      r.noise = f4{t[0], t[1], t[2], t[3]};
       if (F == kCut && c.skip > 0)  // the block of the lane's own columns, moved to where they are
-        noise = f4{t[0], c.skip == 1 ? t[0] : t[1], c.skip == 1 ? t[1] : t[0], c.skip == 1 ? t[2] : c.skip == 2 ? t[1] : t[0]};
+        r.noise = f4{t[0], c.skip == 1 ? t[0] : t[1], c.skip == 1 ? t[1] : t[0], c.skip == 1 ? t[2] : c.skip == 2 ? t[1] : t[0]};
     }
     __builtin_amdgcn_sched_barrier(0);
-    const f4 x = load4<F, A>(X, off, c, d), bb = load4<F, A>(b, off, c, d), hh = load4<F, A>(h, HPW ? off : 0, c, d);
+    r.x = load4<F, A>(X, off, c, d), r.b = load4<F, A>(b, off, c, d), r.h = load4<F, A>(h, HPW ? off : 0, c, d);
+    r.y = load4<F, A>(Y, off, c, d), r.go = load4<F, A>(G, off, c, d);
+    return r;
+  }, [&](auto F, int s, int64_t off, Columns c, bool mine, const Row &r) {
     f4 g;
+    const f4 x = floats(r.x), y = floats(r.y);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) g[e] = fmaf(sigma, noise[e], hh[e] * (x[e] - bb[e]));
-    __builtin_amdgcn_sched_barrier(0);
-    const f4 y = load4<F, A>(Y, off, c, d), go = load4<F, A>(G, off, c, d);
+    for (int e = 0; e < 4; ++e) g[e] = fmaf(sigma, r.noise[e], r.h[e] * (x[e] - r.b[e]));
     z[s] = fma4(-alpha, y, x);
-    f4 t = y + g - go;
-    pin4(t);
+    f4 t = y + g - r.go;
+    pin4(z[s]), pin4(t);
     v.put(p, s, t);
     if (mine) store4<F, A>(G, off, c, d, g);
   });
