@@ -122,33 +122,79 @@ __device__ __forceinline__ vf4_t load4(const bf16_t *p) {
   return v;
 }
 
+// acc[q][k] += the products of row q and x, pieces k, k + 4, ... of 256 columns, for ROWS rows side by side: a lane takes four
+// columns of a piece, and the loads of four pieces are in flight.  In the last d % 1024 columns a lane whose four do not all
+// exist takes the row's last four and leaves those out that are not its own (column by column, 64 at a time, their loads
+// waited for one another: 8 workers, 64 x 1000 10.4 us in one launch, so 7.1; 32, 33 x 777 6.0 us for the first of two, so
+// 3.6; 16, 100 x 4999 11.0, so 8.0).
+constexpr int kPieces = 4;
+template <int ROWS, typename ST>
+__device__ __forceinline__ void lstsq_dot(const float *const (&row)[ROWS], const ST *x, int64_t d, int lane,
+                                          float (&acc)[ROWS][kPieces]) {
+  int64_t c = lane * 4;
+  vf4_t av[ROWS][kPieces], xv[kPieces];
+  auto add = [&](int k) {
+#pragma unroll
+    for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[q][k] = fmaf(av[q][k][e], xv[k][e], acc[q][k]);
+  };
+  for (; c - lane * 4 + kPieces * 256 <= d; c += kPieces * 256) {
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+      xv[k] = load4(x + c + 256 * k);
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) av[q][k] = load4(row[q] + c + 256 * k);
+    }
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) add(k);
+  }
+  const int left = int(d - (c - lane * 4));  // uniform, < 1024
+  if (d < 4) {
+    if (lane < left) {
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) acc[q][0] = fmaf(row[q][lane], to_f32(x[lane]), acc[q][0]);
+    }
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < kPieces; ++k)
+    if (256 * k < left) {
+      const int64_t own = c + 256 * k, at = own < d - 4 ? own : d - 4;
+      const int skip = int(own - at);
+      xv[k] = load4(x + at);
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q) av[q][k] = load4(row[q] + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xv[k][e] = e < skip ? 0.f : xv[k][e];
+#pragma unroll
+      for (int q = 0; q < ROWS; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) av[q][k][e] = e < skip ? 0.f : av[q][k][e];
+    }
+#pragma unroll
+  for (int k = 0; k < kPieces; ++k)
+    if (256 * k < left) add(k);
+}
+
 // resid[i*m + r] = A_i[r,:] . x_i - b_i[r]; one block of one wavefront per (i, r), which spreads a few hundred rows over
 // all compute units.  Four 16-byte pieces of the row and of x are in flight per lane, each with a sum of its own.
 template <typename ST>
 __global__ __launch_bounds__(64) void lstsq_resid_kernel(int64_t first_row, int m, int64_t d, int64_t ld, const ST *__restrict__ X,
                                                          const float *__restrict__ A, const float *__restrict__ b,
                                                          float *__restrict__ resid) {
-  constexpr int kPieces = 4;
   const int64_t row = first_row + blockIdx.x;  // = i*m + r
   const int lane = threadIdx.x;
   const float *a = A + row * d;
-  const ST *x = X + row / m * ld;
-  float acc[kPieces] = {0.f, 0.f, 0.f, 0.f};
-  int64_t c = lane * 4;
-  for (; c - lane * 4 + kPieces * 256 <= d; c += kPieces * 256) {
-    vf4_t av[kPieces], xv[kPieces];
-#pragma unroll
-    for (int k = 0; k < kPieces; ++k) av[k] = load4(a + c + 256 * k), xv[k] = load4(x + c + 256 * k);
-#pragma unroll
-    for (int k = 0; k < kPieces; ++k)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[k] = fmaf(av[k][e], xv[k][e], acc[k]);
-  }
-  for (int64_t t = c - lane * 3; t < d; t += 64) acc[0] = fmaf(a[t], to_f32(x[t]), acc[0]);  // the last d % 1024 columns
-  float sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  const ST *x = X + (row >> 32 ? row / m : int64_t(uint32_t(row) / uint32_t(m))) * ld;
+  const float target = b[row];  // not behind the sum
+  float acc[1][kPieces] = {};
+  const float *const only[1] = {a};
+  lstsq_dot(only, x, d, lane, acc);
+  float sum = (acc[0][0] + acc[0][1]) + (acc[0][2] + acc[0][3]);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_down(sum, o, 64);
-  if (lane == 0) resid[row] = sum - b[row];
+  if (lane == 0) resid[row] = sum - target;
 }
 
 // G[i,c] = sum_r A_i[r,c] * resid[i,r].  A block owns 4 * LANES columns of one worker; LANES lanes side by side take a
@@ -208,8 +254,8 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_c
 // in one go: a wavefront per row as in lstsq_resid_kernel, whose sums they are bit for bit, kSumRows rows side by side.  What
 // such a call costs is the host behind its launches, not the GPU: called back to back, two launches and one, 8 workers, 64 x
 // 1024 8.3 and 6.0 us a call, 32 workers, 64 x 500 8.7 and 6.2, while on the GPU (a recorded graph of 20 calls, a replay of
-// it by the call) they take 5.4 and 6.7, 6.7 and 6.7.  Blocks of a worker go to one XCD where n is a multiple of eight, so
-// that its L2 serves all of them but the first.  Blocks of 128 and 256 columns repeat less of the first product and are
+// it by the call) they take 5.4 and 6.7, 6.7 and 6.7 (measured with the last columns one by one, as were the figures of the
+// rule below).  Blocks of a worker go to one XCD where n is a multiple of eight, so that its L2 serves all of them but the first.  Blocks of 128 and 256 columns repeat less of the first product and are
 // slower both ways (8 workers, 64 x 1024 6.8 and 8.7 us a call).
 constexpr int kSumRows = 4;
 constexpr int kSmallRows = kSumRows * (kSumThreads / 64), kSmallCols = 1024;
@@ -217,7 +263,7 @@ template <typename ST>
 __global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t d, int64_t ld, const ST *__restrict__ X,
                                                                   const float *__restrict__ A, const float *__restrict__ b,
                                                                   float *__restrict__ G) {
-  constexpr int kPieces = 4, kLanes = 16, kCols = 4 * kLanes, kWaves = kSumThreads / 64;
+  constexpr int kLanes = 16, kCols = 4 * kLanes, kWaves = kSumThreads / 64;
   __shared__ float res[kSmallRows];
   __shared__ float part[kWaves][kCols];
   const int i = blockIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -229,27 +275,7 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t
     const float *row[kSumRows];
 #pragma unroll
     for (int q = 0; q < kSumRows; ++q) row[q] = a + int64_t(wave + q * kWaves < m ? wave + q * kWaves : r0) * d;
-    int64_t c = lane * 4;
-    for (; c - lane * 4 + kPieces * 256 <= d; c += kPieces * 256) {
-      vf4_t av[kSumRows][kPieces], xv[kPieces];
-#pragma unroll
-      for (int k = 0; k < kPieces; ++k) {
-        xv[k] = load4(x + c + 256 * k);
-#pragma unroll
-        for (int q = 0; q < kSumRows; ++q) av[q][k] = load4(row[q] + c + 256 * k);
-      }
-#pragma unroll
-      for (int q = 0; q < kSumRows; ++q)
-#pragma unroll
-        for (int k = 0; k < kPieces; ++k)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[q][k] = fmaf(av[q][k][e], xv[k][e], acc[q][k]);
-    }
-    for (int64_t t = c - lane * 3; t < d; t += 64) {  // the last d % 1024 columns
-      const float xt = to_f32(x[t]);
-#pragma unroll
-      for (int q = 0; q < kSumRows; ++q) acc[q][0] = fmaf(row[q][t], xt, acc[q][0]);
-    }
+    lstsq_dot(row, x, d, lane, acc);
 #pragma unroll
     for (int q = 0; q < kSumRows; ++q) {
       float sum = (acc[q][0] + acc[q][1]) + (acc[q][2] + acc[q][3]);

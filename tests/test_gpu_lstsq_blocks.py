@@ -34,6 +34,19 @@ def test_blocks(n, d, m, pad, dtype):
     assert padding_ok(G, d)
 
 
+@pytest.mark.parametrize("d", [2, 3, 4, 6, 7, 258, 511, 770, 1027])
+@pytest.mark.parametrize("m", [3, 65])  # one launch and two (both two beyond 1024 columns)
+def test_the_last_columns_of_a_row(d, m):
+    """A lane whose four columns do not all exist reads the row's last four: each product is counted once.  Small whole
+    numbers, so that every sum is exact in any order."""
+    n, rng = 3, np.random.default_rng(d * m)
+    X, A, b = (rng.integers(-3, 4, shape).astype(np.float64) for shape in ((n, d), (n, m, d), (n, m)))
+    ctx = D.detag_create(D.Topology.ring(), n, d, d)
+    G = to_dev(np.zeros((n, d)), d)
+    ctx.grad_lstsq(to_dev(X, d), *(torch.from_numpy(t.astype(np.float32)).to(DEV) for t in (A, b)), G)
+    assert np.array_equal(to_host(G, d), OO.grad_lstsq(X, A, b))
+
+
 def _alone(d):
     return D.detag_create(D.Topology.from_dense(np.ones((1, 1))), 1, d, d)
 
