@@ -23,7 +23,7 @@
 //     multiplies on the matrix cores.  (The products in fp32 on the vector ALUs, samples shared among the wavefronts
 //     and summed in LDS at the end, took 16 to 17 us: 4.9 us of multiplications and a 3 us tail.)
 // The times at the two kernels are for 32 workers, 128 samples, 3072 features and 10 classes; with the phase after them
-// the call takes 29.7 us, 47.3 before.
+// the call takes 25.8 us.
 //
 // MFMA 16x16x32 operand layout (lane l, m = l % 16, q = l / 16):
 //   A: row m, k = 8q..8q+7      B: column m, k = 8q..8q+7
@@ -65,7 +65,7 @@ __device__ __forceinline__ void bf16_split(float w, uint16_t (&t)[3]) {
 __device__ __forceinline__ int clamped(int v, int n) { return v < 0 ? 0 : v >= n ? n - 1 : v; }
 
 // grid (chunks, n), B/16 wavefronts.  part[i][chunk][c][s] = sum over the chunk's features.
-// 32 workers x 8 chunks: 9.7 us (formerly a splitting kernel, 5.7 us, and 128 blocks that split the features over 16
+// 32 workers x 8 chunks: 7.4 us (formerly a splitting kernel, 5.7 us, and 128 blocks that split the features over 16
 // wavefronts and summed in LDS, 20.7 us).
 __global__ __launch_bounds__(64 * kSamplesMax / 16) void softmax_logits_kernel(
     int64_t ld, const float *__restrict__ X, const uint16_t *__restrict__ feat, const int32_t *__restrict__ batch, int S, int F,
@@ -75,13 +75,29 @@ __global__ __launch_bounds__(64 * kSamplesMax / 16) void softmax_logits_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m = lane & 15, q = lane >> 4;
   const int idx = clamped(batch[int64_t(i) * B + wave * 16 + m], S);
   const uint16_t *frow = feat + (int64_t(i) * S + idx) * F + f0 + 8 * q;
+  // the weights are asked for ahead of the features, which wait for the numbers of the samples, and split while those arrive
+  // (behind them 32 workers, 128 samples, 3072 features 8.6 us, so 7.4; 8, 32 samples, 64 features 3.8 and 3.1;
+  // but 32, 256 samples, 4096 features 17.4 and 18.0)
+  auto weights = [&](int k) {
+    const int c = k / nf, f = k % nf;  // nf is a multiple of 32: the four stay in a row
+    return *reinterpret_cast<const f32x4_any *>(X + int64_t(i) * ld + int64_t(c) * F + f0 + f);
+  };
+  constexpr int kFirst = 2;
+  const int step = blockDim.x * 4;
+  f32x4 first[kFirst];
+#pragma unroll
+  for (int j = 0; j < kFirst; ++j) {
+    const int k = threadIdx.x * 4 + j * step;
+    if (j * step < C * nf) first[j] = weights(k < C * nf ? k : 0);  // uniform
+  }
+  __builtin_amdgcn_sched_barrier(0);
   u16x8 fv[kStepsMax];
 #pragma unroll
   for (int st = 0; st < kStepsMax; ++st)
     if (st < steps) fv[st] = *reinterpret_cast<const u16x8 *>(frow + 32 * st);  // uniform condition
-  for (int k = threadIdx.x * 4; k < C * nf; k += blockDim.x * 4) {
-    const int c = k / nf, f = k % nf;  // nf is a multiple of 32: the four stay in a row
-    const f32x4 w = *reinterpret_cast<const f32x4_any *>(X + int64_t(i) * ld + int64_t(c) * F + f0 + f);
+  __builtin_amdgcn_sched_barrier(0);
+  auto split = [&](int k, f32x4 w) {
+    const int c = k / nf, f = k % nf;
     u16x4 t[3];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -91,7 +107,13 @@ __global__ __launch_bounds__(64 * kSamplesMax / 16) void softmax_logits_kernel(
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<u16x4 *>(&weight[p][c][f]) = t[p];
+  };
+#pragma unroll
+  for (int j = 0; j < kFirst; ++j) {
+    const int k = threadIdx.x * 4 + j * step;
+    if (k < C * nf) split(k, first[j]);
   }
+  for (int k = threadIdx.x * 4 + kFirst * step; k < C * nf; k += step) split(k, weights(k));
   __syncthreads();
   const int row = m < C ? m : C - 1;  // rows past C of the tile repeat the last class and are not stored
   // the upper term and the two small ones in accumulators of their own: added to one, the small terms would triple the
@@ -116,8 +138,8 @@ __global__ __launch_bounds__(64 * kSamplesMax / 16) void softmax_logits_kernel(
     if (4 * q + r < C) out[int64_t(4 * q + r) * B] = acc[r];
 }
 
-// grid (chunks, n).  32 workers x 8 chunks: 12.2 us; with column groups that do not match the first launch's, whose
-// features then come from beyond the L2, 15.6 us.
+// grid (chunks, n).  32 workers x 8 chunks: 11.8 us; with column groups that do not match the first launch's, whose
+// features then come from beyond the L2, 15.6 us then.
 __global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
     int64_t ld, const float *__restrict__ X, const uint16_t *__restrict__ feat, const int32_t *__restrict__ labels,
     const int32_t *__restrict__ batch, int S, int F, int C, int B, int chunk, const float *__restrict__ part, int parts,
@@ -132,26 +154,46 @@ __global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
   const int32_t *rows = batch + int64_t(i) * B;
   // a stage's rows: four lanes to a row of 64 B, sixteen rows an instruction
   u16x8 v[kHeld][kStage / 16];
-  auto fetch = [&](int from) {
+  int at[kHeld][kStage / 16];
+  auto each_piece = [&](int from, auto f) {
 #pragma unroll
     for (int h = 0; h < kHeld; ++h)
 #pragma unroll
       for (int k = 0; k < kStage / 16; ++k) {
         const int s = from + h * kStage + k * 16;  // uniform; B is a multiple of 32
-        if (cols_ok && s < B)
-          v[h][k] = *reinterpret_cast<const u16x8 *>(
-              feat + (int64_t(i) * S + clamped(rows[s + (lane >> 2)], S)) * F + f0 + (lane & 3) * 8);
+        if (cols_ok && s < B) f(h, k, s);
       }
   };
-  // Memory answers a wavefront in the order it asked: the parts of the logits first, the labels, then the feature rows,
-  // which arrive under the softmax.  This thread's (class, sample) pairs:
+  auto find = [&](int from) { each_piece(from, [&](int h, int k, int s) { at[h][k] = rows[s + (lane >> 2)]; }); };
+  auto fetch = [&](int from) {
+    each_piece(from, [&](int h, int k, int) {
+      v[h][k] = *reinterpret_cast<const u16x8 *>(feat + (int64_t(i) * S + clamped(at[h][k], S)) * F + f0 + (lane & 3) * 8);
+    });
+  };
+  // Memory answers a wavefront in the order it asked: the numbers of the samples first, on which labels and features wait,
+  // then the parts of the logits and the bias, the labels, and the feature rows, which arrive under the softmax.  (Numbers
+  // behind the parts and the bias behind the features, each a latency more in the chain: 32 workers, 256 samples, 4096
+  // features 33.1 us, so 26.4; 4, 160 samples, 1024 features 10.4 and 8.7; 32, 128 samples, 3072 features 12.6 and 11.8.)
+  // This thread's (class, sample) pairs:
   constexpr int kPairs = (kClassesMax * kSamplesMax + kGradThreads - 1) / kGradThreads;
   constexpr int kPasses = (kSamplesMax * 4 + kGradThreads - 1) / kGradThreads;
   float sums[kPairs];
   // four lanes share a sample: lane j takes classes j, j + 4, j + 8
   int y[kPasses];
+  float bias[kPairs];
 #pragma unroll
-  for (int j = 0; j < kPairs; ++j) sums[j] = 0.f;
+  for (int r = 0; r < kPasses; ++r) {
+    const int s = int(threadIdx.x) / 4 + r * (kGradThreads / 4);
+    y[r] = rows[s < B ? s : 0];
+  }
+  find(0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < kPairs; ++j) {
+    const int k = int(threadIdx.x) + j * kGradThreads;
+    sums[j] = 0.f;
+    bias[j] = k < C * B ? X[int64_t(i) * ld + int64_t(C) * F + k / B] : 0.f;
+  }
   for (int q0 = 0; q0 < parts; q0 += 8) {
     float t[kPairs][8];
 #pragma unroll
@@ -167,7 +209,7 @@ __global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
 #pragma unroll
       for (int r = 0; r < kPasses; ++r) {
         const int s = int(threadIdx.x) / 4 + r * (kGradThreads / 4);
-        y[r] = s < B ? clamped(labels[int64_t(i) * S + clamped(rows[s], S)], C) : 0;
+        y[r] = s < B ? labels[int64_t(i) * S + clamped(y[r], S)] : 0;
       }
       fetch(0);
       __builtin_amdgcn_sched_barrier(0);
@@ -184,13 +226,14 @@ __global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
     const int k = int(threadIdx.x) + j * kGradThreads;
     if (k < C * B) {
       const int c = k / B;
-      logits[c * kSamplesMax + k % B] = sums[j] + X[int64_t(i) * ld + int64_t(C) * F + c];
+      logits[c * kSamplesMax + k % B] = sums[j] + bias[j];
     }
   }
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < kPasses; ++r) {
     const int s = int(threadIdx.x) / 4 + r * (kGradThreads / 4), j = threadIdx.x & 3;
+    y[r] = clamped(y[r], C);
     if (s < B) {  // the four lanes of a sample together
       float e[kLanesClasses / 4], mx = -__builtin_inff();
 #pragma unroll
@@ -233,7 +276,7 @@ __global__ __launch_bounds__(kGradThreads) void softmax_grad_kernel(
     const int row = m < C ? m : C - 1;  // rows past C of the tile repeat the last class and are not stored
     uint16_t(&stage)[kStage][kStagePitch] = stages[wave];
     for (int from = 0; from < B; from += kHeld * kStage) {
-      if (from > 0) fetch(from);
+      if (from > 0) find(from), fetch(from);
 #pragma unroll
       for (int h = 0; h < kHeld; ++h) {
         const int s0 = from + h * kStage;
