@@ -3,6 +3,7 @@ streams, without a GPU."""
 import pytest
 import torch
 
+import paper_2006_08085_amd as D
 from paper_2006_08085_amd.algorithms import ByPhase
 
 
@@ -86,3 +87,28 @@ def test_a_phase_goes_through_iteration(monkeypatch):
     bp = _by_phase(_Cuda(monkeypatch), lambda t, q, X, g: None, cls=Counting)
     bp.phase(4)
     assert bp.seen == 4 and bp.k == 1
+
+
+class _RegisterTile(_Recorder):
+    """A context whose graph the register-resident kernels serve: a phase's rounds are one call."""
+
+    def kernel(self):
+        return D.DETAG_KERNEL_REGISTER_TILE
+
+
+@pytest.mark.parametrize("overlap", [True, False])
+def test_the_rounds_of_a_phase_in_one_call(monkeypatch, overlap):
+    cuda = _Cuda(monkeypatch)
+    bp = ByPhase(_RegisterTile(cuda), torch.zeros(3, 5), 0.1, lambda t, q, X, g: None, overlap=overlap)
+    now = cuda.current.cuda_stream
+    for _ in range(2):
+        cuda.log.clear()
+        bp.phase(3)
+        gossip = [e for e in cuda.log if e[0].startswith("gossip")]
+        if overlap:                            # behind what made its inputs, and waited for by the phase end
+            comm = bp.comm.cuda_stream
+            assert comm != now and gossip == [("gossip_rounds", comm)]
+            assert cuda.log[:2] == [("wait", comm, now), ("gossip_rounds", comm)]
+            assert cuda.log[-2:] == [("wait", now, comm), ("phase_end", now)]
+        else:
+            assert gossip == [("gossip_rounds", now)] == cuda.log[:1]
