@@ -91,7 +91,8 @@ class ByPhase:
         self.k = 0           # phases done
         self.r = 0           # step within the current phase
         self._whole = False  # within phase(): R and eta hold for every iteration of this phase
-        self._ahead = 0      # gossip steps of the current phase that are issued already
+        self._ahead = 0      # gossip steps of the current phase that are issued already; a gradient that raised may have
+        self._issued = None  # left more than r; (R, eta) they were issued for, where that was all of them in one call
 
     @property
     def Y(self):
@@ -105,21 +106,27 @@ class ByPhase:
     def iteration(self, R: int, eta: float = -1.0):
         """One iteration of a phase of length R (the same R for all iterations of one phase)."""
         ctx, r, comm = self.ctx, self.r, self.comm
+        if self._issued not in (None, (R, eta)):
+            raise RuntimeError("the gossip of the phase in progress is issued for R = %s, eta = %s" % self._issued)
         if r == 0 and comm is not None:
             comm.wait_stream(self._current_stream())   # the last phase end produced Xt and Y
         # handed to the calls: entering and leaving a stream takes the host longer than they do
         on = comm.cuda_stream if comm is not None else None
-        if self.granularity == "phase":
+        if r < self._ahead:
+            pass
+        elif self.granularity == "phase":
             if r == 0:
                 ctx.gossip_accel(self.xt[0], R, eta, stream=on)
                 ctx.gossip_accel(self.y[0], R, eta, stream=on)
+                self._ahead = R
         elif r == 0 and self._whole and ctx.kernel() == DETAG_KERNEL_REGISTER_TILE:
             ctx.gossip_rounds(self.xt[0], self.y[0], int(R), eta, stream=on)
-            self._ahead = R
-        elif r >= self._ahead:
+            self._ahead, self._issued = R, (R, eta)
+        else:
             for z in (self.xt, self.y):
                 ctx.gossip_round(z[0], z[0] if r == 0 else z[1], z[1], eta, stream=on)
                 z[0], z[1] = z[1], z[0]
+            self._ahead = r + 1
         for q in range(self.B):
             self.grad(self.t, q, self.X, self.g)
             ctx.accumulate(self.G_k, self.g, self.scale)
@@ -130,7 +137,7 @@ class ByPhase:
                 self._current_stream().wait_stream(comm)
             ctx.phase_end(self.X, self.xt[0], self.y[0], self.G_k, self.G_km1, self.alpha)
             self.G_k, self.G_km1 = self.G_km1, self.G_k
-            self.r = self._ahead = 0
+            self.r, self._ahead, self._issued = 0, 0, None
             self.k += 1
 
     def phase(self, R: int, eta: float = -1.0):
@@ -144,22 +151,27 @@ class ByPhase:
             self._whole = False
 
     def capture_two_phases(self, R: int, eta: float = -1.0):
-        """Record two consecutive phases of length R into a HIP graph (two, because the gradient buffers and,
-        for odd R, the gossip buffers change roles every phase and are back where they started after two).
+        """Record two consecutive phases of length R into a HIP graph (two, because the gradient buffers and, for
+        odd R where the rounds are issued one by one, the gossip buffers change roles every phase and are back where
+        they started after two).
         The graph fixes every pointer and scalar argument: grad must take whatever changes between
         iterations (batch indices, noise) from device buffers the caller refreshes between replays, and it is
         called here with the iteration numbers of the recorded phases.  Run at least two phases eagerly first
         so that every scratch buffer the library allocates on first use exists.  Returns the graph; call
         replay_two_phases(graph) to run it."""
         import torch
-        if self.r != 0:
+        if self.r != 0 or self._ahead:
             raise RuntimeError("a phase is in progress")
-        t0, k0 = self.t, self.k
+        before = {k: getattr(self, k) for k in ("t", "k", "r", "_ahead", "_issued", "G_k", "G_km1")}
+        xt, y = self.xt[:], self.y[:]
         graph = torch.cuda.CUDAGraph()
-        with torch.cuda.graph(graph):
-            self.phase(R, eta)
-            self.phase(R, eta)
-        self.t, self.k = t0, k0          # recording executes nothing
+        try:
+            with torch.cuda.graph(graph):
+                self.phase(R, eta)
+                self.phase(R, eta)
+        finally:
+            vars(self).update(before)    # recording executes nothing, whole or not
+            self.xt[:], self.y[:] = xt, y
         self._graph_R = R
         return graph
 

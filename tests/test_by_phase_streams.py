@@ -1,5 +1,7 @@
 """On which streams ByPhase issues its calls, and which of them wait for which: recorded by stand-ins for the context and the
 streams, without a GPU."""
+import contextlib
+
 import pytest
 import torch
 
@@ -112,3 +114,69 @@ def test_the_rounds_of_a_phase_in_one_call(monkeypatch, overlap):
             assert cuda.log[-2:] == [("wait", now, comm), ("phase_end", now)]
         else:
             assert gossip == [("gossip_rounds", now)] == cuda.log[:1]
+
+
+class _Failing:
+    """A gradient that raises once, in iteration `at`."""
+
+    def __init__(self, at):
+        self.at = at
+
+    def __call__(self, t, q, X, g):
+        if t == self.at:
+            self.at = None
+            raise KeyError("no gradient")
+
+
+@pytest.mark.parametrize("context,granularity,calls", [(_RegisterTile, "iteration", ["gossip_rounds"]),
+                                                       (_Recorder, "iteration", ["gossip_round"] * 6),
+                                                       (_RegisterTile, "phase", ["gossip_accel"] * 2)])
+def test_a_phase_interrupted_by_its_first_gradient_is_not_gossiped_again(monkeypatch, context, granularity, calls):
+    cuda = _Cuda(monkeypatch)
+    bp = ByPhase(context(cuda), torch.zeros(3, 5), 0.1, _Failing(0), granularity=granularity)
+    with pytest.raises(KeyError):
+        bp.phase(3)
+    bp.phase(3)
+    assert [e[0] for e in cuda.log if e[0].startswith("gossip")] == calls and (bp.t, bp.k, bp.r) == (3, 1, 0)
+    cuda.log.clear()
+    bp.phase(3)
+    assert [e[0] for e in cuda.log if e[0].startswith("gossip")] == calls
+
+
+@pytest.mark.parametrize("at", [0, 1])
+def test_an_interrupted_phase_ends_as_it_was_issued(monkeypatch, at):
+    """Its rounds are issued for one R and eta, whatever the iterations that finish it ask for."""
+    cuda = _Cuda(monkeypatch)
+    bp = ByPhase(_RegisterTile(cuda), torch.zeros(3, 5), 0.1, _Failing(at))
+    with pytest.raises(KeyError):
+        bp.phase(3, 0.5)
+    cuda.log.clear()
+    for R, eta in ((4, 0.5), (3, 0.25)):
+        with pytest.raises(RuntimeError, match="issued for"):
+            bp.iteration(R, eta)
+    assert not cuda.log and bp.t == at
+    while bp.k == 0:
+        bp.iteration(3, 0.5)
+    assert bp.t == 3 and not [e for e in cuda.log if e[0].startswith("gossip")]
+    bp.iteration(4, 0.25)
+
+
+@pytest.mark.parametrize("context", [_RegisterTile, _Recorder])
+@pytest.mark.parametrize("at", [0, 1, 3, 4])
+def test_a_recording_that_fails_leaves_everything_as_it_was(monkeypatch, context, at):
+    cuda = _Cuda(monkeypatch)
+    monkeypatch.setattr(torch.cuda, "CUDAGraph", lambda: None)
+    monkeypatch.setattr(torch.cuda, "graph", lambda graph: contextlib.nullcontext())
+    bp = ByPhase(context(cuda), torch.zeros(3, 5), 0.1, _Failing(at))
+    held = [id(t) for t in (*bp.xt, *bp.y, bp.G_k, bp.G_km1)]
+    with pytest.raises(KeyError):
+        bp.capture_two_phases(3)
+    assert [id(t) for t in (*bp.xt, *bp.y, bp.G_k, bp.G_km1)] == held and (bp.t, bp.k, bp.r) == (0, 0, 0)
+    cuda.log.clear()
+    bp.phase(3)
+    assert len([e for e in cuda.log if e[0].startswith("gossip")]) == (1 if context is _RegisterTile else 6)
+    bp.grad = _Failing(3)
+    with pytest.raises(KeyError):
+        bp.phase(3)
+    with pytest.raises(RuntimeError, match="in progress"):     # its gossip would be missing from the recording
+        bp.capture_two_phases(3)
