@@ -135,9 +135,8 @@ def main():
     import paper_2006_08085_amd as D
     from workloads import CONFIGS, generate as gen
 
-    if not os.path.exists(D.LIB_PATH):
-        from paper_2006_08085_amd.build import build
-        build(verbose=False)
+    from paper_2006_08085_amd.build import ensure_built
+    ensure_built()
     if not torch.cuda.is_available():
         print("bench.py: no GPU visible", file=sys.stderr)
         sys.exit(1)

@@ -1,4 +1,4 @@
-"""Binding of libdetag.so: argument marshalling only, by ctypes, the calls of the hot path in native code (_calls.so).
+"""Binding of libdetag.so: argument marshalling only, by ctypes, the calls of the hot path also in native code, where that is built.
 
 Every function mirrors one entry point of include/detag.h (same name, same
 argument order) and takes torch tensors where the C call takes device
@@ -159,16 +159,18 @@ def lib() -> C.CDLL:
 
 
 def calls():
-    """The native form of the hot path's calls (once, with the first of them: it needs torch).  Raises if it has not been
-    built."""
+    """The native form of the hot path's calls (looked for once, with the first of them: it needs torch).  None where it has
+    not been built for this interpreter, this torch and these sources: ctypes serves the same calls."""
     global _calls
     if _calls is None:
         import importlib.machinery
         import importlib.util
+        from . import build
+        path = build.calls_path()
+        if path is None or not os.path.exists(path):
+            _calls = False
+            return None
         import torch
-        path = os.path.join(_HERE, "_calls.so")
-        if not os.path.exists(path):
-            raise RuntimeError(f"{path} is missing: build it with `python -m paper_2006_08085_amd.build`")
         loader = importlib.machinery.ExtensionFileLoader("_calls", path)
         module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_calls", path, loader=loader))
         loader.exec_module(module)
@@ -176,7 +178,17 @@ def calls():
         module.bind({name: C.cast(getattr(L, name), C.c_void_p).value for name in EXPORTS}, torch._C._cuda_getDevice,
                     torch._C._cuda_getCurrentRawStream)
         _calls = module
-    return _calls
+    return _calls or None
+
+
+class _NoCalls:
+    """In the place of the native calls: leaves every one to ctypes."""
+
+    def close(self):
+        pass
+
+    def __getattr__(self, name):
+        return lambda *args: None
 
 
 @dataclass
@@ -331,7 +343,8 @@ class Context:
     def _native(self):
         """The native calls on this context: each returns a status, or None for arguments that it leaves to ctypes."""
         if self._fast is None:
-            self._fast = calls().Calls(self._h.value or 0, self.n, self.d, self.ld, self.dtype == DETAG_BF16)
+            native = calls()
+            self._fast = native.Calls(self._h.value or 0, self.n, self.d, self.ld, self.dtype == DETAG_BF16) if native else _NoCalls()
         return self._fast
 
     def _check(self, status: int):

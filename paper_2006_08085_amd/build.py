@@ -1,23 +1,30 @@
-"""Build libdetag.so (HIP, gfx950 only) in-tree with hipcc, and _calls.so (host code) with g++.
+"""Build libdetag.so (HIP, gfx950 only) in-tree with hipcc, and the binding's native calls (host code) with g++ where
+torch and the headers for that are there.
 
     python -m paper_2006_08085_amd.build [--sanitize-host]
 
-Objects go to _build/ at the repository root; the shared library lands next to
-this file so that it travels with the source tree.
+Objects go to _build/ at the repository root; the shared libraries land next to
+this file so that they travel with the source tree.
 """
 from __future__ import annotations
 
+import glob
+import hashlib
 import os
+import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from typing import List, Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdetag.so")
-CALLS = os.path.join(HERE, "_calls.so")
+TAG_DIGITS = 12
+CALLS_SOURCES = [os.path.join(CSRC, "py_calls.cpp"), os.path.join(ROOT, "include", "detag.h")]
 
 SOURCES = ["topology.cpp", "consensus.cpp", "detag_api.hip", "k_stream.hip", "k_fused.hip", "k_fused_quad.hip", "k_fused_generic.hip", "k_fused_generic_quad.hip",
            "k_diag.hip", "k_grad.hip", "k_softmax.hip", "k_consensus.hip", "k_dense.hip", "k_dense_resident.hip"]
@@ -56,28 +63,69 @@ def sanitizer_runtime() -> str:
     return hits[-1]
 
 
-def build_calls() -> str:
-    """Builds _calls.so next to this file: the Python calls of the hot path, host code against torch's headers."""
-    import sysconfig
-    from importlib.util import find_spec
-    torch_dir = os.path.dirname(find_spec("torch").origin)
+def calls_path() -> Optional[str]:
+    """Where the native calls are for this interpreter, this torch and these sources: built for another, they have another
+    name and are not loaded.  None without torch or the sources."""
+    try:
+        import torch
+        tag = hashlib.sha256(b"".join(open(f, "rb").read() for f in CALLS_SOURCES)).hexdigest()[:TAG_DIGITS]
+    except (ImportError, OSError):
+        return None
+    torch_version = re.sub(r"[^\w.]", "_", torch.__version__)
+    return os.path.join(HERE, f"_calls-torch{torch_version}-{tag}{sysconfig.get_config_var('EXT_SUFFIX')}")
+
+
+def calls_command(source: str, out: str) -> Optional[List[str]]:
+    """The command that builds such a module; None where the compiler, torch or the headers it needs are not there."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    gxx, python_include = shutil.which("g++"), sysconfig.get_paths()["include"]
+    torch_dir = os.path.dirname(torch.__file__)
     torch_include = os.path.join(torch_dir, "include")
-    tmp = CALLS + ".tmp"
-    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
-           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"], "-isystem", torch_include,
-           "-isystem", os.path.join(torch_include, "torch", "csrc", "api", "include"),
-           os.path.join(CSRC, "py_calls.cpp"), "-o", tmp,
-           # loaded already, with torch, when this library is
-           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if not gxx or not os.path.exists(os.path.join(python_include, "Python.h")) \
+            or not os.path.exists(os.path.join(torch_include, "torch", "csrc", "autograd", "python_variable.h")):
+        return None
+    return [gxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unknown-pragmas",
+            "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", python_include, "-isystem", torch_include,
+            "-isystem", os.path.join(torch_include, "torch", "csrc", "api", "include"), source, "-o", out,
+            # loaded already, with torch, when this library is
+            "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
+def build_calls() -> Optional[str]:
+    """Builds the Python calls of the hot path (host code against torch's headers) next to this file.  The binding does
+    without them, by ctypes, so what keeps them from being built is reported and no error: returns None then."""
+    out = calls_path()
+    tmp = f"{out}.{os.getpid()}.tmp"
+    cmd = out and calls_command(CALLS_SOURCES[0], tmp)
+    if not cmd:
+        print("native calls not built: they need g++, torch with its headers and Python's", file=sys.stderr)
+        return None
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
-        raise RuntimeError("g++ failed on py_calls.cpp:\n" + r.stdout + r.stderr)
-    os.replace(tmp, CALLS)
-    return CALLS
+        print(f"native calls not built: g++ failed on {CALLS_SOURCES[0]}:\n{r.stdout}{r.stderr}", file=sys.stderr)
+        return None
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    for other in glob.glob(out[:-len(suffix) - TAG_DIGITS] + "*" + suffix):  # of other sources
+        if other != out:
+            os.remove(other)
+    os.replace(tmp, out)
+    return out
+
+
+def ensure_built() -> None:
+    """Builds what the binding loads and is not there."""
+    from .binding import LIB_PATH
+    if not os.path.exists(LIB_PATH):
+        build(verbose=False)
+    elif LIB_PATH == LIB and calls_path() and not os.path.exists(calls_path()):
+        build_calls()
 
 
 def build(verbose: bool = True, jobs: int = 8, sanitize_host: bool = False) -> str:
-    """Builds libdetag.so next to this file; with sanitize_host the instrumented SAN_LIB under _build/san instead
+    """Builds libdetag.so and the native calls next to this file; with sanitize_host the instrumented SAN_LIB under _build/san instead
     (load it with DETAG_LIB=<path> and LD_PRELOAD=sanitizer_runtime())."""
     hipcc = _hipcc()
     bdir = os.path.join(ROOT, "_build", "san") if sanitize_host else os.path.join(ROOT, "_build")
@@ -99,10 +147,9 @@ def build(verbose: bool = True, jobs: int = 8, sanitize_host: bool = False) -> s
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        native_calls = None if sanitize_host else ex.submit(build_calls)
+        if not sanitize_host:
+            ex.submit(build_calls)
         objs = list(ex.map(compile_one, srcs))
-        if native_calls:
-            native_calls.result()
     lib_out = SAN_LIB if sanitize_host else LIB
     tmp = lib_out + ".tmp"
     r = subprocess.run([hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", "-fno-gpu-rdc", *link_extra, "-o", tmp, *objs],

@@ -1,7 +1,5 @@
 """Helpers shared by the GPU parity tests: host <-> device matrices with
 sentinel-filled padding, and matching (library context, dense oracle W) pairs."""
-import os
-
 import numpy as np
 import pytest
 import torch
@@ -16,9 +14,8 @@ SENTINEL = 12345.0
 
 @pytest.fixture(scope="module", autouse=True)
 def _built():
-    if not os.path.exists(D.LIB_PATH):
-        from paper_2006_08085_amd.build import build
-        build(verbose=False)
+    from paper_2006_08085_amd.build import ensure_built
+    ensure_built()
     assert torch.cuda.is_available(), "these tests need the GPU"
 
 

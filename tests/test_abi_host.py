@@ -17,9 +17,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 @pytest.fixture(scope="module", autouse=True)
 def _built():
-    if not os.path.exists(D.LIB_PATH):
-        from paper_2006_08085_amd.build import build
-        build(verbose=False)
+    from paper_2006_08085_amd.build import ensure_built
+    ensure_built()
 
 
 def test_library_exports_every_declared_symbol():

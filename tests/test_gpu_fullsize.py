@@ -2,8 +2,6 @@
 n=64, 8x8 torus, d=11,173,962 fp32, K=8, in-kernel counter noise.  Columns are
 independent for this objective, so the oracle recomputes a sample of columns
 exactly (first tile, last ragged tile, tile boundaries, random columns)."""
-import os
-
 import numpy as np
 import pytest
 import torch
@@ -23,9 +21,8 @@ TIGHT = 1.0 / 64.0      # entry-by-entry floor at the full sizes: S/64 instead o
 
 @pytest.fixture(scope="module", autouse=True)
 def _built():
-    if not os.path.exists(D.LIB_PATH):
-        from paper_2006_08085_amd.build import build
-        build(verbose=False)
+    from paper_2006_08085_amd.build import ensure_built
+    ensure_built()
     assert torch.cuda.is_available()
 
 

@@ -1,7 +1,5 @@
 """bf16-MFMA softmax-regression gradient against the fp64 oracle, on the
 label-sorted shards that stand in for the paper's unshuffled-data experiment."""
-import os
-
 import numpy as np
 import pytest
 import torch
@@ -19,9 +17,8 @@ DEV = "cuda:0"
 
 @pytest.fixture(scope="module", autouse=True)
 def _built():
-    if not os.path.exists(D.LIB_PATH):
-        from paper_2006_08085_amd.build import build
-        build(verbose=False)
+    from paper_2006_08085_amd.build import ensure_built
+    ensure_built()
     assert torch.cuda.is_available()
 
 

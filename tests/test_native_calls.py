@@ -1,10 +1,22 @@
 """The native form of the hot path's calls takes plain arguments only and leaves the rest to ctypes, which words the refusals:
 both ways accept the same and give the same."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2006_08085_amd as D
+from paper_2006_08085_amd import binding, build
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _built():
+    build.ensure_built()
+    assert binding.calls() is not None
 
 
 def test_what_is_not_plain_is_left_to_ctypes():
@@ -22,6 +34,62 @@ def test_what_is_not_plain_is_left_to_ctypes():
         ctx.accumulate(t, t)
     ctx.close()
     assert f.track(t, t, t) is None
+
+
+@pytest.fixture
+def sources(monkeypatch, tmp_path):
+    """Copies of the sources of the native calls, and an empty place for what is built from them."""
+    copies = [shutil.copy(f, tmp_path) for f in build.CALLS_SOURCES]
+    monkeypatch.setattr(build, "CALLS_SOURCES", copies)
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(binding, "_calls", None)
+    return copies
+
+
+def _ctypes_serves():
+    """The calls work, and word their refusals, without a native form."""
+    assert binding.calls() is None
+    ctx, t = D.detag_create(D.Topology.ring(), 6, 100, 104), torch.zeros(6, 104)
+    with pytest.raises(ValueError, match="X must be a GPU tensor"):
+        ctx.step(t, t, t, t, 0.1, 1)
+    factors = D.Factors(ctx, 0)
+    with pytest.raises(ValueError, match="Z must be a GPU tensor"):
+        factors.average(t)
+    assert ctx._native().step(t, t, t, t, 0.1, 1, -1.0, 0) is None
+    ctx.close()
+
+
+def test_without_the_native_form_ctypes_serves(sources):
+    _ctypes_serves()
+
+
+def test_a_native_form_of_other_sources_or_another_torch_is_not_loaded(sources, monkeypatch):
+    built = build.calls_path()
+    with open(built, "w") as f:
+        f.write("loading this would raise")
+    with open(sources[1], "a") as f:
+        f.write("/* a declaration that changed */")
+    assert build.calls_path() != built
+    _ctypes_serves()
+    monkeypatch.setattr(torch, "__version__", "0.0.1+other")
+    assert "0.0.1_other" in build.calls_path()
+    monkeypatch.setattr(binding, "_calls", None)
+    _ctypes_serves()
+
+
+def test_what_keeps_the_native_form_from_being_built_is_reported_and_no_error(sources, monkeypatch, capfd):
+    with monkeypatch.context() as m:
+        m.setattr(shutil, "which", lambda name: None)
+        assert build.build_calls() is None
+    with monkeypatch.context() as m:
+        m.setitem(sys.modules, "torch", None)                          # not importable
+        assert build.build_calls() is None and build.calls_path() is None
+    with open(sources[0], "a") as f:
+        f.write("#error another torch")
+    assert build.build_calls() is None
+    err = capfd.readouterr().err
+    assert err.count("native calls not built") == 3 and "#error another torch" in err
+    assert not [f for f in os.listdir(build.HERE) if f.endswith(".so")]
 
 
 @pytest.mark.gpu
