@@ -211,8 +211,12 @@ detag_status dense_poly(detag_ctx *ctx, int K, float eta, const uint16_t **frag,
       return refuse_while_capturing(ctx, "and upload the gossip polynomial of this (K, eta)", "detag_reserve_gossip");
     const int terms = dense_poly_terms(ctx->shape.bf16);
     std::vector<uint16_t> host;
-    if (!build_dense_poly(ctx->W, K, double(eta), terms, host))
-      return set_err(ctx, DETAG_EUNSUPPORTED, "the dense path needs n <= 256");
+    try {
+      if (!build_dense_poly(ctx->W, K, double(eta), terms, host))
+        return set_err(ctx, DETAG_EUNSUPPORTED, "the dense path needs n <= 256");
+    } catch (const std::bad_alloc &) {
+      return set_err(ctx, DETAG_ENOMEM, "out of host memory");
+    }
     for (auto &e : ctx->poly)
       if (!slot || e.used < slot->used) slot = &e;  // least recently used (unused slots have used == 0)
     hipError_t err = hipSuccess;

@@ -11,6 +11,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <new>
 
 #include "detag.h"
 
@@ -110,6 +111,11 @@ struct Args {
   }
 };
 
+struct WithoutInterpreter {  // other Python threads run; held again when this goes, however that comes about
+  PyThreadState *state = PyEval_SaveThread();
+  ~WithoutInterpreter() { PyEval_RestoreThread(state); }
+};
+
 // body(args) reads the arguments and returns the call as a function of nothing.
 template <class F>
 PyObject *call(PyObject *self, PyObject *const *a, Py_ssize_t nargs, Py_ssize_t want, F &&body) {
@@ -120,9 +126,10 @@ PyObject *call(PyObject *self, PyObject *const *a, Py_ssize_t nargs, Py_ssize_t 
   try {
     auto go = body(args);
     if (!args.ok) Py_RETURN_NONE;
-    Py_BEGIN_ALLOW_THREADS
+    WithoutInterpreter released;
     st = go();
-    Py_END_ALLOW_THREADS
+  } catch (const std::bad_alloc &) {  // the entry points should not, but not every one of them ends its exceptions
+    return PyErr_NoMemory();
   } catch (...) {  // a tensor without storage: the other way words it
     PyErr_Clear();
     Py_RETURN_NONE;

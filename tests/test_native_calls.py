@@ -161,3 +161,37 @@ def test_both_ways_accept_the_same_and_give_the_same(monkeypatch):
     by_ctypes = everything()
     for one in (streamed, odd, by_ctypes):
         assert all(torch.equal(a, b) for a, b in zip(native, one))
+
+
+THROWING = """
+#include "py_calls.cpp"
+extern "C" PyObject *throwing() {  // an entry point that runs out of memory, called as every other one is
+  Calls c{};
+  c.ctx = reinterpret_cast<detag_ctx *>(&c);
+  return call(reinterpret_cast<PyObject *>(&c), nullptr, 0, 0, [](Args &) {
+    return []() -> detag_status { throw std::bad_alloc(); };
+  });
+}
+"""
+CALLER = """
+import ctypes, sys, threading, torch
+throwing = ctypes.PyDLL(sys.argv[1]).throwing
+throwing.restype = ctypes.py_object
+for _ in range(3):
+    try:
+        throwing()
+        sys.exit("no error")
+    except MemoryError:
+        pass
+t = threading.Thread(target=lambda: [[] for _ in range(100000)])       # the interpreter lock is held again
+t.start(), t.join()
+print("went on")
+"""
+
+
+def test_an_exception_behind_an_entry_point_leaves_the_interpreter_whole(tmp_path):
+    source, lib = tmp_path / "throwing.cpp", str(tmp_path / "throwing.so")
+    source.write_text(THROWING)
+    subprocess.run(build.calls_command(str(source), lib), check=True, capture_output=True)
+    r = subprocess.run([sys.executable, "-c", CALLER, lib], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and "went on" in r.stdout, (r.returncode, r.stderr[-2000:])
