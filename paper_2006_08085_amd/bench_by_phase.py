@@ -4,9 +4,11 @@ workloads whose step is bound by launches rather than by HBM:
     python -m paper_2006_08085_amd.bench_by_phase [--phases 200]
 
 Compared: the phase-at-a-time entry point (gradient, then detag_step), the
-iteration-by-iteration form on one stream, on two streams (gossip beside the
-gradient queries), with the phase's gossip as one on-chip call, and as a
-recorded HIP graph of two phases.  Prints one JSON line per workload.
+iteration-by-iteration form (one gossip round per matrix and iteration) on one
+stream and on two (gossip beside the gradient queries), the phase's rounds in
+one launch with the bits of that form (what ByPhase.phase() issues here) on one
+stream, on two and as a recorded HIP graph of two phases, and the phase's
+gossip as one on-chip call per matrix.  Prints one JSON line per workload.
 """
 from __future__ import annotations
 
@@ -30,6 +32,12 @@ def _time_phases(run_phase, phases, per_call=1):
         run_phase()
     torch.cuda.synchronize()
     return (time.perf_counter() - t0) / (phases // per_call * per_call) * 1e6
+
+
+def iterations(bp, R):
+    """One phase, iteration by iteration."""
+    for _ in range(R):
+        bp.iteration(R)
 
 
 def _workload(cfg_id, dev):
@@ -82,15 +90,19 @@ def main():
                 ctx.accumulate(Ga, g, 1.0 / R)
             ctx.step(X, Y, Ga, Gb, alpha, R, -1.0, D.DETAG_VARIANT_ALG2)
         out["phase_at_a_time_R_queries"] = _time_phases(phase_call_R, args.phases)
-        for name, kw in (("iterations_one_stream", dict(overlap=False)), ("iterations_two_streams", dict(overlap=True)),
-                         ("phase_gossip_two_streams", dict(overlap=True, granularity="phase"))):
-            bp = ALG.ByPhase(ctx, D.new_matrix(n, d, ld, device=dev), alpha, grad, scale=1.0 / R, **kw)
-            out[name] = _time_phases(lambda: bp.phase(R), args.phases)
-        bp = ALG.ByPhase(ctx, D.new_matrix(n, d, ld, device=dev), alpha, grad, scale=1.0 / R, overlap=True)
+        by_phase = lambda **kw: ALG.ByPhase(ctx, D.new_matrix(n, d, ld, device=dev), alpha, grad, scale=1.0 / R, **kw)  # noqa: E731
+        for overlap, streams in ((False, "one_stream"), (True, "two_streams")):
+            bp = by_phase(overlap=overlap)
+            out["iterations_" + streams] = _time_phases(lambda: iterations(bp, R), args.phases)
+            bp = by_phase(overlap=overlap)
+            out["rounds_in_one_launch_" + streams] = _time_phases(lambda: bp.phase(R), args.phases)
+        bp = by_phase(granularity="phase")
+        out["phase_gossip_two_streams"] = _time_phases(lambda: bp.phase(R), args.phases)
+        bp = by_phase()
         bp.phase(R), bp.phase(R)
         torch.cuda.synchronize()
         graph = bp.capture_two_phases(R)
-        out["iterations_two_streams_graph"] = _time_phases(lambda: bp.replay_two_phases(graph), args.phases, per_call=2)
+        out["rounds_in_one_launch_two_streams_graph"] = _time_phases(lambda: bp.replay_two_phases(graph), args.phases, per_call=2)
         print(json.dumps(out), flush=True)
         ctx.close()
 

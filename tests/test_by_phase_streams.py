@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2006_08085_amd as D
+from paper_2006_08085_amd import bench_by_phase
 from paper_2006_08085_amd.algorithms import ByPhase
 
 
@@ -114,6 +115,14 @@ def test_the_rounds_of_a_phase_in_one_call(monkeypatch, overlap):
             assert cuda.log[-2:] == [("wait", now, comm), ("phase_end", now)]
         else:
             assert gossip == [("gossip_rounds", now)] == cuda.log[:1]
+
+
+def test_what_the_measuring_tool_calls_iterations(monkeypatch):
+    """A launch per round, also where phase() issues the rounds in one."""
+    cuda = _Cuda(monkeypatch)
+    bp = ByPhase(_RegisterTile(cuda), torch.zeros(3, 5), 0.1, lambda t, q, X, g: None)
+    bench_by_phase.iterations(bp, 3)
+    assert [e[0] for e in cuda.log if e[0].startswith("gossip")] == ["gossip_round"] * 6 and bp.k == 1
 
 
 class _Failing:
