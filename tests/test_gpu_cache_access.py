@@ -144,3 +144,23 @@ def test_row_walking_kernels_on_both_sides_of_128_mib(dtype):
 
     for k, (got, want) in enumerate(zip(calls(many), calls(few))):
         assert torch.equal(got, want), k
+
+
+@pytest.mark.parametrize("n", [20, 64, 100, 200])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_dense_gossip_that_streams(n, dtype):
+    """Plain gossip on the dense path beyond 64 and 80 MiB: on lines it streams and walks its tiles in order, at an odd pitch
+    it does neither."""
+    d = (22_000_000 if dtype == torch.float32 else 44_000_000) // n | 1
+    values = torch.empty(n, d, device=DEV).normal_(generator=torch.Generator(device=DEV).manual_seed(d))
+    got = []
+    for ld in (D.padded_ld(d), d):
+        ctx = D.detag_create(_topology("rr", n), n, d, ld, D.DETAG_BF16 if dtype == torch.bfloat16 else D.DETAG_F32)
+        ctx.set_path(D.DETAG_PATH_DENSE)
+        z = _place(values, ld, 0, dtype)
+        ctx.gossip_accel(z, 3, 0.35)
+        torch.cuda.synchronize()
+        ctx.close()
+        assert torch.equal(z[:, d:], torch.full_like(z[:, d:], SENTINEL))
+        got.append(z[:, :d])
+    assert torch.equal(*got)
