@@ -14,8 +14,10 @@
 // inputs on the device), and the products that matter at the state's precision
 // are accumulated: for fp32 state 3 + 3 terms, the 6 products down to 2^-24;
 // for bf16 state 2 + 2 terms and 3 products (a bf16 input is its own first
-// term).  An infinite input leaves NaN in its column (Inf - Inf in the split),
-// where the round-by-round kernels leave Inf or NaN.
+// term).  What is not finite leaves nothing finite in its column: NaN where it is
+// split (Inf - Inf), Inf or NaN, as the round-by-round kernels leave, where it is
+// one whole term (k_dense_resident.hip: plain gossip of bf16 state, and the
+// tracker of Algorithm 2's phase).
 //
 // This is the general kernel; all but the smallest calls with bf16 state, or
 // with fp32 state and up to 128 workers, take the one in k_dense_resident.hip.

@@ -9,7 +9,9 @@
 // Lane (m, g) of a unit loads columns 2m, 2m+1 of rows 8g..8g+7, which is what it holds of the B operand of two column tiles
 // (even columns, odd columns).  So the terms go to LDS in fragment order, 16 bytes a lane, read and written without bank
 // conflicts, and an accumulator pair is one 32-bit word of two columns at the store: no transposition, one instruction moves
-// 128 bytes of each of two rows.  Same operands, products and order as the general kernel: the same values bit for bit.
+// 128 bytes of each of two rows.  Same products and order as the general kernel: the same values bit for bit where all are
+// finite.  (State that is multiplied as it is stored is one term here, two there, the second of which is zero, or NaN beside
+// an infinity.)
 //
 // Measured (K = 16, three states in turn, general kernel and this one): 256 workers, d = 1,000,000, pitch 1,000,064, ATC 1310
 // and 911 us (4.5 TB/s; without its products 777), plain gossip 472 and 273; pitch 1,048,576, whose rows all start on the same
@@ -685,8 +687,9 @@ int launch_dense_resident(const Shape &s, int mode, void *X, void *Y, const floa
   // Tiles that share cache lines go to one XCD and leave their accesses to the caches (streamed and kept, ATC: 256 x 200,001
   // 316 and 213 us, 64 x 546,113 164 and 128, 20 x 1,747,585 166 and 143), and so do calls that the memory-side cache serves
   // (256 workers, 60 MiB 31.0 and 27.7, 100 MiB 44.2 and 43.3, 130 MiB 47.0 and 47.0, 200 MiB 75.1 and 79.4; 64 workers 80 MiB
-  // 24.3 and 22.3, 200 MiB 57.3 and 66.2; fp32, 128 workers 100 MiB 43.2 and 42.0, 140 MiB 54.9 and 58.0; Algorithm 2's phase the same; plain gossip of 256 workers, 33 MiB 25.5 and 24.3, 95
-  // MiB of 64 and 100 workers 49.6 and 53.1, 95.5 and 97.5, fp32 50 MiB 24.7 and 21.6, 200 MiB 82.4 and 91.4).
+  // 24.3 and 22.3, 200 MiB 57.3 and 66.2; fp32, 128 workers 100 MiB 43.2 and 42.0, 140 MiB 54.9 and 58.0; Algorithm 2's phase
+  // the same; plain gossip of 256 workers, 33 MiB 25.5 and 24.3, 95 MiB of 64 and 100 workers 49.6 and 53.1, 95.5 and 97.5, fp32
+  // 50 MiB 24.7 and 21.6, 200 MiB 82.4 and 91.4).
   const int64_t bytes = fused::footprint(s, (mode == 0 ? 1 : 2) * (s.bf16 ? 2 : 4) + (mode == 0 ? 0 : 8));
   const bool keep = fused::shares_lines(s, {X, Y, Gn, Go}) || bytes <= (int64_t(mode == 0 ? 64 : 104) << 20);
   return keep ? launch_access<kKeep>(s, mode, X, Y, Gn, Go, alpha, frag, st)

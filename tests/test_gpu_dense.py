@@ -197,3 +197,36 @@ def test_resident_kernel_gives_the_bits_of_the_general_one(n, d, ld, dtype):
             xs, ys = X.clone(), Y.clone()
             call(narrow, mode, xs[:, c:], ys[:, c:], Gn[:, c:], Go[:, c:])
             assert torch.equal(xs[:, c:c + 63], x[:, c:c + 63]) and torch.equal(ys[:, c:c + 63], y[:, c:c + 63]), (mode, c)
+
+
+@pytest.mark.parametrize("n,d", [(20, 63), (20, 40000), (100, 700), (256, 700)])   # the general kernel, and P in registers
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_what_is_not_finite_stays_in_its_column(n, d, dtype):
+    """An infinity or a NaN of one worker leaves nothing finite in its column of what depends on it, and the bits of every other
+    column as they are without it."""
+    topo, _, eta = _graph(n, "rr")
+    ctx = D.detag_create(topo, n, d, d, D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32)
+    ctx.set_path(D.DETAG_PATH_DENSE)
+    g = torch.Generator(device=DEV).manual_seed(d)
+    clean = [torch.randn(n, d, device=DEV, generator=g) for _ in range(4)]
+    clean[:2] = [t.bfloat16() if dtype == "bf16" else t for t in clean[:2]]
+    bad = [t.clone() for t in clean]
+    bad[0][0, 5], bad[0][n - 1, 11], bad[1][n // 2, 20], bad[2][n - 1, 33] = float("inf"), -float("inf"), float("inf"), float("nan")
+    for mode in (0, 1, 2):
+        outs = []
+        for x, y, gn, go in ([t.clone() for t in clean], [t.clone() for t in bad]):
+            if mode == 0:
+                ctx.gossip_accel(x, 3, eta)
+                ctx.gossip_accel(y, 3, eta)
+            else:
+                ctx.step(x, y, gn, go, 0.05, 3, eta, D.DETAG_VARIANT_ATC if mode == 1 else D.DETAG_VARIANT_ALG2)
+            outs.append((x, y))
+        for k, spoiled in enumerate(([5, 11] if mode == 0 else [5, 11, 20], [20] if mode == 0 else [20, 33])):
+            want, got = outs[0][k], outs[1][k]
+            rows = torch.isfinite(got[:, spoiled]).any(0)
+            if mode == 2 and k == 1:           # the gradients enter behind the rounds: one worker's entry
+                assert not torch.isfinite(got[n - 1, 33]) and torch.equal(got[:n - 1, 33], want[:n - 1, 33])
+                rows = rows[:1]
+            assert not rows.any(), (mode, k, rows)
+            others = [c for c in range(d) if c not in spoiled]
+            assert torch.equal(got[:, others], want[:, others]), (mode, k)
