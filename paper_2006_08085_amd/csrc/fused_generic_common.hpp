@@ -182,9 +182,11 @@ constexpr bool kFetchFirst = S < kSlotsMax;
 // half of the blocks of a compute unit are in their rounds, and the others did not keep the memory busy.  Within 64 registers
 // one row fits ahead, none beside the noise, whose Philox state then spills (bf16 values unpacked next to their loads took
 // two registers to one and spilled 22).  One by one and ahead: phase, 300 workers, 4-regular, d = 100,000, K = 8 fp32 253 ->
-// 240 us, K = 2, bf16 140 -> 115; 200 irregular workers, d = 300,000, K = 8, bf16 505 -> 455; fused step, 100 irregular
-// workers, d = 500,000, K = 8 460 -> 425, 30, d = 1,000,000, K = 3, bf16 158 -> 135, 64 workers, 4-regular, d = 1,000,000,
-// K = 8 375 -> 368, 24 irregular workers, d = 3,000, K = 4 with its gradient 12.7 -> 10.9.
+// 240 us, K = 2, bf16 140 -> 115; fused step, 100 irregular workers, d = 500,000, K = 8 460 -> 425, 30, d = 1,000,000, K = 3,
+// bf16 158 -> 135, 64 workers, 4-regular, d = 1,000,000, K = 8 375 -> 368, 24 irregular workers, d = 3,000, K = 4 with its
+// gradient 12.7 -> 10.9.  The fused step of few workers with one weight, fp32, K <= 4, whose call just outgrows the caches, pays
+// for it (64 workers, 4 and 8 neighbours, 4.5 Mi elements, K = 1 and 2 4 to 8 %) and gains elsewhere.
+constexpr int kInOneGo = -1;  // a row's loads and their use between the same two fences
 template <class R, int PLENTY>
 constexpr int kAhead = R::kSlots < kSlotsMax ? R::kSlots - 1 : PLENTY - (R::kWaves == 8);
 
@@ -509,8 +511,8 @@ __device__ __forceinline__ void gossip(f4 (&z)[R::kSlots], R &rounds, Place &p, 
 
 // Calls request(tile, s, row offset, columns, row) for the lane's rows in turn and, AHEAD rows behind, use(tile, s, row offset,
 // columns, mine, what request returned), with the scheduler fenced in between: left alone, the compiler issues every row's
-// loads at once and spills.  `tile` is a compile-time value of Tile.  A position past the last row reads row 0 and must not
-// store (mine = false); no list names it.  CUT as above.
+// loads at once and spills.  (kInOneGo: both between the same two fences.)  `tile` is a compile-time value of Tile.  A position
+// past the last row reads row 0 and must not store (mine = false); no list names it.  CUT as above.
 template <int AHEAD, class R, bool CUT, class Request, class Use>
 __device__ __forceinline__ void each_row(const R &rounds, const typename R::Args &ra, Place &p, int tile, int n, int64_t d,
                                          int64_t ld, int64_t first, Request &&request, Use &&use) {
@@ -523,6 +525,20 @@ __device__ __forceinline__ void each_row(const R &rounds, const typename R::Args
     __builtin_amdgcn_sched_barrier(0);
   }
   auto go = [&](auto of) {
+    if constexpr (AHEAD == kInOneGo) {  // as below, but written out: through a function ByteRounds spill 2 to 4 registers more
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        p.forget();
+        Columns c{first + p.col(), 0};
+        if (of == kCut && c.at > d - 4) c = Columns{d - 4, int(c.at - (d - 4))};
+        const int row = R::kRowsInMemory ? rows[s] : rounds.row(ra, p, s);
+        const bool mine = row >= 0 && row < n;
+        const int64_t off = int64_t(mine ? row : 0) * ld;
+        use(of, s, off, c, mine, request(of, s, off, c, row));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
     auto at = [&](int s, auto &&f) {
       p.forget();
       Columns c{first + p.col(), 0};
@@ -552,8 +568,8 @@ struct Nothing {};
 template <class R, bool CUT, class Use>
 __device__ __forceinline__ void each_row(const R &rounds, const typename R::Args &ra, Place &p, int tile, int n, int64_t d,
                                          int64_t ld, int64_t first, Use &&use) {
-  each_row<0, R, CUT>(rounds, ra, p, tile, n, d, ld, first, [&](auto, int, int64_t, Columns, int) { return Nothing{}; },
-                      [&](auto F, int s, int64_t off, Columns c, bool mine, Nothing) { use(F, s, off, c, mine); });
+  each_row<kInOneGo, R, CUT>(rounds, ra, p, tile, n, d, ld, first, [&](auto, int, int64_t, Columns, int) { return Nothing{}; },
+                             [&](auto F, int s, int64_t off, Columns c, bool mine, Nothing) { use(F, s, off, c, mine); });
 }
 
 // Columns, rows per lane and threads of a block.  A tile takes 16 bytes per lane and row: 64 KiB at most.

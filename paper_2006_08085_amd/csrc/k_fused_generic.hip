@@ -33,13 +33,21 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     each_row<ahead, R, true>(rounds, ra, p, tile, n, d, ld, first, request, use);
   };
   constexpr std::integral_constant<int, R::kSlots - 1> kAllAhead;
-  auto load_all = [&](const ST *from) {
-    rows_ahead(kAllAhead, [&](auto F, int, int64_t off, Columns c, int) { return load4<F, A>(from, off, c, d); },
-               [&](auto, int s, int64_t, Columns, bool, Raw<ST> r) { z[s] = floats(r); });
+  // z <- a matrix, all of its loads in flight at once; before(s) comes ahead of those of slot s.
+  auto load_all = [&](const ST *from, auto before) {
+    if constexpr (std::is_same_v<ST, float>) {
+      rows([&](auto F, int s, int64_t off, Columns c, bool) { before(s), z[s] = load4<F, A>(from, off, c, d); });
+    } else {
+      Raw<ST> r[R::kSlots];
+      rows([&](auto F, int s, int64_t off, Columns c, bool) { before(s), r[s] = load4<F, A>(from, off, c, d); });
+#pragma unroll
+      for (int s = 0; s < R::kSlots; ++s) z[s] = floats(r[s]);
+    }
   };
+  auto nothing = [](int) {};
   if constexpr (kFetchFirst<R::kSlots>) rounds.fetch(ra, p);
   if constexpr (MODE == 0) {
-    load_all(X);
+    load_all(X, nothing);
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) { if (mine) store4<F, A>(X, off, c, d, z[s]); });
@@ -49,15 +57,29 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
       Raw<ST> x, y;
       f4 gn, go;
     };
-    rows_ahead(std::integral_constant<int, kAhead<R, 2>>{}, [&](auto F, int, int64_t off, Columns c, int) {
+    auto request = [&](auto F, int, int64_t off, Columns c, int) {
       return Row{load4<F, A>(X, off, c, d), load4<F, A>(Y, off, c, d), load4<F, A>(Gn, off, c, d), load4<F, A>(Go, off, c, d)};
-    }, [&](auto, int s, int64_t, Columns, bool, const Row &r) {
+    };
+    auto use = [&](auto, int s, int64_t, Columns, bool, const Row &r) {
       const f4 y = floats(r.y);
       z[s] = fma4(-alpha, y, floats(r.x));
       f4 t = y + r.gn - r.go;
       pin4(z[s]), pin4(t);  // the sums now, not their operands carried through the rounds
       v.put(p, s, t);
-    });
+    };
+    constexpr std::integral_constant<int, kAhead<R, 2>> kSomeAhead;
+    constexpr std::integral_constant<int, kInOneGo> kNoneAhead;
+    // With one weight, fp32 state and few rounds to hide them, blocks of few threads do better with one row's loads at a time,
+    // eight neighbours, whose table leaves no register for a row ahead, with any K.  One row at a time and ahead, replayed:
+    // 64 workers, 4 neighbours, 3 Mi elements, K = 1 12.8 and 15.6 us, K = 2 14.2 and 15.9, 7 Mi, K = 4 37 and 39, but K = 8
+    // 46.3 and 43.7; 24, 4.5 Mi, K = 1 18.6 and 20.6, 12 Mi, K = 8 72 and 66; 128, 4 Mi, K = 1 19 and 20, 200, 12 Mi, K = 2 68
+    // and 65, K = 4 79 and 75; 64 workers, 8 neighbours, 4.5 Mi, K = 1 23.0 and 26.9, K = 2 24.9 and 29.8.
+    if constexpr (R::kWaves == 8 && std::is_same_v<ST, float>) {
+      if (R::kWords > 1 || K * int(blockDim.x) <= 1024) rows_ahead(kNoneAhead, request, use);
+      else rows_ahead(kSomeAhead, request, use);
+    } else {
+      rows_ahead(kSomeAhead, request, use);
+    }
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
@@ -89,23 +111,19 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     });
   } else {
     // M(Y) first: both outputs need it
-    load_all(Y);
+    load_all(Y, nothing);
     rounds.init(ra, p, eta);
     gossip(z, rounds, p, eta, K);
-#pragma unroll
-    for (int s = 0; s < R::kSlots; ++s) v.put(p, s, z[s]);
-    load_all(X);
+    load_all(X, [&](int s) { v.put(p, s, z[s]); });
     gossip(z, rounds, p, eta, K);
-    struct Row {
-      f4 gn, go;
-    };
-    rows_ahead(std::integral_constant<int, kAhead<R, 2>>{}, [&](auto F, int, int64_t off, Columns c, int) {
-      return Row{load4<F, A>(Gn, off, c, d), load4<F, A>(Go, off, c, d)};
-    }, [&](auto F, int s, int64_t off, Columns c, bool mine, const Row &r) {
-      const f4 my = v.get(p, s);
+    // one row's gradients at a time: two rows ahead take eight registers more, and with them a wavefront per SIMD (lists of 24
+    // and 64 workers, 7 Mi elements, K = 4 45.9 and 39.9 us, 48.5 and 41.2), a block per compute unit (300 workers, 1.8 Mi 20.4
+    // and 15.4) or spills (200 workers, 8 neighbours, 4.5 Mi, K = 1 29.5 and 24.7)
+    rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
+      const f4 gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d), my = v.get(p, s);
       if (mine) {
         store4<F, A>(X, off, c, d, fma4(-alpha, my, z[s]));
-        store4<F, A>(Y, off, c, d, my + r.gn - r.go);
+        store4<F, A>(Y, off, c, d, my + gn - go);
       }
     });
   }

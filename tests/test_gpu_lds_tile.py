@@ -325,3 +325,33 @@ def test_one_weight_beyond_256_workers(n, degree, dtype, K):
     ctx.dpsgd_step(Xr, Gn, alpha)
     assert torch.equal(Xp, Xr)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,kind", [(16, "rr"), (24, "rr8"), (100, "ring"), (64, "rr"), (64, "rr8"), (64, "irregular"),
+                                    (128, "rr"), (128, "rr8"), (300, "irregular")])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_how_rows_are_requested_does_not_change_the_bits(n, kind, dtype):
+    """How many rows' loads are in flight depends on the form, the state type, K and the threads of a block: the first columns
+    of a matrix that takes four rows per lane, and the same columns alone, which take one or two."""
+    topo = D.Topology.ring() if kind == "ring" else D.Topology.from_edges(_graph(kind, n), D.DETAG_W_METROPOLIS)
+    wide, narrow = (1 << 19) // n * 4 + 1003, 1001
+    ld, sd = wide + 2, torch.bfloat16 if dtype == "bf16" else torch.float32
+    code = D.DETAG_BF16 if dtype == "bf16" else D.DETAG_F32
+    X, Y, Gn, Go = (_matrix(n, wide, ld, k, sd if k < 2 else torch.float32) for k in range(4))
+    for K in (1, 2, 3, 4, 5, 6):
+        out = []
+        for d in (wide, narrow):
+            ctx = D.detag_create(topo, n, d, ld, code)
+            z = X.clone()
+            ctx.gossip_accel(z, K, 0.35)
+            got = [z]
+            for variant in (D.DETAG_VARIANT_ATC, D.DETAG_VARIANT_ALG2):
+                x, y = X.clone(), Y.clone()
+                ctx.step(x, y, Gn, Go, 0.2, K, 0.35, variant)
+                got += [x, y]
+            ctx.close()
+            for t, before in zip(got, (X, X, Y, X, Y)):
+                assert torch.equal(t[:, d:], before[:, d:])
+            out.append([t[:, :narrow] for t in got])
+        for k, (a, b) in enumerate(zip(*out)):
+            assert torch.equal(a, b), (K, k)
