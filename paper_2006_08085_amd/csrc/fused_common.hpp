@@ -17,7 +17,7 @@ constexpr int kThreads = 256;
 // Threads of a block.  No two wavefronts of a block work together, so its size only decides how columns spread over the
 // chip: up to 32,768 columns make 128 blocks of 256 threads or fewer and take one wavefront per block, which spreads them
 // over all compute units (rounds of 4 to 64 workers 1 to 5 % faster at 8,192 to 32,768 columns).  Beyond, both sizes are
-// within 2 %.
+// within 2 %.  Phases of so few columns take the kernels of pair_serves.
 inline int block_threads(int64_t d) { return d <= 32768 ? 64 : kThreads; }
 
 // Small calls run the model side and the tracker side of a phase in two wavefronts of a block (fused_pair_kernel,

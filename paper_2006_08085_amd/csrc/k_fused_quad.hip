@@ -324,8 +324,8 @@ template <class T>
 int launch_s(const Shape &s, bool alg2, void *X, void *Y, float *G, const float *h, bool hpw, const float *b,
              const Coef &c, float alpha, int K, float sigma, uint64_t seed, uint32_t step, void *stream) {
   const bool pair = pair_serves(s.d, K, true);
-  const int threads = pair ? kPairThreads : block_threads(s.d);
-  const dim3 grid(ceil_div_i64(s.d, pair ? 64 : threads));
+  const int threads = pair ? kPairThreads : kThreads;
+  const dim3 grid(ceil_div_i64(s.d, pair ? 64 : kThreads));
   auto st = static_cast<hipStream_t>(stream);
   const uint32_t slo = uint32_t(seed & 0xffffffffu), shi = uint32_t(seed >> 32);
   auto go = [&](auto *kernel, auto *x) {
