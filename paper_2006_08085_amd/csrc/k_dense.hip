@@ -350,15 +350,16 @@ int launch_ks(const Shape &s, int mode, void *X, void *Y, const float *Gn, const
       default: return go(&dense_phase_kernel<ST, TP, TU, 2, KS, access>);
     }
   };
-  // Where rows do not start on a cache line, neighbouring tiles share lines: they go to one XCD (64 x 1,000,003 fp32: 616 ->
-  // 470 us) and leave their accesses to the caches (pitch 1,000,001, K = 4 505 -> 414 us; 256 x 200,001 of bf16 397 -> 355).
-  // Where they do, tiles keep their order, in which 256 workers with bf16 state measured 1 % faster, and stream, but not calls
-  // of up to 80 MiB that read a matrix twice (streamed and kept, K = 4, three states in turn: Algorithm 2's phase of 64 workers
-  // 64 MiB 56.8 and 41.8 us, 96 MiB 86.7 and 82.4, 126 MiB 96.4 and 98.5; the ATC phase of 128 workers 80 MiB 79.7 and 75.0,
-  // 96 MiB 81.2 and 90.6, 126 MiB 88.2 and 104.5; with bf16 state 256 workers 40 MiB 40.3 and 45.4, which streams), nor plain
-  // gossip of fp32 state from 32 to 80 MiB (128 workers 14 MiB 14.3 and 15.2, 40 MiB 33.3 and 33.1, 80 MiB 58.3 and 55.1, 96
-  // MiB 69.9 and 75.3; 256 workers 64 MiB 58.5 and 52.4).  A kernel for each: the choice made at run time cost the aligned one
-  // 0.6 to 5 %.
+  // Where rows do not start on a cache line, neighbouring tiles share lines: they go to one XCD and leave their accesses to the
+  // caches (64 x 1,000,003 fp32, which came here then: 616 -> 470 us for the XCDs, 505 -> 414 for the accesses).
+  // Where they do, tiles keep their order and stream, but not calls of up to 80 MiB that read a matrix twice, nor plain gossip
+  // of fp32 state from 32 to 80 MiB.  Streamed and kept, K = 4, three states in turn, fp32 and more than 128 workers, which is
+  // what comes here with columns to spare: ATC phase, 200 workers, 20 MiB 42.7 and 38.1 us, 80 MiB 61.0 and 54.0, 96 MiB 63.5
+  // and 65.0, 126 MiB 105.1 and 106.4, 256, 64 MiB 51.9 and 48.8, 126 MiB 73.3 and 76.3; Algorithm 2's phase of 256, 40 MiB 61.3
+  // and 49.9, 80 MiB 81.1 and 65.2, 126 MiB 87.9 and 92.2; plain gossip of 130, 20 MiB 29.9 and 31.5, 64 MiB 71.3 and 71.5, of
+  // 256, 64 MiB 60.3 and 56.7, 126 MiB 108.9 and 109.5.  The small calls of few workers that come here are level (12 workers,
+  // bf16, ATC phase, d = 1,000 5.3 and 5.5, 30,000 6.8 and 6.4).  A kernel for each: the choice made at run time cost the
+  // aligned one 0.6 to 5 %.
   const int state = sizeof(ST);
   const int64_t bytes = fused::footprint(s, mode == 0 ? state : 2 * state + 8);
   const bool gains = mode == 2 || (!s.bf16 && (mode == 1 || bytes >= 32 * kMiB));

@@ -671,14 +671,16 @@ int launch_access(const Shape &s, int mode, void *X, void *Y, const float *Gn, c
 
 // What this kernel takes: lanes count their offsets within 32 rows of fp32 in 32 bits, a lone last column is loaded with the one
 // before it, and the P of a call is read by every block before its first tile, which the smallest calls of few workers notice
-// (general kernel and this one: 12 workers, bf16, ATC, d = 1,000 6.8 and 7.6 us, 16,000 6.9 and 7.6, 50,000 10.3 and 7.8, but
-// fp32 6.8 and 6.6; plain gossip of 32 workers, bf16, d = 1,000 4.9 and 5.2, 16,000 5.0 and 5.3, 50,000 6.4 and 5.2, fp32 4.5
-// and 4.9, 4.6 and 4.9, 6.6 and 5.4; Algorithm 2's phase of 12 7.2 and 6.5).
+// (general kernel and this one, replayed, K = 4: ATC phase, 12 workers, fp32, d = 1,000 5.6 and 6.2 us, 16,000 5.9 and 6.5,
+// 26,000 6.4 and 6.5, 16 workers 5.8 and 6.3, 6.1 and 6.6, 17 level; bf16, d = 1,000 6.8 and 7.6, 16,000 6.9 and 7.6, 50,000
+// 10.3 and 7.8; plain gossip of 32 workers, bf16, d = 1,000 4.9 and 5.2, 16,000 5.0 and 5.3, 50,000 6.4 and 5.2, fp32 4.5 and
+// 4.9, 4.6 and 4.9, 6.6 and 5.4; Algorithm 2's phase of 5, bf16, d = 8,000 5.7 and 6.3, of 7 6.1 and 6.4, of 8 level, fp32 within
+// 4 % both ways).
 bool dense_resident_serves(const Shape &s, int mode) {
   if (!s.bf16 && s.n > 128) return false;
   if (s.d < 64 || s.ld > (int64_t(1) << 25)) return false;
-  const int few = mode == 0 ? 32 : mode == 1 && s.bf16 ? 16 : 0;
-  return s.n > few || s.d >= 32768;
+  const int few = mode == 0 ? 32 : mode == 1 ? 16 : s.bf16 ? 7 : 0;
+  return s.n > few || s.d >= (mode == 0 || (mode == 1 && s.bf16) ? 32768 : 20480);
 }
 
 int launch_dense_resident(const Shape &s, int mode, void *X, void *Y, const float *Gn, const float *Go, float alpha,
