@@ -116,7 +116,9 @@ __global__ __launch_bounds__(kThreads, waves_per_simd(T::n, MODE)) void fused_st
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         u[i] = lx[i], v[i] = ly[i];
-        pin_vgpr(u[i]);  // or its load moves behind the tracker's rounds
+        // bf16: or its load moves behind the tracker's rounds; fp32 rows may arrive under them (waited for ahead of them, torus
+        // 8x8, d = 312,500, K = 12 117 and 125 us, K = 4 the same)
+        if constexpr (sizeof(ST) == 2) pin_vgpr(u[i]);
       }
       ag_rounds<T>(v, p, c, K);
       __builtin_amdgcn_sched_barrier(0);
