@@ -252,11 +252,12 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_grad_kernel(int64_t first_c
 
 // Both products in one launch, for problems so small that a block of 64 columns computes all residuals of its worker itself,
 // in one go: a wavefront per row as in lstsq_resid_kernel, whose sums they are bit for bit, kSumRows rows side by side.  What
-// such a call costs is the host behind its launches, not the GPU: called back to back, two launches and one, 8 workers, 64 x
-// 1024 8.3 and 6.0 us a call, 32 workers, 64 x 500 8.7 and 6.2, while on the GPU (a recorded graph of 20 calls, a replay of
-// it by the call) they take 5.4 and 6.7, 6.7 and 6.7 (measured with the last columns one by one, as were the figures of the
-// rule below).  Blocks of a worker go to one XCD where n is a multiple of eight, so that its L2 serves all of them but the first.  Blocks of 128 and 256 columns repeat less of the first product and are
-// slower both ways (8 workers, 64 x 1024 6.8 and 8.7 us a call).
+// such a call costs is the host behind its launches, not the GPU.  With a step after it, called back to back, two launches and
+// one: 8 workers, 64 x 512 9.6 and 7.6 us, 64 x 1024 9.4 and 9.0, 16 x 1024 9.7 and 8.6, 16 workers, 64 x 768 9.4 and 9.2, 32,
+// 64 x 384 9.7 and 9.5; on the GPU (replayed, the gradient alone) they take 5.2 and 5.2, 5.3 and 6.3, 4.9 and 5.9, 5.7 and 6.0,
+// 5.7 and 5.4.  Blocks of a worker go to one XCD where n is a multiple of eight, so that its L2 serves all of them but the
+// first.  Blocks of 128 and 256 columns repeat less of the first product and are slower both ways (8 workers, 64 x 1024 6.8
+// and 8.7 us a call then).
 constexpr int kSumRows = 4;
 constexpr int kSmallRows = kSumRows * (kSumThreads / 64), kSmallCols = 1024;
 template <typename ST>
@@ -292,14 +293,20 @@ __global__ __launch_bounds__(kSumThreads) void lstsq_small_kernel(int m, int64_t
   if (threadIdx.x < kCols && c0 + threadIdx.x < d) G[int64_t(i) * ld + c0 + threadIdx.x] = lstsq_total(part, threadIdx.x);
 }
 
-// One launch while a block takes its rows in one go and the blocks take a compute unit each.  With twice the rows or columns
-// it is slower on the GPU by more than the launch it saves (8 workers, 128 x 1024 8.7 and 8.4 us, 256 x 512 8.8 and 13.1).
-// A recorded call costs the host nothing at its replay and takes what is faster on the GPU, which is one launch up to 256
-// columns (two and one: 8 workers, 32 x 200 5.2 and 5.1 us, 64 workers, 64 x 256 6.6 and 5.7, 85, 40 x 129 6.3 and 5.3; but 32
-// workers, 8 x 512 5.8 and 6.0, 8 workers, 64 x 1000 6.9 and 7.9).
+// One launch while a block takes its rows in one go, the blocks take a compute unit each and what they repeat of the first
+// product stays small (with a step after it, called back to back, two launches and one: 16 workers, 64 x 900 9.6 and 10.4 us,
+// 64 x 1024 9.2 and 9.7, which repeat 14 and 17 million products; 16, 64 x 768 and 32, 64 x 512, 9.4 and 8.4 million, are within
+// 3 %).  With twice the rows or columns it is slower on the GPU by more than the launch it saves (16 workers, 64 x 2048 6.8 and
+// 15.7 us a call, 8, 64 x 2000 6.2 and 9.1).
+// A recorded call costs the host nothing at its replay and takes what is faster on the GPU: one launch up to 256 columns (two and
+// one: 8 workers, 32 x 200 4.8 and 4.5 us, 64 workers, 64 x 256 6.1 and 4.9, 85, 40 x 129 5.8 and 4.8), from there to 512 either
+// (8, 64 x 300 with the step 8.0 and 8.0, 512 7.6 and 7.8, 32, 64 x 384 9.9 and 9.5), then two (8, 64 x 640 8.2 and 8.5, 1024
+// 7.7 and 8.8).
 constexpr int kRecordedCols = 256;
+constexpr int64_t kRepeated = int64_t(10) << 20;
 bool lstsq_is_small(const Shape &s, int m, void *stream) {
-  return m <= kSmallRows && s.d <= kSmallCols && (s.d + 63) / 64 * s.n <= 256 &&
+  const int64_t blocks = (s.d + 63) / 64 * s.n;
+  return m <= kSmallRows && s.d <= kSmallCols && blocks <= 256 && blocks * m * s.d <= kRepeated &&
          (s.d <= kRecordedCols || !is_capturing(stream));
 }
 
