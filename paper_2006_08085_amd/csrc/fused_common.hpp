@@ -26,7 +26,10 @@ inline int block_threads(int64_t d) { return d <= 32768 ? 64 : kThreads; }
 // of it), replayed from a recorded graph: phase, torus 8x8 d = 1,000 15.4 and 9.2 us, 32,000 19.6 and 15.3, 65,000 26.1 and
 // 22.5, 130,000 41.2 and 50.6; ring of 32 6.7 and 4.5, 8.8 and 7.5, 12.8 and 11.7, 18.3 and 17.7; fused step, torus 8x8 19.6
 // and 13.7, 22.7 and 16.9, at 45,000 25.1 and 18.8, at 65,000 28.8 and 24.8; ring of 16 at 60,000 7.5 and 7.8; Algorithm 2 as
-// printed gains more.  K = 1: phase, ring of 32, d = 5,001 3.9 and 3.1, 32,000 5.5 and 5.5, 45,000 7.3 and 7.5.
+// printed gains more.  K = 1: phase, ring of 32, d = 5,001 3.9 and 3.1, 32,000 5.5 and 5.5, 45,000 7.3 and 7.5.  Three states in
+// turn: K = 1, step, torus 8x8 24,000 12.5 and 11.9, 32,000 13.9 and 12.4, ring of 32 32,000 7.6 and 7.7; K = 2 and 3, phase, ring
+// of 16 48,000 4.7 and 4.7, 5.0 and 4.8, 65,000 6.0 and 6.0, 6.2 and 6.2, step 5.7 and 5.7, 6.1 and 5.9, 65,000 6.5 and 7.1, 6.7
+// and 7.2; bf16 gains a little more.
 constexpr int kPairThreads = 128;
 inline bool pair_serves(int64_t d, int K, bool with_query) {
   return d <= (K == 1 ? 32768 : K >= 4 && !with_query ? 65536 : 49152);
