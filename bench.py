@@ -290,10 +290,10 @@ def main():
         note = "sum over the launches of one detag_step call; every round crosses HBM"
     else:
         bpe = 4 * sb + 8
-        kernel = ("dense_phase_kernel" if args.dense else "fused_structured_kernel" if structured
-                  else "fused_generic_kernel") + " (detag_step)"
+        kernel = (("dense_resident_kernel" if bf16 else "dense_resident_f32_kernel") if args.dense
+                  else "fused_structured_kernel" if structured else "fused_generic_kernel") + " (detag_step)"
         if args.dense:
-            note = "bound by the latency of its staging loads and by instruction issue, not yet by HBM or the matrix cores"
+            note = "256 workers: bound by its products (matrix cores 42 % busy) and the staging between two barriers a tile; fewer: by HBM"
         elif not structured:
             note = "this kernel keeps all rows of a tile in LDS and is bound by LDS bandwidth and VALU issue, partly by HBM"
     if not bf16 and what == "step" and not per_round:

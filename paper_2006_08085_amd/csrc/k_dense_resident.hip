@@ -7,17 +7,17 @@
 // the present ones.
 //
 // Lane (m, g) of a unit loads columns 2m, 2m+1 of rows 8g..8g+7, which is what it holds of the B operand of two column tiles
-// (even columns, odd columns).  So the terms go to LDS in fragment order, 16 bytes a lane, read and written without bank
-// conflicts, and an accumulator pair is one 32-bit word of two columns at the store: no transposition, one instruction moves
+// (even columns, odd columns).  So the terms go to LDS in fragment order, 16 bytes a lane (conflicts are a tenth of the
+// LDS cycles), and an accumulator pair is one 32-bit word of two columns at the store: no transposition, one instruction moves
 // 128 bytes of each of two rows.  Same products and order as the general kernel: the same values bit for bit where all are
 // finite.  (State that is multiplied as it is stored is one term here, two there, the second of which is zero, or NaN beside
 // an infinity.)
 //
 // Measured (K = 16, three states in turn, general kernel and this one): 256 workers, d = 1,000,000, pitch 1,000,064, ATC 1310
-// and 911 us (4.5 TB/s; without its products 777), plain gossip 472 and 273; pitch 1,048,576, whose rows all start on the same
+// and 911 us (4.5 TB/s), plain gossip 472 and 273; pitch 1,048,576, whose rows all start on the same
 // memory channel, 1400 and 1063, 505 and 305; 128 workers, d = 2,000,000 1510 and 787 (5.2 TB/s: memory), 486 and 209; 64
 // workers, d = 1,000,000 380 and 194, 102 and 50; 256 workers, d = 1,000 37 and 16, 15 and 7.5.  At 256 workers the matrix
-// cores are busy 40 % of the time and staging takes another 20 % of the issue slots, between two barriers a tile; a deeper
+// cores are busy 42 % of the time, the vector ALUs, with the staging, 19 %, and both wait at two barriers a tile; a deeper
 // prefetch (one more quarter of the gradient rows) spills and loses, wavefront priorities change nothing.
 #include "detag_internal.h"
 #include "dev_common.hpp"

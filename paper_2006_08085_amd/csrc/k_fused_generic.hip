@@ -116,9 +116,9 @@ __global__ __launch_bounds__(kThreadsMax, R::kWaves) void fused_generic_kernel(S
     gossip(z, rounds, p, eta, K);
     load_all(X, [&](int s) { v.put(p, s, z[s]); });
     gossip(z, rounds, p, eta, K);
-    // one row's gradients at a time: two rows ahead take eight registers more, and with them a wavefront per SIMD (lists of 24
-    // and 64 workers, 7 Mi elements, K = 4 45.9 and 39.9 us, 48.5 and 41.2), a block per compute unit (300 workers, 1.8 Mi 20.4
-    // and 15.4) or spills (200 workers, 8 neighbours, 4.5 Mi, K = 1 29.5 and 24.7)
+    // one row's gradients at a time: two rows ahead take eight registers more, and with them a wavefront per SIMD (lists of 64
+    // workers, 7 Mi elements, K = 4 48.0 and 42.7 us), a block per compute unit (300 workers, 4 neighbours, 1.8 Mi, K = 4 19.3
+    // and 15.5) or spills (200 workers, 8 neighbours, 4.5 Mi, K = 1 29.5 and 24.7)
     rows([&](auto F, int s, int64_t off, Columns c, bool mine) {
       const f4 gn = load4<F, A>(Gn, off, c, d), go = load4<F, A>(Go, off, c, d), my = v.get(p, s);
       if (mine) {
